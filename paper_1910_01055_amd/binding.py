@@ -105,28 +105,52 @@ def load():
     lib.aq_policy_import_blob.argtypes = [vp, vp, C.c_uint64, vp]
     lib.aq_policy_explore.argtypes = [vp, vp, i64, C.POINTER(AqExplore), vp]
     lib.aq_policy_step_int8.argtypes = [vp, vp, i64, vp, C.POINTER(AqExplore), C.POINTER(AqTaps), vp]
+    lib.aq_policy_packed_blob_size.argtypes = [vp, C.POINTER(C.c_uint64)]
+    lib.aq_policy_export_packed_blob.argtypes = [vp, vp, C.c_uint64, vp]
+    lib.aq_policy_import_packed_blob.argtypes = [vp, vp, C.c_uint64, vp]
+    lib.aq_convert_params_fp16.argtypes = [vp, pp, pp, pp, pp, vp]
+    lib.aq_policy_forward_fp16.argtypes = [vp, vp, i64, vp, pp, vp]
     for name in EXPORTS:
+        fn = getattr(lib, name)
+        # (addresses travel as plain integers, which ctypes cuts to 32 bits where no argument types are declared)
+        if fn.argtypes is None:
+            raise RuntimeError(f"{name} has no argument types")
         if name != "aq_status_string":
-            getattr(lib, name).restype = C.c_int
+            fn.restype = C.c_int
     _lib = lib
     return lib
 
 
-def _stream():
+def _first_stream():
+    """The current stream as a raw handle; afterwards without building a torch.cuda.Stream object for every call,
+    which took 2.7 of the 7.5 us that a small policy's forward took in all (the handle itself is 0.1 us)."""
+    global _stream
     import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    handle = torch.cuda.current_stream().cuda_stream  # (initializes CUDA)
+    device, raw = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    _stream = lambda: raw(device())  # noqa: E731
+    return handle
+
+
+_stream = _first_stream
 
 
 def _ptr(t):
-    return C.c_void_p(0 if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_PTR_ARRAYS = [C.c_void_p * n for n in range(MAX_LAYERS + 1)]
+_RANGE_ARRAYS = [AqRange * n for n in range(MAX_LAYERS + 1)]
 
 
 def _ptr_array(tensors, n):
-    arr = (C.c_void_p * n)()
-    for i in range(n):
-        t = tensors[i] if tensors is not None and i < len(tensors) else None
-        arr[i] = 0 if t is None else t.data_ptr()
-    return arr
+    if tensors is None:
+        return _PTR_ARRAYS[n]()
+    return _PTR_ARRAYS[n](*[None if t is None else t.data_ptr() for t in tensors[:n]])
+
+
+def _range_array(ranges, n):
+    return _RANGE_ARRAYS[n](*[(float(lo), float(hi)) for lo, hi in ranges])
 
 
 def _check(status, where):
@@ -207,14 +231,14 @@ class Policy:
     def policy_step_int8(self, obs, actions, seed, step, sigma=None, epsilon=0.0):
         """8-bit forward plus exploration in one call (fused into the forward kernel where possible)."""
         ex = AqExplore(int(seed), int(step), 0 if sigma is None else sigma.data_ptr(), float(epsilon))
-        _check(load().aq_policy_step_int8(self._h, _ptr(obs), int(obs.shape[0]), _ptr(actions), C.byref(ex), None,
+        _check(load().aq_policy_step_int8(self._h, _ptr(obs), obs.shape[0], _ptr(actions), C.byref(ex), None,
                                           _stream()), "aq_policy_step_int8")
 
     def policy_explore(self, actions, seed, step, sigma=None, epsilon=0.0):
         """In place on the actions of a forward: Gaussian noise with per-row sigma (device fp32 [batch]) for
         continuous heads, epsilon-greedy for argmax heads."""
         ex = AqExplore(int(seed), int(step), 0 if sigma is None else sigma.data_ptr(), float(epsilon))
-        _check(load().aq_policy_explore(self._h, _ptr(actions), int(actions.shape[0]), C.byref(ex), _stream()),
+        _check(load().aq_policy_explore(self._h, _ptr(actions), actions.shape[0], C.byref(ex), _stream()),
                "aq_policy_explore")
 
     def policy_blob_size(self):
@@ -248,9 +272,7 @@ class Policy:
         """w, b, gamma, beta: per-layer lists of device tensors (entries or lists may be None);
         ranges: n_layers (lo, hi) pairs."""
         n = self.n_layers
-        r = (AqRange * n)()
-        for i, (lo, hi) in enumerate(ranges):
-            r[i] = AqRange(float(lo), float(hi))
+        r = _range_array(ranges, n)
         _check(load().aq_quantize_params(self._h, _ptr_array(w, n), _ptr_array(b, n), _ptr_array(gamma, n),
                                          _ptr_array(beta, n), r, _stream()), "aq_quantize_params")
 
@@ -266,7 +288,7 @@ class Policy:
 
     def policy_forward_int8(self, obs, actions, taps=None):
         """taps: dict with optional keys acc/act/ln_t (per-layer lists of tensors or None), a0, y."""
-        batch = int(obs.shape[0])
+        batch = obs.shape[0]
         ctaps = None
         if taps:
             n = self.n_layers
@@ -279,13 +301,13 @@ class Policy:
 
     def policy_forward_int8_static(self, obs, actions):
         """The 8-bit forward that allocates nothing (scratch in the library's static device buffer)."""
-        _check(load().aq_policy_forward_int8_static(self._h, _ptr(obs), int(obs.shape[0]), _ptr(actions), _stream()),
+        _check(load().aq_policy_forward_int8_static(self._h, _ptr(obs), obs.shape[0], _ptr(actions), _stream()),
                "aq_policy_forward_int8_static")
 
     def policy_forward_fp32_params(self, w, b, gamma, beta, obs, actions, ranges_out=None):
         n = self.n_layers
         _check(load().aq_policy_forward_fp32_params(self._h, _ptr_array(w, n), _ptr_array(b, n), _ptr_array(gamma, n),
-                                                    _ptr_array(beta, n), _ptr(obs), int(obs.shape[0]), _ptr(actions),
+                                                    _ptr_array(beta, n), _ptr(obs), obs.shape[0], _ptr(actions),
                                                     _ptr(ranges_out), _stream()), "aq_policy_forward_fp32_params")
 
     def policy_set_params_fp32(self, w, b, gamma, beta):
@@ -294,21 +316,19 @@ class Policy:
                                                 _ptr_array(beta, n), _stream()), "aq_policy_set_params_fp32")
 
     def policy_forward_fp32(self, obs, actions):
-        _check(load().aq_policy_forward_fp32(self._h, _ptr(obs), int(obs.shape[0]), _ptr(actions), _stream()),
+        _check(load().aq_policy_forward_fp32(self._h, _ptr(obs), obs.shape[0], _ptr(actions), _stream()),
                "aq_policy_forward_fp32")
 
     def calibrate_fp32(self, obs):
         """(min, max) per activation tensor over this batch, as a list of n_layers pairs (waits for the stream)."""
-        r = (AqRange * self.n_layers)()
-        _check(load().aq_calibrate_fp32(self._h, _ptr(obs), int(obs.shape[0]), r, _stream()), "aq_calibrate_fp32")
+        r = _RANGE_ARRAYS[self.n_layers]()
+        _check(load().aq_calibrate_fp32(self._h, _ptr(obs), obs.shape[0], r, _stream()), "aq_calibrate_fp32")
         return [(float(x.lo), float(x.hi)) for x in r]
 
     def quantize_kept_params(self, ranges):
         """aq_quantize_params on the parameters kept by policy_set_params_fp32 (NULL parameter arrays)."""
         n = self.n_layers
-        r = (AqRange * n)()
-        for i, (lo, hi) in enumerate(ranges):
-            r[i] = AqRange(float(lo), float(hi))
+        r = _range_array(ranges, n)
         _check(load().aq_quantize_params(self._h, None, None, None, None, r, _stream()), "aq_quantize_params")
 
     def convert_params_fp16(self, w, b, gamma, beta):
@@ -318,7 +338,7 @@ class Policy:
 
     def policy_forward_fp16(self, obs, actions, taps_out=None):
         taps = _ptr_array(taps_out, self.n_layers) if taps_out is not None else None
-        _check(load().aq_policy_forward_fp16(self._h, _ptr(obs), int(obs.shape[0]), _ptr(actions), taps, _stream()),
+        _check(load().aq_policy_forward_fp16(self._h, _ptr(obs), obs.shape[0], _ptr(actions), taps, _stream()),
                "aq_policy_forward_fp16")
 
 

@@ -502,8 +502,7 @@ extern "C" aq_status aq_policy_set_path(aq_policy* p, int32_t path) {
 
 extern "C" aq_status aq_policy_conv_stack_layers(const aq_policy* p, int32_t* n_layers) {
     if (!p || !n_layers) return AQ_EINVAL;
-    FwdArgs a{};
-    a.net = p->h_net;
+    FwdArgs a(p->h_net);
     a.c.batch = 1;
     *n_layers = p->conv_stack ? conv_stack_layers(a) : 0;
     return AQ_OK;
@@ -512,8 +511,7 @@ extern "C" aq_status aq_policy_conv_stack_layers(const aq_policy* p, int32_t* n_
 extern "C" aq_status aq_policy_fused_plan(const aq_policy* p, int64_t batch, int32_t* rows, int32_t* tiles,
                                           int32_t* kind) {
     if (!p || !rows || !tiles || !kind || batch < 1) return AQ_EINVAL;
-    FwdArgs a{};
-    a.net = p->h_net;
+    FwdArgs a(p->h_net);
     a.c.batch = batch;
     int r = 0, t = 0;
     size_t lds = 0;
@@ -526,8 +524,7 @@ extern "C" aq_status aq_policy_fused_plan(const aq_policy* p, int64_t batch, int
 
 extern "C" aq_status aq_policy_subbyte_layers(const aq_policy* p, int64_t batch, int32_t* n_layers) {
     if (!p || !n_layers || batch < 1) return AQ_EINVAL;
-    FwdArgs a{};
-    a.net = p->h_net;
+    FwdArgs a(p->h_net);
     a.c.batch = batch;
     int r = 0;
     size_t lds = 0;
@@ -874,8 +871,7 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
     if (batch > (1LL << 40)) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
     const int nl = p->net.n_layers;
-    FwdArgs a{};
-    a.net = p->h_net;
+    FwdArgs a(p->h_net);
     a.d_net = p->d_net;
     a.c.obs = d_obs;
     a.c.actions = d_actions;
@@ -889,6 +885,7 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
     }
     for (int l = 0; l < nl; ++l) a.w4[l] = p->subbyte ? p->w4[l] : nullptr;
     if (taps) {
+        a.taps = true;
         for (int l = 0; l < nl; ++l) {
             a.t.acc[l] = taps->acc ? taps->acc[l] : nullptr;
             a.t.act[l] = taps->act ? taps->act[l] : nullptr;
@@ -900,12 +897,12 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
 
     int rows;
     size_t lds;
-    const bool can_fuse = fused_mlp_supported(a, &rows, &lds);
+    const bool can_fuse = p->path != 2 && fused_mlp_supported(a, &rows, &lds);
     if (p->path == 1 && !can_fuse) return AQ_ESHAPE;
     // an MLP that fits the fused kernel always runs fused: measured faster than one launch per layer at
     // every batch size (activations stay in LDS, one launch)
     const int A = p->L.back().N * p->L.back().oh * p->L.back().ow;
-    if (can_fuse && p->path != 2) {
+    if (can_fuse) {
         // Gaussian noise rides in the kernel where it writes the actions itself (an elementwise head on
         // a narrow last layer); every other case takes the separate exploration launch below
         const bool fuse_ex = ex && p->net.head != AQ_HEAD_ARGMAX && p->L.back().NT <= 2;
@@ -989,8 +986,7 @@ extern "C" aq_status aq_policy_forward_int8_static(aq_policy* p, const void* d_o
     const size_t map = up(i8_map_bytes(p, batch));
     const size_t ln = up((size_t)batch * (size_t)p->ln_elems * 4);
     const size_t y = up((size_t)batch * (size_t)p->y_elems * 4);
-    FwdArgs probe{};
-    probe.net = p->h_net;
+    FwdArgs probe(p->h_net);
     probe.c.batch = batch > 0 ? batch : 1;
     int rows = 0;
     size_t lds = 0;

@@ -267,6 +267,21 @@ struct TapArgs {
     uint8_t* a0;
     float* y;
 };
+// The same as a kernel's last-but-unused argument: a launch without taps hands over one word instead of 208 bytes of
+// null pointers.  The host writes every argument into uncached memory at each launch: measured 2.65 us per launch
+// with 8 bytes of arguments, 3.4 us with 256, 4.1 us with 1 KiB, which is the whole time of a small policy's call.
+template <bool TAPS>
+struct TapParam {
+    TapArgs t;
+    explicit TapParam(const TapArgs& a) : t(a) {}
+};
+template <>
+struct TapParam<false> {
+    int none;
+    explicit TapParam(const TapArgs&) : none(0) {}
+};
+__device__ __forceinline__ TapArgs taps_of(const TapParam<true>& p) { return p.t; }
+__device__ __forceinline__ TapArgs taps_of(const TapParam<false>&) { return TapArgs{}; }
 struct LayerTaps {
     int32_t* acc;
     uint8_t* act;

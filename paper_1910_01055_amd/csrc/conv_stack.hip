@@ -90,10 +90,11 @@ bool plan_stack(const FwdArgs& a, StackPlan* p) {
 }  // namespace
 
 template <bool TAPS, int W, int NC>
-__global__ __launch_bounds__(W * 64) void k_conv_stack(const NetDev* __restrict__ netp, const TapArgs t, const StackArgs sa,
+__global__ __launch_bounds__(W * 64) void k_conv_stack(const NetDev* __restrict__ netp, const TapParam<TAPS> tp, const StackArgs sa,
                                                      const uint8_t* __restrict__ frames, int8_t* __restrict__ out,
                                                      const int off_b, const int off_c) {
     extern __shared__ __align__(16) int8_t smem[];
+    const TapArgs t = taps_of(tp);
     const NetDev& a = *netp;
     // (the wave index stays a vector value here: it only selects tiles, in a loop; the tests that guard MFMAs are on
     // the scalar K.  An MFMA behind a lane-mask test could run under an empty mask, which the matrix cores ignore)
@@ -277,7 +278,7 @@ aq_status launch_conv_stack(const FwdArgs& a, int8_t* out, hipStream_t st) {
                 return AQ_EHIP;                                                                                      \
             attr_set = true;                                                                                         \
         }                                                                                                            \
-        hipLaunchKernelGGL((k_conv_stack<TP, WV, NCV>), grid, dim3(WV * 64), p.lds, st, a.d_net, a.t, sa,            \
+        hipLaunchKernelGGL((k_conv_stack<TP, WV, NCV>), grid, dim3(WV * 64), p.lds, st, a.d_net, TapParam<TP>(a.t), sa, \
                            (const uint8_t*)a.c.obs, out, p.off_b, p.off_c);                                          \
     } while (0)
 #define AQ_STACK_NC(TP, WV)                 \

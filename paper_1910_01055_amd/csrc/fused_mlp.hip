@@ -98,6 +98,7 @@ bool make_plan(const FwdArgs& a, Plan* p) {
 }  // namespace
 
 bool any_taps(const FwdArgs& a) {
+    if (!a.taps) return false;
     if (a.t.a0 || a.t.y) return true;
     for (int l = 0; l < a.net.n_layers; ++l)
         if (a.t.acc[l] || a.t.act[l] || a.t.ln[l]) return true;
@@ -105,36 +106,40 @@ bool any_taps(const FwdArgs& a) {
 }
 
 bool fused_mlp_supported(const FwdArgs& a, int* rows_out, size_t* lds_out, int* tiles_out) {
+    if (rows16_mlp_supported(a)) {  // (given a 16-byte aligned observation buffer; every such network also has a plan)
+        *rows_out = 16 * rows16_mlp_row_tiles(a.c.batch);
+        *lds_out = 0;
+        if (tiles_out) *tiles_out = 1;
+        return true;
+    }
     Plan p;
     if (!make_plan(a, &p)) return false;
     *rows_out = p.half ? 16 : 32 * p.mt;
     *lds_out = p.lds;
     if (tiles_out) *tiles_out = p.nb;
-    if (fused_mlp_kernel_kind(a) >= 2) {  // (given a 16-byte aligned observation buffer)
-        *rows_out = 16 * rows16_mlp_row_tiles(a.c.batch);
-        if (tiles_out) *tiles_out = 1;
-    }
     return true;
 }
 
 int fused_mlp_kernel_kind(const FwdArgs& a) {
+    if (rows16_mlp_supported(a)) return rows16_mlp_alone_on_cu(a.c.batch) ? 3 : 2;
     Plan p;
     int ld;
     if (!make_plan(a, &p)) return 0;
-    if (rows16_mlp_supported(a)) return rows16_mlp_alone_on_cu(a.c.batch) ? 3 : 2;
     if (p.half) return 0;
     if (p.nb == 2 && p.mt == 2 && wide_mlp_supported(a, &ld)) return 1;
     return 0;
 }
 
 aq_status launch_fused_mlp(const FwdArgs& a_in, hipStream_t st) {
+    // 16-row workgroups on small networks: the kernel built for that case (asked first, before any planning: at
+    // these sizes the call's host time is what a launch costs)
+    const bool aligned = ((uintptr_t)a_in.c.obs & 15) == 0;
+    if (aligned && rows16_mlp_supported(a_in)) return launch_rows16_mlp(a_in, st);
     Plan p;
     if (!make_plan(a_in, &p)) return AQ_ESHAPE;
     // 64-row workgroups on wide layers: the pipelined kernel where the shapes and the address allow it
-    // 16-row workgroups on small networks: the kernel built for that case
-    const int kind = ((uintptr_t)a_in.c.obs & 15) == 0 ? fused_mlp_kernel_kind(a_in) : 0;
-    if (kind == 1) return launch_wide_mlp(a_in, st);
-    if (kind >= 2) return launch_rows16_mlp(a_in, st);
+    int wide_ld;
+    if (aligned && !p.half && p.nb == 2 && p.mt == 2 && wide_mlp_supported(a_in, &wide_ld)) return launch_wide_mlp(a_in, st);
     FwdArgs a = a_in;
     a.c.ld = p.ld;
     a.c.cst_n = p.cst_n;

@@ -195,7 +195,8 @@ __device__ __forceinline__ void narrow_reduce(const int32_t* part, const CPtrs& 
 // epilogues, which are what bounds small networks, do half the work per lane.
 template <int MT, int NB, bool ASYM, bool TAPS, bool HALF>
 __global__ __launch_bounds__(FT) void k_mlp_fused(const NetDev* __restrict__ netp, const CallArgs c,
-                                                  const TapArgs t) {
+                                                  const TapParam<TAPS> tp) {
+    const TapArgs t = taps_of(tp);
     extern __shared__ __align__(16) int8_t smem[];
     static_assert(!HALF || (MT == 1 && NB == 1), "16-row workgroups use one tile per wave");
     constexpr int ROWS = HALF ? 16 : 32 * MT;  // rows this workgroup owns
@@ -724,7 +725,8 @@ aq_status launch_fused_t(const FwdArgs& a, size_t lds, hipStream_t st) {
     }
     const int rows = HALF ? 16 : 32 * MT;
     const unsigned grid = (unsigned)((a.c.batch + rows - 1) / rows);
-    hipLaunchKernelGGL((k_mlp_fused<MT, NB, ASYM, TAPS, HALF>), dim3(grid), dim3(FT), lds, st, a.d_net, a.c, a.t);
+    hipLaunchKernelGGL((k_mlp_fused<MT, NB, ASYM, TAPS, HALF>), dim3(grid), dim3(FT), lds, st, a.d_net, a.c,
+                       TapParam<TAPS>(a.t));
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
 

@@ -35,12 +35,14 @@ aq_status launch_explore(void* d_actions, int64_t rows, int A, int head, const f
 
 // ---- 8-bit forward (forward_int8.hip)
 struct FwdArgs {
-    NetDev net;           // host copy, for planning
-    const NetDev* d_net;  // the same, in device memory
-    CallArgs c;
-    TapArgs t;
+    explicit FwdArgs(const NetDev& n) : net(n) {}
+    const NetDev& net;              // the handle's host copy, for planning
+    const NetDev* d_net = nullptr;  // the same, in device memory
+    CallArgs c{};
+    TapArgs t{};
+    bool taps = false;              // any pointer of `t` is set
     // host side only: per layer, the weights as nibbles for the few-row kernel (policies of at most 4 bits), or NULL
-    const uint8_t* w4[AQ_MAX_LAYERS];
+    const uint8_t* w4[AQ_MAX_LAYERS] = {};
 };
 
 // whole-network fused MLP kernel; returns AQ_ESHAPE when the network does not fit it

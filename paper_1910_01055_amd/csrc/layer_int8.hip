@@ -33,12 +33,13 @@ constexpr int ST_F32X4 = 2;   // first FC layer on fp32 observations, K a multip
 // stream and its latency, not bandwidth, sets the pace.  It costs registers, hence occupancy, so
 // layers with many workgroups keep the shallow pipeline.
 template <int W, int MT, int NB, bool ASYM, bool TAPS, bool DEEP>
-__global__ __launch_bounds__(W * 64, (W <= 2 && !DEEP) ? 4 : 1) void k_layer_int8(const NetDev* __restrict__ netp, const TapArgs t, const int l,
+__global__ __launch_bounds__(W * 64, (W <= 2 && !DEEP) ? 4 : 1) void k_layer_int8(const NetDev* __restrict__ netp, const TapParam<TAPS> tp, const int l,
                                                       const LayerIO io, const int64_t rows, const int stage_mode,
                                                       const int kc, const void* __restrict__ actions) {
     constexpr int ROWS = 32 * MT;
     constexpr int NT_ = W * 64;
     extern __shared__ __align__(16) int8_t xs[];
+    const TapArgs t = taps_of(tp);
     const int LD = kc * 32 + 16;
     const NetDev& a = *netp;
     const LayerDev& L = a.L[l];
@@ -399,7 +400,7 @@ static aq_status launch_layer_t(const FwdArgs& a, int l, const LayerIO& io, int6
                 return AQ_EHIP;                                                                                     \
             attr_set = true;                                                                                        \
         }                                                                                                           \
-        hipLaunchKernelGGL((k_layer_int8<W, MT, NB, AS, TP, DEEP>), grid, dim3(W * 64), lds, st, a.d_net, a.t, l, io, rows, \
+        hipLaunchKernelGGL((k_layer_int8<W, MT, NB, AS, TP, DEEP>), grid, dim3(W * 64), lds, st, a.d_net, TapParam<TP>(a.t), l, io, rows, \
                            stage_mode, kc, actions);                                                                \
     } while (0)
     if (asym) {

@@ -132,7 +132,8 @@ __device__ __forceinline__ float sum_rows4(float s) {
 // request_layer below.
 template <int MT, int NH, bool ASYM, bool TAPS, bool LATE = false>
 __global__ __launch_bounds__(RT, MT == 1 ? 2 : 4) void k_mlp_rows16(const NetDev* __restrict__ netp, const R16Args c,
-                                                                     const TapArgs t) {
+                                                                     const TapParam<TAPS> tp) {
+    const TapArgs t = taps_of(tp);
     constexpr int ROWS = 16 * MT;
     constexpr int NQ = 2 * MT;  // observation quads per thread at most (64 quads per row)
     __shared__ __align__(16) int8_t s_buf[2][ROWS * RLD];
@@ -804,12 +805,13 @@ __global__ __launch_bounds__(RT, MT == 1 ? 2 : 4) void k_mlp_rows16(const NetDev
 
 template <int MT, bool ASYM, bool TAPS, bool LATE = false>
 aq_status launch_rows16_t(const NetDev* d_net, const R16Args& ra, const TapArgs& t, hipStream_t st) {
+    const TapParam<TAPS> tp(t);
     const unsigned grid = (unsigned)((ra.batch + 16 * MT - 1) / (16 * MT));
     switch (ra.shape & 255) {
-        case 1: hipLaunchKernelGGL((k_mlp_rows16<MT, 0, ASYM, TAPS, LATE>), dim3(grid), dim3(RT), 0, st, d_net, ra, t); break;
-        case 2: hipLaunchKernelGGL((k_mlp_rows16<MT, 1, ASYM, TAPS, LATE>), dim3(grid), dim3(RT), 0, st, d_net, ra, t); break;
-        case 3: hipLaunchKernelGGL((k_mlp_rows16<MT, 2, ASYM, TAPS, LATE>), dim3(grid), dim3(RT), 0, st, d_net, ra, t); break;
-        case 4: hipLaunchKernelGGL((k_mlp_rows16<MT, 3, ASYM, TAPS, LATE>), dim3(grid), dim3(RT), 0, st, d_net, ra, t); break;
+        case 1: hipLaunchKernelGGL((k_mlp_rows16<MT, 0, ASYM, TAPS, LATE>), dim3(grid), dim3(RT), 0, st, d_net, ra, tp); break;
+        case 2: hipLaunchKernelGGL((k_mlp_rows16<MT, 1, ASYM, TAPS, LATE>), dim3(grid), dim3(RT), 0, st, d_net, ra, tp); break;
+        case 3: hipLaunchKernelGGL((k_mlp_rows16<MT, 2, ASYM, TAPS, LATE>), dim3(grid), dim3(RT), 0, st, d_net, ra, tp); break;
+        case 4: hipLaunchKernelGGL((k_mlp_rows16<MT, 3, ASYM, TAPS, LATE>), dim3(grid), dim3(RT), 0, st, d_net, ra, tp); break;
         default: return AQ_ESHAPE;
     }
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;

@@ -74,11 +74,12 @@ __global__ __launch_bounds__(256) void k_pack_nibbles(const v4i* __restrict__ wp
 // W4: weights read as nibbles (per-channel symmetric only).  PF: see above.
 template <bool ASYM, bool TAPS, int TR, bool W4, int PF>
 __global__ __launch_bounds__(SK_W * 64) void k_layer_skinny(const NetDev* __restrict__ netp, const SkinnyLayer L,
-                                                           const TapArgs t, const int l,
+                                                           const TapParam<TAPS> tp, const int l,
                                                            const LayerIO io, const int64_t rows, const int kchunk,
                                                            const int in_mode, const void* __restrict__ actions,
                                                            void* __restrict__ argmax_out) {
     extern __shared__ __align__(16) int8_t smem[];
+    const TapArgs t = taps_of(tp);
     static_assert(!(ASYM && W4), "nibble weights are per-channel symmetric codes");
     constexpr bool RS = ASYM || W4;  // the epilogue needs the row sums of the activations
     const NetDev& a = *netp;
@@ -360,7 +361,7 @@ aq_status skinny_launch(const SkinnyCall& c) {
             return AQ_EHIP;
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_layer_skinny<AS, TP, TRV, W4V, PFV>), c.grid, dim3(SK_W * 64), c.lds, c.st, c.d_net, c.sl, c.t,
+    hipLaunchKernelGGL((k_layer_skinny<AS, TP, TRV, W4V, PFV>), c.grid, dim3(SK_W * 64), c.lds, c.st, c.d_net, c.sl, TapParam<TP>(c.t),
                        c.l, c.io, c.rows, c.kchunk, c.in_mode, c.actions, c.argmax_out);
     return AQ_OK;
 }

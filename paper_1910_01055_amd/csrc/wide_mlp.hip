@@ -35,7 +35,8 @@ __host__ __device__ inline size_t wide_lds_bytes(int ld) {
 }
 
 template <bool TAPS>
-__global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp, const CallArgs c, const TapArgs t) {
+__global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp, const CallArgs c, const TapParam<TAPS> tp) {
+    const TapArgs t = taps_of(tp);
     extern __shared__ __align__(16) int8_t smem[];
     const NetDev& a = *netp;
     const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6), g = lane >> 5, mrow = lane & 31;
@@ -421,7 +422,7 @@ aq_status launch_wide_t(const FwdArgs& a, size_t lds, hipStream_t st) {
     });
     if (attr_err != hipSuccess) return AQ_EHIP;
     const unsigned grid = (unsigned)((a.c.batch + WROWS - 1) / WROWS);
-    hipLaunchKernelGGL((k_mlp_wide<TAPS>), dim3(grid), dim3(FT), lds, st, a.d_net, a.c, a.t);
+    hipLaunchKernelGGL((k_mlp_wide<TAPS>), dim3(grid), dim3(FT), lds, st, a.d_net, a.c, TapParam<TAPS>(a.t));
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
 
