@@ -61,6 +61,14 @@ struct LayerBuf {
 
 }  // namespace
 
+struct F32Store {
+    void* slab = nullptr;
+    F32Ptrs ptrs{};            // host copy, and its device copy for the whole-MLP kernel
+    F32Ptrs* d_ptrs = nullptr;
+    F32KeepTab tab{};
+    F32KeepTab* d_tab = nullptr;
+};
+
 struct aq_policy {
     aq_net net;
     std::vector<LayerBuf> L;
@@ -68,7 +76,8 @@ struct aq_policy {
     ActQ* actq = nullptr;
     int* status = nullptr;
     uint32_t* mm = nullptr;
-    uint32_t* keys = nullptr;
+    RangeSlot* slots = nullptr;   // kRangeSlots per activation tensor, neutral between calls
+    bool slots_dirty = false;     // a calibration ended early: clear them first
     NetDev h_net{};            // host copy of the device-resident network description
     NetDev* d_net = nullptr;
     QTab h_qtab{};             // the quantizer's table of the policy, host copy and device copy
@@ -96,9 +105,9 @@ struct aq_policy {
     bool h16_ready = false;
     int64_t cap_f16 = 0;
     void* act_f16[2] = {nullptr, nullptr};
-    // the learner's fp32 parameters, copied by aq_policy_set_params_fp32 (one allocation at its first call)
-    void* f32_slab = nullptr;
-    std::vector<float*> f32_w, f32_b, f32_gamma, f32_beta;
+    // the learner's fp32 parameters, copied by aq_policy_set_params_fp32, and the packed weights of parameters passed
+    // with a call (one allocation each, at the first call that needs it)
+    F32Store f32_kept, f32_passed;
     bool f32_ready = false;
     // policies of at most 4 bits, per-channel symmetric, under launch plan 4: the fully connected layers' weights
     // once more as nibbles, for the few-row kernel (one allocation when the plan is first chosen; rewritten by
@@ -106,7 +115,10 @@ struct aq_policy {
     void* w4_slab = nullptr;
     std::vector<uint8_t*> w4;
     bool w4_stale = true;
-    float* calib = nullptr;        // 2 * AQ_MAX_LAYERS floats: (min, max) per activation tensor, for aq_calibrate_fp32
+    // aq_calibrate_fp32's answer, in host memory that the GPU writes (made by its first call): the number of the
+    // calibration that is ready, then (min, max) per activation tensor
+    uint32_t* calib = nullptr;
+    uint32_t calib_ticket = 0;
     int64_t max_hidden_elems = 0;  // per sample, over hidden layer outputs
     int64_t max_out_elems = 0;     // per sample, over all layer outputs
 };
@@ -251,10 +263,9 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     p->layer_bytes = bytes;
     size_t off_status = take(256);
     size_t off_mm = take(256);
-    size_t off_keys = take(sizeof(uint32_t) * 2 * (AQ_MAX_LAYERS + 1));
+    size_t off_slots = take(sizeof(RangeSlot) * kRangeSlots * AQ_MAX_LAYERS);
     size_t off_net = take(sizeof(NetDev));
     size_t off_qtab = take(sizeof(QTab));
-    size_t off_calib = take(sizeof(float) * 2 * AQ_MAX_LAYERS);
     if (hipMalloc(&p->slab, bytes) != hipSuccess) {
         delete p;
         return AQ_ENOMEM;
@@ -287,10 +298,9 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     }
     p->status = (int*)(base + off_status);
     p->mm = (uint32_t*)(base + off_mm);
-    p->keys = (uint32_t*)(base + off_keys);
+    p->slots = (RangeSlot*)(base + off_slots);
     p->d_net = (NetDev*)(base + off_net);
     p->d_qtab = (QTab*)(base + off_qtab);
-    p->calib = (float*)(base + off_calib);
     p->actq = p->d_net->actq;  // device address arithmetic only
     for (int l = 0; l < net->n_layers; ++l) {
         fill_layer_dev(p, l, p->h_net.L[l]);
@@ -389,7 +399,9 @@ extern "C" aq_status aq_policy_destroy(aq_policy* p) {
     if (p->ln_x) (void)hipFree(p->ln_x);
     if (p->y_rows) (void)hipFree(p->y_rows);
     if (p->h16_slab) (void)hipFree(p->h16_slab);
-    if (p->f32_slab) (void)hipFree(p->f32_slab);
+    if (p->f32_kept.slab) (void)hipFree(p->f32_kept.slab);
+    if (p->f32_passed.slab) (void)hipFree(p->f32_passed.slab);
+    if (p->calib) (void)hipHostFree(p->calib);
     delete p;
     return AQ_OK;
 }
@@ -784,10 +796,10 @@ extern "C" aq_status aq_quantize_params(aq_policy* p, const float* const* h_d_w,
     if (!h_d_w) {  // the parameters kept by aq_policy_set_params_fp32
         if (h_d_b || h_d_gamma || h_d_beta) return AQ_EINVAL;
         if (!p->f32_ready) return AQ_ENOTQUANT;
-        h_d_w = p->f32_w.data();
-        h_d_b = p->f32_b.data();
-        h_d_gamma = p->f32_gamma.data();
-        h_d_beta = p->f32_beta.data();
+        h_d_w = p->f32_kept.ptrs.w;
+        h_d_b = p->f32_kept.ptrs.b;
+        h_d_gamma = p->f32_kept.ptrs.gamma;
+        h_d_beta = p->f32_kept.ptrs.beta;
     }
     for (int l = 0; l < nl; ++l)
         if (!h_d_w[l]) return AQ_EINVAL;
@@ -1004,63 +1016,137 @@ extern "C" aq_status aq_policy_forward_int8_static(aq_policy* p, const void* d_o
     return forward_int8_impl(p, d_obs, batch, d_actions, nullptr, nullptr, stream, &sc);
 }
 
-// The fp32 actor on explicit parameter arrays.  d_actions may be NULL (calibration only: the head is skipped).
-static aq_status forward_fp32_impl(aq_policy* p, const float* const* h_d_w, const float* const* h_d_b,
-                                   const float* const* h_d_gamma, const float* const* h_d_beta, const void* d_obs,
-                                   int64_t batch, void* d_actions, float* d_ranges_out, hipStream_t st) {
+// The fp32 actor on explicit parameter arrays (d_ptrs: the same table in device memory, or NULL).  d_actions may be
+// NULL (calibration only: the last layer is not run).  d_ranges_out, if given, receives the ranges; with `ready` it is
+// host memory and *ready becomes `ticket` once they are there.
+static aq_status forward_fp32_impl(aq_policy* p, const F32Ptrs& ptrs, const F32Ptrs* d_ptrs, const void* d_obs,
+                                   int64_t batch, void* d_actions, float* d_ranges_out, uint32_t* ready, uint32_t ticket,
+                                   hipStream_t st) {
     const int nl = p->net.n_layers;
-    aq_status s = ensure_f32(p, batch, st);
-    if (s != AQ_OK) return s;
     const int in_u8 = p->net.in_type == AQ_IN_U8;
-    if (d_ranges_out) {
-        s = launch_init_keys(p->keys, nl, st);
-        if (s != AQ_OK) return s;
-        const LayerBuf& b0 = p->L[0];
-        s = launch_minmax_keys(d_obs, in_u8, batch * (int64_t)b0.d.in_h * b0.d.in_w * b0.d.in_c, p->keys, st);
-        if (s != AQ_OK) return s;
+    RangeSlot* const slots = d_ranges_out ? p->slots : nullptr;
+    aq_status s = AQ_OK;
+    if (slots) {
+        if (p->slots_dirty) {
+            s = launch_fill_u32((uint32_t*)slots, (int)(sizeof(RangeSlot) / 4) * kRangeSlots * AQ_MAX_LAYERS, 0u, st);
+            if (s != AQ_OK) return s;
+        }
+        p->slots_dirty = true;
     }
+    int rt = 1;
+    if (fp32_mlp_fits(p->h_net, batch, &rt)) {
+        s = launch_fp32_mlp(p->h_net, p->d_net, ptrs, d_ptrs, d_obs, batch, d_actions, slots, rt, st);
+        if (s != AQ_OK) return s;
+    } else {
+        s = ensure_f32(p, batch, st);
+        if (s != AQ_OK) return s;
+        if (slots) {
+            const LayerBuf& b0 = p->L[0];
+            s = launch_input_range(d_obs, in_u8, batch * (int64_t)b0.d.in_h * b0.d.in_w * b0.d.in_c, slots, st);
+            if (s != AQ_OK) return s;
+        }
+        for (int l = 0; l < nl; ++l) {
+            const LayerBuf& b = p->L[l];
+            const bool last = l == nl - 1;
+            if (last && !d_actions) break;
+            const bool ln = !last && b.d.act == AQ_ACT_LN_TANH, argmax = last && p->net.head == AQ_HEAD_ARGMAX;
+            Fp32Layer L{};
+            L.wpk = ptrs.wpk[l];
+            L.b = ptrs.b[l];
+            L.K = b.K;
+            L.N = b.N;
+            L.relu = !last && b.d.act == AQ_ACT_RELU;
+            L.head = last && !argmax ? p->net.head : -1;
+            L.in_h = b.d.in_h;
+            L.in_w = b.d.in_w;
+            L.in_c = b.d.in_c;
+            L.kh = b.d.kh;
+            L.kw = b.d.kw;
+            L.stride = b.d.stride;
+            L.oh = b.oh;
+            L.ow = b.ow;
+            const int64_t rows_l = batch * b.oh * b.ow;
+            const void* in = l == 0 ? d_obs : (const void*)p->act_f32[(l - 1) & 1];
+            float* out = last && !argmax ? (float*)d_actions : p->act_f32[l & 1];
+            RangeSlot* const sl = slots && !last ? slots + (l + 1) * kRangeSlots : nullptr;
+            s = launch_fp32_layer(L, in, l == 0 ? in_u8 : 0, out, rows_l, ln ? nullptr : sl, st);
+            if (s != AQ_OK) return s;
+            if (ln) {
+                s = launch_fp32_ln_tanh(out, rows_l, b.N, ptrs.gamma[l], ptrs.beta[l], p->net.ln_eps, sl, st);
+                if (s != AQ_OK) return s;
+            }
+            if (argmax) {
+                s = launch_fp32_argmax(out, rows_l, b.N, (int32_t*)d_actions, st);
+                if (s != AQ_OK) return s;
+            }
+        }
+    }
+    if (slots) {
+        s = launch_ranges_out(slots, nl, d_ranges_out, ready, ticket, st);
+        if (s != AQ_OK) return s;
+        p->slots_dirty = false;
+    }
+    return AQ_OK;
+}
+
+// the caller's arrays of per-layer pointers (the optional ones may be absent) as one table
+static F32Ptrs f32_ptr_table(int nl, const float* const* w, const float* const* b, const float* const* gamma,
+                             const float* const* beta) {
+    F32Ptrs t{};
+    for (int l = 0; l < nl; ++l) {
+        t.w[l] = w[l];
+        t.b[l] = b ? b[l] : nullptr;
+        t.gamma[l] = gamma ? gamma[l] : nullptr;
+        t.beta[l] = beta ? beta[l] : nullptr;
+    }
+    return t;
+}
+
+// Storage for a set of fp32 parameters: the packed weights, with `keep` also row-major copies, biases, gains and
+// offsets, and the tables over them.
+static aq_status ensure_f32_store(aq_policy* p, F32Store& S, bool keep, hipStream_t st) {
+    if (S.slab) return AQ_OK;
+    if (capturing(st)) return AQ_ETOOBIG;
+    const int nl = p->net.n_layers;
+    size_t bytes = 0;
+    int blk = 0;
+    F32KeepTab tab{};
+    std::vector<size_t> offs;
+    auto add = [&](int64_t n, int kind, int l) {
+        offs.push_back(bytes);
+        bytes += ((size_t)n * 4 + 255) / 256 * 256;
+        tab.blk0[tab.n] = blk;
+        tab.e[tab.n++] = F32KeepTab::Entry{nullptr, n, kind, l, p->L[l].N, p->L[l].K};
+        blk += (int)((n + kKeepPiece - 1) / kKeepPiece);
+    };
     for (int l = 0; l < nl; ++l) {
         const LayerBuf& b = p->L[l];
-        const bool last = l == nl - 1;
-        if (last && !d_actions) break;
-        Fp32Layer L{};
-        L.w = h_d_w[l];
-        L.b = h_d_b ? h_d_b[l] : nullptr;
-        L.gamma = h_d_gamma ? h_d_gamma[l] : nullptr;
-        L.beta = h_d_beta ? h_d_beta[l] : nullptr;
-        L.K = b.K;
-        L.N = b.N;
-        L.act = b.d.act;
-        L.in_h = b.d.in_h;
-        L.in_w = b.d.in_w;
-        L.in_c = b.d.in_c;
-        L.kh = b.d.kh;
-        L.kw = b.d.kw;
-        L.stride = b.d.stride;
-        L.oh = b.oh;
-        L.ow = b.ow;
-        const int64_t rows_l = batch * b.oh * b.ow;
-        const void* in = l == 0 ? d_obs : (const void*)p->act_f32[(l - 1) & 1];
-        float* out = p->act_f32[l & 1];
-        s = launch_fp32_layer(L, in, l == 0 ? in_u8 : 0, out, rows_l, !last && b.d.act == AQ_ACT_RELU, st);
-        if (s != AQ_OK) return s;
-        if (!last && b.d.act == AQ_ACT_LN_TANH) {
-            s = launch_fp32_ln_tanh(out, rows_l, b.N, L.gamma, L.beta, p->net.ln_eps, st);
-            if (s != AQ_OK) return s;
+        if (keep) {
+            add((int64_t)b.N * b.K, 0, l);
+            for (int i = 1; i < 4; ++i) add(b.N, i, l);
         }
-        if (!last && d_ranges_out) {
-            s = launch_minmax_keys(out, 0, rows_l * b.N, p->keys + 2 * (l + 1), st);
-            if (s != AQ_OK) return s;
-        }
-        if (last) {
-            s = launch_fp32_head(out, rows_l, b.N, p->net.head, d_actions, st);
-            if (s != AQ_OK) return s;
-        }
+        add((int64_t)((b.N + 15) / 16) * ((b.K + 15) / 16) * 256, 4, l);
     }
-    if (d_ranges_out) {
-        s = launch_keys_to_ranges(p->keys, 2 * nl, d_ranges_out, st);
-        if (s != AQ_OK) return s;
+    tab.blocks = blk;
+    const size_t off_ptrs = bytes, off_tab = bytes + (sizeof(F32Ptrs) + 255) / 256 * 256;
+    void* slab = nullptr;
+    if (hipMalloc(&slab, off_tab + sizeof(F32KeepTab)) != hipSuccess) return AQ_ENOMEM;
+    F32Ptrs ptrs{};
+    for (int i = 0; i < tab.n; ++i) {
+        F32KeepTab::Entry& e = tab.e[i];
+        e.dst = (float*)((char*)slab + offs[i]);
+        (e.kind == 0 ? ptrs.w : e.kind == 1 ? ptrs.b : e.kind == 2 ? ptrs.gamma : e.kind == 3 ? ptrs.beta : ptrs.wpk)[e.layer] = e.dst;
     }
+    S.d_ptrs = (F32Ptrs*)((char*)slab + off_ptrs);
+    S.d_tab = (F32KeepTab*)((char*)slab + off_tab);
+    if (hipMemcpy(S.d_ptrs, &ptrs, sizeof(ptrs), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(S.d_tab, &tab, sizeof(tab), hipMemcpyHostToDevice) != hipSuccess) {
+        (void)hipFree(slab);
+        return AQ_EHIP;
+    }
+    S.slab = slab;
+    S.ptrs = ptrs;
+    S.tab = tab;
     return AQ_OK;
 }
 
@@ -1073,8 +1159,14 @@ extern "C" aq_status aq_policy_forward_fp32_params(aq_policy* p, const float* co
     if (!d_obs || !d_actions) return AQ_EINVAL;
     for (int l = 0; l < p->net.n_layers; ++l)
         if (!h_d_w[l]) return AQ_EINVAL;
-    return forward_fp32_impl(p, h_d_w, h_d_b, h_d_gamma, h_d_beta, d_obs, batch, d_actions, d_ranges_out,
-                             as_stream(stream));
+    hipStream_t st = as_stream(stream);
+    aq_status s = ensure_f32_store(p, p->f32_passed, false, st);
+    if (s != AQ_OK) return s;
+    F32Ptrs ptrs = f32_ptr_table(p->net.n_layers, h_d_w, h_d_b, h_d_gamma, h_d_beta);
+    s = launch_keep_params(ptrs, p->f32_passed.d_tab, p->f32_passed.tab.blocks, st);
+    if (s != AQ_OK) return s;
+    for (int l = 0; l < p->net.n_layers; ++l) ptrs.wpk[l] = p->f32_passed.ptrs.wpk[l];
+    return forward_fp32_impl(p, ptrs, nullptr, d_obs, batch, d_actions, d_ranges_out, nullptr, 0, st);
 }
 
 extern "C" aq_status aq_policy_set_params_fp32(aq_policy* p, const float* const* h_d_w, const float* const* h_d_b,
@@ -1085,41 +1177,12 @@ extern "C" aq_status aq_policy_set_params_fp32(aq_policy* p, const float* const*
     for (int l = 0; l < nl; ++l)
         if (!h_d_w[l]) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
-    if (!p->f32_slab) {
-        if (capturing(st)) return AQ_ETOOBIG;
-        size_t bytes = 0;
-        std::vector<size_t> offs;
-        auto take = [&](size_t n) {
-            size_t off = bytes;
-            bytes += (n + 255) / 256 * 256;
-            return off;
-        };
-        for (const LayerBuf& b : p->L) {
-            offs.push_back(take((size_t)b.N * b.K * 4));
-            for (int i = 0; i < 3; ++i) offs.push_back(take((size_t)b.N * 4));
-        }
-        if (hipMalloc(&p->f32_slab, bytes) != hipSuccess) return AQ_ENOMEM;
-        char* base = (char*)p->f32_slab;
-        size_t oi = 0;
-        for (int l = 0; l < nl; ++l) {
-            p->f32_w.push_back((float*)(base + offs[oi++]));
-            p->f32_b.push_back((float*)(base + offs[oi++]));
-            p->f32_gamma.push_back((float*)(base + offs[oi++]));
-            p->f32_beta.push_back((float*)(base + offs[oi++]));
-        }
-    }
-    for (int l = 0; l < nl; ++l) {
-        const LayerBuf& b = p->L[l];
-        const size_t nb = (size_t)b.N * 4;
-        AQ_HIP_CHECK(hipMemcpyAsync(p->f32_w[l], h_d_w[l], (size_t)b.N * b.K * 4, hipMemcpyDeviceToDevice, st));
-        // absent biases, gains and offsets take their defaults (0, 1, 0), written by a fill launch
-        if (h_d_b && h_d_b[l]) AQ_HIP_CHECK(hipMemcpyAsync(p->f32_b[l], h_d_b[l], nb, hipMemcpyDeviceToDevice, st));
-        else if (launch_fill_u32((uint32_t*)p->f32_b[l], b.N, 0u, st) != AQ_OK) return AQ_EHIP;
-        if (h_d_gamma && h_d_gamma[l]) AQ_HIP_CHECK(hipMemcpyAsync(p->f32_gamma[l], h_d_gamma[l], nb, hipMemcpyDeviceToDevice, st));
-        else if (launch_fill_u32((uint32_t*)p->f32_gamma[l], b.N, 0x3f800000u, st) != AQ_OK) return AQ_EHIP;
-        if (h_d_beta && h_d_beta[l]) AQ_HIP_CHECK(hipMemcpyAsync(p->f32_beta[l], h_d_beta[l], nb, hipMemcpyDeviceToDevice, st));
-        else if (launch_fill_u32((uint32_t*)p->f32_beta[l], b.N, 0u, st) != AQ_OK) return AQ_EHIP;
-    }
+    aq_status s = ensure_f32_store(p, p->f32_kept, true, st);
+    if (s != AQ_OK) return s;
+    // (absent biases, gains and offsets take their defaults 0, 1, 0)
+    s = launch_keep_params(f32_ptr_table(nl, h_d_w, h_d_b, h_d_gamma, h_d_beta), p->f32_kept.d_tab,
+                           p->f32_kept.tab.blocks, st);
+    if (s != AQ_OK) return s;
     p->f32_ready = true;
     return AQ_OK;
 }
@@ -1130,8 +1193,7 @@ extern "C" aq_status aq_policy_forward_fp32(aq_policy* p, const void* d_obs, int
     if (!p->f32_ready) return AQ_ENOTQUANT;
     if (batch == 0) return AQ_OK;
     if (!d_obs || !d_actions) return AQ_EINVAL;
-    return forward_fp32_impl(p, p->f32_w.data(), p->f32_b.data(), p->f32_gamma.data(), p->f32_beta.data(), d_obs, batch,
-                             d_actions, nullptr, as_stream(stream));
+    return forward_fp32_impl(p, p->f32_kept.ptrs, p->f32_kept.d_ptrs, d_obs, batch, d_actions, nullptr, nullptr, 0, as_stream(stream));
 }
 
 extern "C" aq_status aq_calibrate_fp32(aq_policy* p, const void* d_obs, int64_t batch, aq_range* h_ranges_out,
@@ -1140,13 +1202,34 @@ extern "C" aq_status aq_calibrate_fp32(aq_policy* p, const void* d_obs, int64_t 
     if (!p->f32_ready) return AQ_ENOTQUANT;
     hipStream_t st = as_stream(stream);
     if (capturing(st)) return AQ_EINVAL;  // the call has to wait for its result
-    const aq_status s = forward_fp32_impl(p, p->f32_w.data(), p->f32_b.data(), p->f32_gamma.data(), p->f32_beta.data(),
-                                          d_obs, batch, nullptr, p->calib, st);
-    if (s != AQ_OK) return s;
-    float h[2 * AQ_MAX_LAYERS];
     const int nl = p->net.n_layers;
-    AQ_HIP_CHECK(hipMemcpyAsync(h, p->calib, sizeof(float) * 2 * nl, hipMemcpyDeviceToHost, st));
-    AQ_HIP_CHECK(hipStreamSynchronize(st));
+    // The ranges come back through host memory that the last kernel writes and this thread watches: a copy to pageable
+    // memory and a stream synchronization cost 23 us, a third of a frame policy's whole calibration.
+    if (!p->calib) {
+        if (hipHostMalloc((void**)&p->calib, 64 + sizeof(float) * 2 * AQ_MAX_LAYERS, hipHostMallocDefault) != hipSuccess) {
+            p->calib = nullptr;
+            return AQ_ENOMEM;
+        }
+        __atomic_store_n(p->calib, 0u, __ATOMIC_RELEASE);
+    }
+    void* d_calib = nullptr;
+    AQ_HIP_CHECK(hipHostGetDevicePointer(&d_calib, p->calib, 0));
+    if (++p->calib_ticket == 0) p->calib_ticket = 1;
+    const uint32_t ticket = p->calib_ticket;
+    const aq_status s = forward_fp32_impl(p, p->f32_kept.ptrs, p->f32_kept.d_ptrs, d_obs, batch, nullptr, (float*)((char*)d_calib + 64),
+                                          (uint32_t*)d_calib, ticket, st);
+    if (s != AQ_OK) return s;
+    // (the stream is asked now and then: a failed one never sets the word)
+    for (int64_t i = 1; __atomic_load_n(p->calib, __ATOMIC_ACQUIRE) != ticket; ++i) {
+        if (i % 65536) {
+            __builtin_ia32_pause();
+            continue;
+        }
+        const hipError_t e = hipStreamQuery(st);
+        if (e == hipErrorNotReady) continue;
+        if (e != hipSuccess || __atomic_load_n(p->calib, __ATOMIC_ACQUIRE) != ticket) return AQ_EHIP;
+    }
+    const float* h = (const float*)((const char*)p->calib + 64);
     for (int l = 0; l < nl; ++l) {
         h_ranges_out[l].lo = h[2 * l];
         h_ranges_out[l].hi = h[2 * l + 1];

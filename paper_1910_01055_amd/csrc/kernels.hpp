@@ -87,21 +87,72 @@ aq_status launch_head_rows(const float* y, int64_t rows, int N, int head, void* 
 
 // ---- fp32 actor (forward_fp32.hip)
 struct Fp32Layer {
-    const float* w;
+    const float* wpk;  // weights in operand order, see forward_fp32.hip
     const float* b;
-    const float* gamma;
-    const float* beta;
-    int K, N, act;
+    int K, N;
+    int relu;
+    int head;  // last layer with an elementwise head applied to the outputs (aq_head), else -1
     int in_h, in_w, in_c, kh, kw, stride, oh, ow;
 };
-aq_status launch_fp32_layer(const Fp32Layer& L, const void* in, int in_u8, float* out, int64_t rows, int relu,
+// (min, max) of an activation tensor as it is collected: kRangeSlots pairs per tensor, each an order-preserving key of
+// the float (the minimum's complemented, so that both are maxima and zero is neutral)
+constexpr int kRangeSlots = 512;
+struct RangeSlot {
+    uint32_t not_lo, hi;
+};
+struct F32Ptrs {
+    const float* w[AQ_MAX_LAYERS];    // row-major
+    const float* wpk[AQ_MAX_LAYERS];  // in operand order
+    const float* b[AQ_MAX_LAYERS];
+    const float* gamma[AQ_MAX_LAYERS];
+    const float* beta[AQ_MAX_LAYERS];
+};
+// the whole-MLP kernel's view of them: by value (parameters passed with the call) or one pointer to the handle's
+// table, which keeps 320 bytes out of every launch
+template <bool BYVAL>
+struct F32PtrArg {
+    F32Ptrs p;
+    F32PtrArg(const F32Ptrs& v, const F32Ptrs*) : p(v) {}
+};
+template <>
+struct F32PtrArg<false> {
+    const F32Ptrs* p;
+    F32PtrArg(const F32Ptrs&, const F32Ptrs* d) : p(d) {}
+};
+__device__ __forceinline__ const F32Ptrs& f32_ptrs(const F32PtrArg<true>& a) { return a.p; }
+__device__ __forceinline__ const F32Ptrs& f32_ptrs(const F32PtrArg<false>& a) { return *a.p; }
+struct F32Call {
+    const void* obs;
+    void* actions;  // NULL: calibration, the last layer is not run
+    int64_t batch;
+    RangeSlot* slots;  // kRangeSlots per activation tensor, or NULL
+    int ld;            // LDS row stride, floats
+};
+// where a set of fp32 parameters goes: each array starts at workgroup blk0 of the copy's grid, one workgroup per
+// kKeepPiece values
+constexpr int kKeepPiece = 4096;
+struct F32KeepTab {
+    struct Entry {
+        float* dst;
+        int64_t count;
+        int kind, layer, N, K;  // kind: 0 weights, 1 bias, 2 gain, 3 offset, 4 packed weights
+    };
+    Entry e[5 * AQ_MAX_LAYERS];
+    int blk0[5 * AQ_MAX_LAYERS];
+    int n, blocks;
+};
+aq_status launch_fp32_layer(const Fp32Layer& L, const void* in, int in_u8, float* out, int64_t rows, RangeSlot* slots,
                             hipStream_t st);
+// whether the network runs as one launch at this batch; rt = 16-row tiles per workgroup then
+bool fp32_mlp_fits(const NetDev& n, int64_t batch, int* rt);
+aq_status launch_fp32_mlp(const NetDev& n, const NetDev* d_net, const F32Ptrs& ptrs, const F32Ptrs* d_ptrs, const void* obs,
+                          int64_t batch, void* actions, RangeSlot* slots, int rt, hipStream_t st);
 aq_status launch_fp32_ln_tanh(float* x, int64_t rows, int N, const float* gamma, const float* beta, float eps,
-                              hipStream_t st);
-aq_status launch_fp32_head(const float* y, int64_t rows, int N, int head, void* actions, hipStream_t st);
-aq_status launch_init_keys(uint32_t* keys, int n_pairs, hipStream_t st);
-aq_status launch_minmax_keys(const void* x, int is_u8, int64_t n, uint32_t* keys, hipStream_t st);
-aq_status launch_keys_to_ranges(const uint32_t* keys, int n, float* out, hipStream_t st);
+                              RangeSlot* slots, hipStream_t st);
+aq_status launch_fp32_argmax(const float* y, int64_t rows, int N, int32_t* actions, hipStream_t st);
+aq_status launch_input_range(const void* x, int is_u8, int64_t n, RangeSlot* slots, hipStream_t st);
+aq_status launch_ranges_out(RangeSlot* slots, int n, float* out, uint32_t* ready, uint32_t ticket, hipStream_t st);
+aq_status launch_keep_params(const F32Ptrs& src, const F32KeepTab* d_tab, int blocks, hipStream_t st);
 
 
 // ---- half-precision actor (fp16_actor.hip)

@@ -1,0 +1,81 @@
+"""The fp32 actor's kernels against the CPU oracle at the sizes where they can go wrong: every tile of the per-layer
+kernel with ragged rows, features and K, convolutions whose windows allow no 16-byte loads, and the whole-MLP kernel's
+layer widths, heads and row counts."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import policy as O
+from paper_1910_01055_amd import synth
+import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+fc, conv = synth.fc, synth.conv
+
+
+def _cases():
+    small = lambda *a, **k: synth.small_net(*a, **k)  # noqa: E731
+    return {
+        # one launch: widths around whole stages and feature tiles, each head, both input types
+        "mlp_tanh": (small([fc(17, 33, "relu"), fc(33, 47, "none"), fc(47, 6, "none")]), [1, 15, 17, 300]),
+        "mlp_ln": (small([fc(111, 400, "ln_tanh"), fc(400, 300, "relu"), fc(300, 8, "none")]), [1, 97]),
+        "mlp_argmax": (small([fc(5, 16, "relu"), fc(16, 64, "relu"), fc(64, 18, "none")], head="argmax"), [1, 33]),
+        "mlp_wide_head": (small([fc(31, 64, "relu"), fc(64, 100, "none")], head="linear"), [1, 40]),
+        "mlp_wide_argmax": (small([fc(31, 64, "relu"), fc(64, 70, "none")], head="argmax"), [50]),
+        "mlp_u8": (small([fc(48, 65, "relu"), fc(65, 5, "none")], head="linear", in_type="u8"), [3, 64]),
+        "mlp_single": (small([fc(50, 37, "none")]), [19]),
+        "mlp_two_tiles": (small([fc(20, 256, "relu"), fc(256, 21, "none")]), [8193 + 16]),  # 32 rows per workgroup
+        # a launch per layer: wide layers, few and many rows
+        "layers_few_rows": (small([fc(67, 1300, "ln_tanh"), fc(1300, 1300, "relu"), fc(1300, 21, "none")]), [1, 16, 17, 70]),
+        "layers_many_rows": (small([fc(70, 1300, "relu"), fc(1300, 130, "none"), fc(130, 66, "none")], head="argmax"), [513, 2100]),
+        "conv": (small([conv(20, 20, 4, 33, 8, 8, 4, "relu"), conv(4, 4, 33, 20, 2, 2, 1, "none"), fc(180, 24, "relu"), fc(24, 5, "none")],
+                       head="linear", in_type="u8", init="he_normal"), [1, 70]),
+        "conv_odd_window": (small([conv(9, 10, 3, 5, 3, 2, 2, "relu"), conv(4, 5, 5, 7, 3, 3, 1, "relu"), fc(42, 11, "none")],
+                                  head="linear", in_type="u8", init="he_normal"), [1, 200]),
+        "conv_f32": (small([conv(12, 12, 3, 64, 4, 4, 2, "relu"), conv(5, 5, 64, 65, 3, 3, 1, "relu"), fc(585, 4, "none")],
+                           head="tanh", init="he_normal"), [90]),
+    }
+
+
+@pytest.mark.parametrize("name,batch", [(n, b) for n, (_, bs) in _cases().items() for b in bs])
+def test_fp32_actor_and_ranges(aq, name, batch):
+    net = _cases()[name][0]
+    print(f"[fp32] {name} batch={batch}", flush=True)
+    params = synth.make_params(net, nonzero_bias=True)
+    obs = synth.make_obs(net, batch)
+    if net["in_type"] == "u8":  # frames are consumed as raw codes: keep the activations near one
+        params[0]["w"] /= 255.0
+    ref, ranges = O.OraclePolicy(net).forward_fp32(params, obs)
+    P = aq.Policy(net)
+    w, b, g, be = U.upload_params(params)
+    P.policy_set_params_fp32(w, b, g, be)
+    d_obs = U.to_dev(obs)
+    argmax = net["head"] == "argmax"
+    out = torch.full((batch,) if argmax else (batch, synth.action_dim(net)), -7, dtype=torch.int32 if argmax else torch.float32,
+                     device=U.DEV)
+    passed = torch.empty_like(out)
+    P.policy_forward_fp32(d_obs, out)
+    P.policy_forward_fp32_params(w, b, g, be, d_obs, passed)
+    for _ in range(2):  # (a calibration leaves its accumulators ready for the next)
+        got = np.array(P.calibrate_fp32(d_obs))
+        want = np.array(ranges)
+        assert (np.abs(got - want) <= 1e-5 * np.abs(want) + 1e-6).all()
+    torch.cuda.synchronize()
+    assert torch.equal(out, passed)
+    if argmax:
+        assert (out.cpu().numpy() == ref).mean() >= 0.99
+    else:
+        assert U.close(out.cpu().numpy(), ref).all()
+    P.close()
+
+
+def test_fp32_calibration_of_a_smaller_batch_forgets_the_larger_ones_ranges(aq):
+    net = synth.net_config("cfg4")
+    params = synth.make_params(net)
+    P = aq.Policy(net)
+    P.policy_set_params_fp32(*U.upload_params(params))
+    obs = U.to_dev(synth.make_obs(net, 12))
+    first = P.calibrate_fp32(obs[:2])
+    P.calibrate_fp32(obs)
+    assert P.calibrate_fp32(obs[:2]) == first
+    P.close()
