@@ -75,7 +75,7 @@ struct aq_policy {
     void* slab = nullptr;  // all per-layer buffers live in one allocation
     ActQ* actq = nullptr;
     int* status = nullptr;
-    uint32_t* mm = nullptr;
+    QOut qout{};
     RangeSlot* slots = nullptr;   // kRangeSlots per activation tensor, neutral between calls
     bool slots_dirty = false;     // a calibration ended early: clear them first
     NetDev h_net{};            // host copy of the device-resident network description
@@ -148,6 +148,12 @@ static void fill_layer_dev(const aq_policy* p, int l, LayerDev& d) {
     d.stride = b.d.stride;
     d.oh = b.oh;
     d.ow = b.ow;
+}
+
+// workgroups that share a layer's range reduction (per-tensor scheme)
+static int range_blocks(int N, int K) {
+    const int64_t b = ((int64_t)N * K / 4 + 1 + 255) / 256;
+    return b > 256 ? 256 : (int)b;
 }
 
 static hipStream_t as_stream(void* s) { return (hipStream_t)s; }
@@ -262,7 +268,10 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     }
     p->layer_bytes = bytes;
     size_t off_status = take(256);
-    size_t off_mm = take(256);
+    int rng_blks = 0;
+    for (const LayerBuf& b : p->L) rng_blks += range_blocks(b.N, b.K);
+    size_t off_part = take((size_t)rng_blks * 3 * 4);
+    size_t off_qptrs = take(sizeof(QPtrs));
     size_t off_slots = take(sizeof(RangeSlot) * kRangeSlots * AQ_MAX_LAYERS);
     size_t off_net = take(sizeof(NetDev));
     size_t off_qtab = take(sizeof(QTab));
@@ -297,11 +306,11 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         b.beta = (float*)b.sh;
     }
     p->status = (int*)(base + off_status);
-    p->mm = (uint32_t*)(base + off_mm);
     p->slots = (RangeSlot*)(base + off_slots);
     p->d_net = (NetDev*)(base + off_net);
     p->d_qtab = (QTab*)(base + off_qtab);
     p->actq = p->d_net->actq;  // device address arithmetic only
+    p->qout = QOut{p->actq, p->d_net->fast, p->status, (QPtrs*)(base + off_qptrs), (uint32_t*)(base + off_part)};
     for (int l = 0; l < net->n_layers; ++l) {
         fill_layer_dev(p, l, p->h_net.L[l]);
     }
@@ -320,7 +329,8 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         q.w_qmax = (1 << wbits) - 1;
         q.w_qw = (1 << (wbits - 1)) - 1;
         q.w_qdenom = net->qdenom == 256 ? (float)(q.w_qmax + 1) : (float)q.w_qmax;
-        int row_blk = 0, cst_blk = 0, rng_blk = 0;
+        int row_blk = 0, rng_blk = 0;
+        for (int l = 0; l < AQ_MAX_LAYERS; ++l) q.row_blk0[l] = q.rng_blk0[l] = 0x7fffffff;
         for (int l = 0; l < net->n_layers; ++l) {
             const LayerBuf& b = p->L[l];
             QLayerTab& t = q.L[l];
@@ -329,18 +339,13 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
             t.N = b.N; t.K = b.K; t.KS = b.KS;
             t.ln = b.d.act == AQ_ACT_LN_TANH;
             t.requant = l < net->n_layers - 1 && !t.ln;
-            t.row_blk0 = row_blk;
-            t.cst_blk0 = cst_blk;
-            t.rng_blk0 = rng_blk;
-            const int64_t n4 = (int64_t)b.N * b.K / 4 + 1;
-            int64_t rb = (n4 + 255) / 256;
-            t.rng_blks = (int)(rb < 1 ? 1 : (rb > 256 ? 256 : rb));
-            row_blk += (b.N + 3) / 4;
-            cst_blk += (b.N + 255) / 256;
+            q.row_blk0[l] = row_blk;
+            q.rng_blk0[l] = rng_blk;
+            t.rng_blks = range_blocks(b.N, b.K);
+            row_blk += (b.N + QR_ROWS - 1) / QR_ROWS;
             rng_blk += t.rng_blks;
         }
         q.row_blks = row_blk;
-        q.cst_blks = cst_blk;
         q.rng_blks_total = rng_blk;
         if (hipMemcpy(p->d_qtab, &q, sizeof(QTab), hipMemcpyHostToDevice) != hipSuccess) {
             (void)hipFree(p->slab);
@@ -602,34 +607,30 @@ extern "C" aq_status aq_policy_blob_size(const aq_policy* p, uint64_t* bytes) {
     return AQ_OK;
 }
 
+static BlobHead blob_head(const uint32_t (&w)[6]) {
+    BlobHead h;
+    for (int i = 0; i < 6; ++i) h.w[i] = w[i];
+    h.tail_words = (int)(kTailBytes / 4);
+    return h;
+}
+
 extern "C" aq_status aq_policy_export_blob(const aq_policy* p, void* d_blob, uint64_t bytes, void* stream) {
     if (!p || !d_blob || ((uintptr_t)d_blob & 15)) return AQ_EINVAL;
     if (bytes < kBlobHeader + kBlobTail + p->layer_bytes) return AQ_EINVAL;
     if (!p->quantized) return AQ_ENOTQUANT;
-    hipStream_t st = as_stream(stream);
     uint32_t w[6];
     blob_words(p, w);
-    char* dst = (char*)d_blob;
-    aq_status s = launch_blob_header_write((uint32_t*)dst, w, st);
-    if (s != AQ_OK) return s;
-    AQ_HIP_CHECK(hipMemcpyAsync(dst + kBlobHeader, p->d_net->actq, kTailBytes, hipMemcpyDeviceToDevice, st));
-    AQ_HIP_CHECK(hipMemcpyAsync(dst + kBlobHeader + kBlobTail, p->slab, p->layer_bytes, hipMemcpyDeviceToDevice, st));
-    return AQ_OK;
+    return launch_blob_export(blob_head(w), p->d_net->actq, p->slab, (int64_t)p->layer_bytes, d_blob, as_stream(stream));
 }
 
 extern "C" aq_status aq_policy_import_blob(aq_policy* p, const void* d_blob, uint64_t bytes, void* stream) {
     if (!p || !d_blob || ((uintptr_t)d_blob & 15)) return AQ_EINVAL;
     if (bytes < kBlobHeader + kBlobTail + p->layer_bytes) return AQ_EINVAL;
-    hipStream_t st = as_stream(stream);
     uint32_t w[6];
     blob_words(p, w);
-    const char* src = (const char*)d_blob;
-    aq_status s = launch_fill_u32((uint32_t*)p->status, 1, 0u, st);
+    const aq_status s = launch_blob_import(blob_head(w), p->d_net->actq, p->slab, (int64_t)p->layer_bytes, d_blob, p->status,
+                                           as_stream(stream));
     if (s != AQ_OK) return s;
-    s = launch_blob_header_check((const uint32_t*)src, w, p->status, st);
-    if (s != AQ_OK) return s;
-    AQ_HIP_CHECK(hipMemcpyAsync(p->d_net->actq, src + kBlobHeader, kTailBytes, hipMemcpyDeviceToDevice, st));
-    AQ_HIP_CHECK(hipMemcpyAsync(p->slab, src + kBlobHeader + kBlobTail, p->layer_bytes, hipMemcpyDeviceToDevice, st));
     p->w4_stale = true;
     p->quantized = true;
     return AQ_OK;
@@ -639,98 +640,77 @@ extern "C" aq_status aq_policy_import_blob(aq_policy* p, const void* d_blob, uin
 // n-bit fields (n = the policy's weight precision) followed by the layer's constants verbatim.
 namespace {
 constexpr uint32_t kPackedMagic = 0x50515141u;  // "AQQP"
-struct PackedLayout {
-    std::vector<size_t> w_off, w_bytes, c_off, c_src, c_bytes;  // blob offsets / slab offsets per layer
-    size_t total = 0;
-};
 int policy_wbits(const aq_policy* p) { return p->net.wbits ? p->net.wbits : 8; }
-PackedLayout packed_layout(const aq_policy* p) {
-    PackedLayout L;
-    const int bits = policy_wbits(p);
+// (also the grid of the launch: workgroup 0 for header and tail, then a layer's codes and its constants)
+PackedArgs packed_layout(const aq_policy* p, size_t* total) {
+    PackedArgs a{};
+    a.n_layers = p->net.n_layers;
+    a.bits = policy_wbits(p);
+    a.off = p->h_net.asym ? 128 : (1 << (a.bits - 1)) - 1;
+    a.blocks = 1;
     size_t at = kBlobHeader + kBlobTail;
     const char* base = (const char*)p->slab;
     for (size_t l = 0; l < p->L.size(); ++l) {
         const LayerBuf& b = p->L[l];
+        PackedLayer& q = a.L[l];
         const size_t wb = (size_t)b.NT * b.KS * 1024;
         const size_t begin = (size_t)((const char*)b.wp - base);
         const size_t end = l + 1 < p->L.size() ? (size_t)((const char*)p->L[l + 1].wp - base) : p->layer_bytes;
-        L.w_off.push_back(at);
-        L.w_bytes.push_back(wb / 8 * bits);
-        at += (wb / 8 * bits + 255) / 256 * 256;
-        L.c_off.push_back(at);
-        L.c_src.push_back(begin + wb);
-        L.c_bytes.push_back(end - begin - wb);
-        at += end - begin - wb;
+        q.w_off = (int64_t)at;
+        q.w_src = (int64_t)begin;
+        q.groups = (int64_t)(wb / 32);
+        at += (wb / 8 * a.bits + 255) / 256 * 256;
+        q.c_off = (int64_t)at;
+        q.c_src = (int64_t)(begin + wb);
+        q.c_bytes = (int64_t)(end - begin - wb);
+        at += (size_t)q.c_bytes;
+        q.N = b.N;
+        q.K = b.K;
+        q.KS = b.KS;
+        q.blk0 = a.blocks;
+        q.code_blks = (int)((q.groups + 255) / 256);
+        q.const_blks = (int)blob_copy_blocks(q.c_bytes);
+        a.blocks += q.code_blks + q.const_blks;
     }
-    L.total = at;
-    return L;
+    *total = at;
+    return a;
 }
-void packed_words(const aq_policy* p, const PackedLayout& L, uint32_t (&w)[6]) {
+void packed_words(const aq_policy* p, size_t total, uint32_t (&w)[6]) {
     blob_words(p, w);
     w[0] = kPackedMagic;
-    w[4] = (uint32_t)(L.total - kBlobHeader);
-    w[5] = (uint32_t)((uint64_t)(L.total - kBlobHeader) >> 32);
+    w[4] = (uint32_t)(total - kBlobHeader);
+    w[5] = (uint32_t)((uint64_t)(total - kBlobHeader) >> 32);
 }
 }  // namespace
 
 extern "C" aq_status aq_policy_packed_blob_size(const aq_policy* p, uint64_t* bytes) {
     if (!p || !bytes) return AQ_EINVAL;
-    *bytes = packed_layout(p).total;
+    size_t total = 0;
+    packed_layout(p, &total);
+    *bytes = total;
     return AQ_OK;
 }
 
 extern "C" aq_status aq_policy_export_packed_blob(const aq_policy* p, void* d_blob, uint64_t bytes, void* stream) {
     if (!p || !d_blob || ((uintptr_t)d_blob & 15)) return AQ_EINVAL;
-    const PackedLayout L = packed_layout(p);
-    if (bytes < L.total) return AQ_EINVAL;
+    size_t total = 0;
+    const PackedArgs a = packed_layout(p, &total);
+    if (bytes < total) return AQ_EINVAL;
     if (!p->quantized) return AQ_ENOTQUANT;
-    hipStream_t st = as_stream(stream);
     uint32_t w[6];
-    packed_words(p, L, w);
-    char* dst = (char*)d_blob;
-    aq_status s = launch_blob_header_write((uint32_t*)dst, w, st);
-    if (s != AQ_OK) return s;
-    AQ_HIP_CHECK(hipMemcpyAsync(dst + kBlobHeader, p->d_net->actq, kTailBytes, hipMemcpyDeviceToDevice, st));
-    const int bits = policy_wbits(p);
-    const int off = p->h_net.asym ? 128 : (1 << (bits - 1)) - 1;
-    for (size_t l = 0; l < p->L.size(); ++l) {
-        const LayerBuf& b = p->L[l];
-        s = launch_pack_bits(b.wp, (uint8_t*)dst + L.w_off[l], (int64_t)b.NT * b.KS * 1024, bits, off, st);
-        if (s != AQ_OK) return s;
-        const size_t gap = L.c_off[l] - (L.w_off[l] + L.w_bytes[l]);  // alignment padding: a multiple of 4, kept zero
-        if (gap) {
-            s = launch_fill_u32((uint32_t*)(dst + L.w_off[l] + L.w_bytes[l]), (int)(gap / 4), 0u, st);
-            if (s != AQ_OK) return s;
-        }
-        AQ_HIP_CHECK(hipMemcpyAsync(dst + L.c_off[l], (const char*)p->slab + L.c_src[l], L.c_bytes[l],
-                                    hipMemcpyDeviceToDevice, st));
-    }
-    return AQ_OK;
+    packed_words(p, total, w);
+    return launch_packed_export(blob_head(w), a, p->d_net->actq, p->slab, d_blob, as_stream(stream));
 }
 
 extern "C" aq_status aq_policy_import_packed_blob(aq_policy* p, const void* d_blob, uint64_t bytes, void* stream) {
     if (!p || !d_blob || ((uintptr_t)d_blob & 15)) return AQ_EINVAL;
-    const PackedLayout L = packed_layout(p);
-    if (bytes < L.total) return AQ_EINVAL;
-    hipStream_t st = as_stream(stream);
+    size_t total = 0;
+    const PackedArgs a = packed_layout(p, &total);
+    if (bytes < total) return AQ_EINVAL;
     uint32_t w[6];
-    packed_words(p, L, w);
-    const char* src = (const char*)d_blob;
-    aq_status s = launch_fill_u32((uint32_t*)p->status, 1, 0u, st);
+    packed_words(p, total, w);
+    const aq_status s = launch_packed_import(blob_head(w), a, p->d_net->actq, p->slab, d_blob, p->status, as_stream(stream));
     if (s != AQ_OK) return s;
-    s = launch_blob_header_check((const uint32_t*)src, w, p->status, st);
-    if (s != AQ_OK) return s;
-    AQ_HIP_CHECK(hipMemcpyAsync(p->d_net->actq, src + kBlobHeader, kTailBytes, hipMemcpyDeviceToDevice, st));
-    const int bits = policy_wbits(p);
-    const int off = p->h_net.asym ? 128 : (1 << (bits - 1)) - 1;
-    for (size_t l = 0; l < p->L.size(); ++l) {
-        const LayerBuf& b = p->L[l];
-        s = launch_unpack_bits((const uint8_t*)src + L.w_off[l], b.wp, (int64_t)b.NT * b.KS * 1024, bits, off, b.N, b.K,
-                               b.KS, st);
-        if (s != AQ_OK) return s;
-        AQ_HIP_CHECK(hipMemcpyAsync((char*)p->slab + L.c_src[l], src + L.c_off[l], L.c_bytes[l],
-                                    hipMemcpyDeviceToDevice, st));
-    }
     p->w4_stale = true;
     p->quantized = true;
     return AQ_OK;
@@ -814,8 +794,7 @@ extern "C" aq_status aq_quantize_params(aq_policy* p, const float* const* h_d_w,
         ptrs.gamma[l] = h_d_gamma ? h_d_gamma[l] : nullptr;
         ptrs.beta[l] = h_d_beta ? h_d_beta[l] : nullptr;
     }
-    aq_status s = launch_quantize_policy(p->d_qtab, p->h_qtab, ptrs, r, p->actq, p->d_net->fast, p->status,
-                                         p->mm, st);
+    aq_status s = launch_quantize_policy(p->d_qtab, p->h_qtab, ptrs, r, p->qout, st);
     if (s != AQ_OK) return s;
     p->w4_stale = true;
     p->quantized = true;

@@ -100,6 +100,37 @@ __device__ __forceinline__ uint32_t quant_code4(float4 v, const QuantScale& q, i
     return (uint32_t)(c0 & 255) | ((uint32_t)(c1 & 255) << 8) | ((uint32_t)(c2 & 255) << 16) | ((uint32_t)c3 << 24);
 }
 
+// Four weight codes in the signed domain, clamp(round(v / s), lo, hi) + add - 128, packed little-endian: quant_code4's
+// values (add = 128 for symmetric codes, the zero-point for unsigned ones) for two thirds of its instructions, by the
+// means of quant_u8x4 below.
+__device__ __forceinline__ uint32_t quant_s8x4(float4 v, const QuantScale& q, float lo, float hi, float add) {
+    float r0, r1, r2, r3;
+    bool exact = !q.rcp_ok;
+    if (!exact) {
+        const float m0 = v.x * q.inv, m1 = v.y * q.inv, m2 = v.z * q.inv, m3 = v.w * q.inv;
+        r0 = rintf(m0);
+        r1 = rintf(m1);
+        r2 = rintf(m2);
+        r3 = rintf(m3);
+        const float c = 9.5367431640625e-7f;  // 2^-20
+        const float t0 = fmaf(fabsf(m0), c, fabsf(m0 - r0)), t1 = fmaf(fabsf(m1), c, fabsf(m1 - r1));
+        const float t2 = fmaf(fabsf(m2), c, fabsf(m2 - r2)), t3 = fmaf(fabsf(m3), c, fabsf(m3 - r3));
+        exact = !(fmaxf(fmaxf(t0, t1), fmaxf(t2, t3)) <= 0.5f - c);
+    }
+    if (exact) {
+        r0 = rintf(v.x / q.s);
+        r1 = rintf(v.y / q.s);
+        r2 = rintf(v.z / q.s);
+        r3 = rintf(v.w / q.s);
+    }
+    uint32_t pack = 0;
+    pack = __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaxf(r0, lo), hi) + add, 0, pack);
+    pack = __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaxf(r1, lo), hi) + add, 1, pack);
+    pack = __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaxf(r2, lo), hi) + add, 2, pack);
+    pack = __builtin_amdgcn_cvt_pk_u8_f32(fminf(fmaxf(r3, lo), hi) + add, 3, pack);
+    return pack ^ 0x80808080u;
+}
+
 // Four unsigned codes clamp(round(v / s) + z, 0, 255) packed little-endian: the form of quant_code4
 // for activations and observations (lo = -z, hi = 255 - z, add = z), with the guard-band test folded
 // into one comparison and the clamp, the conversion and the packing done by the saturating
@@ -198,6 +229,7 @@ struct NetDev {
 
 // The quantizer's view of a policy (device-resident, built once per handle): where every layer's
 // outputs go, and where each layer starts in the three grids that cover all layers at once.
+constexpr int QR_ROWS = 8;
 struct QLayerTab {
     int8_t* wp;
     float* s_w;
@@ -214,18 +246,18 @@ struct QLayerTab {
     int N, K, KS;
     int requant;  // hidden layer without LayerNorm
     int ln;
-    int row_blk0;  // first workgroup of the row-quantize grid (4 output channels per workgroup)
-    int cst_blk0;  // first workgroup of the constants grid (256 channels per workgroup)
-    int rng_blk0;  // first workgroup of the range grid (per-tensor scheme)
-    int rng_blks;
+    int rng_blks;  // workgroups of the range grid (per-tensor scheme)
 };
 struct QTab {
     QLayerTab L[AQ_MAX_LAYERS];
+    // first workgroup of each layer in the row grid (QR_ROWS output channels per workgroup) and in the range grid;
+    // INT_MAX past the last layer
+    int row_blk0[AQ_MAX_LAYERS], rng_blk0[AQ_MAX_LAYERS];
     int n_layers, asym, in_u8;
     float qdenom;  // activations (8 bits)
     float w_qdenom;  // weights at n bits: denominator of delta, largest unsigned and symmetric codes
     int w_qmax, w_qw;
-    int row_blks, cst_blks, rng_blks_total;
+    int row_blks, rng_blks_total;
 };
 // The caller's fp32 parameters of one quantize pass (by value: they change from call to call).
 struct QPtrs {
@@ -233,6 +265,15 @@ struct QPtrs {
     const float* b[AQ_MAX_LAYERS];
     const float* gamma[AQ_MAX_LAYERS];
     const float* beta[AQ_MAX_LAYERS];
+};
+
+// Where a quantize pass leaves what is not per layer (device memory of the handle).
+struct QOut {
+    ActQ* actq;
+    int* fast;
+    int* status;
+    QPtrs* ptrs;     // the pass's own copy of the caller's pointers
+    uint32_t* part;  // per-tensor scheme: three words per workgroup of the range grid
 };
 
 // Per-call arguments (small, by value).

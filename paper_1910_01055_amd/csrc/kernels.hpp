@@ -10,9 +10,9 @@ aq_status launch_fill_u32(uint32_t* p, int n, uint32_t v, hipStream_t st);
 aq_status launch_quantize_tensor(const float* d_w, int64_t rows, int64_t cols, int wscheme, float qdenom,
                                  int qmax, int qw, void* d_codes, float* d_scale, int32_t* d_zp, uint32_t* d_ws, hipStream_t st);
 // The whole policy: activation parameters, weight ranges (per-tensor scheme), packed 8-bit weights and
-// per-channel constants of every layer, in three or four launches.
-aq_status launch_quantize_policy(const QTab* d_tab, const QTab& h_tab, const QPtrs& ptrs, const RangesArg& r,
-                                 ActQ* actq, int* fast, int* status, uint32_t* mm, hipStream_t st);
+// per-channel constants of every layer, in two launches.
+aq_status launch_quantize_policy(const QTab* d_tab, const QTab& h_tab, const QPtrs& ptrs, const RangesArg& r, const QOut& o,
+                                 hipStream_t st);
 // the quantize pass's traffic without its arithmetic (n a multiple of 4)
 aq_status launch_stream_reference(const float* d_in, int64_t n, void* d_out, hipStream_t st);
 // the pipelined wide kernel's k-step loop alone (mfma_reference.hip); sizes as in aq_mfma_loop_reference
@@ -20,14 +20,30 @@ aq_status launch_mfma_reference(const void* d_weights, const void* d_acts, int k
                                 int32_t* d_acc, hipStream_t st);
 aq_status launch_unpack_weights(const int8_t* wp, int N, int K, int KS, int asym, uint8_t* codes, hipStream_t st);
 
-// ---- policy blob (quantize.hip): header words [0..15] = magic, version, hash lo/hi, payload bytes lo/hi, 0...
-aq_status launch_blob_header_write(uint32_t* d_hdr, const uint32_t* h_words, hipStream_t st);
-aq_status launch_blob_header_check(const uint32_t* d_hdr, const uint32_t* h_words, int* status, hipStream_t st);
-
-// n-bit weight codes of one layer (operand order, signed domain) <-> sub-byte fields, 8 codes per n bytes
-aq_status launch_pack_bits(const int8_t* wp, uint8_t* out, int64_t n_codes, int bits, int off, hipStream_t st);
-aq_status launch_unpack_bits(const uint8_t* in, int8_t* wp, int64_t n_codes, int bits, int off, int N, int K, int KS,
-                             hipStream_t st);
+// ---- policy blob (quantize.hip): header words [0..15] = magic, version, hash lo/hi, payload bytes lo/hi, 0...; then
+// 32 words of which tail_words are the activation parameters and short-form flags; then the layer part of the slab
+struct BlobHead {
+    uint32_t w[6];
+    int tail_words;
+};
+inline int64_t blob_copy_blocks(int64_t bytes) {  // 16 KiB per workgroup, at most four resident workgroups per CU
+    const int64_t g = (bytes + 16383) / 16384;
+    return g < 1 ? 1 : g > 2048 ? 2048 : g;
+}
+aq_status launch_blob_export(const BlobHead& h, const void* d_tail, const void* slab, int64_t bytes, void* blob, hipStream_t st);
+aq_status launch_blob_import(const BlobHead& h, void* d_tail, void* slab, int64_t bytes, const void* blob, int* status, hipStream_t st);
+// The packed blob: per layer the weight codes (operand order, signed domain) as n-bit fields, padded to 256 bytes, then
+// the layer's constants as they are; offsets in bytes within blob and slab.
+struct PackedLayer {
+    int64_t w_off, w_src, c_off, c_src, c_bytes, groups;  // groups of 32 codes
+    int N, K, KS, blk0, code_blks, const_blks;
+};
+struct PackedArgs {
+    PackedLayer L[AQ_MAX_LAYERS];
+    int n_layers, bits, off, blocks;
+};
+aq_status launch_packed_export(const BlobHead& h, const PackedArgs& a, const void* d_tail, const void* slab, void* blob, hipStream_t st);
+aq_status launch_packed_import(const BlobHead& h, const PackedArgs& a, void* d_tail, void* slab, const void* blob, int* status, hipStream_t st);
 
 // ---- exploration on the produced actions (explore.hip)
 aq_status launch_explore(void* d_actions, int64_t rows, int A, int head, const float* d_sigma, float epsilon,

@@ -31,35 +31,27 @@ __device__ __forceinline__ void asym_qparams(float hi, float nlo, float qdenom, 
 }
 
 // ---------------------------------------------------------------------------------------------
-// per-tensor range: hi = max(W, 0), nlo = max(-W, 0).  Both are non-negative floats, whose bit
-// patterns order like unsigned integers, so the grid-wide reduction is one atomicMax each.
-// mm[0] = hi bits, mm[1] = nlo bits, mm[2] = status flag; mm must be zero before the launch.
+// per-tensor range of a workgroup's share of a tensor: hi = max(W, 0), nlo = max(-W, 0), non-finite flag; thread 0
+// publishes the three words.  Nothing has to be cleared first.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ void range_nonneg_block(const float4* __restrict__ w4, int64_t n4,
-                                                   const float* __restrict__ w, int64_t n,
-                                                   uint32_t* __restrict__ mm, int blk, int nblk) {
+__device__ __forceinline__ void range_partial_block(const float* __restrict__ w, int64_t n, int64_t first, int64_t stride,
+                                                    uint32_t* __restrict__ part) {
     float hi = 0.0f, nlo = 0.0f;
     int bad = 0;
-    const int64_t stride = (int64_t)nblk * blockDim.x;
-    for (int64_t i = (int64_t)blk * blockDim.x + threadIdx.x; i < n4; i += stride) {
-        float4 v = w4[i];
-        float e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            bad |= !finite_f(e[j]);
-            hi = e[j] > hi ? e[j] : hi;
-            float t = -e[j];
-            nlo = t > nlo ? t : nlo;
-        }
-    }
-    // scalar tail (tensor length not a multiple of 4)
-    for (int64_t i = n4 * 4 + (int64_t)blk * blockDim.x + threadIdx.x; i < n; i += stride) {
-        float e = w[i];
+    auto take = [&](float e) {
         bad |= !finite_f(e);
         hi = e > hi ? e : hi;
-        float t = -e;
+        const float t = -e;
         nlo = t > nlo ? t : nlo;
+    };
+    const f4v AQ_GLOBAL* w4 = (const f4v AQ_GLOBAL*)w;
+    const int64_t n4 = ((uintptr_t)w & 15) == 0 ? n / 4 : 0;
+    for (int64_t i = first; i < n4; i += stride) {
+        const f4v v = w4[i];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) take(v[j]);
     }
+    for (int64_t i = n4 * 4 + first; i < n; i += stride) take(((const float AQ_GLOBAL*)w)[i]);
     hi = wave_max(hi);
     nlo = wave_max(nlo);
     bad = wave_or_i32(bad);
@@ -73,52 +65,16 @@ __device__ __forceinline__ void range_nonneg_block(const float4* __restrict__ w4
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < 4; ++i) {
-            hi = fmaxf(hi, s_hi[i]);
-            nlo = fmaxf(nlo, s_nlo[i]);
-            bad |= s_bad[i];
-        }
-        atomicMax(&mm[0], __float_as_uint(hi));
-        atomicMax(&mm[1], __float_as_uint(nlo));
-        if (bad) atomicOr(&mm[2], 1u);
+        part[0] = __float_as_uint(fmaxf(fmaxf(s_hi[0], s_hi[1]), fmaxf(s_hi[2], s_hi[3])));
+        part[1] = __float_as_uint(fmaxf(fmaxf(s_nlo[0], s_nlo[1]), fmaxf(s_nlo[2], s_nlo[3])));
+        part[2] = (uint32_t)(s_bad[0] | s_bad[1] | s_bad[2] | s_bad[3]);
     }
 }
 
 // Pass 1 of the per-tensor scheme for a large flat tensor: every workgroup publishes its partial
 // range (hi bits, -lo bits, non-finite flag) in part[3 * block]; nothing has to be cleared first.
-__global__ __launch_bounds__(256) void k_range_partials(const float4* __restrict__ w4, int64_t n4,
-                                                        uint32_t* __restrict__ part) {
-    float hi = 0.0f, nlo = 0.0f;
-    int bad = 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
-        const float4 v = w4[i];
-        const float e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            bad |= !finite_f(e[j]);
-            hi = e[j] > hi ? e[j] : hi;
-            const float t = -e[j];
-            nlo = t > nlo ? t : nlo;
-        }
-    }
-    hi = wave_max(hi);
-    nlo = wave_max(nlo);
-    bad = wave_or_i32(bad);
-    __shared__ float s_hi[4], s_nlo[4];
-    __shared__ int s_bad[4];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) {
-        s_hi[wv] = hi;
-        s_nlo[wv] = nlo;
-        s_bad[wv] = bad;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        part[3 * blockIdx.x + 0] = __float_as_uint(fmaxf(fmaxf(s_hi[0], s_hi[1]), fmaxf(s_hi[2], s_hi[3])));
-        part[3 * blockIdx.x + 1] = __float_as_uint(fmaxf(fmaxf(s_nlo[0], s_nlo[1]), fmaxf(s_nlo[2], s_nlo[3])));
-        part[3 * blockIdx.x + 2] = (uint32_t)(s_bad[0] | s_bad[1] | s_bad[2] | s_bad[3]);
-    }
+__global__ __launch_bounds__(256) void k_range_partials(const float* __restrict__ w, int64_t n, uint32_t* __restrict__ part) {
+    range_partial_block(w, n, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256, part + 3 * blockIdx.x);
 }
 
 // Pass 2: every workgroup folds the partials (a few KiB, cache resident), then streams its share of
@@ -295,58 +251,6 @@ __global__ __launch_bounds__(256) void k_quant_sym_rows_long(const float4* __res
     }
 }
 
-// ---------------------------------------------------------------------------------------------
-// Policy weights: one wavefront per output channel n of W[N][K]; codes are written in the
-// signed domain (unsigned codes minus 128; symmetric codes as they are) straight into the
-// MFMA operand order used by the forward kernels:
-//   tile (nt = n / 32, ks = k / 32) is 1 KiB: lane = n % 32 + 32 * ((k % 32) / 16), byte = k % 16.
-// Also produced per channel: scale, zero-point, and the sum of the signed-domain codes (needed to
-// fold the activation zero-point into the integer bias).
-// ---------------------------------------------------------------------------------------------
-template <bool SYM>
-__device__ __forceinline__ void quant_row_packed(const float* __restrict__ w, int n, int N, int K, int KS,
-                                                 float qdenom, int qmax, int qw, const uint32_t* __restrict__ mm,
-                                                 int8_t* __restrict__ wp, float* __restrict__ s_w,
-                                                 int32_t* __restrict__ z_w, int32_t* __restrict__ rowsum,
-                                                 int* __restrict__ status) {
-    const int lane = threadIdx.x & 63;
-    if (n >= N) return;
-    const float* src = w + (int64_t)n * K;
-    float s;
-    int z = 0;
-    if (SYM) {
-        float amax = 0.0f;
-        int bad = 0;
-        for (int k = lane; k < K; k += 64) {
-            float a = fabsf(src[k]);
-            bad |= !(a <= FLT_MAX);
-            amax = fmaxf(amax, a);
-        }
-        amax = wave_max(amax);
-        bad = wave_or_i32(bad);
-        s = amax / (float)qw;
-        if (amax == 0.0f) s = 1.0f;
-        if (bad && lane == 0) atomicOr(status, kStatNonFinite);
-    } else {
-        asym_qparams(__uint_as_float(mm[0]), __uint_as_float(mm[1]), qdenom, qmax, s, z);
-        if (mm[2] && lane == 0) atomicOr(status, kStatNonFinite);
-    }
-    int8_t* tile_row = wp + ((int64_t)(n >> 5) * KS * 64 + (n & 31)) * 16;
-    int sum = 0;
-    const QuantScale qs = make_quant_scale(s);
-    for (int k = lane; k < K; k += 64) {
-        int q = SYM ? quant_code(src[k], qs, -qw, qw) : quant_code(src[k], qs, -z, qmax - z) + z - 128;
-        sum += q;
-        tile_row[((int64_t)(k >> 5) * 64 + 32 * ((k & 31) >> 4)) * 16 + (k & 15)] = (int8_t)q;
-    }
-    sum = wave_sum_i32(sum);
-    if (lane == 0) {
-        s_w[n] = s;
-        z_w[n] = z;
-        rowsum[n] = sum;
-    }
-}
-
 // packed signed-domain weights -> canonical codes (the inverse permutation), for export
 __global__ void k_unpack_weights(const int8_t* __restrict__ wp, int N, int K, int KS, int asym,
                                  uint8_t* __restrict__ codes) {
@@ -361,33 +265,39 @@ __global__ void k_unpack_weights(const int8_t* __restrict__ wp, int N, int K, in
 // activation (scale, zero-point) from the supplied ranges: the same formula as for weights,
 // the range being extended to contain zero.
 // ---------------------------------------------------------------------------------------------
-// One small launch opens a quantize pass: it also clears the status word and the per-layer range
-// words, and presets the short-form flags (1 for requantized layers; a channel that does not
-// qualify clears its layer's flag later).
-__global__ void k_qp_prep(const QTab* __restrict__ tab, RangesArg r, ActQ* __restrict__ actq, int* __restrict__ fast,
-                          int* __restrict__ status, uint32_t* __restrict__ mm) {
+// What opens a quantize pass, done by one wavefront of its first launch: activation parameters, a clear status word,
+// the short-form flags (1 for requantized layers; a channel that does not qualify clears its layer's flag later), and
+// the caller's parameter pointers in device memory, where the row kernel reads them (a launch is 0.7 us dearer with
+// them among its arguments).
+__device__ __forceinline__ void open_pass(const QTab& tab, const QPtrs& p, const RangesArg& r, const QOut& o) {
     const int i = threadIdx.x;
-    const int nl = tab->n_layers;
-    if (i == 63) *status = 0;
-    if (i < 4 * AQ_MAX_LAYERS) mm[i] = 0u;
-    if (i >= 32 && i < 32 + nl) fast[i - 32] = tab->L[i - 32].requant;
+    const int nl = tab.n_layers;
+    if (i == 63) *o.status = 0;
+    if (i >= 32 && i < 32 + nl) o.fast[i - 32] = tab.L[i - 32].requant;
     if (i >= nl) return;
-    if (i == 0 && tab->in_u8) {
-        actq[0].s = 1.0f;
-        actq[0].z = 0;
+    o.ptrs->w[i] = p.w[i];
+    o.ptrs->b[i] = p.b[i];
+    o.ptrs->gamma[i] = p.gamma[i];
+    o.ptrs->beta[i] = p.beta[i];
+    if (i == 0 && tab.in_u8) {
+        o.actq[0].s = 1.0f;
+        o.actq[0].z = 0;
         return;
     }
     float hi = r.hi[i] > 0.0f ? r.hi[i] : 0.0f;
     float nlo = -r.lo[i] > 0.0f ? -r.lo[i] : 0.0f;
     float s;
     int z;
-    asym_qparams(hi, nlo, tab->qdenom, 255, s, z);  // activations stay at 8 bits
-    actq[i].s = s;
-    actq[i].z = z;
+    asym_qparams(hi, nlo, tab.qdenom, 255, s, z);  // activations stay at 8 bits
+    o.actq[i].s = s;
+    o.actq[i].z = z;
+}
+__global__ void k_qp_prep(const QTab* __restrict__ tab, const QPtrs p, const RangesArg r, const QOut o) {
+    open_pass(*tab, p, r, o);
 }
 
 // ---------------------------------------------------------------------------------------------
-// per-channel layer constants (one thread per output channel):
+// per-channel layer constants:
 //   m[n]      = s_in * s_w[n]                                   (fp32)
 //   bias_q[n] = round(b[n] / (s_in * s_w[n]))                   (fp64, saturated)
 //   M[n]      = s_in * s_w[n] / s_out = f * 2^e, f in [0.5,1);  M0 = round(f * 2^31), r = 31 - e
@@ -397,25 +307,19 @@ __global__ void k_qp_prep(const QTab* __restrict__ tab, RangesArg r, ActQ* __res
 //   z_w' = z_w - 128 (symmetric codes: w_s = w, z_w' = 0).  The "- z_w' sum_k a_s" term depends on
 //   the batch row and is applied inside the forward kernel.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ void layer_consts_channel(const ActQ* __restrict__ actq, int layer, int requant, int asym,
-                                                     const float* __restrict__ s_w, const int32_t* __restrict__ z_w,
-                                                     const float* __restrict__ bias, const int32_t* __restrict__ rowsum,
-                                                     int n, int K, float* __restrict__ m, int32_t* __restrict__ bias_q,
-                                                     int32_t* __restrict__ M0, int32_t* __restrict__ rshift,
-                                                     int32_t* __restrict__ bias_fold, int32_t* __restrict__ pack1,
-                                                     int32_t* __restrict__ rz, int32_t* __restrict__ sh,
-                                                     int* __restrict__ fast, int* __restrict__ status) {
-    const float s_in = actq[layer].s;
-    const int z_a = actq[layer].z;
-    m[n] = s_in * s_w[n];
-    double sw = (double)s_in * (double)s_w[n];
-    double bq = rint((double)(bias ? bias[n] : 0.0f) / sw);
+__device__ __forceinline__ void layer_consts_channel(const QLayerTab& L, int asym, ActQ in, ActQ out, float s_w, int z_w, float bias,
+                                                     int rowsum, int n, int* __restrict__ fast, int* __restrict__ status) {
+    const float s_in = in.s;
+    const int z_a = in.z;
+    L.m[n] = s_in * s_w;
+    double sw = (double)s_in * (double)s_w;
+    double bq = rint((double)bias / sw);
     if (!(bq >= -2147483647.0)) bq = -2147483647.0;
     if (bq > 2147483647.0) bq = 2147483647.0;
     int32_t bqi = (int32_t)bq;
-    bias_q[n] = bqi;
-    if (requant) {
-        double M = sw / (double)actq[layer + 1].s;
+    L.bias_q[n] = bqi;
+    if (L.requant) {
+        double M = sw / (double)out.s;
         int e;
         double f = frexp(M, &e);
         long long q = llround(f * 2147483648.0);
@@ -429,95 +333,257 @@ __device__ __forceinline__ void layer_consts_channel(const ActQ* __restrict__ ac
             q = 0;
             r = 1;
         }
-        M0[n] = (int32_t)q;
-        pack1[n] = (int32_t)q;
-        rshift[n] = r;
+        L.M0[n] = (int32_t)q;
+        L.pack1[n] = (int32_t)q;
+        L.rshift[n] = r;
         // Short form of the same requantization for 33 <= r <= 54: the rounding constant 2^(r-1) has a
         // zero low word, so (acc*M0 + 2^(r-1)) >> r = (mulhi(acc, M0) + 2^(r-33)) >> (r-32), and the
         // output zero-point can ride along as z_out << (r-32).  One layer-wide flag says whether every
         // channel qualifies.
         if (r >= 33 && r <= 54) {
-            sh[n] = r - 32;
-            rz[n] = (1 << (r - 33)) + (actq[layer + 1].z << (r - 32));
+            L.sh[n] = r - 32;
+            L.rz[n] = (1 << (r - 33)) + (out.z << (r - 32));
         } else {
-            sh[n] = 0;
-            rz[n] = 0;
+            L.sh[n] = 0;
+            L.rz[n] = 0;
             atomicAnd(fast, 0);
         }
     } else {
-        M0[n] = 0;
-        rshift[n] = 0;
-        pack1[n] = __float_as_int(s_in * s_w[n]);
+        L.M0[n] = 0;
+        L.rshift[n] = 0;
+        L.pack1[n] = __float_as_int(s_in * s_w);
     }
     const int za_s = z_a - 128;
-    const int zw_s = asym ? z_w[n] - 128 : 0;
+    const int zw_s = asym ? z_w - 128 : 0;
     // (a saturated integer bias can push the folded value out of the accumulator's range: reported, like a
     // multiplier outside the shift range, instead of wrapping silently)
-    const long long bf = (long long)bqi - (long long)za_s * rowsum[n] + (long long)K * za_s * zw_s;
+    const long long bf = (long long)bqi - (long long)za_s * rowsum + (long long)L.K * za_s * zw_s;
     if (bf > 2147483647LL || bf < -2147483648LL) atomicOr(status, kStatRange);
-    bias_fold[n] = (int32_t)bf;
+    L.bias_fold[n] = (int32_t)bf;
 }
 
 // ---------------------------------------------------------------------------------------------
-// The whole policy in three or four launches: each grid covers every layer, a workgroup finds its
+// The whole policy in two launches: what opens the pass (with the per-tensor scheme: together with every layer's
+// partial ranges), then the rows of every layer with their constants.  A grid covers all layers; a workgroup finds its
 // layer from the table's first-workgroup indices (at most 8 compares).
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ int layer_of_block(const QTab& t, int blk, int which) {
-    int l = t.n_layers - 1;
-    while (l > 0 && blk < (which == 0 ? t.L[l].row_blk0 : which == 1 ? t.L[l].cst_blk0 : t.L[l].rng_blk0)) --l;
+__device__ __forceinline__ int layer_of_block(const QTab& t, int blk, bool rows) {
+    // (entries past the last layer hold INT_MAX; all eight in one scalar load instead of a chain of them)
+    int l = 0;
+#pragma unroll
+    for (int i = 1; i < AQ_MAX_LAYERS; ++i) l += blk >= (rows ? t.row_blk0[i] : t.rng_blk0[i]);
     return l;
 }
 
-__global__ __launch_bounds__(256) void k_qp_ranges(const QTab* __restrict__ tab, const QPtrs p, uint32_t* __restrict__ mm) {
+__global__ __launch_bounds__(256) void k_qp_ranges(const QTab* __restrict__ tab, const QPtrs p, const RangesArg r, const QOut o) {
     const QTab& t = *tab;
-    const int l = layer_of_block(t, blockIdx.x, 2);
+    if (blockIdx.x == 0 && threadIdx.x < 64) open_pass(t, p, r, o);
+    const int l = layer_of_block(t, blockIdx.x, false);
     const QLayerTab& L = t.L[l];
-    const int64_t n = (int64_t)L.N * L.K;
-    range_nonneg_block((const float4*)p.w[l], n / 4, p.w[l], n, mm + 4 * l, blockIdx.x - L.rng_blk0, L.rng_blks);
+    range_partial_block(p.w[l], (int64_t)L.N * L.K, (int64_t)((int)blockIdx.x - t.rng_blk0[l]) * 256 + threadIdx.x,
+                        (int64_t)L.rng_blks * 256, o.part + 3 * blockIdx.x);
 }
 
+// Policy weights: a workgroup of 8 wavefronts quantizes 8 output channels of W[N][K], one per wavefront.  Codes go,
+// in the signed domain (unsigned codes minus 128; symmetric codes as they are), into the MFMA operand order the forward
+// kernels read:
+//   tile (nt = n / 32, ks = k / 32) is 1 KiB: lane = n % 32 + 32 * ((k % 32) / 16), byte = k % 16.
+// The 8 rows' bytes of a k-half of a tile are 128 consecutive bytes: the codes are collected row by row in LDS, 2048 k at
+// a time, and leave as 16-byte pieces in that order.  Rows of up to 2048 floats stay in registers between the range
+// and the rounding (read from HBM once, all of a row's requests in flight); longer ones are read again.
+// Per channel also: scale, zero-point, the sum of the signed-domain codes (it folds the activation zero-point into
+// the integer bias) and, from them, the layer constants - so they need no launch of their own.
+// Bound by memory and its latency: 8.6 M parameters (three hidden layers of 2048) 26 us with one wavefront per row storing
+// single bytes, plus 4.5 us for the constants' launch.
+constexpr int QR_CHUNK = 2048, QR_LD = QR_CHUNK + 16;
 template <bool SYM>
-__global__ __launch_bounds__(256) void k_qp_rows(const QTab* __restrict__ tab, const QPtrs p,
-                                                 const uint32_t* __restrict__ mm, int* __restrict__ status) {
+__global__ __launch_bounds__(512) void k_qp_rows(const QTab* __restrict__ tab, const QOut o) {
+    __shared__ __align__(16) int8_t codes[QR_ROWS * QR_LD];
+    __shared__ float s_red[2][8];
+    __shared__ int s_bad[8];
     const QTab& t = *tab;
-    const int l = layer_of_block(t, blockIdx.x, 0);
-    const QLayerTab& L = t.L[l];
-    const int n = (blockIdx.x - L.row_blk0) * 4 + (threadIdx.x >> 6);
-    quant_row_packed<SYM>(p.w[l], n, L.N, L.K, L.KS, t.w_qdenom, t.w_qmax, t.w_qw, mm + 4 * l, L.wp, L.s_w, L.z_w, L.rowsum, status);
-}
+    const int l = layer_of_block(t, blockIdx.x, true);
+    const QLayerTab L = t.L[l];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int N = L.N, K = L.K, n0 = ((int)blockIdx.x - t.row_blk0[l]) * QR_ROWS;
+    const float AQ_GLOBAL* w = (const float AQ_GLOBAL*)o.ptrs->w[l];
+    const bool vec = (K & 3) == 0 && ((uintptr_t)o.ptrs->w[l] & 15) == 0;
+    const bool held = K <= QR_CHUNK;
+    constexpr int R = QR_CHUNK / 256;  // float4 per lane and row chunk
 
-__global__ __launch_bounds__(256) void k_qp_consts(const QTab* __restrict__ tab, const QPtrs p,
-                                                   const ActQ* __restrict__ actq, int* __restrict__ fast,
-                                                   int* __restrict__ status) {
-    const QTab& t = *tab;
-    const int l = layer_of_block(t, blockIdx.x, 1);
-    const QLayerTab& L = t.L[l];
-    const int n = (blockIdx.x - L.cst_blk0) * 256 + threadIdx.x;
-    if (n >= L.N) return;
-    layer_consts_channel(actq, l, L.requant, t.asym, L.s_w, L.z_w, p.b[l], L.rowsum, n, L.K, L.m, L.bias_q, L.M0,
-                         L.rshift, L.bias_fold, L.pack1, L.rz, L.sh, fast + l, status);
+    // (rows past the end re-read the last one)
+    const float AQ_GLOBAL* src = w + (int64_t)(n0 + wave < N ? n0 + wave : N - 1) * K;
+    f4v v[R];
+    auto load = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+            const int k = k0 + 4 * (lane + 64 * c);
+            v[c] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+            if (k0 + 256 * c >= K) continue;  // (scalar)
+            if (vec) {
+                if (k < K) v[c] = *(const f4v AQ_GLOBAL*)(src + k);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (k + j < K) v[c][j] = src[k + j];
+            }
+        }
+    };
+    if (held) load(0);
+    // what the constants of this wavefront's channel need, requested now: at the end of the kernel each of these was a
+    // round trip of its own
+    const int n_own = n0 + wave;
+    float c_bias = 0.0f, c_gamma = 1.0f, c_beta = 0.0f;
+    const ActQ a_in = o.actq[l], a_out = o.actq[l + 1];
+    if (n_own < N) {
+        if (const float* p = o.ptrs->b[l]) c_bias = ((const float AQ_GLOBAL*)p)[n_own];
+        if (L.ln) {
+            if (const float* p = o.ptrs->gamma[l]) c_gamma = ((const float AQ_GLOBAL*)p)[n_own];
+            if (const float* p = o.ptrs->beta[l]) c_beta = ((const float AQ_GLOBAL*)p)[n_own];
+        }
+    }
+
+    float s;
+    int z = 0;
+    if (SYM) {
+        float amax = 0.0f;
+        int bad = 0;
+        for (int k0 = 0; k0 < K; k0 += QR_CHUNK) {
+            if (!held) load(k0);
+#pragma unroll
+            for (int c = 0; c < R; ++c)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float a = fabsf(v[c][j]);
+                    bad |= !(a <= FLT_MAX);
+                    amax = fmaxf(amax, a);
+                }
+        }
+        amax = wave_max(amax);
+        s = amax / (float)t.w_qw;
+        if (amax == 0.0f) s = 1.0f;
+        if (bad) atomicOr(o.status, kStatNonFinite);
+    } else {
+        // the layer's range from its workgroups' partial ones (at most 256)
+        float hi = 0.0f, nlo = 0.0f;
+        int bad = 0;
+        for (int i = tid; i < L.rng_blks; i += 512) {
+            const uint32_t* q = o.part + 3 * (t.rng_blk0[l] + i);
+            hi = fmaxf(hi, __uint_as_float(q[0]));
+            nlo = fmaxf(nlo, __uint_as_float(q[1]));
+            bad |= (int)q[2];
+        }
+        hi = wave_max(hi);
+        nlo = wave_max(nlo);
+        bad = wave_or_i32(bad);
+        if (lane == 0) {
+            s_red[0][wave] = hi;
+            s_red[1][wave] = nlo;
+            s_bad[wave] = bad;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            hi = fmaxf(hi, s_red[0][i]);
+            nlo = fmaxf(nlo, s_red[1][i]);
+            bad |= s_bad[i];
+        }
+        asym_qparams(hi, nlo, t.w_qdenom, t.w_qmax, s, z);
+        if (bad && n0 == 0 && tid == 0) atomicOr(o.status, kStatNonFinite);
+    }
+
+    const QuantScale qs = make_quant_scale(s);
+    const float lo = SYM ? -(float)t.w_qw : -(float)z, hi = SYM ? (float)t.w_qw : (float)(t.w_qmax - z), add = SYM ? 128.0f : (float)z;
+    int sum = 0;
+    for (int k0 = 0; k0 < K; k0 += QR_CHUNK) {
+        if (!held) load(k0);
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+            if (k0 + 256 * c >= L.KS * 32) continue;  // (scalar)
+            const int kk = 4 * (lane + 64 * c);
+            uint32_t q = quant_s8x4(make_float4(v[c][0], v[c][1], v[c][2], v[c][3]), qs, lo, hi, add);
+            // entries behind the end of K are zeros in the signed domain
+            const int left = K - k0 - kk;
+            if (left < 4) q = left <= 0 ? 0u : q & (0xffffffffu >> (8 * (4 - left)));
+            sum = __builtin_amdgcn_sdot4((int)q, 0x01010101, sum, false);
+            *(uint32_t*)(codes + wave * QR_LD + kk) = q;
+        }
+        __syncthreads();
+        const int ks0 = k0 >> 5, halves = 2 * (L.KS - ks0 < QR_CHUNK / 32 ? L.KS - ks0 : QR_CHUNK / 32);
+        for (int idx = tid; idx < QR_ROWS * halves; idx += 512) {
+            const int row = idx & (QR_ROWS - 1), c = idx / QR_ROWS, n = n0 + row;
+            if (n < N)
+                *(v4i AQ_GLOBAL*)(L.wp + (((int64_t)(n >> 5) * L.KS + ks0 + (c >> 1)) * 64 + (n & 31) + 32 * (c & 1)) * 16) =
+                    *(const v4i*)(codes + row * QR_LD + 16 * c);
+        }
+        if (k0 + QR_CHUNK < K) __syncthreads();
+    }
+    sum = wave_sum_i32(sum);
+    if (lane != 0 || n_own >= N) return;
+    L.s_w[n_own] = s;
+    L.z_w[n_own] = z;
+    L.rowsum[n_own] = sum;
+    layer_consts_channel(L, t.asym, a_in, a_out, s, z, c_bias, sum, n_own, o.fast + l, o.status);
     if (L.ln) {  // LayerNorm gain and offset (defaults 1 and 0) into their slots of the constant pack
-        L.rz[n] = __float_as_int(p.gamma[l] ? p.gamma[l][n] : 1.0f);
-        L.sh[n] = __float_as_int(p.beta[l] ? p.beta[l][n] : 0.0f);
+        L.rz[n_own] = __float_as_int(c_gamma);
+        L.sh[n_own] = __float_as_int(c_beta);
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// policy blob header: six words written / compared by one small launch (the expected words travel
-// as kernel arguments, so neither call needs a host round trip)
+// Policy blob, one launch each way: 64 header bytes (six words, then zeros), 128 bytes of activation parameters and
+// short-form flags (padded with zeros), the layer part of the slab.  (As a header launch and two copies an export or
+// an import cost the host 8 us.)
 // ---------------------------------------------------------------------------------------------
-struct BlobWords {
-    uint32_t w[6];
-};
-__global__ void k_blob_header_write(uint32_t* __restrict__ hdr, const BlobWords b) {
-    // the 16 header words, and zeros over the 32 words behind them (the tail's padding; its
-    // contents are copied in afterwards)
-    const int i = threadIdx.x;
-    if (i < 48) hdr[i] = i < 6 ? b.w[i] : 0u;
+__device__ __forceinline__ void copy16(v4i* __restrict__ dst, const v4i* __restrict__ src, int64_t n, int64_t first, int64_t stride) {
+    for (int64_t i = first; i < n; i += 4 * stride) {
+        v4i v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i + u * stride < n) v[u] = src[i + u * stride];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i + u * stride < n) dst[i + u * stride] = v[u];
+    }
 }
-__global__ void k_blob_header_check(const uint32_t* __restrict__ hdr, const BlobWords b, int* __restrict__ status) {
+// header and tail of a blob, by the first 64 threads of one workgroup
+__device__ __forceinline__ void blob_head_out(uint32_t* __restrict__ blob, const uint32_t (&w)[6], const uint32_t* __restrict__ tail,
+                                              int tail_words) {
     const int i = threadIdx.x;
-    if (i < 6 && hdr[i] != b.w[i]) atomicOr(status, kStatBlob);
+    if (i < 16) {
+        uint32_t v = 0u;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) v = i == j ? w[j] : v;
+        blob[i] = v;
+    } else if (i < 48) {
+        blob[i] = i - 16 < tail_words ? tail[i - 16] : 0u;
+    }
+}
+__device__ __forceinline__ void blob_head_in(const uint32_t* __restrict__ blob, const uint32_t (&w)[6], uint32_t* __restrict__ tail,
+                                             int tail_words, int* __restrict__ status) {
+    const int i = threadIdx.x;
+    bool wrong = false;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) wrong |= i == j && blob[j] != w[j];
+    if (i < tail_words) tail[i] = blob[16 + i];
+    const uint64_t any = __ballot(wrong);
+    if (i == 0) *status = any ? kStatBlob : 0;
+}
+__global__ __launch_bounds__(256) void k_blob_export(const BlobHead h, const uint32_t* __restrict__ tail, const v4i* __restrict__ slab,
+                                                     int64_t n16, uint32_t* __restrict__ blob) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < 64) blob_head_out(blob, h.w, tail, h.tail_words);
+        return;
+    }
+    copy16((v4i*)(blob + 48), slab, n16, (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x, (int64_t)(gridDim.x - 1) * 256);
+}
+__global__ __launch_bounds__(256) void k_blob_import(const BlobHead h, uint32_t* __restrict__ tail, v4i* __restrict__ slab, int64_t n16,
+                                                     const uint32_t* __restrict__ blob, int* __restrict__ status) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < 64) blob_head_in(blob, h.w, tail, h.tail_words, status);
+        return;
+    }
+    copy16(slab, (const v4i*)(blob + 48), n16, (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x, (int64_t)(gridDim.x - 1) * 256);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -528,46 +594,97 @@ __global__ void k_blob_header_check(const uint32_t* __restrict__ hdr, const Blob
 // signed domain, which the per-tensor scheme cannot store in n < 8 bits: they are written as field 0
 // and restored from their position when unpacking.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_pack_bits(const int8_t* __restrict__ wp, uint8_t* __restrict__ out,
-                                                   int64_t groups, int bits, int off) {
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (g >= groups) return;
-    const uint64_t v = *(const uint64_t*)(wp + 8 * g);
+// One launch each way for the whole packed blob: workgroup 0 does header and tail, then every layer has its workgroups
+// for the codes (a thread takes 32 codes = n words) and for its constants, copied as they are.
+__device__ __forceinline__ int packed_layer_of(const PackedArgs& a, int blk) {
+    int l = a.n_layers - 1;
+    while (l > 0 && blk < a.L[l].blk0) --l;
+    return l;
+}
+__global__ __launch_bounds__(256) void k_packed_export(const BlobHead h, const PackedArgs a, const uint32_t* __restrict__ tail,
+                                                       const char* __restrict__ slab, uint32_t* __restrict__ blob) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < 64) blob_head_out(blob, h.w, tail, h.tail_words);
+        return;
+    }
+    const PackedLayer& L = a.L[packed_layer_of(a, blockIdx.x)];
+    const int rel = blockIdx.x - L.blk0, bits = a.bits, off = a.off;
+    if (rel >= L.code_blks) {
+        copy16((v4i*)((char*)blob + L.c_off), (const v4i*)(slab + L.c_src), L.c_bytes / 16, (int64_t)(rel - L.code_blks) * 256 + threadIdx.x,
+               (int64_t)L.const_blks * 256);
+        return;
+    }
+    uint32_t* out = (uint32_t*)((char*)blob + L.w_off);
+    if (rel == 0 && threadIdx.x < 64) {  // alignment padding behind the codes: kept zero
+        const int64_t end = (int64_t)L.groups * bits, padded = (L.c_off - L.w_off) / 4;
+        if (end + threadIdx.x < padded) out[end + threadIdx.x] = 0u;
+    }
+    const int64_t g = (int64_t)rel * 256 + threadIdx.x;
+    if (g >= L.groups) return;
+    const int8_t* wp = (const int8_t*)(slab + L.w_src) + 32 * g;
+    const v4i c[2] = {((const v4i*)wp)[0], ((const v4i*)wp)[1]};
     const int fmax = (1 << bits) - 1;
     uint64_t acc = 0;
+    int have = 0, word = 0;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        int u = (int)(int8_t)(v >> (8 * j)) + off;
+    for (int j = 0; j < 32; ++j) {
+        int u = (int)(int8_t)((uint32_t)c[j >> 4][(j >> 2) & 3] >> (8 * (j & 3))) + off;
         u = u < 0 ? 0 : (u > fmax ? 0 : u);
-        acc |= (uint64_t)u << (j * bits);
+        acc |= (uint64_t)u << have;
+        have += bits;
+        if (have >= 32) {
+            out[g * bits + word++] = (uint32_t)acc;
+            acc >>= 32;
+            have -= 32;
+        }
     }
-    uint8_t* dst = out + g * bits;
-    for (int b = 0; b < bits; ++b) dst[b] = (uint8_t)(acc >> (8 * b));
 }
-
-__global__ __launch_bounds__(256) void k_unpack_bits(const uint8_t* __restrict__ in, int8_t* __restrict__ wp,
-                                                     int64_t groups, int bits, int off, int N, int K, int KS) {
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (g >= groups) return;
-    const uint8_t* src = in + g * bits;
-    uint64_t acc = 0;
-    for (int b = 0; b < bits; ++b) acc |= (uint64_t)src[b] << (8 * b);
-    // position of the group's first element in the operand order: tile (n / 32, k / 32) = 1 KiB,
-    // lane = n % 32 + 32 * ((k % 32) / 16), byte = k % 16
-    const int64_t e = 8 * g;
-    const int64_t tile = e >> 10;
-    const int nt = (int)(tile / KS), ks = (int)(tile - (int64_t)nt * KS);
-    const int lane = (int)((e & 1023) >> 4), byte0 = (int)(e & 15);
-    const int n = nt * 32 + (lane & 31), k0 = ks * 32 + 16 * (lane >> 5) + byte0;
-    const uint64_t fmask = ((uint64_t)1 << bits) - 1;
-    uint64_t v = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        int sgn = (int)((acc >> (j * bits)) & fmask) - off;
-        if (n >= N || k0 + j >= K) sgn = 0;
-        v |= (uint64_t)(uint8_t)(int8_t)sgn << (8 * j);
+__global__ __launch_bounds__(256) void k_packed_import(const BlobHead h, const PackedArgs a, uint32_t* __restrict__ tail,
+                                                       char* __restrict__ slab, const uint32_t* __restrict__ blob, int* __restrict__ status) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x < 64) blob_head_in(blob, h.w, tail, h.tail_words, status);
+        return;
     }
-    *(uint64_t*)(wp + 8 * g) = v;
+    const PackedLayer& L = a.L[packed_layer_of(a, blockIdx.x)];
+    const int rel = blockIdx.x - L.blk0, bits = a.bits, off = a.off;
+    if (rel >= L.code_blks) {
+        copy16((v4i*)(slab + L.c_src), (const v4i*)((const char*)blob + L.c_off), L.c_bytes / 16,
+               (int64_t)(rel - L.code_blks) * 256 + threadIdx.x, (int64_t)L.const_blks * 256);
+        return;
+    }
+    const int64_t g = (int64_t)rel * 256 + threadIdx.x;
+    if (g >= L.groups) return;
+    const uint32_t* src = (const uint32_t*)((const char*)blob + L.w_off) + g * bits;
+    // position of the group's two 16-byte pieces in the operand order: tile (n / 32, k / 32) = 1 KiB,
+    // lane = n % 32 + 32 * ((k % 32) / 16), byte = k % 16
+    const uint32_t fmask = (1u << bits) - 1u;
+    uint64_t acc = 0;
+    int have = 0, word = 0;
+    v4i v[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int64_t e = 32 * g + 16 * p;
+        const uint32_t tile = (uint32_t)(e >> 10);
+        const int nt = (int)(tile / (uint32_t)L.KS), ks = (int)(tile - (uint32_t)nt * (uint32_t)L.KS);
+        const int lane = (int)((e & 1023) >> 4);
+        const int n = nt * 32 + (lane & 31), k0 = ks * 32 + 16 * (lane >> 5);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            if (have < bits) {
+                acc |= (uint64_t)src[word++] << have;
+                have += 32;
+            }
+            int sgn = (int)((uint32_t)acc & fmask) - off;
+            acc >>= bits;
+            have -= bits;
+            if (n >= L.N || k0 + j >= L.K) sgn = 0;
+            const uint32_t b = (uint32_t)(uint8_t)(int8_t)sgn << (8 * (j & 3));
+            v[p][j >> 2] = (j & 3) == 0 ? (int)b : (int)((uint32_t)v[p][j >> 2] | b);
+        }
+    }
+    v4i* dst = (v4i*)(slab + L.w_src) + 2 * g;
+    dst[0] = v[0];
+    dst[1] = v[1];
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -605,29 +722,22 @@ aq_status launch_stream_reference(const float* d_in, int64_t n, void* d_out, hip
 // ---------------------------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------------------------
-aq_status launch_pack_bits(const int8_t* wp, uint8_t* out, int64_t n_codes, int bits, int off, hipStream_t st) {
-    const int64_t groups = n_codes / 8;
-    hipLaunchKernelGGL(k_pack_bits, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, st, wp, out, groups, bits, off);
+aq_status launch_blob_export(const BlobHead& h, const void* d_tail, const void* slab, int64_t bytes, void* blob, hipStream_t st) {
+    const unsigned g = 1 + (unsigned)blob_copy_blocks(bytes);
+    hipLaunchKernelGGL(k_blob_export, dim3(g), dim3(256), 0, st, h, (const uint32_t*)d_tail, (const v4i*)slab, bytes / 16, (uint32_t*)blob);
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
-aq_status launch_unpack_bits(const uint8_t* in, int8_t* wp, int64_t n_codes, int bits, int off, int N, int K, int KS,
-                             hipStream_t st) {
-    const int64_t groups = n_codes / 8;
-    hipLaunchKernelGGL(k_unpack_bits, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, st, in, wp, groups, bits, off,
-                       N, K, KS);
+aq_status launch_blob_import(const BlobHead& h, void* d_tail, void* slab, int64_t bytes, const void* blob, int* status, hipStream_t st) {
+    const unsigned g = 1 + (unsigned)blob_copy_blocks(bytes);
+    hipLaunchKernelGGL(k_blob_import, dim3(g), dim3(256), 0, st, h, (uint32_t*)d_tail, (v4i*)slab, bytes / 16, (const uint32_t*)blob, status);
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
-
-aq_status launch_blob_header_write(uint32_t* d_hdr, const uint32_t* h_words, hipStream_t st) {
-    BlobWords b;
-    for (int i = 0; i < 6; ++i) b.w[i] = h_words[i];
-    hipLaunchKernelGGL(k_blob_header_write, dim3(1), dim3(64), 0, st, d_hdr, b);
+aq_status launch_packed_export(const BlobHead& h, const PackedArgs& a, const void* d_tail, const void* slab, void* blob, hipStream_t st) {
+    hipLaunchKernelGGL(k_packed_export, dim3((unsigned)a.blocks), dim3(256), 0, st, h, a, (const uint32_t*)d_tail, (const char*)slab, (uint32_t*)blob);
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
-aq_status launch_blob_header_check(const uint32_t* d_hdr, const uint32_t* h_words, int* status, hipStream_t st) {
-    BlobWords b;
-    for (int i = 0; i < 6; ++i) b.w[i] = h_words[i];
-    hipLaunchKernelGGL(k_blob_header_check, dim3(1), dim3(64), 0, st, d_hdr, b, status);
+aq_status launch_packed_import(const BlobHead& h, const PackedArgs& a, void* d_tail, void* slab, const void* blob, int* status, hipStream_t st) {
+    hipLaunchKernelGGL(k_packed_import, dim3((unsigned)a.blocks), dim3(256), 0, st, h, a, (uint32_t*)d_tail, (char*)slab, (const uint32_t*)blob, status);
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
 
@@ -652,7 +762,7 @@ aq_status launch_quantize_tensor(const float* d_w, int64_t rows, int64_t cols, i
         const int64_t n4 = n / 4;
         // enough workgroups to keep every CU's memory pipeline full; partial ranges go to d_ws[16..]
         const int g1 = grid_for(n4, 256 * 4, 1024);
-        hipLaunchKernelGGL(k_range_partials, dim3(g1), dim3(256), 0, st, w4, n4, d_ws + 16);
+        hipLaunchKernelGGL(k_range_partials, dim3(g1), dim3(256), 0, st, d_w, n, d_ws + 16);
         const int g2 = grid_for(n4, 256 * 4, 2048);
         hipLaunchKernelGGL(k_quant_asym_flat, dim3(g2), dim3(256), 0, st, w4, n4, d_ws + 16, g1, qdenom, qmax, c4, d_scale,
                            d_zp, d_ws + 2);
@@ -684,16 +794,15 @@ aq_status launch_unpack_weights(const int8_t* wp, int N, int K, int KS, int asym
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
 
-aq_status launch_quantize_policy(const QTab* d_tab, const QTab& h_tab, const QPtrs& ptrs, const RangesArg& r,
-                                 ActQ* actq, int* fast, int* status, uint32_t* mm, hipStream_t st) {
-    hipLaunchKernelGGL(k_qp_prep, dim3(1), dim3(64), 0, st, d_tab, r, actq, fast, status, mm);
+aq_status launch_quantize_policy(const QTab* d_tab, const QTab& h_tab, const QPtrs& ptrs, const RangesArg& r, const QOut& o,
+                                 hipStream_t st) {
     if (h_tab.asym) {
-        hipLaunchKernelGGL(k_qp_ranges, dim3(h_tab.rng_blks_total), dim3(256), 0, st, d_tab, ptrs, mm);
-        hipLaunchKernelGGL(k_qp_rows<false>, dim3(h_tab.row_blks), dim3(256), 0, st, d_tab, ptrs, mm, status);
+        hipLaunchKernelGGL(k_qp_ranges, dim3(h_tab.rng_blks_total), dim3(256), 0, st, d_tab, ptrs, r, o);
+        hipLaunchKernelGGL(k_qp_rows<false>, dim3(h_tab.row_blks), dim3(512), 0, st, d_tab, o);
     } else {
-        hipLaunchKernelGGL(k_qp_rows<true>, dim3(h_tab.row_blks), dim3(256), 0, st, d_tab, ptrs, mm, status);
+        hipLaunchKernelGGL(k_qp_prep, dim3(1), dim3(64), 0, st, d_tab, ptrs, r, o);
+        hipLaunchKernelGGL(k_qp_rows<true>, dim3(h_tab.row_blks), dim3(512), 0, st, d_tab, o);
     }
-    hipLaunchKernelGGL(k_qp_consts, dim3(h_tab.cst_blks), dim3(256), 0, st, d_tab, ptrs, actq, fast, status);
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
 
