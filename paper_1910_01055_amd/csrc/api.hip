@@ -103,6 +103,10 @@ struct aq_policy {
     std::vector<void*> h16_wp;
     std::vector<float*> h16_bias, h16_gamma, h16_beta;
     bool h16_ready = false;
+    Fp16Net h16_net{};              // a fully connected policy's description for the whole-network kernel ...
+    Fp16Net* d_h16_net = nullptr;   // ... and its device copy
+    Fp16ConvTab* d_h16_tab = nullptr;
+    int h16_blocks = 0;
     int64_t cap_f16 = 0;
     void* act_f16[2] = {nullptr, nullptr};
     // the learner's fp32 parameters, copied by aq_policy_set_params_fp32, and the packed weights of parameters passed
@@ -1216,7 +1220,72 @@ extern "C" aq_status aq_calibrate_fp32(aq_policy* p, const void* d_obs, int64_t 
     return AQ_OK;
 }
 
-// ---- half-precision actor
+// ---- half-precision actor: storage of its parameters (one allocation, made once) and the tables over it
+static aq_status ensure_h16(aq_policy* p) {
+    if (p->h16_slab) return AQ_OK;
+    const int nl = p->net.n_layers;
+    size_t bytes = 0;
+    auto take = [&](size_t n) {
+        size_t off = bytes;
+        bytes += (n + 255) / 256 * 256;
+        return off;
+    };
+    std::vector<size_t> offs;
+    bool fc = true;
+    int cst = 0;
+    std::vector<int> c_off;
+    for (const LayerBuf& b : p->L) {
+        offs.push_back(take((size_t)b.NT * (round_up(b.K, 64) / 16) * 1024));
+        for (int i = 0; i < 3; ++i) offs.push_back(take((size_t)b.N_pad * 4));
+        fc = fc && b.fc;
+        c_off.push_back(cst);
+        cst += b.N_pad * (b.d.act == AQ_ACT_LN_TANH ? 3 : 1);
+    }
+    const size_t off_h = take((size_t)cst * 2), off_net = take(sizeof(Fp16Net)), off_tab = take(sizeof(Fp16ConvTab));
+    void* slab = nullptr;
+    if (hipMalloc(&slab, bytes) != hipSuccess) return AQ_ENOMEM;
+    char* base = (char*)slab;
+    Fp16Net net{};
+    Fp16ConvTab tab{};
+    int blk = 0;
+    net.n_layers = fc ? nl : 0;
+    net.head = p->net.head;
+    net.cst = cst;
+    net.eps = p->net.ln_eps;
+    net.consts = base + off_h;
+    for (int l = 0; l < nl; ++l) {
+        const LayerBuf& b = p->L[l];
+        const int ks16 = round_up(b.K, 64) / 16;
+        net.L[l] = Fp16LayerDev{base + offs[4 * l], b.K, b.N, ks16, b.NT, b.d.act, c_off[l]};
+        for (int i = 0; i < 4; ++i) {
+            const bool ln = b.d.act == AQ_ACT_LN_TANH;
+            if (i >= 2 && !ln) continue;
+            void* half = i == 0 ? nullptr : base + off_h + 2 * ((size_t)c_off[l] + (size_t)(i - 1) * b.N_pad);
+            tab.blk0[tab.n] = blk;
+            tab.e[tab.n++] = Fp16ConvTab::Entry{base + offs[4 * l + i], half, i, l, b.N, b.K, ks16, b.NT};
+            blk += i == 0 ? (int)(((int64_t)b.NT * ks16 + kConvTiles - 1) / kConvTiles) : (b.N_pad + 255) / 256;
+        }
+    }
+    tab.blocks = blk;
+    if (hipMemcpy(base + off_net, &net, sizeof(net), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(base + off_tab, &tab, sizeof(tab), hipMemcpyHostToDevice) != hipSuccess) {
+        (void)hipFree(slab);
+        return AQ_EHIP;
+    }
+    for (int l = 0; l < nl; ++l) {
+        p->h16_wp.push_back(base + offs[4 * l]);
+        p->h16_bias.push_back((float*)(base + offs[4 * l + 1]));
+        p->h16_gamma.push_back((float*)(base + offs[4 * l + 2]));
+        p->h16_beta.push_back((float*)(base + offs[4 * l + 3]));
+    }
+    p->h16_slab = slab;
+    p->h16_net = net;
+    p->d_h16_net = (Fp16Net*)(base + off_net);
+    p->d_h16_tab = (Fp16ConvTab*)(base + off_tab);
+    p->h16_blocks = blk;
+    return AQ_OK;
+}
+
 extern "C" aq_status aq_convert_params_fp16(aq_policy* p, const float* const* h_d_w, const float* const* h_d_b,
                                             const float* const* h_d_gamma, const float* const* h_d_beta,
                                             void* stream) {
@@ -1225,46 +1294,13 @@ extern "C" aq_status aq_convert_params_fp16(aq_policy* p, const float* const* h_
     for (int l = 0; l < nl; ++l)
         if (!h_d_w[l]) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
-    if (!p->h16_slab) {
-        size_t bytes = 0;
-        std::vector<size_t> offs;
-        auto take = [&](size_t n) {
-            size_t off = bytes;
-            bytes += (n + 255) / 256 * 256;
-            return off;
-        };
-        for (const LayerBuf& b : p->L) {
-            const int ks16 = round_up(b.K, 64) / 16;
-            offs.push_back(take((size_t)b.NT * ks16 * 1024));
-            for (int i = 0; i < 3; ++i) offs.push_back(take((size_t)b.N_pad * 4));
-        }
-        if (hipMalloc(&p->h16_slab, bytes) != hipSuccess) return AQ_ENOMEM;
-        char* base = (char*)p->h16_slab;
-        size_t oi = 0;
-        for (int l = 0; l < nl; ++l) {
-            p->h16_wp.push_back(base + offs[oi++]);
-            p->h16_bias.push_back((float*)(base + offs[oi++]));
-            p->h16_gamma.push_back((float*)(base + offs[oi++]));
-            p->h16_beta.push_back((float*)(base + offs[oi++]));
-        }
-    }
-    int* st16 = p->status + 1;
-    aq_status s = launch_fill_u32((uint32_t*)st16, 1, 0u, st);
+    aq_status s = ensure_h16(p);
     if (s != AQ_OK) return s;
-    for (int l = 0; l < nl; ++l) {
-        const LayerBuf& b = p->L[l];
-        const int ks16 = round_up(b.K, 64) / 16;
-        s = launch_fp16_pack_weights(h_d_w[l], b.N, b.K, ks16, b.NT, p->h16_wp[l], st16, st);
-        if (s != AQ_OK) return s;
-        s = launch_fp16_round_vec(h_d_b ? h_d_b[l] : nullptr, b.N, b.N_pad, 0.0f, p->h16_bias[l], st16, st);
-        if (s != AQ_OK) return s;
-        if (b.d.act == AQ_ACT_LN_TANH) {
-            s = launch_fp16_round_vec(h_d_gamma ? h_d_gamma[l] : nullptr, b.N, b.N_pad, 1.0f, p->h16_gamma[l], st16, st);
-            if (s != AQ_OK) return s;
-            s = launch_fp16_round_vec(h_d_beta ? h_d_beta[l] : nullptr, b.N, b.N_pad, 0.0f, p->h16_beta[l], st16, st);
-            if (s != AQ_OK) return s;
-        }
-    }
+    int* st16 = p->status + 1;
+    s = launch_fill_u32((uint32_t*)st16, 1, 0u, st);
+    if (s != AQ_OK) return s;
+    s = launch_fp16_convert(f32_ptr_table(nl, h_d_w, h_d_b, h_d_gamma, h_d_beta), p->d_h16_tab, p->h16_blocks, st16, st);
+    if (s != AQ_OK) return s;
     p->h16_ready = true;
     return AQ_OK;
 }
@@ -1312,6 +1348,8 @@ extern "C" aq_status aq_policy_forward_fp16(aq_policy* p, const void* d_obs, int
     if (batch == 0) return AQ_OK;
     if (!d_obs || !d_actions) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
+    if (fp16_mlp_fits(p->h16_net, batch))
+        return launch_fp16_mlp(p->h16_net, p->d_h16_net, d_obs, p->h_net.in_u8, batch, d_actions, taps_out, st);
     aq_status s = ensure_f16(p, batch, st);
     if (s != AQ_OK) return s;
     const int nl = p->net.n_layers;

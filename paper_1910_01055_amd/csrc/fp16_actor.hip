@@ -2,10 +2,11 @@
 // observation and every operator's output are IEEE binary16 values; products are exact and sums are
 // kept in fp32 by v_mfma_f32_32x32x16_f16, rounded to binary16 once per operator.
 //
-//   k_fp16_pack_weights   fp32 [N][K] -> binary16 in MFMA operand order (tile (n/32, k/16) = 1 KiB,
-//                         lane = n % 32 + 32 * ((k % 16) / 8), 8 consecutive k per lane), zero padded
-//   k_fp16_round_vec      biases / LayerNorm gain and offset rounded to binary16 (kept widened)
+//   k_fp16_convert        fp32 parameters -> binary16: weights in MFMA operand order (tile (n/32, k/16) = 1 KiB,
+//                         lane = n % 32 + 32 * ((k % 16) / 8), 8 consecutive k per lane), zero padded;
+//                         biases / LayerNorm gain and offset rounded to binary16 (kept widened, and as halfs)
 //   k_layer_fp16          affine layer (FC or implicit-GEMM convolution) + bias (+ReLU), one launch per layer
+//                         (whole fully connected policies in one launch: fp16_mlp.hip)
 //   k_fp16_ln_tanh        LayerNorm, rounded, then tanh, rounded, in place
 //   k_fp16_head           tanh / identity / argmax on the last layer's rows
 #include "kernels.hpp"
@@ -22,33 +23,63 @@ constexpr int HW = 4;     // waves per workgroup
 constexpr int HKC = 64;   // k per staged chunk
 constexpr int HLD = HKC + 8;  // LDS row stride in halfs (144 bytes: 16-byte reads of 8 rows hit 32 banks)
 
-__global__ __launch_bounds__(256) void k_fp16_pack_weights(const float* __restrict__ w, int N, int K, int KS16,
-                                                           int NT, _Float16* __restrict__ wp, int* status) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t total = (int64_t)NT * KS16 * 512;
-    if (i >= total) return;
-    const int j = (int)(i & 7), lane = (int)((i >> 3) & 63);
-    const int64_t tile = i >> 9;
-    const int ks = (int)(tile % KS16), nt = (int)(tile / KS16);
-    const int n = nt * 32 + (lane & 31), k = ks * 16 + 8 * (lane >> 5) + j;
-    _Float16 v = (_Float16)0.0f;
-    if (n < N && k < K) {
-        v = (_Float16)w[(int64_t)n * K + k];
-        if (!(fabsf((float)v) <= 65504.0f)) atomicOr(status, kStatNonFinite);
+// One launch for the whole policy (as one launch per array it cost the host 2.6 us each).  Weights: a wave makes four
+// tiles, a lane's 8 consecutive k of one feature per tile.
+__global__ __launch_bounds__(256) void k_fp16_convert(const F32Ptrs src, const Fp16ConvTab* __restrict__ tab, int* status) {
+    const int blk = (int)blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t before = __ballot(lane < tab->n && blk >= tab->blk0[lane < tab->n ? lane : 0]);
+    const int a = __builtin_amdgcn_readfirstlane(63 - __builtin_clzll(before));
+    const Fp16ConvTab::Entry e = tab->e[a];
+    const int l = e.layer, rel = blk - tab->blk0[a];
+    bool bad = false;
+    if (e.kind == 0) {
+        const float AQ_GLOBAL* w = (const float AQ_GLOBAL*)src.w[l];
+        const bool al = (e.K & 3) == 0 && ((uintptr_t)src.w[l] & 15) == 0;
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        const uint32_t tiles = (uint32_t)e.NT * (uint32_t)e.KS16;
+        h8 v[kConvTiles / 4];
+#pragma unroll
+        for (int i = 0; i < kConvTiles / 4; ++i) {
+            const uint32_t t = (uint32_t)rel * kConvTiles + i * 4 + wave;
+            const int nt = (int)(t / (uint32_t)e.KS16), ks = (int)(t - (uint32_t)nt * (uint32_t)e.KS16);
+            const int n = nt * 32 + (lane & 31), k = ks * 16 + 8 * (lane >> 5);
+            f4 q[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+            if (t < tiles && n < e.N) {
+                const float AQ_GLOBAL* p = w + (int64_t)n * e.K + k;
+                if (al) {
+                    if (k < e.K) q[0] = *(const f4 AQ_GLOBAL*)p;
+                    if (k + 4 < e.K) q[1] = *(const f4 AQ_GLOBAL*)(p + 4);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (k + j < e.K) q[j >> 2][j & 3] = p[j];
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                v[i][j] = (_Float16)q[j >> 2][j & 3];
+                bad |= !(fabsf((float)v[i][j]) <= 65504.0f);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kConvTiles / 4; ++i) {
+            const uint32_t t = (uint32_t)rel * kConvTiles + i * 4 + wave;
+            if (t < tiles) ((h8 AQ_GLOBAL*)e.dst)[(int64_t)t * 64 + lane] = v[i];
+        }
+    } else {
+        const float* s = e.kind == 1 ? src.b[l] : e.kind == 2 ? src.gamma[l] : src.beta[l];
+        const int i = rel * 256 + threadIdx.x;
+        if (i < e.NT * 32) {
+            _Float16 v = (_Float16)(e.kind == 2 ? 1.0f : 0.0f);
+            if (s && i < e.N) {
+                v = (_Float16)s[i];
+                bad = !(fabsf((float)v) <= 65504.0f);
+            }
+            ((float*)e.dst)[i] = (float)v;
+            if (e.dst_h) ((_Float16*)e.dst_h)[i] = v;
+        }
     }
-    wp[i] = v;
-}
-
-__global__ __launch_bounds__(256) void k_fp16_round_vec(const float* __restrict__ src, int n, int n_pad, float fill,
-                                                        float* __restrict__ dst, int* status) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n_pad) return;
-    float v = fill;
-    if (i < n && src) {
-        v = (float)(_Float16)src[i];
-        if (!(fabsf(v) <= 65504.0f)) atomicOr(status, kStatNonFinite);
-    }
-    dst[i] = v;
+    if (bad) atomicOr(status, kStatNonFinite);
 }
 
 // tanh with relative error below 1e-6 (far inside half a binary16 spacing, 2.4e-4): odd polynomial
@@ -569,18 +600,8 @@ __global__ __launch_bounds__(256) void k_fp16_head(const _Float16* __restrict__ 
 
 }  // namespace
 
-aq_status launch_fp16_pack_weights(const float* w, int N, int K, int KS16, int NT, void* wp, int* status,
-                                   hipStream_t st) {
-    const int64_t total = (int64_t)NT * KS16 * 512;
-    hipLaunchKernelGGL(k_fp16_pack_weights, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, w, N, K, KS16, NT,
-                       (_Float16*)wp, status);
-    return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
-}
-
-aq_status launch_fp16_round_vec(const float* src, int n, int n_pad, float fill, float* dst, int* status,
-                                hipStream_t st) {
-    hipLaunchKernelGGL(k_fp16_round_vec, dim3((unsigned)((n_pad + 255) / 256)), dim3(256), 0, st, src, n, n_pad, fill,
-                       dst, status);
+aq_status launch_fp16_convert(const F32Ptrs& src, const Fp16ConvTab* d_tab, int blocks, int* status, hipStream_t st) {
+    hipLaunchKernelGGL(k_fp16_convert, dim3((unsigned)blocks), dim3(256), 0, st, src, d_tab, status);
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
 

@@ -182,10 +182,57 @@ struct Fp16Layer {
     int32_t* head_argmax;  // last layer of an argmax policy run by the few-row kernel with one feature tile:
                            // action indices [rows], else NULL
 };
-aq_status launch_fp16_pack_weights(const float* w, int N, int K, int KS16, int NT, void* wp, int* status,
-                                   hipStream_t st);
-aq_status launch_fp16_round_vec(const float* src, int n, int n_pad, float fill, float* dst, int* status,
-                                hipStream_t st);
+// The learner's parameters -> binary16, every array of every layer in one launch: entry i starts at workgroup blk0[i].
+// Weights go into operand order (kind 0: 16 tiles of 32 features x 16 k per workgroup), biases, gains and offsets
+// (kinds 1 to 3, padded to NT * 32) into a vector of widened values and one of halfs.
+struct Fp16ConvTab {
+    struct Entry {
+        void* dst;
+        void* dst_h;
+        int kind, layer, N, K, KS16, NT;
+    };
+    Entry e[4 * AQ_MAX_LAYERS];
+    int blk0[4 * AQ_MAX_LAYERS];
+    int n, blocks;
+};
+constexpr int kConvTiles = 16;
+aq_status launch_fp16_convert(const F32Ptrs& src, const Fp16ConvTab* d_tab, int blocks, int* status, hipStream_t st);
+
+// ---- whole fully connected policies in half precision (fp16_mlp.hip)
+struct Fp16LayerDev {
+    const void* wp;
+    int K, N, KS16, NT, act;
+    int c_off;  // where the layer's constants begin among the network's, in halfs: bias, then gain and offset, NT * 32 each
+};
+struct Fp16Net {
+    Fp16LayerDev L[AQ_MAX_LAYERS];
+    const void* consts;
+    int n_layers;  // 0: not a fully connected policy
+    int head, cst;  // cst: halfs of constants, a multiple of 8
+    float eps;
+};
+struct Fp16Call {
+    const void* obs;
+    void* actions;
+    int64_t batch;
+    int ld, off_const, off_y;  // LDS, in halfs: row stride of the activations, the constants, a narrow argmax head's logits
+};
+template <bool TAPS>
+struct Fp16Taps {
+    void* p[AQ_MAX_LAYERS];
+    Fp16Taps(void* const* t, int n) {
+        for (int l = 0; l < AQ_MAX_LAYERS; ++l) p[l] = l < n ? t[l] : nullptr;
+    }
+};
+template <>
+struct Fp16Taps<false> {
+    int none;
+    Fp16Taps(void* const*, int) : none(0) {}
+};
+// whether the policy runs as one launch at this batch size
+bool fp16_mlp_fits(const Fp16Net& n, int64_t batch);
+aq_status launch_fp16_mlp(const Fp16Net& n, const Fp16Net* d_net, const void* obs, int in_u8, int64_t batch, void* actions,
+                          void* const* taps, hipStream_t st);
 // in_mode: 0 = binary16 activations, 1 = fp32 observations, 2 = uint8 observations
 aq_status launch_layer_fp16(const Fp16Layer& L, const void* in, int in_mode, void* out, int64_t rows,
                             hipStream_t st);

@@ -1,0 +1,37 @@
+"""The whole-network half-precision kernel at 16, 32 and 64 rows per workgroup: ragged rows, one to four feature tiles per
+wavefront and wavefronts without one, LayerNorm rows, narrow and wide heads; every layer's output of sampled rows against
+the CPU oracle (the launch without taps must give the same actions)."""
+import numpy as np
+import pytest
+
+from paper_1910_01055_amd import synth
+from test_gpu_fp16 import _check, _run_gpu
+
+pytestmark = pytest.mark.gpu
+fc = synth.fc
+
+
+def _nets():
+    return {
+        "tiles_4_3_1": synth.small_net([fc(67, 1000, "relu"), fc(1000, 600, "relu"), fc(600, 70, "none"), fc(70, 21, "none")]),
+        "ln_wide": synth.small_net([fc(30, 1000, "ln_tanh"), fc(1000, 40, "none")], head="linear"),
+        "ln_odd": synth.small_net([fc(111, 257, "ln_tanh"), fc(257, 96, "relu"), fc(96, 3, "none")]),
+        "wide_argmax": synth.small_net([fc(33, 130, "relu"), fc(130, 100, "none")], head="argmax"),
+        "narrow_argmax": synth.small_net([fc(17, 200, "relu"), fc(200, 50, "none")], head="argmax"),
+        "u8_wide_head": synth.small_net([fc(48, 130, "relu"), fc(130, 70, "none")], head="tanh", in_type="u8"),
+        "aligned": synth.small_net([fc(256, 512, "relu"), fc(512, 512, "relu"), fc(512, 64, "none")]),
+    }
+
+
+@pytest.mark.parametrize("name", list(_nets()))
+@pytest.mark.parametrize("batch", [1, 49, 4099, 8200, 16391])
+def test_whole_network_half_precision_kernel(aq, name, batch):
+    print(f"[fp16 mlp] {name} batch={batch}", flush=True)
+    net = _nets()[name]
+    params = synth.make_params(net, nonzero_bias=True)
+    obs = synth.make_obs(net, batch)
+    actions, outs = _run_gpu(aq, net, params, obs)
+    rows = np.unique(np.minimum(np.concatenate([[0, 15, 16, 31, 32, 63, 64, batch - 2, batch - 1],
+                                                np.random.default_rng(3).integers(0, batch, 24)]), batch - 1))
+    rows = rows[rows >= 0]
+    _check(net, params, obs[rows], actions[rows], [o.reshape(batch, -1)[rows] for o in outs], end_to_end=False)
