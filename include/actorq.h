@@ -136,9 +136,9 @@ aq_status aq_policy_reserve(aq_policy* p, int64_t max_batch);
 aq_status aq_policy_set_path(aq_policy* p, int32_t path);
 
 /* *n_layers = how many leading convolution layers the 8-bit forward of this handle runs as a single
- * launch under the current launch plan (0: none; it takes 8-bit frames, per-channel symmetric weights,
- * kh * kw * in_c and kw * in_c multiples of 32, stride * in_c and in_w * in_c multiples of 16), given a
- * 16-byte aligned observation buffer.  No GPU work. */
+ * launch under the current launch plan (0: none; it takes 8-bit frames of one to three channels or a multiple
+ * of four, per-channel symmetric weights, out_c a multiple of 4, kw * c and stride * c multiples of 16 with c = in_c
+ * or, for fewer than four channels, 4, and frames that fit into local memory with their feature maps).  No GPU work. */
 aq_status aq_policy_conv_stack_layers(const aq_policy* p, int32_t* n_layers);
 /* The same for the half-precision forward (its rules: 8-bit frames, kw * in_c a multiple of 16,
  * stride * in_c and in_w * in_c multiples of 8, out_c a multiple of 4, two to four convolutions). */
@@ -181,7 +181,7 @@ aq_status aq_policy_status(aq_policy* p, void* stream);
  * actor's model re-packs the weights).  The blob holds the 8-bit weights already in the forward
  * kernels' operand order, every per-channel constant and the activation quantization parameters,
  * behind a 64-byte header (magic, format version, a hash of the network description, payload size):
- * importing it is two device-to-device copies and no arithmetic.  A blob is valid only for a handle
+ * importing it is one launch that copies and no arithmetic.  A blob is valid only for a handle
  * created from the same aq_net on the same library version.
  *   aq_policy_blob_size: *bytes = size of the blob for this handle's network (no GPU work).
  *   aq_policy_export_blob: writes the blob to d_blob (caller-owned device memory, 16-byte aligned,

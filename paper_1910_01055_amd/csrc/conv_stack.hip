@@ -1,61 +1,83 @@
 // The leading convolution layers of a frame policy (Sec. 4.1: the Atari-style policies take stacked
-// 8-bit frames through three convolutions before the fully connected layers) in one launch: one
-// workgroup per image keeps the frame, every intermediate feature map and the layers' epilogue
-// constants in LDS.  Frame and constants are requested in one burst at its start (one round trip);
-// the maps never travel through global memory, and the three launches of the per-layer path become one.
-// Weights stream from L2 in operand order (staging them in LDS as well was measured slower: the burst
-// grows to 100 KB per workgroup and only one workgroup fits a CU).
+// 8-bit frames through three convolutions before the fully connected layers) in one launch: a workgroup
+// of 16 wavefronts keeps a frame, every intermediate feature map, the layers' weights and epilogue constants
+// in LDS and goes from image to image (grid = one workgroup per CU at most), so that weights and constants
+// are fetched once per workgroup and a frame is fetched under the previous image's convolutions.
 //
-// No im2col: with NHWC maps a 32-byte k-step of the implicit GEMM is 32 contiguous bytes of the input
-// map (part of one kernel row), so an MFMA's activation operand is one 16-byte LDS read per lane at an
-// address computed from the output position.  A wave owns a (32 output positions) x (32 features)
-// tile at a time.
+// No im2col: with NHWC maps a 16-byte piece of the implicit GEMM's K is 16 contiguous bytes of one kernel row of
+// the input map, so an MFMA's activation operand is one 16-byte LDS read per lane at an address computed from the
+// output position.  v_mfma_i32_16x16x64_i8: lane (i = lane % 16, g = lane / 16) of k-step s holds bytes
+// 64 s + 16 g .. + 15 of K, for weights a piece of the 32 x 32 operand tiles the library stores.  A wavefront's task is
+// 16 output positions x 32 features.
 //
-// Shapes it takes (the host checks them, anything else goes one launch per layer): 8-bit frames,
-// per-channel symmetric weights, K = kh*kw*in_c a multiple of 32, kw*in_c, stride*in_c and in_w*in_c
-// multiples of 16 and kw*in_c a multiple of 32 (operand reads stay aligned and a k-step stays inside one
-// kernel row), N a multiple of 4, and a frame and constants within the burst's register budget (32 KB,
-// 2048 words).
+// What bounds it: the chain of phases of one workgroup (arguments, frame round trip, three layers of a barrier, a task's
+// operand reads and products, an epilogue) and, within a phase, instruction issue: what all sixteen wavefronts execute
+// costs sixteen clocks an instruction.  Hence one wavefront per layer for constants and tables, four per layer for the
+// weights (straight into LDS), one code for all layers with arguments read per layer, windows' places from a table.  An
+// 84 x 84 x 4 frame through 32, 32 and 16 channels at 256 images takes 7.6 us back to back, 2.6 of them the launch; 2048
+// images 44 us.  The same with a copy of the code per layer and weights through registers: 13 us.  One workgroup per
+// image with 32 x 32 tiles and weights from L2 per tile (what stood here before) was as fast at 256 images, half as fast
+// at 2048, and took none but rows of 16 bytes: a policy on 65 x 65 x 3 frames at batch 25 went layer by layer with byte
+// gathers, 55.4 us, now 19.3.
+//
+// Frames of fewer than four channels are expanded to four on their way into LDS, and the first layer's weights with
+// them (zeros in the channels that do not exist), so that every frame has aligned pieces; rows in LDS are padded to 16
+// bytes.
+//
+// Shapes it takes (the host checks them, anything else goes one launch per layer): 8-bit frames, per-channel
+// symmetric weights, two to four convolutions before a fully connected layer; per layer kw * C and stride * C multiples
+// of 16 (C = channels, at least 4 for the frame), N a multiple of 4; frame, maps and constants within LDS and the
+// registers they pass through.
 #include "int8_device.hpp"
 
 namespace aq {
 
 namespace {
-constexpr int CS_W = 8;          // waves per workgroup (16 when every image gets a CU to itself)
-constexpr int CS_T = CS_W * 64;  // threads of the smaller workgroup: sizes the burst's limits
-constexpr int CS_FU = 4;         // 16-byte pieces of the frame per thread
-constexpr int CS_CU = 4;         // words of epilogue constants per thread
-constexpr int CS_CONSTS = 5;     // arrays per layer: bias_fold | M0 | rz | sh (one contiguous pack), rshift
+constexpr int CS_W = 16;         // wavefronts per workgroup
+constexpr int CS_T = CS_W * 64;
+constexpr int CS_FU = 3;         // 16-byte pieces of the frame (in LDS) per thread
 constexpr size_t CS_MAX_LDS = 160 * 1024;
 constexpr int CS_MAXC = 4;       // convolution layers of a stack at most
 
-// What the host knows of the stack at launch time, by value: the burst's requests and every layer's tile loop
-// then need nothing but the kernel arguments (one scalar round trip at the start; read from the device-resident
-// description the burst's addresses took four thousand clocks of dependent scalar loads to work out, and every
-// layer began with a round trip for its own entry).  Only what the quantizer kernels write (activation zero-points,
-// short-form flags) still comes from the description, requested at the start.
+// What the host knows of the stack at launch time, by value: no layer begins with a round trip for its own entry of
+// the device-resident description.  Only what the quantizer kernels write (activation zero-points, short-form flags)
+// comes from there, requested at the start.
 struct StackLayer {
     const int8_t* wp;
-    int oh, ow, in_w, in_c, kw, stride, N, NT, KS, act;
+    const int32_t* pack;  // epilogue constants: bias_fold | M0 | rz | sh, each NT * 32 words
+    const int32_t* rsh;   // shifts of the general form (read where they are used)
+    int per_nt, per_inv;  // wavefronts per tile of 32 features; 65536 / that, rounded up
+    int NT, RT, R, ow;    // tiles of 32 features, tiles of 16 positions, output positions, positions per row
+    float inv_ow;
+    int pos_x, pos_y;     // bytes from an output position's window to the next one's, in LDS
+    int K, N, KS, act;
+    int in_off, out_off, out_row;  // LDS: input map, output map and its row stride
+    int w_off, w_tiles;   // LDS: weights, and how many 1 KiB tiles of them
+    int c_off;            // LDS: constants
+    int k_off, k_len;     // LDS: where each 16-byte piece of K lies relative to a window's first byte; entries per g
+    int run, row;         // bytes of a window row, of an input map row in LDS
 };
 struct StackArgs {
-    int f_pieces;            // 16-byte pieces of a frame
-    int c_words;             // constant words of all layers
-    int cnt[CS_MAXC];        // ... of each layer, and where they come from: four arrays in one pack, then rshift
-    int np4[CS_MAXC];
-    const int32_t* pack[CS_MAXC];
-    const int32_t* rsh[CS_MAXC];
+    int pieces, pieces_row;  // 16-byte pieces of the frame in LDS, and of one of its rows
+    float inv_row;
+    int src_piece, src_row;  // bytes of a piece and of a row in the frame as given
+    int last;                // where its last 16 bytes begin
+    int64_t frame_bytes;
+    int ragged;              // a piece reaches past the image's end
+    int expand;              // first layer: channels below four, their number; else 0
+    int KS0;                 // first layer's k-steps as stored
+    int batch, nc;
     StackLayer L[CS_MAXC];
 };
 
 struct StackPlan {
-    int nc;          // leading convolution layers taken
-    int off_b;       // LDS offsets: second map buffer, constants
-    int off_c;
+    int nc;         // leading convolution layers taken
+    bool resident;  // weights in LDS
     size_t lds;
 };
 
-bool plan_stack(const FwdArgs& a, StackPlan* p) {
+// `sa` may be NULL: only whether and how many
+bool plan_stack(const FwdArgs& a, StackPlan* p, StackArgs* sa) {
     const NetDev& net = a.net;
     if (!net.in_u8 || net.asym) return false;
     int nc = 0;
@@ -66,237 +88,352 @@ bool plan_stack(const FwdArgs& a, StackPlan* p) {
         ++nc;
     }
     if (nc < 2 || nc > CS_MAXC || nc >= net.n_layers) return false;  // a fully connected layer must follow
-    size_t sz[2] = {0, 0}, c_words = 0;
+    if (a.c.batch > 0x7fffffffLL) return false;
+    StackArgs s{};
+    const LayerDev& L0 = net.L[0];
+    s.expand = L0.in_c < 4 ? L0.in_c : 0;
+    if (!s.expand && L0.in_c % 4) return false;
+    const int c0 = s.expand ? 4 : L0.in_c;
+    s.pieces_row = (L0.in_w * c0 + 15) / 16;
+    s.pieces = L0.in_h * s.pieces_row;
+    s.inv_row = 1.0f / (float)s.pieces_row;
+    s.src_piece = s.expand ? 4 * L0.in_c : 16;
+    s.src_row = L0.in_w * L0.in_c;
+    s.frame_bytes = (int64_t)L0.in_h * s.src_row;
+    s.KS0 = L0.KS;
+    s.ragged = s.pieces_row * s.src_piece > s.src_row || s.src_piece < 16;
+    s.last = (int)s.frame_bytes - 16;
+    s.batch = (int)a.c.batch;
+    s.nc = nc;
+    if (s.pieces > CS_FU * CS_T || s.frame_bytes < 16) return false;
+    size_t map[2] = {0, 0};
     for (int l = 0; l < nc; ++l) {
         const LayerDev& L = net.L[l];
-        const int run = L.kw * L.in_c;
-        if (L.act == AQ_ACT_LN_TANH) return false;
-        if (L.K != L.KS * 32 || run % 32 || (L.stride * L.in_c) % 16 || (L.in_w * L.in_c) % 16 || (L.N & 3)) return false;
-        if (a.t.ln[l]) return false;
-        const size_t in_bytes = (size_t)L.in_h * L.in_w * L.in_c;
-        if (in_bytes % 16) return false;
-        if (in_bytes > sz[l & 1]) sz[l & 1] = in_bytes;
-        c_words += (size_t)CS_CONSTS * L.NT * 32;
+        StackLayer& q = s.L[l];
+        const int C = l == 0 ? c0 : L.in_c;
+        if (L.act == AQ_ACT_LN_TANH || a.t.ln[l]) return false;
+        if ((L.kw * C) % 16 || (L.stride * C) % 16 || (L.N & 3)) return false;
+        q.wp = L.wp;
+        q.pack = L.bias_fold;
+        q.rsh = L.rshift;
+        q.R = L.oh * L.ow;
+        q.ow = L.ow;
+        q.inv_ow = 1.0f / (float)L.ow;
+        q.RT = (q.R + 15) / 16;
+        q.per_nt = L.NT < CS_W ? CS_W / L.NT : 1;
+        q.per_inv = (65536 + q.per_nt - 1) / q.per_nt;
+        q.run = L.kw * C;
+        q.row = l == 0 ? s.pieces_row * 16 : s.L[l - 1].out_row;
+        q.pos_x = L.stride * C;
+        q.pos_y = L.stride * q.row;
+        q.K = L.kh * L.kw * C;
+        q.N = L.N;
+        q.NT = L.NT;
+        q.KS = (q.K + 31) / 32;
+        q.act = L.act;
+        q.out_row = round_up(L.ow * L.N, 16);
+        const size_t out = (size_t)L.oh * q.out_row;
+        if (l < nc - 1 && out > map[l & 1]) map[l & 1] = out;
     }
-    const size_t frame = (size_t)net.L[0].in_h * net.L[0].in_w * net.L[0].in_c;
-    if (frame > (size_t)CS_FU * CS_T * 16 || c_words > (size_t)CS_CU * CS_T) return false;
-    if (((uintptr_t)a.c.obs & 15) || a.c.batch > 0x7fffffffLL) return false;
+    // LDS: frame, the two map areas, constants, tables of K
+    size_t at = (size_t)s.pieces * 16;
+    const size_t off_map[2] = {at, at + map[0]};
+    at += map[0] + map[1];
+    for (int l = 0; l < nc; ++l) {
+        StackLayer& q = s.L[l];
+        q.in_off = l == 0 ? 0 : (int)off_map[(l - 1) & 1];
+        q.out_off = (int)off_map[l & 1];
+        q.c_off = (int)at;
+        at += (size_t)q.NT * 512;
+        q.k_off = (int)at;
+        q.k_len = round_up((q.K + 63) / 64, 4);
+        at += (size_t)q.k_len * 16;
+    }
+    // the weights, if all of them fit; an expanded first layer's have to
+    size_t w_at = at;
+    for (int l = 0; l < nc; ++l) {
+        StackLayer& q = s.L[l];
+        q.w_off = (int)w_at;
+        q.w_tiles = q.NT * q.KS;
+        w_at += (size_t)q.w_tiles * 1024;
+    }
     p->nc = nc;
-    p->off_b = (int)sz[0];
-    p->off_c = (int)(sz[0] + sz[1]);
-    p->lds = sz[0] + sz[1] + c_words * 4;
-    return p->lds <= CS_MAX_LDS;
+    p->resident = w_at <= CS_MAX_LDS;
+    p->lds = p->resident ? w_at : at;
+    if (p->lds > CS_MAX_LDS || (s.expand && !p->resident)) return false;
+    if (sa) *sa = s;
+    return true;
+}
+
+typedef v4i v4i_any __attribute__((aligned(1)));
+#define AQ_CONST __attribute__((address_space(4)))
+
+// 1 KiB of weights straight into LDS (no registers, nothing to wait for until they are used)
+__device__ __forceinline__ void lds_fetch_1k(const int8_t* src, int8_t* dst, int lane) {
+    __builtin_amdgcn_global_load_lds((const AQ_GLOBAL void*)(src + lane * 16), (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
 }
 }  // namespace
 
-template <bool TAPS, int W, int NC>
-__global__ __launch_bounds__(W * 64) void k_conv_stack(const NetDev* __restrict__ netp, const TapParam<TAPS> tp, const StackArgs sa,
-                                                     const uint8_t* __restrict__ frames, int8_t* __restrict__ out,
-                                                     const int off_b, const int off_c) {
+// WLDS: weights in LDS (else from L2, operand by operand)
+template <bool TAPS, bool WLDS>
+__global__ __launch_bounds__(CS_T) void k_conv_stack(const NetDev* __restrict__ netp, const uint8_t* __restrict__ frames,
+                                                     int8_t* __restrict__ out, const StackArgs sa_, const TapParam<TAPS> tp) {
     extern __shared__ __align__(16) int8_t smem[];
-    const TapArgs t = taps_of(tp);
-    const NetDev& a = *netp;
-    // (the wave index stays a vector value here: it only selects tiles, in a loop; the tests that guard MFMAs are on
-    // the scalar K.  An MFMA behind a lane-mask test could run under an empty mask, which the matrix cores ignore)
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, n = lane & 31;
-    const int64_t img = blockIdx.x;
-    constexpr int NTHR = W * 64;
-    constexpr int nc = NC;
-    // (written by the quantizer kernels: requested now, used by the epilogues)
-    int z_q[NC], fastf[NC];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, i16 = lane & 15;
+    const StackArgs AQ_CONST* const sa = (const StackArgs AQ_CONST*)((const char AQ_CONST*)__builtin_amdgcn_kernarg_segment_ptr() + 24);
+    (void)sa_;
+    // (every cache line of the arguments is a round trip over the host link when it is first read: all of them at once)
+    int warm[(sizeof(StackArgs) + 63) / 64];
 #pragma unroll
-    for (int l = 0; l < NC; ++l) {
-        z_q[l] = a.actq[l + 1].z;
-        fastf[l] = a.fast[l];
-    }
-    {   // the burst: frame pieces and the constant words of all layers, then their LDS stores
-        const int f_pieces = sa.f_pieces;
-        const int c_words = sa.c_words;
-        const v4i* fsrc = (const v4i*)frames + img * f_pieces;
-        v4i fr[CS_FU];
-        int cr[CS_CU];
+    for (int i = 0; i < (int)(sizeof(warm) / 4); ++i) warm[i] = ((const int AQ_CONST*)sa)[16 * i];
+    const int pieces = sa->pieces;
+
+    // ---- frames: pieces of 16 bytes (in LDS).  A piece that would reach past the image's end is read as the image's last
+    // 16 bytes and shifted down; past a row's end there is whatever follows, in LDS bytes that no window covers.
+    v4i fr[CS_FU];
+    auto source = [&](int u, int* back) __attribute__((always_inline)) {
+        const int i = tid + u * CS_T, y = (int)(((float)i + 0.5f) * sa->inv_row);
+        const int at = __mul24(y, sa->src_row) + __mul24(i - __mul24(y, sa->pieces_row), sa->src_piece);
+        *back = at > sa->last ? at - sa->last : 0;
+        return at > sa->last ? sa->last : at;
+    };
+    auto fetch_frame = [&](int64_t img) __attribute__((always_inline)) {
+        const uint8_t AQ_GLOBAL* f = (const uint8_t AQ_GLOBAL*)frames + img * sa->frame_bytes;
 #pragma unroll
         for (int u = 0; u < CS_FU; ++u) {
-            const int i = tid + u * NTHR;
-            fr[u] = fsrc[i < f_pieces ? i : f_pieces - 1];
+            if (u * CS_T >= pieces) continue;  // (scalar)
+            int back;
+            const uint32_t at = (uint32_t)source(u, &back);
+            fr[u] = *(const v4i_any AQ_GLOBAL*)(f + at);
         }
+    };
+    auto store_frame = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < CS_CU; ++u) {
-            int i = tid + u * NTHR;
-            i = i < c_words ? i : c_words - 1;
-            // which layer word i belongs to: per-lane selects over per-layer scalars
-            const int32_t* pack = sa.pack[0];
-            const int32_t* rsh = sa.rsh[0];
-            int np4 = sa.np4[0];
-            bool found = false;
-#pragma unroll
-            for (int j = 0; j + 1 < NC; ++j) {
-                const int cnt = sa.cnt[j];
-                if (!found && i >= cnt) {
-                    i -= cnt;
-                    pack = sa.pack[j + 1];
-                    rsh = sa.rsh[j + 1];
-                    np4 = sa.np4[j + 1];
-                } else {
-                    found = true;
+        for (int u = 0; u < CS_FU; ++u) {
+            if (u * CS_T >= pieces) continue;
+            const int i = tid + u * CS_T;
+            v4i x = fr[u];
+            int back = 0;
+            if (sa->ragged) (void)source(u, &back);  // (scalar)
+            if (back) {
+                uint64_t p0 = (uint32_t)x[0] | (uint64_t)(uint32_t)x[1] << 32, p1 = (uint32_t)x[2] | (uint64_t)(uint32_t)x[3] << 32;
+                const int b = (back & 7) * 8;
+                if (back & 8) {
+                    p0 = p1;
+                    p1 = 0;
                 }
+                if (b) {
+                    p0 = p0 >> b | p1 << (64 - b);
+                    p1 >>= b;
+                }
+                x = v4i{(int)p0, (int)(p0 >> 32), (int)p1, (int)(p1 >> 32)};
             }
-            cr[u] = i < np4 ? pack[i] : rsh[i - np4];
-        }
-        v4i* fdst = (v4i*)smem;
-        int* cdst = (int*)(smem + off_c);
-#pragma unroll
-        for (int u = 0; u < CS_FU; ++u) {
-            const int i = tid + u * NTHR;
-            if (i < f_pieces) {   // into the signed domain (code - 128)
-                v4i x = fr[u];
-                x[0] ^= 0x80808080;
-                x[1] ^= 0x80808080;
-                x[2] ^= 0x80808080;
-                x[3] ^= 0x80808080;
-                fdst[i] = x;
+            if (sa->expand) {  // (scalar) four pixels of one to three bytes
+                const uint32_t d0 = x[0], d1 = x[1], d2 = x[2];
+                if (sa->expand == 3)
+                    x = v4i{(int)(d0 & 0xffffffu), (int)(d0 >> 24 | (d1 & 0xffffu) << 8), (int)(d1 >> 16 | (d2 & 0xffu) << 16), (int)(d2 >> 8)};
+                else if (sa->expand == 2)
+                    x = v4i{(int)(d0 & 0xffffu), (int)(d0 >> 16), (int)(d1 & 0xffffu), (int)(d1 >> 16)};
+                else
+                    x = v4i{(int)(d0 & 255u), (int)(d0 >> 8 & 255u), (int)(d0 >> 16 & 255u), (int)(d0 >> 24)};
             }
-        }
 #pragma unroll
-        for (int u = 0; u < CS_CU; ++u) {
-            const int i = tid + u * NTHR;
-            if (i < c_words) cdst[i] = cr[u];
+            for (int j = 0; j < 4; ++j) x[j] ^= (int)0x80808080;  // into the signed domain (code - 128)
+            if (i < pieces) *(v4i*)(smem + 16 * i) = x;
+        }
+    };
+
+    // ---- the start: the first frame, the weights, the constants and the tables of K.  An instruction that all sixteen
+    // wavefronts execute takes 16 clocks of the CU, so that what a single wavefront can do a single one does.
+    const int64_t step = gridDim.x;
+    int64_t img = blockIdx.x;
+    fetch_frame(img);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(warm) / 4); ++i) asm volatile("" ::"s"(warm[i]));
+    const int nc = sa->nc;
+    if (wave >= CS_W - nc) {  // (scalar) one wavefront per layer
+        const StackLayer AQ_CONST& L = sa->L[CS_W - 1 - wave];
+        const v4i c0 = ((gv4i_ptr)L.pack)[lane < L.NT * 32 ? lane : 0];
+        const float inv_run = 1.0f / (float)L.run;
+        for (int i = lane; i < 4 * L.k_len; i += 64) {  // k-step i / 4, piece i % 4
+            const int k1 = 16 * i, k = k1 < L.K ? k1 : L.K - 16, ky = (int)(((float)k + 0.5f) * inv_run);
+            ((int*)(smem + L.k_off))[(i & 3) * L.k_len + (i >> 2)] = __mul24(ky, L.row) + (k - __mul24(ky, L.run));
+        }
+        if (lane < L.NT * 32) *(v4i*)(smem + L.c_off + 16 * lane) = c0;
+        for (int i = 64 + lane; i < L.NT * 32; i += 64) *(v4i*)(smem + L.c_off + 16 * i) = ((gv4i_ptr)L.pack)[i];
+    }
+    if (WLDS) {
+        const int l = wave >> 2;  // (scalar) four wavefronts per layer
+        if (l < nc && !(l == 0 && sa->expand)) {
+            const StackLayer AQ_CONST& L = sa->L[l];
+            for (int j = wave & 3; j < L.w_tiles; j += 4) lds_fetch_1k(L.wp + j * 1024, smem + L.w_off + j * 1024, lane);
         }
     }
-    __syncthreads();
-    int c_at = off_c;  // this layer's constants in LDS
-    static_for<0, NC>([&](auto l_c) __attribute__((always_inline)) {
-        constexpr int l = decltype(l_c)::value;
-        const StackLayer& L = sa.L[l];
-        const int8_t* in = smem + ((l & 1) ? off_b : 0);
-        int8_t* map_out = smem + ((l & 1) ? 0 : off_b);
-        const int R = L.oh * L.ow, RT = (R + 31) >> 5, NT = L.NT, KS = L.KS, N = L.N;
-        const int run = L.kw * L.in_c, row_bytes = L.in_w * L.in_c;
-        constexpr bool to_global = l == nc - 1;
-        const int z_out = z_q[l];
-        const int lo = L.act == AQ_ACT_RELU ? z_out : 0;
-        const bool fast = fastf[l] != 0;
-        LayerTaps T{nullptr, nullptr, nullptr};
-        if (TAPS) T = LayerTaps{t.acc[l], t.act[l], nullptr};
-        const int np = NT * 32;
-        const int32_t* cst = (const int32_t*)(smem + c_at);
-        const CPtrs C{cst, cst + np, cst + 4 * np, cst + 2 * np, cst + 3 * np, nullptr};
-        for (int tile = wave; tile < RT * NT; tile += W) {
-            const int nt = tile % NT, rt = tile / NT;
-            const int r = rt * 32 + n;           // this lane's output position (operand column)
-            const int rc = r < R ? r : R - 1;    // a ragged last tile re-reads the last position; never stored
-            const int oy = rc / L.ow, ox = rc - oy * L.ow;
-            const int8_t* base = in + (oy * L.stride * L.in_w + ox * L.stride) * L.in_c;
-            gv4i_ptr wg = (gv4i_ptr)L.wp + (int64_t)nt * KS * 64 + lane;
-            v16i acc[1][1];
-            acc[0][0] = zero16();
-            // Operands of four k-steps at a time, two sets in flight: the reads of one set run under the
-            // MFMAs of the other.  px walks this lane's half of the k-steps through the input map: 32 bytes
-            // on, and at the end of a kernel row (kr == run) down to the next map row.
-            const int8_t* px = base + g * 16;
-            int kr = 0;
-            auto load4 = [&](int k0, v4i (&A)[4], v4i (&X)[4]) __attribute__((always_inline)) {
+    if (WLDS && sa->expand) {  // the first layer's weights with four channels per tap: a thread makes the four bytes of one
+        const StackLayer AQ_CONST& L = sa->L[0];
+        const int KS = L.KS, words = L.w_tiles * 256, ch = sa->expand;
+        const int8_t AQ_GLOBAL* wp = (const int8_t AQ_GLOBAL*)L.wp;
+        for (int i = tid; i < words; i += CS_T) {
+            const int tile = i >> 8, ln = (i >> 2) & 63, nt = tile / KS, ks = tile - nt * KS;
+            const int tap = (ks * 32 + 16 * (ln >> 5)) / 4 + (i & 3);
+            uint32_t w = 0;
+            if (4 * tap < L.K)
+                for (int c = 0; c < ch; ++c) {
+                    const int k = tap * ch + c;
+                    const int8_t v = wp[(((int64_t)nt * sa->KS0 + (k >> 5)) * 64 + (ln & 31) + 32 * ((k & 31) >> 4)) * 16 + (k & 15)];
+                    w |= (uint32_t)(uint8_t)v << (8 * c);
+                }
+            *(uint32_t*)(smem + L.w_off + 4 * i) = w;
+        }
+    }
+    store_frame();
+    if (WLDS) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (this wavefront's share of the weights is in LDS)
+
+    const int a_lane = (g >> 1) * 1024 + (i16 + 32 * (g & 1)) * 16;  // this lane's piece of a k-step's two weight tiles
+    for (;;) {
+        const bool more = img + step < sa->batch;
+        for (int l = 0; l < nc; ++l) {
+            lds_barrier();
+            // (read anew each time: kept across the loop, four layers' arguments are more than there are scalar registers)
+            const StackLayer AQ_CONST* Lp = &sa->L[l];
+            asm volatile("" : "+s"(Lp));
+            const StackLayer AQ_CONST& L = *Lp;
+            const int N = L.N, np = L.NT * 32, K = L.K, KS = L.KS;
+            const int z_out = ((const NetDev AQ_CONST*)netp)->actq[l + 1].z, fast = ((const NetDev AQ_CONST*)netp)->fast[l];
+            const int lo = L.act == AQ_ACT_RELU ? z_out : 0;
+            int lo_v = lo;
+            asm volatile("" : "+v"(lo_v));
+            const int32_t* const koff = (const int32_t*)(smem + L.k_off) + g * L.k_len;
+            const int w_nt = (wave * L.per_inv) >> 16, w_rt = wave - w_nt * L.per_nt;
+            for (int nt = w_nt; nt < L.NT; nt += CS_W) {
+                const int8_t* const wl = smem + L.w_off + nt * KS * 1024 + a_lane;
+                const int8_t AQ_GLOBAL* const wg = (const int8_t AQ_GLOBAL*)L.wp + nt * KS * 1024 + a_lane;
+                auto weights = [&](int off) __attribute__((always_inline)) {
+                    return WLDS ? *(const v4i*)(wl + off) : *(const v4i AQ_GLOBAL*)(wg + off);
+                };
+                const int32_t* const cst = (const int32_t*)(smem + L.c_off) + nt * 32 + 4 * g;
+                v4i bias[2];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int k = k0 + j;
-                    const int kc = k < KS ? k : KS - 1;
-                    A[j] = wg[(int64_t)kc * 64];
-                    X[j] = *(const v4i*)px;
-                    if (k < KS - 1) {   // (uniform) never steps past the last k-step's bytes
-                        kr += 32;
-                        const bool wrap = kr == run;
-                        px += wrap ? 32 + row_bytes - run : 32;
-                        kr = wrap ? 0 : kr;
+                for (int f = 0; f < 2; ++f) bias[f] = *(const v4i*)(cst + 16 * f);
+                for (int rt = w_rt; rt < L.RT; rt += L.per_nt) {
+                    const int r = rt * 16 + i16;           // this lane's output position (operand column)
+                    const int rc = r < L.R ? r : L.R - 1;  // a ragged last tile re-reads the last position; never stored
+                    const int oy = (int)(((float)rc + 0.5f) * L.inv_ow), ox = rc - __mul24(oy, L.ow);
+                    const int8_t* const xb = smem + L.in_off + __mul24(oy, L.pos_y) + __mul24(ox, L.pos_x);
+                    v4i acc[2] = {bias[0], bias[1]};
+                    int s = 0;
+                    for (; (s + 4) * 64 <= K; s += 4) {  // (one read for the places of four k-steps)
+                        const v4i ko = *(const v4i*)(koff + s);
+                        v4i X[4], A[4][2];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            A[j][0] = weights((s + j) * 2048);
+                            A[j][1] = weights((s + j) * 2048 + 256);
+                        }
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) X[j] = *(const v4i*)(xb + ko[j]);
+                        __builtin_amdgcn_sched_barrier(0);  // (all twelve requests before the first product)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            acc[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[j][0], X[j], acc[0], 0, 0, 0);
+                            acc[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[j][1], X[j], acc[1], 0, 0, 0);
+                        }
+                    }
+                    for (; s * 64 < K; ++s) {
+                        // (a k-step that K ends in: zeros from there on, and no weights from past the last tile)
+                        const bool ok = 64 * s + 16 * g < K;
+                        const int back = 2 * s + (g >> 1) < KS ? 0 : 1024;
+                        v4i X = *(const v4i*)(xb + koff[s]);
+                        const v4i A0 = weights(s * 2048 - back), A1 = weights(s * 2048 + 256 - back);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) X[j] = ok ? X[j] : 0;
+                        acc[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A0, X, acc[0], 0, 0, 0);
+                        acc[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A1, X, acc[1], 0, 0, 0);
+                    }
+                    const int c255 = 255;
+                    uint32_t pack[2];
+#pragma unroll
+                    for (int f = 0; f < 2; ++f) {
+                        const v4i val = acc[f], M = *(const v4i*)(cst + np + 16 * f);
+                        int code[4];
+                        if (fast) {  // (scalar)
+                            const v4i Z = *(const v4i*)(cst + 2 * np + 16 * f), S = *(const v4i*)(cst + 3 * np + 16 * f);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) code[i] = clamp_code((__mulhi(val[i], M[i]) + Z[i]) >> S[i], lo_v, c255);
+                        } else {
+                            const v4i S = *(gv4i_ptr)(L.rsh + nt * 32 + 16 * f + 4 * g);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) code[i] = requant_code(val[i], M[i], S[i], z_out, lo);
+                        }
+                        if (TAPS) {
+                            const int64_t at = (img * L.R + r) * N + nt * 32 + 16 * f + 4 * g;
+                            const TapArgs t = taps_of(tp);
+                            int32_t* const t_acc = t.acc[l];
+                            uint8_t* const t_act = t.act[l];
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const bool ok = r < L.R && nt * 32 + 16 * f + 4 * g + i < N;
+                                if (t_acc && ok) t_acc[at + i] = val[i];
+                                if (t_act && ok) t_act[at + i] = (uint8_t)code[i];
+                            }
+                        }
+                        pack[f] = ((uint32_t)code[0] | (uint32_t)code[1] << 8 | (uint32_t)code[2] << 16 | (uint32_t)code[3] << 24) ^ 0x80808080u;
+                    }
+                    const int n0 = nt * 32 + 4 * g;
+                    if (r < L.R) {
+                        if (l == nc - 1) {  // (scalar)
+                            int8_t AQ_GLOBAL* o = (int8_t AQ_GLOBAL*)out + (img * L.R + r) * N + n0;
+                            if (n0 < N) *(uint32_t AQ_GLOBAL*)o = pack[0];
+                            if (n0 + 16 < N) *(uint32_t AQ_GLOBAL*)(o + 16) = pack[1];
+                        } else {
+                            int8_t* o = smem + L.out_off + __mul24(oy, L.out_row) + __mul24(ox, N) + n0;
+                            if (n0 < N) *(uint32_t*)o = pack[0];
+                            if (n0 + 16 < N) *(uint32_t*)(o + 16) = pack[1];
+                        }
                     }
                 }
-            };
-            auto mma4 = [&](int k0, v4i (&A)[4], v4i (&X)[4]) __attribute__((always_inline)) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (k0 + j < KS) acc[0][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[j], X[j], acc[0][0], 0, 0, 0);
-            };
-            v4i A0[4], X0[4], A1[4], X1[4];
-            load4(0, A0, X0);
-            int k0 = 0;
-            for (; k0 + 8 < KS; k0 += 8) {
-                load4(k0 + 4, A1, X1);
-                mma4(k0, A0, X0);
-                load4(k0 + 8, A0, X0);
-                mma4(k0 + 4, A1, X1);
             }
-            // the last eight k-steps or fewer, without the request for a group after them: past K a request
-            // re-reads the last k-step and still takes its slot on the vector memory path
-            if (k0 + 4 < KS) load4(k0 + 4, A1, X1);
-            mma4(k0, A0, X0);
-            mma4(k0 + 4, A1, X1);
-            v16i rs[1];
-            rs[0] = zero16();
-            const int64_t row_g = img * R + r;  // row of the layer's [batch * oh * ow][N] output
-            int8_t* out0 = to_global ? out + row_g * N : map_out + r * N;
-            if (fast)
-                epi_hidden_wave<1, 1, false, TAPS, true>(N, NT, T, C, acc, rs, 0, nt, g, row_g, img * R + R, true, z_out, lo,
-                                                        out0, 0, true, N);
-            else
-                epi_hidden_wave<1, 1, false, TAPS, false>(N, NT, T, C, acc, rs, 0, nt, g, row_g, img * R + R, true, z_out, lo,
-                                                         out0, 0, true, N);
+            if (l == 0) {
+                if (more) fetch_frame(img + step);
+                asm volatile("" ::: "memory");  // (the requests stay in front of the layers)
+            }
         }
-        c_at += CS_CONSTS * np * 4;
-        __syncthreads();
-    });
+        if (!more) break;
+        store_frame();  // (the first layer was the frame's only reader)
+        img += step;
+    }
 }
 
 int conv_stack_layers(const FwdArgs& a) {
     StackPlan p;
-    return plan_stack(a, &p) ? p.nc : 0;
+    return plan_stack(a, &p, nullptr) ? p.nc : 0;
 }
 
 aq_status launch_conv_stack(const FwdArgs& a, int8_t* out, hipStream_t st) {
     StackPlan p;
-    if (!plan_stack(a, &p)) return AQ_ESHAPE;
+    StackArgs sa;
+    if (!plan_stack(a, &p, &sa)) return AQ_ESHAPE;
     const bool taps = any_taps(a);
-    dim3 grid((unsigned)a.c.batch);
-    StackArgs sa{};
-    {
-        const LayerDev& L0 = a.net.L[0];
-        sa.f_pieces = (L0.in_h * L0.in_w * L0.in_c) >> 4;
-        for (int l = 0; l < p.nc; ++l) {
-            const LayerDev& L = a.net.L[l];
-            sa.cnt[l] = CS_CONSTS * L.NT * 32;
-            sa.np4[l] = 4 * L.NT * 32;
-            sa.pack[l] = L.bias_fold;
-            sa.rsh[l] = L.rshift;
-            sa.c_words += sa.cnt[l];
-            sa.L[l] = StackLayer{L.wp, L.oh, L.ow, L.in_w, L.in_c, L.kw, L.stride, L.N, L.NT, L.KS, L.act};
-        }
-    }
-#define AQ_STACK(TP, WV, NCV)                                                                                        \
+    const dim3 grid((unsigned)(a.c.batch < 256 ? a.c.batch : 256));
+#define AQ_STACK(TP, WL)                                                                                             \
     do {                                                                                                             \
         static std::atomic<bool> attr_set{false};                                                                    \
         if (!attr_set) {                                                                                             \
-            if (hipFuncSetAttribute((const void*)k_conv_stack<TP, WV, NCV>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+            if (hipFuncSetAttribute((const void*)k_conv_stack<TP, WL>, hipFuncAttributeMaxDynamicSharedMemorySize,   \
                                     (int)CS_MAX_LDS) != hipSuccess)                                                  \
                 return AQ_EHIP;                                                                                      \
             attr_set = true;                                                                                         \
         }                                                                                                            \
-        hipLaunchKernelGGL((k_conv_stack<TP, WV, NCV>), grid, dim3(WV * 64), p.lds, st, a.d_net, TapParam<TP>(a.t), sa, \
-                           (const uint8_t*)a.c.obs, out, p.off_b, p.off_c);                                          \
+        hipLaunchKernelGGL((k_conv_stack<TP, WL>), grid, dim3(CS_T), p.lds, st, a.d_net, (const uint8_t*)a.c.obs,    \
+                           out, sa, TapParam<TP>(a.t));                                                              \
     } while (0)
-#define AQ_STACK_NC(TP, WV)                 \
-    switch (p.nc) {                         \
-        case 2: AQ_STACK(TP, WV, 2); break; \
-        case 3: AQ_STACK(TP, WV, 3); break; \
-        default: AQ_STACK(TP, WV, 4); break; \
-    }
-    // up to one image per CU: sixteen waves (the first layer's tiles then run in one round); beyond that
-    // eight, so that two workgroups share a CU
-    if (a.c.batch <= 256) {
-        if (taps) AQ_STACK_NC(true, 16)
-        else AQ_STACK_NC(false, 16)
+    if (p.resident) {
+        if (taps) AQ_STACK(true, true);
+        else AQ_STACK(false, true);
     } else {
-        if (taps) AQ_STACK_NC(true, 8)
-        else AQ_STACK_NC(false, 8)
+        if (taps) AQ_STACK(true, false);
+        else AQ_STACK(false, false);
     }
-#undef AQ_STACK_NC
 #undef AQ_STACK
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
