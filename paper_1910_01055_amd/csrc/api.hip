@@ -1,4 +1,6 @@
 // C ABI of the library: the policy handle, argument checks and the launch sequences.
+#include <cstddef>
+#include <cstring>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -65,8 +67,8 @@ struct F32Store {
     void* slab = nullptr;
     F32Ptrs ptrs{};            // host copy, and its device copy for the whole-MLP kernel
     F32Ptrs* d_ptrs = nullptr;
-    F32KeepTab tab{};
     F32KeepTab* d_tab = nullptr;
+    int blocks = 0;            // of the launch that fills it
 };
 
 struct aq_policy {
@@ -111,7 +113,8 @@ struct aq_policy {
     void* act_f16[2] = {nullptr, nullptr};
     // the learner's fp32 parameters, copied by aq_policy_set_params_fp32, and the packed weights of parameters passed
     // with a call (one allocation each, at the first call that needs it)
-    F32Store f32_kept, f32_passed;
+    F32Store f32_kept;    // allocated by the first aq_policy_set_params_fp32
+    F32Store f32_passed;  // of parameters passed with a call (packed weights only), part of the policy's slab
     bool f32_ready = false;
     // policies of at most 4 bits, per-channel symmetric, under launch plan 4: the fully connected layers' weights
     // once more as nibbles, for the few-row kernel (one allocation when the plan is first chosen; rewritten by
@@ -177,6 +180,41 @@ extern "C" const char* aq_status_string(aq_status s) {
         case AQ_ETOOBIG: return "needs more scratch memory than is available without allocating";
     }
     return "unknown";
+}
+
+// A set of fp32 parameters: the packed weights, with `keep` also row-major copies, biases, gains and offsets.  Fills
+// all of the table that fills them but the destinations, their places into offs, and returns the bytes they take.
+static size_t f32_store_layout(const aq_policy* p, bool keep, F32KeepTab& tab, size_t* offs) {
+    size_t bytes = 0;
+    int blk = 0;
+    auto add = [&](int64_t n, int kind, int l) {
+        offs[tab.n] = bytes;
+        bytes += ((size_t)n * 4 + 255) / 256 * 256;
+        tab.blk0[tab.n] = blk;
+        tab.e[tab.n++] = F32KeepTab::Entry{nullptr, n, kind, l, p->L[l].N, p->L[l].K};
+        blk += (int)((n + kKeepPiece - 1) / kKeepPiece);
+    };
+    for (int l = 0; l < p->net.n_layers; ++l) {
+        const LayerBuf& b = p->L[l];
+        if (keep) {
+            add((int64_t)b.N * b.K, 0, l);
+            for (int i = 1; i < 4; ++i) add(b.N, i, l);
+        }
+        add((int64_t)((b.N + 15) / 16) * ((b.K + 15) / 16) * 256, 4, l);
+    }
+    tab.blocks = blk;
+    return bytes;
+}
+
+// ... and the destinations, from where the set begins
+static F32Ptrs f32_store_place(F32KeepTab& tab, char* base, const size_t* offs) {
+    F32Ptrs ptrs{};
+    for (int i = 0; i < tab.n; ++i) {
+        F32KeepTab::Entry& e = tab.e[i];
+        e.dst = (float*)(base + offs[i]);
+        (e.kind == 0 ? ptrs.w : e.kind == 1 ? ptrs.b : e.kind == 2 ? ptrs.gamma : e.kind == 3 ? ptrs.beta : ptrs.wpk)[e.layer] = e.dst;
+    }
+    return ptrs;
 }
 
 extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
@@ -277,14 +315,21 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     size_t off_part = take((size_t)rng_blks * 3 * 4);
     size_t off_qptrs = take(sizeof(QPtrs));
     size_t off_slots = take(sizeof(RangeSlot) * kRangeSlots * AQ_MAX_LAYERS);
+    // what the host writes, side by side: one copy
     size_t off_net = take(sizeof(NetDev));
     size_t off_qtab = take(sizeof(QTab));
+    size_t off_ftab = take(sizeof(F32KeepTab));
+    // the packed weights of aq_policy_forward_fp32_params, whose first call may be one into a graph: part of the slab, as
+    // an allocation of their own they would cost every policy 0.1 ms
+    F32KeepTab ftab{};
+    size_t f32_offs[5 * AQ_MAX_LAYERS];
+    const size_t used = bytes, off_f32 = take(f32_store_layout(p, false, ftab, f32_offs));
     if (hipMalloc(&p->slab, bytes) != hipSuccess) {
         delete p;
         return AQ_ENOMEM;
     }
     // zero once: padding rows / k-steps of the packed weights and padded constants stay zero for good
-    if (hipMemset(p->slab, 0, bytes) != hipSuccess) {
+    if (hipMemset(p->slab, 0, used) != hipSuccess) {
         (void)hipFree(p->slab);
         delete p;
         return AQ_EHIP;
@@ -351,11 +396,6 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         }
         q.row_blks = row_blk;
         q.rng_blks_total = rng_blk;
-        if (hipMemcpy(p->d_qtab, &q, sizeof(QTab), hipMemcpyHostToDevice) != hipSuccess) {
-            (void)hipFree(p->slab);
-            delete p;
-            return AQ_EHIP;
-        }
     }
     {   // FNV-1a over everything that fixes the blob's layout and meaning
         uint64_t h = 1469598103934665603ull;
@@ -378,7 +418,14 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         mix((int64_t)p->layer_bytes);
         p->net_hash = h;
     }
-    if (hipMemcpy(p->d_net, &p->h_net, sizeof(NetDev), hipMemcpyHostToDevice) != hipSuccess) {
+    p->f32_passed.ptrs = f32_store_place(ftab, base + off_f32, f32_offs);
+    p->f32_passed.d_tab = (F32KeepTab*)(base + off_ftab);
+    p->f32_passed.blocks = ftab.blocks;
+    std::vector<char> up(off_ftab + sizeof(F32KeepTab) - off_net);
+    memcpy(up.data(), &p->h_net, sizeof(NetDev));
+    memcpy(up.data() + (off_qtab - off_net), &p->h_qtab, sizeof(QTab));
+    memcpy(up.data() + (off_ftab - off_net), &ftab, sizeof(F32KeepTab));
+    if (hipMemcpy(p->d_net, up.data(), up.size(), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(p->slab);
         delete p;
         return AQ_EHIP;
@@ -409,7 +456,6 @@ extern "C" aq_status aq_policy_destroy(aq_policy* p) {
     if (p->y_rows) (void)hipFree(p->y_rows);
     if (p->h16_slab) (void)hipFree(p->h16_slab);
     if (p->f32_kept.slab) (void)hipFree(p->f32_kept.slab);
-    if (p->f32_passed.slab) (void)hipFree(p->f32_passed.slab);
     if (p->calib) (void)hipHostFree(p->calib);
     delete p;
     return AQ_OK;
@@ -1085,51 +1131,31 @@ static F32Ptrs f32_ptr_table(int nl, const float* const* w, const float* const* 
     return t;
 }
 
-// Storage for a set of fp32 parameters: the packed weights, with `keep` also row-major copies, biases, gains and
-// offsets, and the tables over them.
-static aq_status ensure_f32_store(aq_policy* p, F32Store& S, bool keep, hipStream_t st) {
+// Storage of the parameters that aq_policy_set_params_fp32 keeps, made once.
+static aq_status ensure_f32_kept(aq_policy* p, hipStream_t st) {
+    F32Store& S = p->f32_kept;
     if (S.slab) return AQ_OK;
     if (capturing(st)) return AQ_ETOOBIG;
-    const int nl = p->net.n_layers;
-    size_t bytes = 0;
-    int blk = 0;
     F32KeepTab tab{};
-    std::vector<size_t> offs;
-    auto add = [&](int64_t n, int kind, int l) {
-        offs.push_back(bytes);
-        bytes += ((size_t)n * 4 + 255) / 256 * 256;
-        tab.blk0[tab.n] = blk;
-        tab.e[tab.n++] = F32KeepTab::Entry{nullptr, n, kind, l, p->L[l].N, p->L[l].K};
-        blk += (int)((n + kKeepPiece - 1) / kKeepPiece);
-    };
-    for (int l = 0; l < nl; ++l) {
-        const LayerBuf& b = p->L[l];
-        if (keep) {
-            add((int64_t)b.N * b.K, 0, l);
-            for (int i = 1; i < 4; ++i) add(b.N, i, l);
-        }
-        add((int64_t)((b.N + 15) / 16) * ((b.K + 15) / 16) * 256, 4, l);
-    }
-    tab.blocks = blk;
-    const size_t off_ptrs = bytes, off_tab = bytes + (sizeof(F32Ptrs) + 255) / 256 * 256;
-    void* slab = nullptr;
-    if (hipMalloc(&slab, off_tab + sizeof(F32KeepTab)) != hipSuccess) return AQ_ENOMEM;
-    F32Ptrs ptrs{};
-    for (int i = 0; i < tab.n; ++i) {
-        F32KeepTab::Entry& e = tab.e[i];
-        e.dst = (float*)((char*)slab + offs[i]);
-        (e.kind == 0 ? ptrs.w : e.kind == 1 ? ptrs.b : e.kind == 2 ? ptrs.gamma : e.kind == 3 ? ptrs.beta : ptrs.wpk)[e.layer] = e.dst;
-    }
-    S.d_ptrs = (F32Ptrs*)((char*)slab + off_ptrs);
-    S.d_tab = (F32KeepTab*)((char*)slab + off_tab);
-    if (hipMemcpy(S.d_ptrs, &ptrs, sizeof(ptrs), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(S.d_tab, &tab, sizeof(tab), hipMemcpyHostToDevice) != hipSuccess) {
+    size_t offs[5 * AQ_MAX_LAYERS];
+    const size_t bytes = f32_store_layout(p, true, tab, offs);
+    struct {
+        F32Ptrs ptrs;
+        F32KeepTab tab;
+    } up{};
+    char* slab = nullptr;
+    if (hipMalloc((void**)&slab, bytes + sizeof(up)) != hipSuccess) return AQ_ENOMEM;
+    up.ptrs = f32_store_place(tab, slab, offs);
+    up.tab = tab;
+    if (hipMemcpy(slab + bytes, &up, sizeof(up), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(slab);
         return AQ_EHIP;
     }
+    S.d_ptrs = (F32Ptrs*)(slab + bytes);
+    S.d_tab = (F32KeepTab*)(slab + bytes + offsetof(decltype(up), tab));
     S.slab = slab;
-    S.ptrs = ptrs;
-    S.tab = tab;
+    S.ptrs = up.ptrs;
+    S.blocks = tab.blocks;
     return AQ_OK;
 }
 
@@ -1143,10 +1169,8 @@ extern "C" aq_status aq_policy_forward_fp32_params(aq_policy* p, const float* co
     for (int l = 0; l < p->net.n_layers; ++l)
         if (!h_d_w[l]) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
-    aq_status s = ensure_f32_store(p, p->f32_passed, false, st);
-    if (s != AQ_OK) return s;
     F32Ptrs ptrs = f32_ptr_table(p->net.n_layers, h_d_w, h_d_b, h_d_gamma, h_d_beta);
-    s = launch_keep_params(ptrs, p->f32_passed.d_tab, p->f32_passed.tab.blocks, st);
+    const aq_status s = launch_keep_params(ptrs, p->f32_passed.d_tab, p->f32_passed.blocks, st);
     if (s != AQ_OK) return s;
     for (int l = 0; l < p->net.n_layers; ++l) ptrs.wpk[l] = p->f32_passed.ptrs.wpk[l];
     return forward_fp32_impl(p, ptrs, nullptr, d_obs, batch, d_actions, d_ranges_out, nullptr, 0, st);
@@ -1160,11 +1184,11 @@ extern "C" aq_status aq_policy_set_params_fp32(aq_policy* p, const float* const*
     for (int l = 0; l < nl; ++l)
         if (!h_d_w[l]) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
-    aq_status s = ensure_f32_store(p, p->f32_kept, true, st);
+    aq_status s = ensure_f32_kept(p, st);
     if (s != AQ_OK) return s;
     // (absent biases, gains and offsets take their defaults 0, 1, 0)
     s = launch_keep_params(f32_ptr_table(nl, h_d_w, h_d_b, h_d_gamma, h_d_beta), p->f32_kept.d_tab,
-                           p->f32_kept.tab.blocks, st);
+                           p->f32_kept.blocks, st);
     if (s != AQ_OK) return s;
     p->f32_ready = true;
     return AQ_OK;

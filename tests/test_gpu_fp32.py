@@ -79,3 +79,26 @@ def test_fp32_calibration_of_a_smaller_batch_forgets_the_larger_ones_ranges(aq):
     P.calibrate_fp32(obs)
     assert P.calibrate_fp32(obs[:2]) == first
     P.close()
+
+
+def test_fp32_forward_on_passed_parameters_is_captured_after_reserve(aq):
+    """After a reserve the first call of the forward that takes its parameters may be one into a graph."""
+    net = synth.small_net([fc(17, 300, "relu"), fc(300, 1100, "relu"), fc(1100, 6, "none")])
+    params = synth.make_params(net, nonzero_bias=True)
+    dev = U.upload_params(params)
+    obs, out = U.to_dev(synth.make_obs(net, 40)), torch.zeros(40, 6, device=U.DEV)
+    P = aq.Policy(net)
+    P.policy_reserve(40)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        P.policy_forward_fp32_params(*dev, obs, out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        replayed = out.clone()
+        P.policy_forward_fp32_params(*dev, obs, out)
+        torch.cuda.synchronize()
+        assert torch.equal(replayed, out)
+    assert U.close(replayed.cpu().numpy(), O.OraclePolicy(net).forward_fp32(params, synth.make_obs(net, 40))[0]).all()
+    P.close()
