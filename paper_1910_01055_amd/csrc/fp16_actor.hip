@@ -464,6 +464,62 @@ __global__ __launch_bounds__(SKH_W * 64) void k_layer_fp16_skinny(const Fp16Laye
     }
 }
 
+// The same for at most 16 rows, on tiles of 16 rows x 16 features (v_mfma_f32_16x16x32_f16): no half of the tile that
+// belongs to nobody, twice the workgroups, and a wave's share of K up to 2048 is at most eight k-steps of 32, all in flight
+// at once (the kernel above needs two round trips of eight there).  Bound by those round trips and the launch: a layer of
+// 2048 x 2048 at one row has 8 MiB of weights on 128 CUs.  67-2048x3-21 at one row: 19.0 us with the kernel above, 15.3.
+// The library's 32 x 16 weight tiles serve it unchanged: lane (i = lane % 16, g = lane / 16) of feature half h and k-step s
+// takes piece h * 16 + i + 32 * (g % 2) of tile 2 s + g / 2.  PF: k-steps in flight, 4 for shares of up to four, else 8
+// (those past the share re-read its last).
+typedef float f4acc __attribute__((ext_vector_type(4)));
+template <int PF>
+__global__ __launch_bounds__(SKH_W * 64) void k_layer_fp16_rows16(const Fp16Layer L, const _Float16* __restrict__ in,
+                                                                 _Float16* __restrict__ out, const int rows) {
+    __shared__ float part[SKH_W * 4 * SKH_LD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i = lane & 15, g = lane >> 4, h = blockIdx.x & 1;
+    const int KSr = (L.K + 31) / 32;  // (the tiles are padded to 64 k)
+    const int kc = (KSr + SKH_W - 1) / SKH_W;
+    const int k0 = wave * kc, k1 = k0 + kc < KSr ? k0 + kc : KSr;
+    const bool row_ok = i < rows;
+    const h8* wsrc = (const h8*)L.wp + (int64_t)(blockIdx.x >> 1) * L.KS16 * 64 + (g >> 1) * 64 + h * 16 + i + 32 * (g & 1);
+    const _Float16* xsrc = in + (int64_t)(row_ok ? i : rows - 1) * L.K;
+    // this thread's output: row m, feature n (bias is padded to the tile)
+    const int m = (tid >> 4) & 15, nl = tid & 15, n = blockIdx.x * 16 + nl;
+    const float bias = L.bias[n];
+    const h8 z8 = {0, 0, 0, 0, 0, 0, 0, 0};
+    f4acc acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int g0 = k0; g0 < k1; g0 += PF) {
+        h8 a[PF], b[PF];
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            const int ks = g0 + u < k1 ? g0 + u : k1 - 1;
+            a[u] = wsrc[(int64_t)ks * 128];
+            // K is a multiple of 8: a piece of 8 columns is whole or lies entirely in the zero padding
+            const int kcol = ks * 32 + 8 * g;
+            b[u] = *(const h8*)(xsrc + (kcol < L.K ? kcol : 0));
+            if (!(row_ok && kcol < L.K && g0 + u < k1)) b[u] = z8;
+            if (g0 + u >= k1) a[u] = z8;  // (scalar; a weight may be infinite)
+        }
+#pragma unroll
+        for (int u = 0; u < PF; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u], b[u], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[(wave * 4 + r) * SKH_LD + lane] = acc[r];
+    __syncthreads();
+    if (tid >= 256 || m >= rows || n >= L.N) return;
+    // register and lane that hold (feature nl, row m)
+    const float* src = part + (nl & 3) * SKH_LD + m + 16 * (nl >> 2);
+    float v = 0.0f;
+#pragma unroll
+    for (int kp = 0; kp < SKH_W; ++kp) v += src[kp * 4 * SKH_LD];
+    _Float16 o = (_Float16)(v + bias);
+    if (L.relu) o = o > (_Float16)0.0f ? o : (_Float16)0.0f;
+    out[(int64_t)m * L.N + n] = o;
+    if (L.head_actions)
+        L.head_actions[(int64_t)m * L.N + n] = L.head_tanh ? (float)(_Float16)tanh_rel((float)o) : (float)o;
+}
+
 // LayerNorm (biased variance, eps inside the root) rounded to binary16, then tanh rounded to binary16,
 // in place.  One wavefront per LN_R rows, the rows in registers between the statistics and the result,
 // all of a wave's loads requested before the first is used (8-byte pieces when N is a multiple of 4).
@@ -656,6 +712,14 @@ aq_status launch_layer_fp16(const Fp16Layer& L, const void* in, int in_mode, voi
     // few rows: one workgroup per output tile with K split over its waves, whenever the tiled kernel would
     // leave most CUs without a workgroup (binary16 rows of whole, aligned 16-byte pieces)
     if (fp16_layer_is_skinny(L, in, in_mode, rows)) {
+        // (an argmax in the launch needs the whole row in one tile)
+        if (rows <= 16 && !L.head_argmax) {
+            if (L.K <= SKH_W * 4 * 32)
+                hipLaunchKernelGGL(k_layer_fp16_rows16<4>, dim3(2 * L.NT), dim3(SKH_W * 64), 0, st, L, (const _Float16*)in, o, (int)rows);
+            else
+                hipLaunchKernelGGL(k_layer_fp16_rows16<8>, dim3(2 * L.NT), dim3(SKH_W * 64), 0, st, L, (const _Float16*)in, o, (int)rows);
+            return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
+        }
         const dim3 grid((unsigned)L.NT, (unsigned)((rows + 31) / 32));
         hipLaunchKernelGGL(k_layer_fp16_skinny, grid, dim3(SKH_W * 64), 0, st, L, (const _Float16*)in, o, rows);
         return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;

@@ -35,3 +35,17 @@ def test_whole_network_half_precision_kernel(aq, name, batch):
                                                 np.random.default_rng(3).integers(0, batch, 24)]), batch - 1))
     rows = rows[rows >= 0]
     _check(net, params, obs[rows], actions[rows], [o.reshape(batch, -1)[rows] for o in outs], end_to_end=False)
+
+
+@pytest.mark.parametrize("head", ["tanh", "argmax"])
+@pytest.mark.parametrize("batch", [1, 15, 16, 17])
+def test_half_precision_layers_of_few_rows(aq, head, batch):
+    """A launch per layer at few rows, around the 16 rows up to which a layer takes 16 x 16 tiles: shares of K of one to
+    nine k-steps, wavefronts without one, ragged features, an argmax that needs its row in one tile."""
+    print(f"[fp16 few rows] {head} batch={batch}", flush=True)
+    net = synth.small_net([fc(67, 2056, "relu"), fc(2056, 1104, "ln_tanh"), fc(1104, 136, "relu"), fc(136, 1032, "relu"),
+                           fc(1032, 1024, "relu"), fc(1024, 37 if head == "tanh" else 18, "none")], head=head)
+    params = synth.make_params(net, nonzero_bias=True)
+    obs = synth.make_obs(net, batch)
+    actions, outs = _run_gpu(aq, net, params, obs)
+    _check(net, params, obs, actions, outs, end_to_end=False)
