@@ -80,6 +80,7 @@ struct aq_policy {
     QOut qout{};
     RangeSlot* slots = nullptr;   // kRangeSlots per activation tensor, neutral between calls
     bool slots_dirty = false;     // a calibration ended early: clear them first
+    const float* f32_zeros = nullptr;  // 1 KiB: the fp32 layers' weights past the end of K
     NetDev h_net{};            // host copy of the device-resident network description
     NetDev* d_net = nullptr;
     QTab h_qtab{};             // the quantizer's table of the policy, host copy and device copy
@@ -315,6 +316,7 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     size_t off_part = take((size_t)rng_blks * 3 * 4);
     size_t off_qptrs = take(sizeof(QPtrs));
     size_t off_slots = take(sizeof(RangeSlot) * kRangeSlots * AQ_MAX_LAYERS);
+    size_t off_zeros = take(1024);
     // what the host writes, side by side: one copy
     size_t off_net = take(sizeof(NetDev));
     size_t off_qtab = take(sizeof(QTab));
@@ -356,6 +358,7 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     }
     p->status = (int*)(base + off_status);
     p->slots = (RangeSlot*)(base + off_slots);
+    p->f32_zeros = (const float*)(base + off_zeros);
     p->d_net = (NetDev*)(base + off_net);
     p->d_qtab = (QTab*)(base + off_qtab);
     p->actq = p->d_net->actq;  // device address arithmetic only
@@ -1081,6 +1084,7 @@ static aq_status forward_fp32_impl(aq_policy* p, const F32Ptrs& ptrs, const F32P
             const bool ln = !last && b.d.act == AQ_ACT_LN_TANH, argmax = last && p->net.head == AQ_HEAD_ARGMAX;
             Fp32Layer L{};
             L.wpk = ptrs.wpk[l];
+            L.zeros = p->f32_zeros;
             L.b = ptrs.b[l];
             L.K = b.K;
             L.N = b.N;

@@ -155,20 +155,20 @@ __global__ __launch_bounds__(FT_) void k_fp32_layer(const Fp32Layer L, const voi
 #pragma unroll
         for (int u = 0; u < XS; ++u) *(v4f*)(d + u * (FT_ / CPR) * LD) = xr[u];
     };
-    // this wave's weight operands of LDS stage s (past the last 16 k: the last ones again, against zeros)
+    // this wave's weight operands of LDS stage s; past the last 16 k zeros, like the inputs there (a weight may be
+    // infinite: no weight but its own input's may meet a zero), from a block of them instead of behind a branch
     const float* wbase[FT];
 #pragma unroll
     for (int f = 0; f < FT; ++f) {
         const int t = t0 + f < tiles ? t0 + f : tiles - 1;
-        wbase[f] = L.wpk + (int64_t)t * nst * 256 + lane * 4;
+        wbase[f] = L.wpk + (int64_t)t * nst * 256;
     }
     v4f wr[KS][FT];
     auto fetch_w = [&](auto j_c, int s) __attribute__((always_inline)) {
         constexpr int j = decltype(j_c)::value;
-        int k16 = (s * WK + wk) * KS + j;
-        k16 = k16 < nst ? k16 : nst - 1;
+        const int k16 = (s * WK + wk) * KS + j;
 #pragma unroll
-        for (int f = 0; f < FT; ++f) wr[j][f] = *(const v4f*)(wbase[f] + (int64_t)k16 * 256);
+        for (int f = 0; f < FT; ++f) wr[j][f] = *(const v4f*)((k16 < nst ? wbase[f] + (int64_t)k16 * 256 : L.zeros) + lane * 4);
     };
 
     v4f acc[FT][RT];

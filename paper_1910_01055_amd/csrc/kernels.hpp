@@ -104,6 +104,7 @@ aq_status launch_head_rows(const float* y, int64_t rows, int N, int head, void* 
 // ---- fp32 actor (forward_fp32.hip)
 struct Fp32Layer {
     const float* wpk;  // weights in operand order, see forward_fp32.hip
+    const float* zeros;  // 1 KiB of them
     const float* b;
     int K, N;
     int relu;

@@ -102,3 +102,26 @@ def test_fp32_forward_on_passed_parameters_is_captured_after_reserve(aq):
         assert torch.equal(replayed, out)
     assert U.close(replayed.cpu().numpy(), O.OraclePolicy(net).forward_fp32(params, synth.make_obs(net, 40))[0]).all()
     P.close()
+
+
+@pytest.mark.parametrize("K,N", [(67, 1300), (3136, 512), (3100, 70)])
+@pytest.mark.parametrize("rows", [1, 40, 700, 4100])
+def test_an_infinite_weight_stays_infinite_in_the_per_layer_kernel(aq, K, N, rows):
+    """A diverged policy: one infinite weight among the last 16 inputs of a layer whose K ends inside a stage.  The unit is
+    +infinity on positive inputs, in the actions and in the calibrated ranges; nothing becomes NaN."""
+    net = synth.small_net([fc(K, N, "relu"), fc(N, 5, "none")], head="linear")
+    print(f"[fp32 inf] K={K} N={N} rows={rows}", flush=True)
+    params = synth.make_params(net, nonzero_bias=True)
+    params[0]["w"][N // 2, K - 3] = np.inf
+    obs = np.abs(synth.make_obs(net, rows)) + np.float32(0.01)
+    hidden = np.maximum(obs.astype(np.float64) @ params[0]["w"].T.astype(np.float64) + params[0]["b"], 0.0)
+    want = hidden @ params[1]["w"].T.astype(np.float64) + params[1]["b"]
+    assert np.isinf(want).all()
+    P = aq.Policy(net)
+    P.policy_set_params_fp32(*U.upload_params(params))
+    out = torch.zeros(rows, 5, device=U.DEV)
+    P.policy_forward_fp32(U.to_dev(obs), out)
+    ranges = P.calibrate_fp32(U.to_dev(obs))
+    assert np.array_equal(out.cpu().numpy(), want.astype(np.float32))
+    assert ranges[1][1] == np.inf and ranges[1][0] == 0.0 and np.isfinite(ranges[0]).all()
+    P.close()
