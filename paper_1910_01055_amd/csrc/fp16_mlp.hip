@@ -302,6 +302,11 @@ __global__ __launch_bounds__(MLT) void k_fp16_mlp(const Fp16Net* __restrict__ ne
                 lds_barrier();
                 break;
         }
+        // The features that pad the layer to whole tiles become zeros, by the wavefront that wrote them (its LDS writes stay
+        // in order): zero weights times an infinite input were no zeros, and the next layer's sums would take them in.
+        // (Selected in the epilogue above, it cost the wide case 8 us in spilled registers.)
+        if (!last && (N & 31) && wave == ((NT - 1) & (MLW - 1)) && lane < ROWS)
+            for (int n = N; n < NT * 32; ++n) xs[lane * ld + n] = (_Float16)0.0f;
         if (!last && a.L[l].act == AQ_ACT_LN_TANH) {
             // LayerNorm (biased variance, eps inside the root) of the rounded outputs, rounded, then tanh, rounded; a
             // wavefront per row, the row in registers

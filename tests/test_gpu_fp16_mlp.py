@@ -49,3 +49,22 @@ def test_half_precision_layers_of_few_rows(aq, head, batch):
     obs = synth.make_obs(net, batch)
     actions, outs = _run_gpu(aq, net, params, obs)
     _check(net, params, obs, actions, outs, end_to_end=False)
+
+
+@pytest.mark.parametrize("hidden", [(40,), (130, 70)])
+@pytest.mark.parametrize("batch", [1, 50, 4099])
+def test_an_overflowing_observation_is_infinite_and_not_nan(aq, hidden, batch):
+    """A binary16 overflow in front of layers without activation, all weights positive: the row's actions are +infinity
+    (the features that pad a layer to whole tiles are no NaN that the next layer adds), the other rows stay finite."""
+    print(f"[fp16 overflow] {hidden} batch={batch}", flush=True)
+    widths = [20, *hidden]
+    net = synth.small_net([fc(k, n, "none") for k, n in zip(widths, widths[1:])] + [fc(widths[-1], 6, "none")], head="linear")
+    params = synth.make_params(net, nonzero_bias=True)
+    for p in params:
+        p["w"] = np.abs(p["w"]) + np.float32(1e-3)
+    obs = np.clip(synth.make_obs(net, batch), -1.0, 1.0)
+    bad = np.arange(0, batch, 3)
+    obs[bad, 7] = 1e5
+    actions, _ = _run_gpu(aq, net, params, obs)
+    assert (actions[bad] == np.inf).all()
+    assert np.isfinite(np.delete(actions, bad, axis=0)).all()
