@@ -136,9 +136,9 @@ aq_status aq_policy_reserve(aq_policy* p, int64_t max_batch);
 aq_status aq_policy_set_path(aq_policy* p, int32_t path);
 
 /* *n_layers = how many leading convolution layers the 8-bit forward of this handle runs as a single
- * launch under the current launch plan (0: none; it takes 8-bit frames of one to three channels or a multiple
- * of four, per-channel symmetric weights, out_c a multiple of 4, kw * c and stride * c multiples of 16 with c = in_c
- * or, for fewer than four channels, 4, and frames that fit into local memory with their feature maps).  No GPU work. */
+ * launch under the current launch plan (0: none; it takes 8-bit frames, per-channel symmetric weights, out_c a multiple
+ * of 4, kw * c and stride * c multiples of 16 with c = in_c -- or 4, for frames of fewer than four channels that need
+ * it --, and frames that fit into local memory with their feature maps).  No GPU work. */
 aq_status aq_policy_conv_stack_layers(const aq_policy* p, int32_t* n_layers);
 /* The same for the half-precision forward (its rules: 8-bit frames, kw * in_c a multiple of 16,
  * stride * in_c and in_w * in_c multiples of 8, out_c a multiple of 4, two to four convolutions). */

@@ -20,14 +20,15 @@
 // at 2048, and took none but rows of 16 bytes: a policy on 65 x 65 x 3 frames at batch 25 went layer by layer with byte
 // gathers, 55.4 us, now 19.3.
 //
-// Frames of fewer than four channels are expanded to four on their way into LDS, and the first layer's weights with
-// them (zeros in the channels that do not exist), so that every frame has aligned pieces; rows in LDS are padded to 16
-// bytes.
+// Frames of fewer than four channels whose windows would not begin and end at whole pieces are expanded to four on
+// their way into LDS, and the first layer's weights with them (zeros in the channels that do not exist), so that every
+// frame has aligned pieces; rows in LDS are padded to 16 bytes.
 //
 // Shapes it takes (the host checks them, anything else goes one launch per layer): 8-bit frames, per-channel
 // symmetric weights, two to four convolutions before a fully connected layer; per layer kw * C and stride * C multiples
-// of 16 (C = channels, at least 4 for the frame), N a multiple of 4; frame, maps and constants within LDS and the
-// registers they pass through.
+// of 16 (C = channels, 4 where the frame is expanded), N a multiple of 4; frame, maps and constants within LDS and the
+// registers they pass through.  The frame and the second map have LDS of their own, so that the next frame is stored
+// while the last layer is still at work; where that is too much they share it, for one barrier more per image.
 #include "int8_device.hpp"
 
 namespace aq {
@@ -66,6 +67,7 @@ struct StackArgs {
     int ragged;              // a piece reaches past the image's end
     int expand;              // first layer: channels below four, their number; else 0
     int KS0;                 // first layer's k-steps as stored
+    int share;               // the second map lies where the frame does
     int batch, nc;
     StackLayer L[CS_MAXC];
 };
@@ -91,8 +93,7 @@ bool plan_stack(const FwdArgs& a, StackPlan* p, StackArgs* sa) {
     if (a.c.batch > 0x7fffffffLL) return false;
     StackArgs s{};
     const LayerDev& L0 = net.L[0];
-    s.expand = L0.in_c < 4 ? L0.in_c : 0;
-    if (!s.expand && L0.in_c % 4) return false;
+    s.expand = L0.in_c < 4 && ((L0.kw * L0.in_c) % 16 || (L0.stride * L0.in_c) % 16) ? L0.in_c : 0;
     const int c0 = s.expand ? 4 : L0.in_c;
     s.pieces_row = (L0.in_w * c0 + 15) / 16;
     s.pieces = L0.in_h * s.pieces_row;
@@ -136,9 +137,13 @@ bool plan_stack(const FwdArgs& a, StackPlan* p, StackArgs* sa) {
         if (l < nc - 1 && out > map[l & 1]) map[l & 1] = out;
     }
     // LDS: frame, the two map areas, constants, tables of K
-    size_t at = (size_t)s.pieces * 16;
-    const size_t off_map[2] = {at, at + map[0]};
-    at += map[0] + map[1];
+    const size_t frame = (size_t)s.pieces * 16;
+    size_t rest = 0;
+    for (int l = 0; l < nc; ++l) rest += (size_t)s.L[l].NT * 512 + (size_t)round_up((s.L[l].K + 63) / 64, 4) * 16;
+    s.share = frame + map[0] + map[1] + rest > CS_MAX_LDS;
+    const size_t first = s.share && map[1] > frame ? map[1] : frame;
+    const size_t off_map[2] = {first, s.share ? 0 : first + map[0]};
+    size_t at = first + map[0] + (s.share ? 0 : map[1]);
     for (int l = 0; l < nc; ++l) {
         StackLayer& q = s.L[l];
         q.in_off = l == 0 ? 0 : (int)off_map[(l - 1) & 1];
@@ -399,7 +404,8 @@ __global__ __launch_bounds__(CS_T) void k_conv_stack(const NetDev* __restrict__ 
             }
         }
         if (!more) break;
-        store_frame();  // (the first layer was the frame's only reader)
+        if (sa->share) lds_barrier();  // (the last layer may read what lies in the frame's place)
+        store_frame();                 // (else the first layer was the frame's only reader)
         img += step;
     }
 }

@@ -1,6 +1,6 @@
 """The 8-bit convolutions in one launch at the frames where they can go wrong: rows that are no multiple of 16 bytes, fewer
 than four channels, kernel rows that end in the middle of an MFMA's k-step, three and four tiles of features, weights that
-do not fit into LDS, more images than workgroups, frames at any address."""
+do not fit into LDS, maps that share LDS with the frame, more images than workgroups, frames at any address."""
 import numpy as np
 import pytest
 
@@ -31,6 +31,13 @@ NETS = {
     "four_layers": _net(64, 60, 4, (16, 8, 4), (32, 3, 1), (16, 3, 1), (48, 3, 1)),
     "weights_from_l2": _net(33, 33, 16, (128, 3, 1), (16, 3, 1)),
     "ragged_channels": _net(30, 26, 4, (20, 4, 4), (36, 4, 4)),
+    # the second map in the frame's place: three layers, and four with that map the larger of the two
+    "shared_maps": _net(64, 64, 8, (112, 4, 2), (32, 4, 1), (16, 4, 2)),
+    "shared_maps_4": _net(30, 30, 16, (96, 4, 1), (128, 3, 1), (16, 4, 1), (8, 4, 2)),
+    # channels that are no multiple of four, and frames of few channels whose windows are whole pieces as they are
+    "channels_6": _net(64, 62, 6, (32, 16, 8), (32, 3, 1)),
+    "channels_5": _net(50, 49, 5, (16, 16, 16), (16, 2, 1)),
+    "one_channel": _net(128, 157, 1, (32, 32, 16), (32, 3, 1)),
 }
 
 
