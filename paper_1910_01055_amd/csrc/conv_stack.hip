@@ -1,8 +1,8 @@
 // The leading convolution layers of a frame policy (Sec. 4.1: the Atari-style policies take stacked
 // 8-bit frames through three convolutions before the fully connected layers) in one launch: a workgroup
-// of 16 wavefronts keeps a frame, every intermediate feature map, the layers' weights and epilogue constants
-// in LDS and goes from image to image (grid = one workgroup per CU at most), so that weights and constants
-// are fetched once per workgroup and a frame is fetched under the previous image's convolutions.
+// of 16 wavefronts (or two of 8, see launch_conv_stack) keeps a frame, every intermediate feature map, the layers'
+// weights and epilogue constants in LDS and goes from image to image (grid = what the CUs hold at once), so that
+// weights and constants are fetched once per workgroup and a frame is fetched under the previous image's convolutions.
 //
 // No im2col: with NHWC maps a 16-byte piece of the implicit GEMM's K is 16 contiguous bytes of one kernel row of
 // the input map, so an MFMA's activation operand is one 16-byte LDS read per lane at an address computed from the
@@ -15,7 +15,7 @@
 // costs sixteen clocks an instruction.  Hence one wavefront per layer for constants and tables, four per layer for the
 // weights (straight into LDS), one code for all layers with arguments read per layer, windows' places from a table.  An
 // 84 x 84 x 4 frame through 32, 32 and 16 channels at 256 images takes 7.6 us back to back, 2.6 of them the launch; 2048
-// images 44 us.  The same with a copy of the code per layer and weights through registers: 13 us.  One workgroup per
+// images 44 us (as two workgroups per CU 36).  The same with a copy of the code per layer and weights through registers: 13 us.  One workgroup per
 // image with 32 x 32 tiles and weights from L2 per tile (what stood here before) was as fast at 256 images, half as fast
 // at 2048, and took none but rows of 16 bytes: a policy on 65 x 65 x 3 frames at batch 25 went layer by layer with byte
 // gathers, 55.4 us, now 19.3.
@@ -34,9 +34,8 @@
 namespace aq {
 
 namespace {
-constexpr int CS_W = 16;         // wavefronts per workgroup
-constexpr int CS_T = CS_W * 64;
-constexpr int CS_FU = 3;         // 16-byte pieces of the frame (in LDS) per thread
+constexpr int CS_W = 16;         // wavefronts per workgroup, or half of them with two workgroups on a CU
+constexpr int cs_pieces(int W) { return W == CS_W ? 3 : 4; }  // 16-byte pieces of the frame (in LDS) per thread
 constexpr size_t CS_MAX_LDS = 160 * 1024;
 constexpr int CS_MAXC = 4;       // convolution layers of a stack at most
 
@@ -78,8 +77,9 @@ struct StackPlan {
     size_t lds;
 };
 
-// `sa` may be NULL: only whether and how many
-bool plan_stack(const FwdArgs& a, StackPlan* p, StackArgs* sa) {
+// For workgroups of W wavefronts, CS_W / W of them on a CU.  `sa` may be NULL: only whether and how many
+bool plan_stack(const FwdArgs& a, int W, StackPlan* p, StackArgs* sa) {
+    const size_t max_lds = CS_MAX_LDS / (CS_W / W);
     const NetDev& net = a.net;
     if (!net.in_u8 || net.asym) return false;
     int nc = 0;
@@ -106,7 +106,7 @@ bool plan_stack(const FwdArgs& a, StackPlan* p, StackArgs* sa) {
     s.last = (int)s.frame_bytes - 16;
     s.batch = (int)a.c.batch;
     s.nc = nc;
-    if (s.pieces > CS_FU * CS_T || s.frame_bytes < 16) return false;
+    if (s.pieces > cs_pieces(W) * W * 64 || s.frame_bytes < 16) return false;
     size_t map[2] = {0, 0};
     for (int l = 0; l < nc; ++l) {
         const LayerDev& L = net.L[l];
@@ -121,7 +121,7 @@ bool plan_stack(const FwdArgs& a, StackPlan* p, StackArgs* sa) {
         q.ow = L.ow;
         q.inv_ow = 1.0f / (float)L.ow;
         q.RT = (q.R + 15) / 16;
-        q.per_nt = L.NT < CS_W ? CS_W / L.NT : 1;
+        q.per_nt = L.NT < W ? W / L.NT : 1;
         q.per_inv = (65536 + q.per_nt - 1) / q.per_nt;
         q.run = L.kw * C;
         q.row = l == 0 ? s.pieces_row * 16 : s.L[l - 1].out_row;
@@ -140,7 +140,7 @@ bool plan_stack(const FwdArgs& a, StackPlan* p, StackArgs* sa) {
     const size_t frame = (size_t)s.pieces * 16;
     size_t rest = 0;
     for (int l = 0; l < nc; ++l) rest += (size_t)s.L[l].NT * 512 + (size_t)round_up((s.L[l].K + 63) / 64, 4) * 16;
-    s.share = frame + map[0] + map[1] + rest > CS_MAX_LDS;
+    s.share = frame + map[0] + map[1] + rest > max_lds;
     const size_t first = s.share && map[1] > frame ? map[1] : frame;
     const size_t off_map[2] = {first, s.share ? 0 : first + map[0]};
     size_t at = first + map[0] + (s.share ? 0 : map[1]);
@@ -163,9 +163,9 @@ bool plan_stack(const FwdArgs& a, StackPlan* p, StackArgs* sa) {
         w_at += (size_t)q.w_tiles * 1024;
     }
     p->nc = nc;
-    p->resident = w_at <= CS_MAX_LDS;
+    p->resident = w_at <= max_lds;
     p->lds = p->resident ? w_at : at;
-    if (p->lds > CS_MAX_LDS || (s.expand && !p->resident)) return false;
+    if (p->lds > max_lds || (s.expand && !p->resident)) return false;
     if (sa) *sa = s;
     return true;
 }
@@ -180,10 +180,11 @@ __device__ __forceinline__ void lds_fetch_1k(const int8_t* src, int8_t* dst, int
 }  // namespace
 
 // WLDS: weights in LDS (else from L2, operand by operand)
-template <bool TAPS, bool WLDS>
-__global__ __launch_bounds__(CS_T) void k_conv_stack(const NetDev* __restrict__ netp, const uint8_t* __restrict__ frames,
+template <bool TAPS, bool WLDS, int W>
+__global__ __launch_bounds__(W * 64, 4) void k_conv_stack(const NetDev* __restrict__ netp, const uint8_t* __restrict__ frames,
                                                      int8_t* __restrict__ out, const StackArgs sa_, const TapParam<TAPS> tp) {
     extern __shared__ __align__(16) int8_t smem[];
+    constexpr int T = W * 64, FU = cs_pieces(W);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 4, i16 = lane & 15;
     const StackArgs AQ_CONST* const sa = (const StackArgs AQ_CONST*)((const char AQ_CONST*)__builtin_amdgcn_kernarg_segment_ptr() + 24);
     (void)sa_;
@@ -195,9 +196,9 @@ __global__ __launch_bounds__(CS_T) void k_conv_stack(const NetDev* __restrict__ 
 
     // ---- frames: pieces of 16 bytes (in LDS).  A piece that would reach past the image's end is read as the image's last
     // 16 bytes and shifted down; past a row's end there is whatever follows, in LDS bytes that no window covers.
-    v4i fr[CS_FU];
+    v4i fr[FU];
     auto source = [&](int u, int* back) __attribute__((always_inline)) {
-        const int i = tid + u * CS_T, y = (int)(((float)i + 0.5f) * sa->inv_row);
+        const int i = tid + u * T, y = (int)(((float)i + 0.5f) * sa->inv_row);
         const int at = __mul24(y, sa->src_row) + __mul24(i - __mul24(y, sa->pieces_row), sa->src_piece);
         *back = at > sa->last ? at - sa->last : 0;
         return at > sa->last ? sa->last : at;
@@ -205,8 +206,8 @@ __global__ __launch_bounds__(CS_T) void k_conv_stack(const NetDev* __restrict__ 
     auto fetch_frame = [&](int64_t img) __attribute__((always_inline)) {
         const uint8_t AQ_GLOBAL* f = (const uint8_t AQ_GLOBAL*)frames + img * sa->frame_bytes;
 #pragma unroll
-        for (int u = 0; u < CS_FU; ++u) {
-            if (u * CS_T >= pieces) continue;  // (scalar)
+        for (int u = 0; u < FU; ++u) {
+            if (u * T >= pieces) continue;  // (scalar)
             int back;
             const uint32_t at = (uint32_t)source(u, &back);
             fr[u] = *(const v4i_any AQ_GLOBAL*)(f + at);
@@ -214,9 +215,9 @@ __global__ __launch_bounds__(CS_T) void k_conv_stack(const NetDev* __restrict__ 
     };
     auto store_frame = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < CS_FU; ++u) {
-            if (u * CS_T >= pieces) continue;
-            const int i = tid + u * CS_T;
+        for (int u = 0; u < FU; ++u) {
+            if (u * T >= pieces) continue;
+            const int i = tid + u * T;
             v4i x = fr[u];
             int back = 0;
             if (sa->ragged) (void)source(u, &back);  // (scalar)
@@ -256,8 +257,8 @@ __global__ __launch_bounds__(CS_T) void k_conv_stack(const NetDev* __restrict__ 
 #pragma unroll
     for (int i = 0; i < (int)(sizeof(warm) / 4); ++i) asm volatile("" ::"s"(warm[i]));
     const int nc = sa->nc;
-    if (wave >= CS_W - nc) {  // (scalar) one wavefront per layer
-        const StackLayer AQ_CONST& L = sa->L[CS_W - 1 - wave];
+    if (wave >= W - nc) {  // (scalar) one wavefront per layer
+        const StackLayer AQ_CONST& L = sa->L[W - 1 - wave];
         const v4i c0 = ((gv4i_ptr)L.pack)[lane < L.NT * 32 ? lane : 0];
         const float inv_run = 1.0f / (float)L.run;
         for (int i = lane; i < 4 * L.k_len; i += 64) {  // k-step i / 4, piece i % 4
@@ -268,17 +269,18 @@ __global__ __launch_bounds__(CS_T) void k_conv_stack(const NetDev* __restrict__ 
         for (int i = 64 + lane; i < L.NT * 32; i += 64) *(v4i*)(smem + L.c_off + 16 * i) = ((gv4i_ptr)L.pack)[i];
     }
     if (WLDS) {
-        const int l = wave >> 2;  // (scalar) four wavefronts per layer
+        constexpr int PER = W / CS_MAXC;
+        const int l = wave / PER;  // (scalar) as many wavefronts for each layer
         if (l < nc && !(l == 0 && sa->expand)) {
             const StackLayer AQ_CONST& L = sa->L[l];
-            for (int j = wave & 3; j < L.w_tiles; j += 4) lds_fetch_1k(L.wp + j * 1024, smem + L.w_off + j * 1024, lane);
+            for (int j = wave % PER; j < L.w_tiles; j += PER) lds_fetch_1k(L.wp + j * 1024, smem + L.w_off + j * 1024, lane);
         }
     }
     if (WLDS && sa->expand) {  // the first layer's weights with four channels per tap: a thread makes the four bytes of one
         const StackLayer AQ_CONST& L = sa->L[0];
         const int KS = L.KS, words = L.w_tiles * 256, ch = sa->expand;
         const int8_t AQ_GLOBAL* wp = (const int8_t AQ_GLOBAL*)L.wp;
-        for (int i = tid; i < words; i += CS_T) {
+        for (int i = tid; i < words; i += T) {
             const int tile = i >> 8, ln = (i >> 2) & 63, nt = tile / KS, ks = tile - nt * KS;
             const int tap = (ks * 32 + 16 * (ln >> 5)) / 4 + (i & 3);
             uint32_t w = 0;
@@ -310,7 +312,7 @@ __global__ __launch_bounds__(CS_T) void k_conv_stack(const NetDev* __restrict__ 
             asm volatile("" : "+v"(lo_v));
             const int32_t* const koff = (const int32_t*)(smem + L.k_off) + g * L.k_len;
             const int w_nt = (wave * L.per_inv) >> 16, w_rt = wave - w_nt * L.per_nt;
-            for (int nt = w_nt; nt < L.NT; nt += CS_W) {
+            for (int nt = w_nt; nt < L.NT; nt += W) {
                 const int8_t* const wl = smem + L.w_off + nt * KS * 1024 + a_lane;
                 const int8_t AQ_GLOBAL* const wg = (const int8_t AQ_GLOBAL*)L.wp + nt * KS * 1024 + a_lane;
                 auto weights = [&](int off) __attribute__((always_inline)) {
@@ -410,38 +412,41 @@ __global__ __launch_bounds__(CS_T) void k_conv_stack(const NetDev* __restrict__ 
     }
 }
 
+namespace {
+template <bool TAPS, bool WLDS, int W>
+aq_status launch_stack_t(const FwdArgs& a, const StackPlan& p, const StackArgs& sa, int8_t* out, hipStream_t st) {
+    auto* const kernel = k_conv_stack<TAPS, WLDS, W>;
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set) {
+        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)CS_MAX_LDS) != hipSuccess) return AQ_EHIP;
+        attr_set = true;
+    }
+    const int64_t most = 256 * (CS_W / W);
+    const dim3 grid((unsigned)(a.c.batch < most ? a.c.batch : most));
+    hipLaunchKernelGGL(kernel, grid, dim3(W * 64), p.lds, st, a.d_net, (const uint8_t*)a.c.obs, out, sa, TapParam<TAPS>(a.t));
+    return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
+}
+}  // namespace
+
 int conv_stack_layers(const FwdArgs& a) {
     StackPlan p;
-    return plan_stack(a, &p, nullptr) ? p.nc : 0;
+    return plan_stack(a, CS_W, &p, nullptr) ? p.nc : 0;
 }
 
+// Two workgroups of half the wavefronts on a CU hide each other's phases: better from the first image beyond one per CU
+// where both hold their weights in LDS (40 x 40 x 4 through 16 and 32 channels, whole forward at 384, 2048 and 16384
+// images 13.3, 26.9 and 157 us as one, 11.6, 20.1 and 104 as two).  With weights from L2 it depends: 64 x 64 x 8 through
+// 32 and 64 channels at 2048 images 510 us as one, 552 as two; 64 x 64 x 6 through 32 and 32 36.5 and 32.5.
 aq_status launch_conv_stack(const FwdArgs& a, int8_t* out, hipStream_t st) {
     StackPlan p;
     StackArgs sa;
-    if (!plan_stack(a, &p, &sa)) return AQ_ESHAPE;
     const bool taps = any_taps(a);
-    const dim3 grid((unsigned)(a.c.batch < 256 ? a.c.batch : 256));
-#define AQ_STACK(TP, WL)                                                                                             \
-    do {                                                                                                             \
-        static std::atomic<bool> attr_set{false};                                                                    \
-        if (!attr_set) {                                                                                             \
-            if (hipFuncSetAttribute((const void*)k_conv_stack<TP, WL>, hipFuncAttributeMaxDynamicSharedMemorySize,   \
-                                    (int)CS_MAX_LDS) != hipSuccess)                                                  \
-                return AQ_EHIP;                                                                                      \
-            attr_set = true;                                                                                         \
-        }                                                                                                            \
-        hipLaunchKernelGGL((k_conv_stack<TP, WL>), grid, dim3(CS_T), p.lds, st, a.d_net, (const uint8_t*)a.c.obs,    \
-                           out, sa, TapParam<TP>(a.t));                                                              \
-    } while (0)
-    if (p.resident) {
-        if (taps) AQ_STACK(true, true);
-        else AQ_STACK(false, true);
-    } else {
-        if (taps) AQ_STACK(true, false);
-        else AQ_STACK(false, false);
-    }
-#undef AQ_STACK
-    return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
+    constexpr int H = CS_W / 2;
+    if (a.c.batch > 256 && plan_stack(a, H, &p, &sa) && p.resident)
+        return taps ? launch_stack_t<true, true, H>(a, p, sa, out, st) : launch_stack_t<false, true, H>(a, p, sa, out, st);
+    if (!plan_stack(a, CS_W, &p, &sa)) return AQ_ESHAPE;
+    if (p.resident) return taps ? launch_stack_t<true, true, CS_W>(a, p, sa, out, st) : launch_stack_t<false, true, CS_W>(a, p, sa, out, st);
+    return taps ? launch_stack_t<true, false, CS_W>(a, p, sa, out, st) : launch_stack_t<false, false, CS_W>(a, p, sa, out, st);
 }
 
 }  // namespace aq
