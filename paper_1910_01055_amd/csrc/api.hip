@@ -113,9 +113,9 @@ struct aq_policy {
     int64_t cap_f16 = 0;
     void* act_f16[2] = {nullptr, nullptr};
     // the learner's fp32 parameters, copied by aq_policy_set_params_fp32, and the packed weights of parameters passed
-    // with a call (one allocation each, at the first call that needs it)
-    F32Store f32_kept;    // allocated by the first aq_policy_set_params_fp32
-    F32Store f32_passed;  // of parameters passed with a call (packed weights only), part of the policy's slab
+    // with a call (one allocation each)
+    F32Store f32_kept;    // made by the first aq_policy_set_params_fp32
+    F32Store f32_passed;  // made by the first aq_policy_forward_fp32_params or an aq_policy_reserve
     bool f32_ready = false;
     // policies of at most 4 bits, per-channel symmetric, under launch plan 4: the fully connected layers' weights
     // once more as nibbles, for the few-row kernel (one allocation when the plan is first chosen; rewritten by
@@ -320,18 +320,12 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     // what the host writes, side by side: one copy
     size_t off_net = take(sizeof(NetDev));
     size_t off_qtab = take(sizeof(QTab));
-    size_t off_ftab = take(sizeof(F32KeepTab));
-    // the packed weights of aq_policy_forward_fp32_params, whose first call may be one into a graph: part of the slab, as
-    // an allocation of their own they would cost every policy 0.1 ms
-    F32KeepTab ftab{};
-    size_t f32_offs[5 * AQ_MAX_LAYERS];
-    const size_t used = bytes, off_f32 = take(f32_store_layout(p, false, ftab, f32_offs));
     if (hipMalloc(&p->slab, bytes) != hipSuccess) {
         delete p;
         return AQ_ENOMEM;
     }
     // zero once: padding rows / k-steps of the packed weights and padded constants stay zero for good
-    if (hipMemset(p->slab, 0, used) != hipSuccess) {
+    if (hipMemset(p->slab, 0, bytes) != hipSuccess) {
         (void)hipFree(p->slab);
         delete p;
         return AQ_EHIP;
@@ -421,13 +415,9 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         mix((int64_t)p->layer_bytes);
         p->net_hash = h;
     }
-    p->f32_passed.ptrs = f32_store_place(ftab, base + off_f32, f32_offs);
-    p->f32_passed.d_tab = (F32KeepTab*)(base + off_ftab);
-    p->f32_passed.blocks = ftab.blocks;
-    std::vector<char> up(off_ftab + sizeof(F32KeepTab) - off_net);
+    std::vector<char> up(off_qtab + sizeof(QTab) - off_net);
     memcpy(up.data(), &p->h_net, sizeof(NetDev));
     memcpy(up.data() + (off_qtab - off_net), &p->h_qtab, sizeof(QTab));
-    memcpy(up.data() + (off_ftab - off_net), &ftab, sizeof(F32KeepTab));
     if (hipMemcpy(p->d_net, up.data(), up.size(), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(p->slab);
         delete p;
@@ -459,6 +449,7 @@ extern "C" aq_status aq_policy_destroy(aq_policy* p) {
     if (p->y_rows) (void)hipFree(p->y_rows);
     if (p->h16_slab) (void)hipFree(p->h16_slab);
     if (p->f32_kept.slab) (void)hipFree(p->f32_kept.slab);
+    if (p->f32_passed.slab) (void)hipFree(p->f32_passed.slab);
     if (p->calib) (void)hipHostFree(p->calib);
     delete p;
     return AQ_OK;
@@ -529,6 +520,33 @@ static aq_status ensure_f16(aq_policy* p, int64_t batch, hipStream_t st) {
     return AQ_OK;
 }
 
+// Storage of a set of fp32 parameters (what it holds: f32_store_layout), made once.
+static aq_status ensure_f32_store(const aq_policy* p, F32Store& S, bool keep, hipStream_t st) {
+    if (S.slab) return AQ_OK;
+    if (capturing(st)) return AQ_ETOOBIG;
+    F32KeepTab tab{};
+    size_t offs[5 * AQ_MAX_LAYERS];
+    const size_t bytes = f32_store_layout(p, keep, tab, offs);
+    struct {
+        F32Ptrs ptrs;
+        F32KeepTab tab;
+    } up{};
+    char* slab = nullptr;
+    if (hipMalloc((void**)&slab, bytes + sizeof(up)) != hipSuccess) return AQ_ENOMEM;
+    up.ptrs = f32_store_place(tab, slab, offs);
+    up.tab = tab;
+    if (hipMemcpy(slab + bytes, &up, sizeof(up), hipMemcpyHostToDevice) != hipSuccess) {
+        (void)hipFree(slab);
+        return AQ_EHIP;
+    }
+    S.d_ptrs = (F32Ptrs*)(slab + bytes);
+    S.d_tab = (F32KeepTab*)(slab + bytes + offsetof(decltype(up), tab));
+    S.slab = slab;
+    S.ptrs = up.ptrs;
+    S.blocks = tab.blocks;
+    return AQ_OK;
+}
+
 extern "C" aq_status aq_policy_reserve(aq_policy* p, int64_t max_batch) {
     if (!p || max_batch < 0) return AQ_EINVAL;
     aq_status s = ensure_i8(p, max_batch, nullptr);
@@ -537,6 +555,8 @@ extern "C" aq_status aq_policy_reserve(aq_policy* p, int64_t max_batch) {
         s = ensure_f16(p, max_batch, nullptr);
         if (s != AQ_OK) return s;
     }
+    s = ensure_f32_store(p, p->f32_passed, false, nullptr);
+    if (s != AQ_OK) return s;
     return ensure_f32(p, max_batch, nullptr);
 }
 
@@ -1135,34 +1155,6 @@ static F32Ptrs f32_ptr_table(int nl, const float* const* w, const float* const* 
     return t;
 }
 
-// Storage of the parameters that aq_policy_set_params_fp32 keeps, made once.
-static aq_status ensure_f32_kept(aq_policy* p, hipStream_t st) {
-    F32Store& S = p->f32_kept;
-    if (S.slab) return AQ_OK;
-    if (capturing(st)) return AQ_ETOOBIG;
-    F32KeepTab tab{};
-    size_t offs[5 * AQ_MAX_LAYERS];
-    const size_t bytes = f32_store_layout(p, true, tab, offs);
-    struct {
-        F32Ptrs ptrs;
-        F32KeepTab tab;
-    } up{};
-    char* slab = nullptr;
-    if (hipMalloc((void**)&slab, bytes + sizeof(up)) != hipSuccess) return AQ_ENOMEM;
-    up.ptrs = f32_store_place(tab, slab, offs);
-    up.tab = tab;
-    if (hipMemcpy(slab + bytes, &up, sizeof(up), hipMemcpyHostToDevice) != hipSuccess) {
-        (void)hipFree(slab);
-        return AQ_EHIP;
-    }
-    S.d_ptrs = (F32Ptrs*)(slab + bytes);
-    S.d_tab = (F32KeepTab*)(slab + bytes + offsetof(decltype(up), tab));
-    S.slab = slab;
-    S.ptrs = up.ptrs;
-    S.blocks = tab.blocks;
-    return AQ_OK;
-}
-
 extern "C" aq_status aq_policy_forward_fp32_params(aq_policy* p, const float* const* h_d_w, const float* const* h_d_b,
                                                    const float* const* h_d_gamma, const float* const* h_d_beta,
                                                    const void* d_obs, int64_t batch, void* d_actions,
@@ -1174,7 +1166,9 @@ extern "C" aq_status aq_policy_forward_fp32_params(aq_policy* p, const float* co
         if (!h_d_w[l]) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
     F32Ptrs ptrs = f32_ptr_table(p->net.n_layers, h_d_w, h_d_b, h_d_gamma, h_d_beta);
-    const aq_status s = launch_keep_params(ptrs, p->f32_passed.d_tab, p->f32_passed.blocks, st);
+    aq_status s = ensure_f32_store(p, p->f32_passed, false, st);
+    if (s != AQ_OK) return s;
+    s = launch_keep_params(ptrs, p->f32_passed.d_tab, p->f32_passed.blocks, st);
     if (s != AQ_OK) return s;
     for (int l = 0; l < p->net.n_layers; ++l) ptrs.wpk[l] = p->f32_passed.ptrs.wpk[l];
     return forward_fp32_impl(p, ptrs, nullptr, d_obs, batch, d_actions, d_ranges_out, nullptr, 0, st);
@@ -1188,7 +1182,7 @@ extern "C" aq_status aq_policy_set_params_fp32(aq_policy* p, const float* const*
     for (int l = 0; l < nl; ++l)
         if (!h_d_w[l]) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
-    aq_status s = ensure_f32_kept(p, st);
+    aq_status s = ensure_f32_store(p, p->f32_kept, true, st);
     if (s != AQ_OK) return s;
     // (absent biases, gains and offsets take their defaults 0, 1, 0)
     s = launch_keep_params(f32_ptr_table(nl, h_d_w, h_d_b, h_d_gamma, h_d_beta), p->f32_kept.d_tab,

@@ -104,6 +104,35 @@ def test_fp32_forward_on_passed_parameters_is_captured_after_reserve(aq):
     P.close()
 
 
+def test_fp32_weights_cost_memory_only_where_they_are_used(aq):
+    """A policy that has run nothing in fp32 holds its 8-bit weights and constants, about a byte per weight; the forward on
+    passed parameters allocates its packed weights at its first call, which a capture refuses like any other allocation."""
+    net = synth.small_net([fc(64, 2048, "relu"), fc(2048, 2048, "relu"), fc(2048, 2048, "relu"), fc(2048, 8, "none")])
+    params = synth.make_params(net, nonzero_bias=True)
+    weights = sum(p["w"].size for p in params)
+    dev = U.upload_params(params)
+    obs, out, want = U.to_dev(synth.make_obs(net, 4)), torch.zeros(4, 8, device=U.DEV), torch.zeros(4, 8, device=U.DEV)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    policies = [aq.Policy(net) for _ in range(8)]
+    held = before - torch.cuda.mem_get_info()[0]
+    assert held < 8 * 1.6 * weights, held / (8 * weights)
+    for P in policies[1:]:
+        P.close()
+    P = policies[0]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out.zero_()
+        with pytest.raises(aq.AqError) as e:
+            P.policy_forward_fp32_params(*dev, obs, out)
+        assert e.value.status == aq.ETOOBIG
+    P.policy_forward_fp32_params(*dev, obs, out)
+    P.policy_set_params_fp32(*dev)
+    P.policy_forward_fp32(obs, want)
+    assert torch.equal(out, want) and U.close(out.cpu().numpy(), O.OraclePolicy(net).forward_fp32(params, synth.make_obs(net, 4))[0]).all()
+    P.close()
+
+
 @pytest.mark.parametrize("K,N", [(67, 1300), (3136, 512), (3100, 70)])
 @pytest.mark.parametrize("rows", [1, 40, 700, 4100])
 def test_an_infinite_weight_stays_infinite_in_the_per_layer_kernel(aq, K, N, rows):
