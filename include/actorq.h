@@ -361,8 +361,8 @@ aq_status aq_policy_forward_fp32_params(aq_policy* p, const float* const* h_d_w,
  *
  * aq_convert_params_fp16: rounds the learner's fp32 parameters (same arrays and layouts as
  * aq_quantize_params; biases, gains, offsets may be NULL as there) to binary16 and stores the weights in
- * matrix-core operand order inside the policy.  The first call allocates that storage (hipMalloc);
- * later calls overwrite it asynchronously on `stream`.  A parameter that is not finite after rounding
+ * matrix-core operand order inside the policy.  The first call allocates that storage (hipMalloc; AQ_ETOOBIG
+ * while `stream` is being captured); later calls overwrite it asynchronously on `stream`.  A parameter that is not finite after rounding
  * (|v| >= 65520) is reported as AQ_ENONFINITE by aq_policy_status.
  *
  * aq_policy_forward_fp16: d_obs (fp32 or uint8 as declared by the policy) -> d_actions (fp32 [batch][A]

@@ -1243,8 +1243,9 @@ extern "C" aq_status aq_calibrate_fp32(aq_policy* p, const void* d_obs, int64_t 
 }
 
 // ---- half-precision actor: storage of its parameters (one allocation, made once) and the tables over it
-static aq_status ensure_h16(aq_policy* p) {
+static aq_status ensure_h16(aq_policy* p, hipStream_t st) {
     if (p->h16_slab) return AQ_OK;
+    if (capturing(st)) return AQ_ETOOBIG;
     const int nl = p->net.n_layers;
     size_t bytes = 0;
     auto take = [&](size_t n) {
@@ -1263,12 +1264,16 @@ static aq_status ensure_h16(aq_policy* p) {
         c_off.push_back(cst);
         cst += b.N_pad * (b.d.act == AQ_ACT_LN_TANH ? 3 : 1);
     }
-    const size_t off_h = take((size_t)cst * 2), off_net = take(sizeof(Fp16Net)), off_tab = take(sizeof(Fp16ConvTab));
+    struct {  // one copy
+        Fp16Net net;
+        Fp16ConvTab tab;
+    } up{};
+    const size_t off_h = take((size_t)cst * 2), off_up = take(sizeof(up));
     void* slab = nullptr;
     if (hipMalloc(&slab, bytes) != hipSuccess) return AQ_ENOMEM;
     char* base = (char*)slab;
-    Fp16Net net{};
-    Fp16ConvTab tab{};
+    Fp16Net& net = up.net;
+    Fp16ConvTab& tab = up.tab;
     int blk = 0;
     net.n_layers = fc ? nl : 0;
     net.head = p->net.head;
@@ -1289,8 +1294,7 @@ static aq_status ensure_h16(aq_policy* p) {
         }
     }
     tab.blocks = blk;
-    if (hipMemcpy(base + off_net, &net, sizeof(net), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(base + off_tab, &tab, sizeof(tab), hipMemcpyHostToDevice) != hipSuccess) {
+    if (hipMemcpy(base + off_up, &up, sizeof(up), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(slab);
         return AQ_EHIP;
     }
@@ -1302,8 +1306,8 @@ static aq_status ensure_h16(aq_policy* p) {
     }
     p->h16_slab = slab;
     p->h16_net = net;
-    p->d_h16_net = (Fp16Net*)(base + off_net);
-    p->d_h16_tab = (Fp16ConvTab*)(base + off_tab);
+    p->d_h16_net = (Fp16Net*)(base + off_up);
+    p->d_h16_tab = (Fp16ConvTab*)(base + off_up + offsetof(decltype(up), tab));
     p->h16_blocks = blk;
     return AQ_OK;
 }
@@ -1316,7 +1320,7 @@ extern "C" aq_status aq_convert_params_fp16(aq_policy* p, const float* const* h_
     for (int l = 0; l < nl; ++l)
         if (!h_d_w[l]) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
-    aq_status s = ensure_h16(p);
+    aq_status s = ensure_h16(p, st);
     if (s != AQ_OK) return s;
     int* st16 = p->status + 1;
     s = launch_fill_u32((uint32_t*)st16, 1, 0u, st);

@@ -375,6 +375,31 @@ def test_fp16_actor_graph_replays_match_eager(aq, name):
     P.close()
 
 
+def test_fp16_first_conversion_is_refused_under_capture(aq):
+    """The first conversion allocates: it leaves a capture as it is, and works outside it."""
+    _say("fp16_first_conversion_under_capture")
+    net = _nets()["cfg2"]
+    params = synth.make_params(net)
+    obs = U.to_dev(synth.make_obs(net, 20))
+    out = torch.ones(20, synth.action_dim(net), device=U.DEV)
+    w, b, g, be = U.upload_params(params)
+    P = aq.Policy(net)
+    torch.cuda.synchronize()
+    gr = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(gr):
+        with pytest.raises(aq.AqError) as e:
+            P.convert_params_fp16(w, b, g, be)
+        out.zero_()
+    assert e.value.status == aq.ETOOBIG
+    gr.replay()
+    torch.cuda.synchronize()
+    assert not out.any()
+    P.convert_params_fp16(w, b, g, be)
+    P.policy_forward_fp16(obs, out, None)
+    assert P.policy_status() == aq.OK and out.any()
+    P.close()
+
+
 def test_fp16_actor_errors_and_nonfinite(aq):
     _say("fp16_actor_errors")
     net = _nets()["argmax_mlp"]
