@@ -29,7 +29,7 @@ EXPORTS = ["aq_policy_create", "aq_policy_destroy", "aq_policy_reserve", "aq_pol
            "aq_policy_packed_blob_size", "aq_policy_export_packed_blob", "aq_policy_import_packed_blob",
            "aq_policy_conv_stack_layers", "aq_policy_fp16_conv_stack_layers", "aq_policy_fused_plan", "aq_policy_forward_int8_static",
            "aq_policy_set_params_fp32", "aq_calibrate_fp32", "aq_policy_forward_fp32_params", "aq_stream_reference",
-           "aq_mfma_loop_reference", "aq_policy_subbyte_layers"]
+           "aq_mfma_loop_reference", "aq_policy_subbyte_layers", "aq_policy_fp32_plan", "aq_policy_fp16_plan"]
 
 
 class AqLayer(C.Structure):
@@ -88,6 +88,8 @@ def load():
     lib.aq_policy_fp16_conv_stack_layers.argtypes = [vp, C.POINTER(C.c_int32)]
     lib.aq_policy_subbyte_layers.argtypes = [vp, i64, C.POINTER(C.c_int32)]
     lib.aq_policy_fused_plan.argtypes = [vp, i64, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
+    lib.aq_policy_fp32_plan.argtypes = [vp, i64, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
+    lib.aq_policy_fp16_plan.argtypes = [vp, i64, C.POINTER(C.c_int32)]
     lib.aq_quantize_tensor.argtypes = [vp, i64, i64, i32, i32, vp, vp, vp, vp, vp]
     lib.aq_stream_reference.argtypes = [vp, i64, vp, vp]
     lib.aq_mfma_loop_reference.argtypes = [vp, vp, i32, i32, i32, vp, vp]
@@ -218,6 +220,19 @@ class Policy:
         r, t, w = C.c_int32(0), C.c_int32(0), C.c_int32(0)
         _check(load().aq_policy_fused_plan(self._h, int(batch), C.byref(r), C.byref(t), C.byref(w)), "aq_policy_fused_plan")
         return int(r.value), int(t.value), int(w.value)
+
+    def policy_fp32_plan(self, batch):
+        """(rows per workgroup of the whole-policy launch or 0, per layer (features, rows) of its tile where each layer
+        has a launch of its own) of the fp32 actor at this batch."""
+        r, t = C.c_int32(0), (C.c_int32 * (2 * self.n_layers))()
+        _check(load().aq_policy_fp32_plan(self._h, int(batch), C.byref(r), t), "aq_policy_fp32_plan")
+        return int(r.value), [] if r.value else list(zip(t[::2], t[1::2]))
+
+    def policy_fp16_plan(self, batch):
+        """Rows per workgroup of the half-precision actor's whole-policy launch at this batch; 0 = a launch per layer."""
+        r = C.c_int32(0)
+        _check(load().aq_policy_fp16_plan(self._h, int(batch), C.byref(r)), "aq_policy_fp16_plan")
+        return int(r.value)
 
     def policy_subbyte_layers(self, batch):
         """Layers of a forward pass at this batch that stream their weights as nibbles (policies of <= 4 bits)."""

@@ -628,6 +628,28 @@ extern "C" aq_status aq_policy_subbyte_layers(const aq_policy* p, int64_t batch,
     return AQ_OK;
 }
 
+extern "C" aq_status aq_policy_fp32_plan(const aq_policy* p, int64_t batch, int32_t* rows, int32_t* tiles) {
+    if (!p || !rows || !tiles || batch < 1) return AQ_EINVAL;
+    int rt = 1;
+    *rows = fp32_mlp_fits(p->h_net, batch, &rt) ? 16 * rt : 0;
+    for (int l = 0; l < p->net.n_layers; ++l) {
+        const LayerBuf& b = p->L[l];
+        Fp32Layer L{};
+        L.K = b.K;
+        L.N = b.N;
+        tiles[2 * l] = tiles[2 * l + 1] = 0;
+        if (!*rows) fp32_layer_tile(L, batch * b.oh * b.ow, &tiles[2 * l], &tiles[2 * l + 1]);
+    }
+    return AQ_OK;
+}
+
+extern "C" aq_status aq_policy_fp16_plan(const aq_policy* p, int64_t batch, int32_t* rows) {
+    if (!p || !rows || batch < 1) return AQ_EINVAL;
+    if (!p->h16_ready) return AQ_ENOTQUANT;
+    *rows = fp16_mlp_rows(p->h16_net, batch);
+    return AQ_OK;
+}
+
 extern "C" aq_status aq_policy_status(aq_policy* p, void* stream) {
     if (!p) return AQ_EINVAL;
     int h2[2] = {0, 0};  // [0] the 8-bit policy's status word, [1] the half-precision policy's
@@ -1374,7 +1396,7 @@ extern "C" aq_status aq_policy_forward_fp16(aq_policy* p, const void* d_obs, int
     if (batch == 0) return AQ_OK;
     if (!d_obs || !d_actions) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
-    if (fp16_mlp_fits(p->h16_net, batch))
+    if (fp16_mlp_rows(p->h16_net, batch))
         return launch_fp16_mlp(p->h16_net, p->d_h16_net, d_obs, p->h_net.in_u8, batch, d_actions, taps_out, st);
     aq_status s = ensure_f16(p, batch, st);
     if (s != AQ_OK) return s;

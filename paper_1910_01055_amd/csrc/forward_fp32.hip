@@ -711,6 +711,12 @@ aq_status launch_tile_kind(const Fp32Layer& L, bool fc, int in_u8, const void* i
 }
 }  // namespace
 
+void fp32_layer_tile(const Fp32Layer& L, int64_t rows, int* features, int* tile_rows) {
+    const TileShape& t = kTiles[pick_tile(L, rows)];
+    *features = 16 * t.ft * t.wn;
+    *tile_rows = 16 * t.rt * t.wm;
+}
+
 aq_status launch_fp32_layer(const Fp32Layer& L, const void* in, int in_u8, float* out, int64_t rows, RangeSlot* slots,
                             hipStream_t st) {
     const bool fc = L.kh == 1 && L.kw == 1 && L.in_h == 1 && L.in_w == 1;

@@ -430,9 +430,9 @@ bool plan_mlp(const Fp16Net& n, int64_t batch, MlpPlan* best) {
 }
 }  // namespace
 
-bool fp16_mlp_fits(const Fp16Net& n, int64_t batch) {
+int fp16_mlp_rows(const Fp16Net& n, int64_t batch) {
     MlpPlan p;
-    return n.n_layers > 0 && plan_mlp(n, batch, &p);
+    return n.n_layers > 0 && plan_mlp(n, batch, &p) ? 16 * p.rt : 0;
 }
 
 aq_status launch_fp16_mlp(const Fp16Net& n, const Fp16Net* d_net, const void* obs, int in_u8, int64_t batch, void* actions,

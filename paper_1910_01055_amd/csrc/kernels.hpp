@@ -160,6 +160,8 @@ struct F32KeepTab {
 };
 aq_status launch_fp32_layer(const Fp32Layer& L, const void* in, int in_u8, float* out, int64_t rows, RangeSlot* slots,
                             hipStream_t st);
+// features and rows of the tile that a layer takes at this number of rows
+void fp32_layer_tile(const Fp32Layer& L, int64_t rows, int* features, int* tile_rows);
 // whether the network runs as one launch at this batch; rt = 16-row tiles per workgroup then
 bool fp32_mlp_fits(const NetDev& n, int64_t batch, int* rt);
 aq_status launch_fp32_mlp(const NetDev& n, const NetDev* d_net, const F32Ptrs& ptrs, const F32Ptrs* d_ptrs, const void* obs,
@@ -230,8 +232,8 @@ struct Fp16Taps<false> {
     int none;
     Fp16Taps(void* const*, int) : none(0) {}
 };
-// whether the policy runs as one launch at this batch size
-bool fp16_mlp_fits(const Fp16Net& n, int64_t batch);
+// rows per workgroup where the policy runs as one launch at this batch size, else 0
+int fp16_mlp_rows(const Fp16Net& n, int64_t batch);
 aq_status launch_fp16_mlp(const Fp16Net& n, const Fp16Net* d_net, const void* obs, int in_u8, int64_t batch, void* actions,
                           void* const* taps, hipStream_t st);
 // in_mode: 0 = binary16 activations, 1 = fp32 observations, 2 = uint8 observations

@@ -1,10 +1,11 @@
-"""The whole-network half-precision kernel at 16, 32 and 64 rows per workgroup: ragged rows, one to four feature tiles per
+"""The whole-network half-precision kernel at 16, 32 and 64 rows per workgroup, beside the launches per layer: ragged rows, one to four feature tiles per
 wavefront and wavefronts without one, LayerNorm rows, narrow and wide heads; every layer's output of sampled rows against
 the CPU oracle (the launch without taps must give the same actions)."""
 import numpy as np
 import pytest
 
 from paper_1910_01055_amd import synth
+import gpu_util as U
 from test_gpu_fp16 import _check, _run_gpu
 
 pytestmark = pytest.mark.gpu
@@ -23,8 +24,22 @@ def _nets():
     }
 
 
+# 16, 32 and 64 rows per workgroup at 2101, 4099 and 12005; the launch per layer at 16391, and of some at fewer rows
+BATCHES = [1, 49, 2101, 4099, 8200, 12005, 16391]
+
+
 @pytest.mark.parametrize("name", list(_nets()))
-@pytest.mark.parametrize("batch", [1, 49, 4099, 8200, 16391])
+def test_the_batches_reach_every_row_count(aq, name):
+    net = _nets()[name]
+    P = aq.Policy(net)
+    P.convert_params_fp16(*U.upload_params(synth.make_params(net)))
+    plan = {batch: P.policy_fp16_plan(batch) for batch in BATCHES}
+    assert (plan[2101], plan[4099], plan[12005], plan[16391]) == (16, 32, 64, 0), plan
+    P.close()
+
+
+@pytest.mark.parametrize("name", list(_nets()))
+@pytest.mark.parametrize("batch", BATCHES)
 def test_whole_network_half_precision_kernel(aq, name, batch):
     print(f"[fp16 mlp] {name} batch={batch}", flush=True)
     net = _nets()[name]

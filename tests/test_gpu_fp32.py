@@ -28,6 +28,9 @@ def _cases():
         # a launch per layer: wide layers, few and many rows
         "layers_few_rows": (small([fc(67, 1300, "ln_tanh"), fc(1300, 1300, "relu"), fc(1300, 21, "none")]), [1, 16, 17, 70]),
         "layers_many_rows": (small([fc(70, 1300, "relu"), fc(1300, 130, "none"), fc(130, 66, "none")], head="argmax"), [513, 2100]),
+        # ... on the two largest tiles, of 64 features x 128 rows and of 64 x 64
+        "layers_tile_64x128": (small([fc(67, 600, "relu"), fc(600, 2047, "none"), fc(2047, 3, "none")]), [1003]),
+        "layers_tile_64x64": (small([fc(70, 1300, "relu"), fc(1300, 190, "none"), fc(190, 4, "none")]), [5437]),
         "conv": (small([conv(20, 20, 4, 33, 8, 8, 4, "relu"), conv(4, 4, 33, 20, 2, 2, 1, "none"), fc(180, 24, "relu"), fc(24, 5, "none")],
                        head="linear", in_type="u8", init="he_normal"), [1, 70]),
         "conv_odd_window": (small([conv(9, 10, 3, 5, 3, 2, 2, "relu"), conv(4, 5, 5, 7, 3, 3, 1, "relu"), fc(42, 11, "none")],
@@ -67,6 +70,20 @@ def test_fp32_actor_and_ranges(aq, name, batch):
     else:
         assert U.close(out.cpu().numpy(), ref).all()
     P.close()
+
+
+def test_the_cases_reach_every_tile(aq):
+    """... of the per-layer kernel, and both forms of the whole-policy kernel."""
+    rows, tiles = set(), set()
+    for net, batches in _cases().values():
+        P = aq.Policy(net)
+        for batch in batches:
+            r, t = P.policy_fp32_plan(batch)
+            rows.add(r)
+            tiles.update(t)
+        P.close()
+    assert rows == {0, 16, 32}
+    assert tiles == {(64, 128), (32, 128), (64, 64), (32, 32), (16, 32), (16, 16)}
 
 
 def test_fp32_calibration_of_a_smaller_batch_forgets_the_larger_ones_ranges(aq):
