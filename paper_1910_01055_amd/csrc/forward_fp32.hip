@@ -678,7 +678,7 @@ int pick_tile(const Fp32Layer& L, int64_t rows) {
         const TileShape& t = kTiles[i];
         const int64_t bn = 16 * t.ft * t.wn, bm = 16 * t.rt * t.wm, bs = t.ks * t.wk;
         const int64_t ny = (L.N + bn - 1) / bn, nx = (rows + bm - 1) / bm;
-        if (ny > 65535) continue;  // (the grid's second dimension)
+        if (ny > 65535 || !grid_ok(nx, FT_)) continue;
         const double stages = (double)((nst + bs - 1) / bs);
         const double per = stages * (t.ks * t.ft * t.rt * 256.0 + 150.0) + (t.wk > 1 ? 1200.0 : 600.0);
         const double c = (double)((nx * ny + 255) / 256) * per + 1500.0;
@@ -757,8 +757,10 @@ bool fp32_mlp_fits(const NetDev& n, int64_t batch, int* rt_out) {
     if (mlp_lds(1, ld) > 160 * 1024) return false;
     const int rt = batch > 16 * 512 && mlp_lds(2, ld) <= 80 * 1024 ? 2 : 1;
     *rt_out = rt;
+    const int64_t workgroups = (batch + 16 * rt - 1) / (16 * rt);
+    if (!grid_ok(workgroups, MT_)) return false;
     // clocks: one launch (weights at 40 B per clock and CU, or 32 per MFMA and SIMD) against a launch per layer
-    const double wgs = (double)((batch + 16 * rt - 1) / (16 * rt)), rounds = (double)(int64_t)((wgs + 255) / 256);
+    const double rounds = (double)((workgroups + 255) / 256);
     const double mm = wbytes / 4.0 / 1024.0 * rt * 128.0 / 4.0, mem = wbytes / 40.0;
     const double fused = rounds * (mm > mem ? mm : mem);
     const double flops = wbytes / 2.0 * (double)batch;

@@ -413,6 +413,7 @@ bool plan_mlp(const Fp16Net& n, int64_t batch, MlpPlan* best) {
             if (l < n.n_layers - 1 && n.L[l].act == AQ_ACT_LN_TANH) per += 1500.0 + 10.0 * rt * n.L[l].N;
         }
         const int64_t wgs = (batch + 16 * rt - 1) / (16 * rt);
+        if (!grid_ok(wgs, MLT)) continue;
         const double c = (double)((wgs + 255) / 256) * per;
         if (!found || c < best_c) {
             best_c = c;

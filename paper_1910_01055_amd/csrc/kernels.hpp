@@ -6,6 +6,8 @@ namespace aq {
 
 // ---- quantizer block (quantize.hip)
 aq_status launch_fill_u32(uint32_t* p, int n, uint32_t v, hipStream_t st);
+// a grid's threads along one dimension are counted in 32 bits
+inline bool grid_ok(int64_t workgroups, int threads) { return workgroups <= 0xffffffffLL / threads; }
 // qdenom, qmax (largest unsigned code) and qw (largest symmetric code) describe the n-bit code range
 aq_status launch_quantize_tensor(const float* d_w, int64_t rows, int64_t cols, int wscheme, float qdenom,
                                  int qmax, int qw, void* d_codes, float* d_scale, int32_t* d_zp, uint32_t* d_ws, hipStream_t st);

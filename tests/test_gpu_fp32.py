@@ -86,6 +86,18 @@ def test_the_cases_reach_every_tile(aq):
     assert tiles == {(64, 128), (32, 128), (64, 64), (32, 32), (16, 32), (16, 16)}
 
 
+def test_batches_beyond_a_grid_of_whole_policy_workgroups_go_layer_by_layer(aq):
+    """A grid holds fewer than 2^32 threads: 1024 for each 32 rows of the whole-policy kernel, 512 for each 128 rows of a
+    layer's largest tile.  (Plans only: such a batch's observations are gigabytes.)"""
+    P = aq.Policy(synth.small_net([fc(4, 64, "relu"), fc(64, 2, "none")]))
+    assert P.policy_fp32_plan((1 << 27) - 32)[0] == 32
+    for batch in ((1 << 27) - 31, 1 << 27, (1 << 30) - 128):
+        rows, tiles = P.policy_fp32_plan(batch)
+        assert rows == 0
+        assert all(-(-batch // r) * 512 < 1 << 32 for _, r in tiles), tiles
+    P.close()
+
+
 def test_fp32_calibration_of_a_smaller_batch_forgets_the_larger_ones_ranges(aq):
     net = synth.net_config("cfg4")
     params = synth.make_params(net)
