@@ -15,6 +15,7 @@
 // What bounds it: at large batch the matrix cores and the CU's vector memory path together (64 rows x 1024 x 1024: 2 MiB of
 // weights at 52 B per clock = 40 k clocks beside as long a run of MFMAs); at small batch the chain of layers of one
 // workgroup.
+#include "fp16_device.hpp"
 #include "int8_device.hpp"
 
 namespace aq {
@@ -40,22 +41,6 @@ constexpr int MLW = 8;               // wavefronts per workgroup
 constexpr int MLT = MLW * 64;
 constexpr int MLMAXW = 1024;         // widest layer input / output
 constexpr int MLY_LD = 68;           // halfs per row of a narrow head's logits (at most 64)
-
-// tanh of a value about to be rounded to binary16, relative error below 1e-6 (as in fp16_actor.hip)
-__device__ __forceinline__ float tanh_rel(float x) {
-    const float ax = fabsf(x);
-    const float u = x * x;
-    float p = 0.0035921280f;
-    p = fmaf(p, u, -0.0088632355f);
-    p = fmaf(p, u, 0.0218694885f);
-    p = fmaf(p, u, -0.0539682540f);
-    p = fmaf(p, u, 0.1333333333f);
-    p = fmaf(p, u, -0.3333333333f);
-    const float small = fmaf(x * u, p, x);
-    const float e = __builtin_amdgcn_exp2f(fminf(ax, 20.0f) * 2.885390081777927f);
-    const float big = copysignf(fmaf(__builtin_amdgcn_rcpf(e + 1.0f), -2.0f, 1.0f), x);
-    return ax < 0.5f ? small : big;
-}
 
 // k-steps (of 32) in flight when a wavefront has NB tiles, two operands each
 template <int NB>
