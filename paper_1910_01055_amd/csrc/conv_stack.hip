@@ -14,11 +14,12 @@
 // operand reads and products, an epilogue) and, within a phase, instruction issue: what all sixteen wavefronts execute
 // costs sixteen clocks an instruction.  Hence one wavefront per layer for constants and tables, four per layer for the
 // weights (straight into LDS), one code for all layers with arguments read per layer, windows' places from a table.  An
-// 84 x 84 x 4 frame through 32, 32 and 16 channels at 256 images takes 7.6 us back to back, 2.6 of them the launch; 2048
-// images 44 us (as two workgroups per CU 36).  The same with a copy of the code per layer and weights through registers: 13 us.  One workgroup per
-// image with 32 x 32 tiles and weights from L2 per tile (what stood here before) was as fast at 256 images, half as fast
-// at 2048, and took none but rows of 16 bytes: a policy on 65 x 65 x 3 frames at batch 25 went layer by layer with byte
-// gathers, 55.4 us, now 19.3.
+// 84 x 84 x 4 frame through 32, 32 and 16 channels at 256 images takes 7.6 us back to back, 2.6 of them the launch.  The
+// same with a copy of the code per layer and weights through registers: 13 us.  One workgroup per image with 32 x 32
+// tiles and weights from L2 per tile (what stood here before) took none but rows of 16 bytes: a policy on 65 x 65 x 3
+// frames at batch 25 went layer by layer with byte gathers, 55.4 us, now 19.3.  Where both run, whole forwards before
+// and now: 84 x 84 x 4 through 32, 32, 16 at 256 / 2048 images 16.0 / 46.6 and 14.5 / 40.9 us; through 32, 64, 64, whose
+// weights leave one workgroup to a CU, 18.6 / 56.6 and 17.4 / 61.2 us.
 //
 // Frames of fewer than four channels whose windows would not begin and end at whole pieces are expanded to four on
 // their way into LDS, and the first layer's weights with them (zeros in the channels that do not exist), so that every
