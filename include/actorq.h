@@ -119,11 +119,10 @@ typedef struct {
 aq_status aq_policy_create(const aq_net* net, aq_policy** out);
 aq_status aq_policy_destroy(aq_policy* p);
 
-/* Pre-allocates the internal activation buffers for batches up to max_batch (and the packed weights of
- * aq_policy_forward_fp32_params, 4 bytes per weight), so that later forwards with batch <= max_batch allocate
- * nothing.  Forwards grow the buffers themselves when needed (such a call waits for the device, frees and
- * allocates; while `stream` is being captured into a graph it returns AQ_ETOOBIG instead, so reserve before
- * capturing). */
+/* Pre-allocates the internal activation buffers for batches up to max_batch, so that later
+ * forwards with batch <= max_batch allocate nothing (but see aq_policy_forward_fp32_params).  Forwards grow the
+ * buffers themselves when needed (such a call waits for the device, frees and allocates; while `stream` is being
+ * captured into a graph it returns AQ_ETOOBIG instead, so reserve before capturing). */
 aq_status aq_policy_reserve(aq_policy* p, int64_t max_batch);
 
 /* Chooses the 8-bit forward's launch plan: 0 = automatic (whole-network fused kernel when the
@@ -349,8 +348,8 @@ aq_status aq_policy_forward_int8_static(aq_policy* p, const void* d_obs, int64_t
  *   activation -- the ranges aq_quantize_params takes.  Waits for `stream` (AQ_EINVAL while it is being
  *   captured).  AQ_ENOTQUANT before aq_policy_set_params_fp32.
  * aq_policy_forward_fp32_params: the same actor on parameter arrays passed with the call (nothing is kept of
- *   them: every call packs them anew, into memory of the handle that the first call or an aq_policy_reserve
- *   allocates), with the calibration as an optional device-side output and no wait: d_ranges_out (may be NULL)
+ *   them: every call packs them anew, into memory of the handle, 4 bytes per weight, that the first call
+ *   allocates, under capture too), with the calibration as an optional device-side output and no wait: d_ranges_out (may be NULL)
  *   receives 2 * n_layers floats, (min, max) per activation tensor as above. */
 aq_status aq_policy_set_params_fp32(aq_policy* p, const float* const* h_d_w, const float* const* h_d_b,
                                     const float* const* h_d_gamma, const float* const* h_d_beta, void* stream);

@@ -115,7 +115,7 @@ struct aq_policy {
     // the learner's fp32 parameters, copied by aq_policy_set_params_fp32, and the packed weights of parameters passed
     // with a call (one allocation each)
     F32Store f32_kept;    // made by the first aq_policy_set_params_fp32
-    F32Store f32_passed;  // made by the first aq_policy_forward_fp32_params or an aq_policy_reserve
+    F32Store f32_passed;  // made by the first aq_policy_forward_fp32_params (its table with the policy)
     bool f32_ready = false;
     // policies of at most 4 bits, per-channel symmetric, under launch plan 4: the fully connected layers' weights
     // once more as nibbles, for the few-row kernel (one allocation when the plan is first chosen; rewritten by
@@ -183,16 +183,15 @@ extern "C" const char* aq_status_string(aq_status s) {
     return "unknown";
 }
 
-// A set of fp32 parameters: the packed weights, with `keep` also row-major copies, biases, gains and offsets.  Fills
-// all of the table that fills them but the destinations, their places into offs, and returns the bytes they take.
-static size_t f32_store_layout(const aq_policy* p, bool keep, F32KeepTab& tab, size_t* offs) {
+// A set of fp32 parameters: the packed weights, with `keep` also row-major copies, biases, gains and offsets.  Fills the
+// table that the launch filling the set reads, and returns the bytes the set takes.
+static size_t f32_store_layout(const aq_policy* p, bool keep, F32KeepTab& tab) {
     size_t bytes = 0;
     int blk = 0;
     auto add = [&](int64_t n, int kind, int l) {
-        offs[tab.n] = bytes;
-        bytes += ((size_t)n * 4 + 255) / 256 * 256;
         tab.blk0[tab.n] = blk;
-        tab.e[tab.n++] = F32KeepTab::Entry{nullptr, n, kind, l, p->L[l].N, p->L[l].K};
+        tab.e[tab.n++] = F32KeepTab::Entry{(int64_t)bytes, n, kind, l, p->L[l].N, p->L[l].K};
+        bytes += ((size_t)n * 4 + 255) / 256 * 256;
         blk += (int)((n + kKeepPiece - 1) / kKeepPiece);
     };
     for (int l = 0; l < p->net.n_layers; ++l) {
@@ -207,13 +206,13 @@ static size_t f32_store_layout(const aq_policy* p, bool keep, F32KeepTab& tab, s
     return bytes;
 }
 
-// ... and the destinations, from where the set begins
-static F32Ptrs f32_store_place(F32KeepTab& tab, char* base, const size_t* offs) {
+// ... and where its arrays are, given where it begins
+static F32Ptrs f32_store_ptrs(const F32KeepTab& tab, char* base) {
     F32Ptrs ptrs{};
     for (int i = 0; i < tab.n; ++i) {
-        F32KeepTab::Entry& e = tab.e[i];
-        e.dst = (float*)(base + offs[i]);
-        (e.kind == 0 ? ptrs.w : e.kind == 1 ? ptrs.b : e.kind == 2 ? ptrs.gamma : e.kind == 3 ? ptrs.beta : ptrs.wpk)[e.layer] = e.dst;
+        const F32KeepTab::Entry& e = tab.e[i];
+        (e.kind == 0 ? ptrs.w : e.kind == 1 ? ptrs.b : e.kind == 2 ? ptrs.gamma : e.kind == 3 ? ptrs.beta : ptrs.wpk)[e.layer] =
+            (float*)(base + e.off);
     }
     return ptrs;
 }
@@ -320,6 +319,9 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     // what the host writes, side by side: one copy
     size_t off_net = take(sizeof(NetDev));
     size_t off_qtab = take(sizeof(QTab));
+    size_t off_ftab = take(sizeof(F32KeepTab));
+    F32KeepTab ftab{};  // of parameters passed with a call
+    (void)f32_store_layout(p, false, ftab);
     if (hipMalloc(&p->slab, bytes) != hipSuccess) {
         delete p;
         return AQ_ENOMEM;
@@ -415,9 +417,12 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         mix((int64_t)p->layer_bytes);
         p->net_hash = h;
     }
-    std::vector<char> up(off_qtab + sizeof(QTab) - off_net);
+    p->f32_passed.d_tab = (F32KeepTab*)(base + off_ftab);
+    p->f32_passed.blocks = ftab.blocks;
+    std::vector<char> up(off_ftab + sizeof(F32KeepTab) - off_net);
     memcpy(up.data(), &p->h_net, sizeof(NetDev));
     memcpy(up.data() + (off_qtab - off_net), &p->h_qtab, sizeof(QTab));
+    memcpy(up.data() + (off_ftab - off_net), &ftab, sizeof(F32KeepTab));
     if (hipMemcpy(p->d_net, up.data(), up.size(), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(p->slab);
         delete p;
@@ -520,21 +525,19 @@ static aq_status ensure_f16(aq_policy* p, int64_t batch, hipStream_t st) {
     return AQ_OK;
 }
 
-// Storage of a set of fp32 parameters (what it holds: f32_store_layout), made once.
-static aq_status ensure_f32_store(const aq_policy* p, F32Store& S, bool keep, hipStream_t st) {
+// Storage of the parameters that aq_policy_set_params_fp32 keeps, made once.
+static aq_status ensure_f32_kept(aq_policy* p, hipStream_t st) {
+    F32Store& S = p->f32_kept;
     if (S.slab) return AQ_OK;
     if (capturing(st)) return AQ_ETOOBIG;
-    F32KeepTab tab{};
-    size_t offs[5 * AQ_MAX_LAYERS];
-    const size_t bytes = f32_store_layout(p, keep, tab, offs);
     struct {
         F32Ptrs ptrs;
         F32KeepTab tab;
     } up{};
+    const size_t bytes = f32_store_layout(p, true, up.tab);
     char* slab = nullptr;
     if (hipMalloc((void**)&slab, bytes + sizeof(up)) != hipSuccess) return AQ_ENOMEM;
-    up.ptrs = f32_store_place(tab, slab, offs);
-    up.tab = tab;
+    up.ptrs = f32_store_ptrs(up.tab, slab);
     if (hipMemcpy(slab + bytes, &up, sizeof(up), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(slab);
         return AQ_EHIP;
@@ -543,7 +546,27 @@ static aq_status ensure_f32_store(const aq_policy* p, F32Store& S, bool keep, hi
     S.d_tab = (F32KeepTab*)(slab + bytes + offsetof(decltype(up), tab));
     S.slab = slab;
     S.ptrs = up.ptrs;
-    S.blocks = tab.blocks;
+    S.blocks = up.tab.blocks;
+    return AQ_OK;
+}
+
+// Memory for the packed weights of parameters passed with a call, made once (their table is there from the start, so
+// that this is an allocation and nothing else).  The call may be one into a graph: an allocation is no part of it,
+// and the relaxed mode of this thread says that it is meant to happen now.
+static aq_status ensure_f32_passed(aq_policy* p) {
+    F32Store& S = p->f32_passed;
+    if (S.slab) return AQ_OK;
+    F32KeepTab tab{};
+    const size_t bytes = f32_store_layout(p, false, tab);
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    AQ_HIP_CHECK(hipThreadExchangeStreamCaptureMode(&mode));
+    const hipError_t e = hipMalloc(&S.slab, bytes);
+    AQ_HIP_CHECK(hipThreadExchangeStreamCaptureMode(&mode));
+    if (e != hipSuccess) {
+        S.slab = nullptr;
+        return AQ_ENOMEM;
+    }
+    S.ptrs = f32_store_ptrs(tab, (char*)S.slab);
     return AQ_OK;
 }
 
@@ -555,8 +578,6 @@ extern "C" aq_status aq_policy_reserve(aq_policy* p, int64_t max_batch) {
         s = ensure_f16(p, max_batch, nullptr);
         if (s != AQ_OK) return s;
     }
-    s = ensure_f32_store(p, p->f32_passed, false, nullptr);
-    if (s != AQ_OK) return s;
     return ensure_f32(p, max_batch, nullptr);
 }
 
@@ -1188,9 +1209,9 @@ extern "C" aq_status aq_policy_forward_fp32_params(aq_policy* p, const float* co
         if (!h_d_w[l]) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
     F32Ptrs ptrs = f32_ptr_table(p->net.n_layers, h_d_w, h_d_b, h_d_gamma, h_d_beta);
-    aq_status s = ensure_f32_store(p, p->f32_passed, false, st);
+    aq_status s = ensure_f32_passed(p);
     if (s != AQ_OK) return s;
-    s = launch_keep_params(ptrs, p->f32_passed.d_tab, p->f32_passed.blocks, st);
+    s = launch_keep_params(ptrs, p->f32_passed.d_tab, p->f32_passed.slab, p->f32_passed.blocks, st);
     if (s != AQ_OK) return s;
     for (int l = 0; l < p->net.n_layers; ++l) ptrs.wpk[l] = p->f32_passed.ptrs.wpk[l];
     return forward_fp32_impl(p, ptrs, nullptr, d_obs, batch, d_actions, d_ranges_out, nullptr, 0, st);
@@ -1204,11 +1225,11 @@ extern "C" aq_status aq_policy_set_params_fp32(aq_policy* p, const float* const*
     for (int l = 0; l < nl; ++l)
         if (!h_d_w[l]) return AQ_EINVAL;
     hipStream_t st = as_stream(stream);
-    aq_status s = ensure_f32_store(p, p->f32_kept, true, st);
+    aq_status s = ensure_f32_kept(p, st);
     if (s != AQ_OK) return s;
     // (absent biases, gains and offsets take their defaults 0, 1, 0)
     s = launch_keep_params(f32_ptr_table(nl, h_d_w, h_d_b, h_d_gamma, h_d_beta), p->f32_kept.d_tab,
-                           p->f32_kept.blocks, st);
+                           p->f32_kept.slab, p->f32_kept.blocks, st);
     if (s != AQ_OK) return s;
     p->f32_ready = true;
     return AQ_OK;

@@ -594,7 +594,7 @@ __global__ __launch_bounds__(64 * AQ_MAX_LAYERS) void k_ranges_out(RangeSlot* __
 // piece of it by the table; an absent source is its default value.  (As one copy or fill per array this was 15 to 20
 // launches of 2.6 us.)  Per layer: weights row-major (the quantizer reads them), bias, gain, offset, and the weights in
 // the operand order of the kernels above (all that is written of parameters passed with a call).
-__global__ __launch_bounds__(256) void k_keep_params(const F32Ptrs src, const F32KeepTab* __restrict__ tab) {
+__global__ __launch_bounds__(256) void k_keep_params(const F32Ptrs src, const F32KeepTab* __restrict__ tab, char* __restrict__ to) {
     const int blk = (int)blockIdx.x;
     // the last array that starts at or before this workgroup (5 * AQ_MAX_LAYERS <= 64: one lane each)
     const int lane = threadIdx.x & 63;
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(256) void k_keep_params(const F32Ptrs src, const F3
     const int kind = tab->e[a].kind, l = tab->e[a].layer;
     const int64_t n = tab->e[a].count, base = (int64_t)(blk - tab->blk0[a]) * kKeepPiece;
     const float* s = kind == 1 ? src.b[l] : kind == 2 ? src.gamma[l] : kind == 3 ? src.beta[l] : src.w[l];
-    float AQ_GLOBAL* d = (float AQ_GLOBAL*)tab->e[a].dst;
+    float AQ_GLOBAL* d = (float AQ_GLOBAL*)(to + tab->e[a].off);
     if (kind == 4) {  // 16 blocks of 16 features x 16 k
         const int N = tab->e[a].N, K = tab->e[a].K, nst = (K + 15) >> 4;
         const int i16 = lane & 15, g = lane >> 4;
@@ -831,8 +831,8 @@ aq_status launch_ranges_out(RangeSlot* slots, int n, float* out, uint32_t* ready
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
 
-aq_status launch_keep_params(const F32Ptrs& src, const F32KeepTab* d_tab, int blocks, hipStream_t st) {
-    hipLaunchKernelGGL(k_keep_params, dim3((unsigned)blocks), dim3(256), 0, st, src, d_tab);
+aq_status launch_keep_params(const F32Ptrs& src, const F32KeepTab* d_tab, void* base, int blocks, hipStream_t st) {
+    hipLaunchKernelGGL(k_keep_params, dim3((unsigned)blocks), dim3(256), 0, st, src, d_tab, (char*)base);
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
 

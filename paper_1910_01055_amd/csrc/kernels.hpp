@@ -152,7 +152,7 @@ struct F32Call {
 constexpr int kKeepPiece = 4096;
 struct F32KeepTab {
     struct Entry {
-        float* dst;
+        int64_t off;  // bytes from where the set begins
         int64_t count;
         int kind, layer, N, K;  // kind: 0 weights, 1 bias, 2 gain, 3 offset, 4 packed weights
     };
@@ -173,7 +173,7 @@ aq_status launch_fp32_ln_tanh(float* x, int64_t rows, int N, const float* gamma,
 aq_status launch_fp32_argmax(const float* y, int64_t rows, int N, int32_t* actions, hipStream_t st);
 aq_status launch_input_range(const void* x, int is_u8, int64_t n, RangeSlot* slots, hipStream_t st);
 aq_status launch_ranges_out(RangeSlot* slots, int n, float* out, uint32_t* ready, uint32_t ticket, hipStream_t st);
-aq_status launch_keep_params(const F32Ptrs& src, const F32KeepTab* d_tab, int blocks, hipStream_t st);
+aq_status launch_keep_params(const F32Ptrs& src, const F32KeepTab* d_tab, void* base, int blocks, hipStream_t st);
 
 
 // ---- half-precision actor (fp16_actor.hip)

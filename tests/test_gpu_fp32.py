@@ -134,31 +134,38 @@ def test_fp32_forward_on_passed_parameters_is_captured_after_reserve(aq):
 
 
 def test_fp32_weights_cost_memory_only_where_they_are_used(aq):
-    """A policy that has run nothing in fp32 holds its 8-bit weights and constants, about a byte per weight; the forward on
-    passed parameters allocates its packed weights at its first call, which a capture refuses like any other allocation."""
+    """A policy that has run nothing in fp32 holds its 8-bit weights and constants, about a byte per weight."""
     net = synth.small_net([fc(64, 2048, "relu"), fc(2048, 2048, "relu"), fc(2048, 2048, "relu"), fc(2048, 8, "none")])
     params = synth.make_params(net, nonzero_bias=True)
     weights = sum(p["w"].size for p in params)
-    dev = U.upload_params(params)
-    obs, out, want = U.to_dev(synth.make_obs(net, 4)), torch.zeros(4, 8, device=U.DEV), torch.zeros(4, 8, device=U.DEV)
     torch.cuda.synchronize()
     before = torch.cuda.mem_get_info()[0]
     policies = [aq.Policy(net) for _ in range(8)]
     held = before - torch.cuda.mem_get_info()[0]
     assert held < 8 * 1.6 * weights, held / (8 * weights)
-    for P in policies[1:]:
+    for P in policies:
         P.close()
-    P = policies[0]
+
+
+def test_first_fp32_forward_on_passed_parameters_under_capture(aq):
+    """The first call allocates its packed weights: a policy that needs no other buffers may make it into a graph."""
+    net = synth.small_net([fc(17, 300, "relu"), fc(300, 200, "ln_tanh"), fc(200, 6, "none")])
+    params = synth.make_params(net, nonzero_bias=True)
+    dev = U.upload_params(params)
+    obs, out, want = U.to_dev(synth.make_obs(net, 40)), torch.zeros(40, 6, device=U.DEV), torch.zeros(40, 6, device=U.DEV)
+    P = aq.Policy(net)
+    assert P.policy_fp32_plan(40)[0] == 16
     graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
     with torch.cuda.graph(graph):
+        P.policy_forward_fp32_params(*dev, obs, out)
+    for _ in range(3):
         out.zero_()
-        with pytest.raises(aq.AqError) as e:
-            P.policy_forward_fp32_params(*dev, obs, out)
-        assert e.value.status == aq.ETOOBIG
-    P.policy_forward_fp32_params(*dev, obs, out)
-    P.policy_set_params_fp32(*dev)
-    P.policy_forward_fp32(obs, want)
-    assert torch.equal(out, want) and U.close(out.cpu().numpy(), O.OraclePolicy(net).forward_fp32(params, synth.make_obs(net, 4))[0]).all()
+        graph.replay()
+        P.policy_forward_fp32_params(*dev, obs, want)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    assert U.close(out.cpu().numpy(), O.OraclePolicy(net).forward_fp32(params, synth.make_obs(net, 40))[0]).all()
     P.close()
 
 
