@@ -1,4 +1,5 @@
 // C ABI of the library: the policy handle, argument checks and the launch sequences.
+#include <algorithm>
 #include <cstddef>
 #include <cstring>
 #include <mutex>
@@ -467,9 +468,16 @@ static bool capturing(hipStream_t st) {
     return hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
 }
 
-// bytes of one 8-bit activation map of the per-layer plan (a little slack behind the last row)
+// bytes of one 8-bit activation map of the per-layer plan (a little slack behind the last row), and the same where
+// fully connected layers' maps may lie in operand order
 static size_t i8_map_bytes(const aq_policy* p, int64_t batch) {
     return (size_t)batch * (size_t)(p->max_hidden_elems > 0 ? p->max_hidden_elems : 1) + 64;
+}
+static size_t i8_map_bytes_blocked(const aq_policy* p, int64_t batch) {
+    size_t n = i8_map_bytes(p, batch);
+    for (const LayerBuf& b : p->L)
+        if (b.fc) n = std::max(n, blocked_map_bytes(batch, b.N));
+    return n;
 }
 
 static aq_status ensure_i8(aq_policy* p, int64_t batch, hipStream_t st) {
@@ -485,7 +493,7 @@ static aq_status ensure_i8(aq_policy* p, int64_t batch, hipStream_t st) {
     p->ln_x = p->y_rows = nullptr;
     p->cap_i8 = 0;
     for (int i = 0; i < 2; ++i)
-        if (hipMalloc((void**)&p->act_i8[i], i8_map_bytes(p, batch)) != hipSuccess) return AQ_ENOMEM;
+        if (hipMalloc((void**)&p->act_i8[i], i8_map_bytes_blocked(p, batch)) != hipSuccess) return AQ_ENOMEM;
     // fp32 rows exist only where the 8-bit path needs them: LayerNorm inputs, argmax logits
     if (p->ln_elems && hipMalloc((void**)&p->ln_x, (size_t)batch * p->ln_elems * 4 + 256) != hipSuccess) return AQ_ENOMEM;
     if (p->y_elems && hipMalloc((void**)&p->y_rows, (size_t)batch * p->y_elems * 4 + 256) != hipSuccess) return AQ_ENOMEM;
@@ -958,6 +966,7 @@ extern "C" aq_status aq_policy_export_act_qparams(const aq_policy* p, float* d_s
 // where the one-launch-per-layer plan keeps its intermediate tensors
 struct FwdScratch {
     int8_t* i8[2];  // 8-bit activation maps, ping-pong
+    bool blocked;   // they hold maps in operand order too (whole tiles of 16 rows and features)
     float* ln_x;    // fp32 rows into a LayerNorm row kernel
     float* y;       // logits of an argmax head
 };
@@ -1033,7 +1042,7 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
     } else {
         s = ensure_i8(p, batch, st);
         if (s != AQ_OK) return s;
-        sc = FwdScratch{{p->act_i8[0], p->act_i8[1]}, p->ln_x, p->y_rows};
+        sc = FwdScratch{{p->act_i8[0], p->act_i8[1]}, true, p->ln_x, p->y_rows};
     }
     if (a.net.in_u8 && a.t.a0) {
         const LayerBuf& b0 = p->L[0];
@@ -1049,10 +1058,14 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
         s = launch_conv_stack(a, sc.i8[(nc - 1) & 1], st);
         if (s != AQ_OK) return s;
     }
+    int blocked = 0;  // how the layer before left its output
     for (int l = nc; l < nl; ++l) {
         const LayerBuf& b = p->L[l];
         const int64_t rows_l = batch * b.oh * b.ow;
         LayerIO io;
+        io.in_blocked = blocked;
+        blocked = sc.blocked && l < nl - 1 && b.fc && b.d.act != AQ_ACT_LN_TANH && layer_uses_skinny(a, l) && layer_uses_skinny(a, l + 1);
+        io.out_blocked = blocked;
         io.in = l == 0 ? d_obs : (const void*)sc.i8[(l - 1) & 1];
         io.out = sc.i8[l & 1];
         io.ln_x = sc.ln_x;
@@ -1090,7 +1103,7 @@ extern "C" aq_status aq_policy_forward_int8_static(aq_policy* p, const void* d_o
     if (ss != AQ_OK) return ss;
     // carve the static array: two 8-bit maps, LayerNorm rows, argmax logits (each piece 256-byte aligned)
     auto up = [](size_t n) { return (n + 255) / 256 * 256; };
-    const size_t map = up(i8_map_bytes(p, batch));
+    size_t map = up(i8_map_bytes(p, batch));
     const size_t ln = up((size_t)batch * (size_t)p->ln_elems * 4);
     const size_t y = up((size_t)batch * (size_t)p->y_elems * 4);
     FwdArgs probe(p->h_net);
@@ -1098,11 +1111,14 @@ extern "C" aq_status aq_policy_forward_int8_static(aq_policy* p, const void* d_o
     int rows = 0;
     size_t lds = 0;
     const bool fused = p->path != 2 && fused_mlp_supported(probe, &rows, &lds);
-    FwdScratch sc{{nullptr, nullptr}, nullptr, nullptr};
+    FwdScratch sc{{nullptr, nullptr}, false, nullptr, nullptr};
     if (!fused) {  // (the whole-network kernel keeps everything in LDS and needs none of it)
         if ((double)batch * (double)(p->max_hidden_elems + 4 * (p->ln_elems + p->y_elems)) > 1e12 ||
             2 * map + ln + y > (size_t)AQ_STATIC_SCRATCH_BYTES)
             return AQ_ETOOBIG;
+        const size_t map_b = up(i8_map_bytes_blocked(p, batch));
+        sc.blocked = 2 * map_b + ln + y <= (size_t)AQ_STATIC_SCRATCH_BYTES;
+        if (sc.blocked) map = map_b;
         sc.i8[0] = (int8_t*)base;
         sc.i8[1] = (int8_t*)(base + map);
         sc.ln_x = (float*)(base + 2 * map);

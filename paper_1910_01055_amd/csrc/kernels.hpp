@@ -86,10 +86,16 @@ struct LayerIO {
     int8_t* out;      // hidden layers: int8 signed-domain [rows][N] (row stride N)
     float* ln_x;      // LN layers: fp32 scratch [rows][N]
     float* y;         // last layer: dequantized outputs [rows][N]
+    // between two layers of the few-row kernel the activations lie in operand order (skinny_layer.hip)
+    int in_blocked = 0, out_blocked = 0;
 };
+// bytes of such a map of `rows` rows and N features
+inline size_t blocked_map_bytes(int64_t rows, int N) { return (size_t)((rows + 15) / 16 * 16) * (size_t)((N + 15) / 16 * 16); }
 aq_status launch_layer_int8(const FwdArgs& a, int layer, const LayerIO& io, hipStream_t st);
-// FC layers at few rows: one workgroup per 32 x 32 output tile, K split over its waves (skinny_layer.hip)
+// FC layers at few rows: small output tiles, K split over a workgroup's waves (skinny_layer.hip)
 bool skinny_layer_supported(const LayerDev& L, int64_t rows);
+// 16-feature and 16-row tiles per workgroup that such a layer takes (argmax: all features in one workgroup)
+void skinny_layer_tile(const LayerDev& L, int64_t rows, bool argmax, int* ft, int* rt);
 bool skinny_layer_does_argmax(const FwdArgs& a, int l);
 // whether launch_layer_int8 hands layer l at this batch to the K-split kernel
 // the leading convolution layers in one launch (0 layers = shapes it does not take); writes the last

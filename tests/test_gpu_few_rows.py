@@ -1,0 +1,43 @@
+"""The few-row layer kernel at the edges of its tiles: 16 x 16, 32 x 16 and 32 x 32 outputs, shares of K that are empty,
+odd and longer than what is in flight, rows that are no multiple of 16, and maps in operand order between its layers."""
+import numpy as np
+import pytest
+
+import gpu_util as U
+from paper_1910_01055_amd import synth
+
+pytestmark = pytest.mark.gpu
+fc = synth.fc
+
+
+def _net(name):
+    return {
+        # K of 37 and 300 (no whole pieces of 16), widths whose last tile of 16 is ragged, an argmax over one tile of 16
+        "odd_argmax16": synth.small_net([fc(37, 300, "relu"), fc(300, 75, "none"), fc(75, 11, "none")], head="argmax"),
+        # the last half of a pair of 32-k tiles missing, an argmax over two tiles, a LayerNorm between two layers
+        "ln_argmax32": synth.small_net([fc(96, 160, "relu"), fc(160, 96, "ln_tanh"), fc(96, 32, "none")], head="argmax"),
+        # a K beyond eight k-steps of 64 per wave
+        "long_k": synth.small_net([fc(300, 4500, "relu"), fc(4500, 130, "none"), fc(130, 20, "none")], head="linear"),
+        "odd_asym": synth.small_net([fc(50, 500, "relu"), fc(500, 333, "none"), fc(333, 40, "none")], head="tanh",
+                                    wscheme="tensor_asym_u8"),
+        "u8_rows": synth.small_net([fc(150, 80, "relu"), fc(80, 50, "none")], head="tanh", in_type="u8"),
+    }[name]
+
+
+@pytest.mark.parametrize("name,batches", [("odd_argmax16", (1, 16, 17, 333, 1700)), ("ln_argmax32", (2, 31, 900)),
+                                          ("long_k", (1, 40, 500)), ("odd_asym", (1, 15, 260, 700)), ("u8_rows", (5, 48, 2000))])
+def test_few_row_layers_against_the_oracle(aq, name, batches):
+    net = _net(name)
+    params = synth.make_params(net, nonzero_bias=True)
+    for batch in batches:
+        print(f"few_rows {name} batch={batch}", flush=True)
+        obs = synth.make_obs(net, batch)
+        pol, ranges = U.make_oracle(net, params, obs[:256])
+        P, _ = U.gpu_quantize(aq, net, params, ranges)
+        P.policy_set_path(2)
+        actions, taps = U.gpu_forward(P, net, obs)
+        rows = np.unique(np.concatenate([[0, batch // 2, batch - 1], np.random.default_rng(3).integers(0, batch, 60)]))
+        U.compare_forward(net, pol, obs, actions, taps, rows)
+        plain, _ = U.gpu_forward(P, net, obs, taps=False)
+        assert np.array_equal(plain, actions)
+        P.close()
