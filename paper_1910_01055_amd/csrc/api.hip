@@ -72,6 +72,8 @@ struct F32Store {
     int blocks = 0;            // of the launch that fills it
 };
 
+constexpr int kFewStreams = 4;
+
 struct aq_policy {
     aq_net net;
     std::vector<LayerBuf> L;
@@ -95,6 +97,13 @@ struct aq_policy {
     // activation scratch of the per-layer path (8-bit maps, the fp32 rows a LayerNorm layer hands to its row
     // kernel, the logits of an argmax head) and of the fp32 actor, grown on demand
     int64_t cap_i8 = 0, cap_f32 = 0;
+    // ... and the maps of a policy that fits the whole-network kernels but runs few rows layer by layer (few_rows_faster): a
+    // pair of them for each of the first kFewStreams streams, since a forward that needs no scratch may overlap another
+    // on a second stream (allocated by aq_policy_reserve or the first such forward on a stream)
+    size_t few_bytes = 0;  // of one map; 0: the policy never takes that route
+    hipStream_t few_stream[kFewStreams] = {};
+    int8_t* few_maps[kFewStreams] = {};
+    int few_streams = 0;
     int8_t* act_i8[2] = {nullptr, nullptr};
     float* ln_x = nullptr;
     float* y_rows = nullptr;
@@ -368,6 +377,14 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     p->h_net.in_u8 = net->in_type == AQ_IN_U8;
     p->h_net.asym = net->wscheme == AQ_W_TENSOR_ASYM_U8;
     p->h_net.ln_eps = net->ln_eps;
+    {
+        FwdArgs probe(p->h_net);
+        probe.c.batch = 1;
+        int r = 0, few_n = 0;
+        size_t lds = 0;
+        for (int l = 0; l < net->n_layers - 1; ++l) few_n = std::max(few_n, p->L[l].N);
+        if (few_n >= kFewMinWidth && fused_mlp_supported(probe, &r, &lds)) p->few_bytes = (blocked_map_bytes(kFewMaxRows, few_n) + 255) & ~(size_t)255;
+    }
     {   // the quantizer's table: outputs per layer and each layer's first workgroup in the shared grids
         QTab& q = p->h_qtab;
         q.n_layers = net->n_layers;
@@ -446,6 +463,8 @@ extern "C" aq_status aq_policy_destroy(aq_policy* p) {
     (void)hipDeviceSynchronize();
     if (p->slab) (void)hipFree(p->slab);
     if (p->w4_slab) (void)hipFree(p->w4_slab);
+    for (int8_t* m : p->few_maps)
+        if (m) (void)hipFree(m);
     for (int i = 0; i < 2; ++i) {
         if (p->act_i8[i]) (void)hipFree(p->act_i8[i]);
         if (p->act_f32[i]) (void)hipFree(p->act_f32[i]);
@@ -578,10 +597,30 @@ static aq_status ensure_f32_passed(aq_policy* p) {
     return AQ_OK;
 }
 
+static bool few_alloc(aq_policy* p, int i) {
+    if (p->few_maps[i]) return true;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another thread may be capturing)
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+    const bool ok = hipMalloc((void**)&p->few_maps[i], 2 * p->few_bytes) == hipSuccess;
+    if (!ok) p->few_maps[i] = nullptr;
+    return hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess && ok;
+}
+
+// the pair of maps that belongs to `st`; NULL: more streams than pairs, a capture, or no memory
+static int8_t* few_maps_of(aq_policy* p, hipStream_t st) {
+    int i = 0;
+    while (i < p->few_streams && p->few_stream[i] != st) ++i;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (i == kFewStreams || hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone || !few_alloc(p, i)) return nullptr;
+    if (i == p->few_streams) p->few_stream[p->few_streams++] = st;
+    return p->few_maps[i];
+}
+
 extern "C" aq_status aq_policy_reserve(aq_policy* p, int64_t max_batch) {
     if (!p || max_batch < 0) return AQ_EINVAL;
     aq_status s = ensure_i8(p, max_batch, nullptr);
     if (s != AQ_OK) return s;
+    if (p->few_bytes) (void)few_alloc(p, 0);  // (without it the whole-network kernels run)
     if (p->h16_ready) {
         s = ensure_f16(p, max_batch, nullptr);
         if (s != AQ_OK) return s;
@@ -634,7 +673,7 @@ extern "C" aq_status aq_policy_fused_plan(const aq_policy* p, int64_t batch, int
     a.c.batch = batch;
     int r = 0, t = 0;
     size_t lds = 0;
-    if (p->path == 2 || !fused_mlp_supported(a, &r, &lds, &t)) r = t = 0;
+    if (p->path == 2 || !fused_mlp_supported(a, &r, &lds, &t) || (p->path == 0 && p->few_bytes && few_rows_faster(a, false))) r = t = 0;
     *rows = r;
     *tiles = t;
     *kind = r != 0 ? fused_mlp_kernel_kind(a) : 0;
@@ -1013,10 +1052,15 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
 
     int rows;
     size_t lds;
-    const bool can_fuse = p->path != 2 && fused_mlp_supported(a, &rows, &lds);
+    bool can_fuse = p->path != 2 && fused_mlp_supported(a, &rows, &lds);
     if (p->path == 1 && !can_fuse) return AQ_ESHAPE;
-    // an MLP that fits the fused kernel always runs fused: measured faster than one launch per layer at
-    // every batch size (activations stay in LDS, one launch)
+    // An MLP that fits a whole-network kernel runs there, but for few rows on wide layers.  (Not under capture, nor for
+    // the allocation-free entry point: what is captured may be replayed on any stream beside any other, and needs no
+    // scratch with the whole-network kernels.)
+    const bool noise = ex && p->net.head != AQ_HEAD_ARGMAX;
+    int8_t* few = nullptr;
+    if (can_fuse && p->path == 0 && p->few_bytes && !fixed && few_rows_faster(a, noise) && (few = few_maps_of(p, st)) != nullptr)
+        can_fuse = false;
     const int A = p->L.back().N * p->L.back().oh * p->L.back().ow;
     if (can_fuse) {
         // Gaussian noise rides in the kernel where it writes the actions itself (an elementwise head on
@@ -1039,6 +1083,8 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
     FwdScratch sc;
     if (fixed) {
         sc = *fixed;
+    } else if (few) {
+        sc = FwdScratch{{few, few + p->few_bytes}, true, nullptr, nullptr};
     } else {
         s = ensure_i8(p, batch, st);
         if (s != AQ_OK) return s;

@@ -97,6 +97,10 @@ bool skinny_layer_supported(const LayerDev& L, int64_t rows);
 // 16-feature and 16-row tiles per workgroup that such a layer takes (argmax: all features in one workgroup)
 void skinny_layer_tile(const LayerDev& L, int64_t rows, bool argmax, int* ft, int* rt);
 bool skinny_layer_does_argmax(const FwdArgs& a, int l);
+// whether an MLP that fits the whole-network kernels is faster layer by layer at this batch (at most kFewMaxRows rows, a
+// hidden layer of at least kFewMinWidth); noise: exploration then takes a launch of its own
+constexpr int kFewMaxRows = 512, kFewMinWidth = 257;
+bool few_rows_faster(const FwdArgs& a, bool noise);
 // whether launch_layer_int8 hands layer l at this batch to the K-split kernel
 // the leading convolution layers in one launch (0 layers = shapes it does not take); writes the last
 // convolution's signed codes to `out` ([batch * oh * ow][N])

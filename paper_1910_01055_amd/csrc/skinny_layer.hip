@@ -60,6 +60,32 @@ void skinny_layer_tile(const LayerDev& L, int64_t rows, bool argmax, int* ft, in
     }
 }
 
+// A whole-network kernel passes every weight through the vector memory path of one CU, however few the rows; the layers'
+// own launches spread them over the chip.  Measured, us (whole network / layers), one to 256 rows: 67-512x2-21 10.6 / 9.4,
+// 67-512x3-21 14.5 / 12.2, 67-1024x2-21 19.8 / 9.3 (256 rows 10.6), 256-1024x3-64 31.3 / 12.0 (256 rows 14.7),
+// 111-400-300-8 10.0 / 9.6; 512 rows: 67-1024x2-21 20.3 / 15.9, 111-800-600-8 15.4 / 16.8; per-tensor weights 67-512x2-21
+// 12.2 / 9.7, 67-1024x2-21 24.1 / 9.5.
+bool few_rows_faster(const FwdArgs& a, bool noise) {
+    const int nl = a.net.n_layers;
+    if (a.c.batch > kFewMaxRows || nl < 2) return false;
+    double weights = 0.0;  // millions
+    int widest = 0;
+    for (int l = 0; l < nl; ++l) {
+        const LayerDev& L = a.net.L[l];
+        weights += 1e-6 * L.K * L.N;
+        if (l == nl - 1) break;
+        if (L.act == AQ_ACT_LN_TANH) return false;  // (a launch and fp32 rows of its own)
+        widest = widest > L.N ? widest : L.N;
+    }
+    if (widest < kFewMinWidth) return false;
+    if (a.net.head == AQ_HEAD_ARGMAX && !skinny_layer_does_argmax(a, nl - 1)) return false;
+    for (int l = 0; l < nl; ++l)
+        if (!layer_uses_skinny(a, l)) return false;
+    const double whole = a.net.asym ? 8.3 + 13.0 * weights : 7.5 + 10.0 * weights;
+    const double layers = nl * (a.c.batch > 256 ? 5.0 : a.c.batch > 128 ? 3.5 : 3.1) + (noise ? 3.1 : 0.0);
+    return layers < whole;
+}
+
 aq_status launch_layer_skinny(const FwdArgs& a, int l, const LayerIO& io, hipStream_t st) {
     const LayerDev& L = a.net.L[l];
     const int64_t rows = a.c.batch;

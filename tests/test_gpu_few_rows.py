@@ -41,3 +41,51 @@ def test_few_row_layers_against_the_oracle(aq, name, batches):
         plain, _ = U.gpu_forward(P, net, obs, taps=False)
         assert np.array_equal(plain, actions)
         P.close()
+
+
+def test_wide_policies_at_few_rows_take_the_layers_launches(aq):
+    """Which plan an MLP that fits the whole-network kernels takes on either side of the rule, and the same integers from both
+    plans, from a second stream while the first is busy, and from more streams than there are pairs of maps."""
+    import torch
+    net = synth.small_net([fc(67, 1000, "relu"), fc(1000, 720, "none"), fc(720, 21, "none")], head="tanh")
+    params = synth.make_params(net, nonzero_bias=True)
+    obs = synth.make_obs(net, 513)
+    _, ranges = U.make_oracle(net, params, obs[:256])
+    P, _ = U.gpu_quantize(aq, net, params, ranges)
+    for batch, layers in ((1, True), (16, True), (250, True), (513, False)):
+        assert (P.policy_fused_plan(batch)[0] == 0) == layers, batch
+        P.policy_set_path(1)
+        whole, _ = U.gpu_forward(P, net, obs[:batch], taps=False)
+        P.policy_set_path(0)
+        assert np.array_equal(U.gpu_forward(P, net, obs[:batch], taps=False)[0], whole)
+    P.policy_set_path(1)
+    want = U.gpu_forward(P, net, obs[:250], taps=False)[0]
+    P.policy_set_path(0)
+    d_obs = aq.to_dev(obs[:250])
+    outs, streams = [], [torch.cuda.Stream() for _ in range(6)]
+    torch.cuda.synchronize()
+    for rep in range(8):
+        for s in streams:
+            with torch.cuda.stream(s):
+                y = torch.zeros((250, 21), device="cuda:0")
+                P.policy_forward_int8(d_obs, y)
+                outs.append(y)
+    torch.cuda.synchronize()
+    assert all(np.array_equal(y.cpu().numpy(), want) for y in outs)
+    P.close()
+    # per-tensor weights, an argmax head within one workgroup, exploration behind the layers
+    net = synth.small_net([fc(40, 1024, "relu"), fc(1024, 1024, "relu"), fc(1024, 30, "none")], head="tanh", wscheme="tensor_asym_u8")
+    params = synth.make_params(net, nonzero_bias=True)
+    obs = synth.make_obs(net, 200)
+    _, ranges = U.make_oracle(net, params, obs)
+    P, _ = U.gpu_quantize(aq, net, params, ranges)
+    assert P.policy_fused_plan(200)[0] == 0
+    d_obs, sigma = aq.to_dev(obs), torch.full((200,), 0.1, device="cuda:0")
+    got = []
+    for path in (0, 1):
+        P.policy_set_path(path)
+        y = torch.zeros((200, 30), device="cuda:0")
+        P.policy_step_int8(d_obs, y, 5, 3, sigma=sigma)
+        got.append(y.cpu().numpy())
+    assert np.array_equal(got[0], got[1])
+    P.close()
