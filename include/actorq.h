@@ -163,7 +163,8 @@ aq_status aq_policy_fused_plan(const aq_policy* p, int64_t batch, int32_t* rows,
 /* The same for the full-precision and the half-precision actor.  *rows = batch rows per workgroup of the kernel that
  * runs the whole policy in one launch (16 or 32 in fp32; 16, 32 or 64 in half precision), 0 where a forward of
  * `batch` >= 1 rows takes a launch per layer instead; tiles[2 * l] and tiles[2 * l + 1], l < n_layers: features and
- * rows of the tile on which layer l then runs in fp32 (0 and 0 with one launch).  The half-precision plan is known from the
+ * rows of the tile on which layer l then runs in fp32 (0 and 0 with one launch, also where that is the convolutions';
+ * launch plan 3 gives every layer its own in fp32 too).  The half-precision plan is known from the
  * first aq_convert_params_fp16 on (AQ_ENOTQUANT before).  No GPU work. */
 aq_status aq_policy_fp32_plan(const aq_policy* p, int64_t batch, int32_t* rows, int32_t* tiles);
 aq_status aq_policy_fp16_plan(const aq_policy* p, int64_t batch, int32_t* rows);

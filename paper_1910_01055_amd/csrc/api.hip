@@ -127,6 +127,7 @@ struct aq_policy {
     F32Store f32_kept;    // made by the first aq_policy_set_params_fp32
     F32Store f32_passed;  // made by the first aq_policy_forward_fp32_params (its table with the policy)
     bool f32_ready = false;
+    int f32_stack = 0;    // leading convolutions that the fp32 actor runs in one launch
     // policies of at most 4 bits, per-channel symmetric, under launch plan 4: the fully connected layers' weights
     // once more as nibbles, for the few-row kernel (one allocation when the plan is first chosen; rewritten by
     // the first forward pass after every quantize / import)
@@ -202,7 +203,7 @@ static size_t f32_store_layout(const aq_policy* p, bool keep, F32KeepTab& tab) {
         tab.blk0[tab.n] = blk;
         tab.e[tab.n++] = F32KeepTab::Entry{(int64_t)bytes, n, kind, l, p->L[l].N, p->L[l].K};
         bytes += ((size_t)n * 4 + 255) / 256 * 256;
-        blk += (int)((n + kKeepPiece - 1) / kKeepPiece);
+        blk += kind == 5 ? (int)((n / 769 + kKeepSplit - 1) / kKeepSplit) : (int)((n + kKeepPiece - 1) / kKeepPiece);
     };
     for (int l = 0; l < p->net.n_layers; ++l) {
         const LayerBuf& b = p->L[l];
@@ -210,6 +211,7 @@ static size_t f32_store_layout(const aq_policy* p, bool keep, F32KeepTab& tab) {
             add((int64_t)b.N * b.K, 0, l);
             for (int i = 1; i < 4; ++i) add(b.N, i, l);
         }
+        if (l < p->f32_stack) add((int64_t)((b.N + 15) / 16) * ((b.K + 31) / 32) * 769, 5, l);
         add((int64_t)((b.N + 15) / 16) * ((b.K + 15) / 16) * 256, 4, l);
     }
     tab.blocks = blk;
@@ -221,7 +223,7 @@ static F32Ptrs f32_store_ptrs(const F32KeepTab& tab, char* base) {
     F32Ptrs ptrs{};
     for (int i = 0; i < tab.n; ++i) {
         const F32KeepTab::Entry& e = tab.e[i];
-        (e.kind == 0 ? ptrs.w : e.kind == 1 ? ptrs.b : e.kind == 2 ? ptrs.gamma : e.kind == 3 ? ptrs.beta : ptrs.wpk)[e.layer] =
+        (e.kind == 0 ? ptrs.w : e.kind == 1 ? ptrs.b : e.kind == 2 ? ptrs.gamma : e.kind == 3 ? ptrs.beta : e.kind == 4 ? ptrs.wpk : ptrs.wsp)[e.layer] =
             (float*)(base + e.off);
     }
     return ptrs;
@@ -330,8 +332,6 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     size_t off_net = take(sizeof(NetDev));
     size_t off_qtab = take(sizeof(QTab));
     size_t off_ftab = take(sizeof(F32KeepTab));
-    F32KeepTab ftab{};  // of parameters passed with a call
-    (void)f32_store_layout(p, false, ftab);
     if (hipMalloc(&p->slab, bytes) != hipSuccess) {
         delete p;
         return AQ_ENOMEM;
@@ -377,6 +377,9 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     p->h_net.in_u8 = net->in_type == AQ_IN_U8;
     p->h_net.asym = net->wscheme == AQ_W_TENSOR_ASYM_U8;
     p->h_net.ln_eps = net->ln_eps;
+    p->f32_stack = fp32_conv_stack_layers(p->h_net);
+    F32KeepTab ftab{};  // of parameters passed with a call
+    (void)f32_store_layout(p, false, ftab);
     {
         FwdArgs probe(p->h_net);
         probe.c.batch = 1;
@@ -696,6 +699,16 @@ extern "C" aq_status aq_policy_subbyte_layers(const aq_policy* p, int64_t batch,
     return AQ_OK;
 }
 
+// A frame policy's convolutions in one launch, an image per CU, where that fills the chip; a few images, or the last ones of
+// a second round, are faster in the layers' own launches, which spread an image over several CUs.  fp32 forward, us (one
+// launch / the layers'): 84 x 84 x 4 through 32, 64, 64 at 32 images 41.6 / 36.0, 48 43.5 / 41.9, 64 43.5 / 46.9, 256
+// 52.0 / 92.3, 300 87 / 100, 600 124 / 168; 61 x 61 x 3 through 16, 32, 32 at 32 images 26.0 / 25.2, 48 25.8 / 27.2, 256
+// 27.3 / 37.3, 300 42.1 / 39.0, 600 60.5 / 61.6.
+static int f32_stack_layers(const aq_policy* p, int64_t batch) {
+    const int64_t rounds = (batch + 255) / 256;
+    return p->conv_stack && batch * 100 >= rounds * 256 * (rounds == 1 ? 19 : 60) ? p->f32_stack : 0;
+}
+
 extern "C" aq_status aq_policy_fp32_plan(const aq_policy* p, int64_t batch, int32_t* rows, int32_t* tiles) {
     if (!p || !rows || !tiles || batch < 1) return AQ_EINVAL;
     int rt = 1;
@@ -706,7 +719,7 @@ extern "C" aq_status aq_policy_fp32_plan(const aq_policy* p, int64_t batch, int3
         L.K = b.K;
         L.N = b.N;
         tiles[2 * l] = tiles[2 * l + 1] = 0;
-        if (!*rows) fp32_layer_tile(L, batch * b.oh * b.ow, &tiles[2 * l], &tiles[2 * l + 1]);
+        if (!*rows && l >= f32_stack_layers(p, batch)) fp32_layer_tile(L, batch * b.oh * b.ow, &tiles[2 * l], &tiles[2 * l + 1]);
     }
     return AQ_OK;
 }
@@ -1197,12 +1210,16 @@ static aq_status forward_fp32_impl(aq_policy* p, const F32Ptrs& ptrs, const F32P
     } else {
         s = ensure_f32(p, batch, st);
         if (s != AQ_OK) return s;
-        if (slots) {
+        const int nc = f32_stack_layers(p, batch);
+        if (nc) {
+            s = launch_fp32_conv_stack(p->h_net, ptrs, d_obs, batch, p->act_f32[(nc - 1) & 1], slots, st);
+            if (s != AQ_OK) return s;
+        } else if (slots) {
             const LayerBuf& b0 = p->L[0];
             s = launch_input_range(d_obs, in_u8, batch * (int64_t)b0.d.in_h * b0.d.in_w * b0.d.in_c, slots, st);
             if (s != AQ_OK) return s;
         }
-        for (int l = 0; l < nl; ++l) {
+        for (int l = nc; l < nl; ++l) {
             const LayerBuf& b = p->L[l];
             const bool last = l == nl - 1;
             if (last && !d_actions) break;
@@ -1275,7 +1292,10 @@ extern "C" aq_status aq_policy_forward_fp32_params(aq_policy* p, const float* co
     if (s != AQ_OK) return s;
     s = launch_keep_params(ptrs, p->f32_passed.d_tab, p->f32_passed.slab, p->f32_passed.blocks, st);
     if (s != AQ_OK) return s;
-    for (int l = 0; l < p->net.n_layers; ++l) ptrs.wpk[l] = p->f32_passed.ptrs.wpk[l];
+    for (int l = 0; l < p->net.n_layers; ++l) {
+        ptrs.wpk[l] = p->f32_passed.ptrs.wpk[l];
+        ptrs.wsp[l] = p->f32_passed.ptrs.wsp[l];
+    }
     return forward_fp32_impl(p, ptrs, nullptr, d_obs, batch, d_actions, d_ranges_out, nullptr, 0, st);
 }
 

@@ -14,17 +14,14 @@
 //
 // k_fp32_layer: one layer (fully connected or implicit-GEMM convolution) from and to global memory, inputs staged in
 //   LDS.  k_fp32_mlp: a whole small MLP in one launch, activations in LDS.
-#include "int8_device.hpp"
+#include "fp32_split.hpp"
 
 namespace aq {
 
 namespace {
 
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef float v4f_u __attribute__((ext_vector_type(4), aligned(4)));  // rows of K floats start at any 4-byte address
 typedef const float AQ_GLOBAL* gf_ptr;
 typedef const v4f AQ_GLOBAL* gv4f_ptr;
-typedef uint32_t u32_u __attribute__((aligned(1)));
 
 constexpr int FW_ = 8;            // waves per workgroup
 constexpr int FT_ = FW_ * 64;
@@ -41,26 +38,6 @@ __device__ __forceinline__ void mma_stage(const v4f (&w)[FT], const v4f (&x)[RT]
         for (int f = 0; f < FT; ++f)
 #pragma unroll
             for (int r = 0; r < RT; ++r) acc[f][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[f][i], x[r][i], acc[f][r], 0, 0, 0);
-}
-
-// ---- min / max of a tensor through order-preserving unsigned keys
-__device__ __forceinline__ uint32_t f2key(float f) {
-    uint32_t b = __float_as_uint(f);
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-__device__ __forceinline__ float key2f(uint32_t k) {
-    return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
-}
-// A wave's (lo, hi) joins slot `who` of a tensor's kRangeSlots.  (With one pair of words per tensor every wave of the
-// chip queued at the same address: 90 us per tensor of a frame policy's calibration.)  All lanes of the wave call it.
-__device__ __forceinline__ void range_note(RangeSlot* __restrict__ slots, uint32_t who, float lo, float hi) {
-    lo = wave_min(lo);
-    hi = wave_max(hi);
-    if ((threadIdx.x & 63) == 0 && lo <= hi) {
-        RangeSlot* s = slots + who % kRangeSlots;
-        atomicMax(&s->not_lo, ~f2key(lo));
-        atomicMax(&s->hi, f2key(hi));
-    }
 }
 
 __device__ __forceinline__ float head_value(float y, int head) { return head == AQ_HEAD_TANH ? tanhf(y) : y; }
@@ -596,7 +573,7 @@ __global__ __launch_bounds__(64 * AQ_MAX_LAYERS) void k_ranges_out(RangeSlot* __
 // the operand order of the kernels above (all that is written of parameters passed with a call).
 __global__ __launch_bounds__(256) void k_keep_params(const F32Ptrs src, const F32KeepTab* __restrict__ tab, char* __restrict__ to) {
     const int blk = (int)blockIdx.x;
-    // the last array that starts at or before this workgroup (5 * AQ_MAX_LAYERS <= 64: one lane each)
+    // the last array that starts at or before this workgroup (5 * AQ_MAX_LAYERS + 4 <= 64: one lane each)
     const int lane = threadIdx.x & 63;
     const uint64_t before = __ballot(lane < tab->n && blk >= tab->blk0[lane < tab->n ? lane : 0]);
     const int a = __builtin_amdgcn_readfirstlane(63 - __builtin_clzll(before));
@@ -635,6 +612,51 @@ __global__ __launch_bounds__(256) void k_keep_params(const F32Ptrs src, const F3
 #pragma unroll
             for (int j = 0; j < 4; ++j) w[j] = __shfl(v[i][j], i16 * 4 + g, 64);
             if (q < nblk) *(v4f AQ_GLOBAL*)(d + (int64_t)q * 256 + lane * 4) = w;
+        }
+        return;
+    }
+    if (kind == 5) {  // kKeepSplit blocks of 16 features x 32 k, each value as three bf16 parts; then a word per block
+        const int N = tab->e[a].N, K = tab->e[a].K, nst = (K + 31) >> 5, nblk = (N + 15) / 16 * nst;
+        const int i16 = lane & 15, g = lane >> 4;
+        const bool al = (K & 3) == 0 && ((uintptr_t)s & 15) == 0;
+        v4f v[kKeepSplit / 4][2];
+#pragma unroll
+        for (int i = 0; i < kKeepSplit / 4; ++i) {
+            const int q = (blk - tab->blk0[a]) * kKeepSplit + i * 4 + (threadIdx.x >> 6);
+            const int t = q / nst, n_ = t * 16 + (lane >> 2), k = (q - t * nst) * 32 + (lane & 3) * 8;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                v[i][h] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+                if (q < nblk && n_ < N) {
+                    const float* p = s + (int64_t)n_ * K + k + 4 * h;
+                    if (al && k + 4 * h < K) {
+                        v[i][h] = *(const v4f AQ_GLOBAL*)p;
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (k + 4 * h + j < K) v[i][h][j] = p[j];
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kKeepSplit / 4; ++i) {
+            const int q = (blk - tab->blk0[a]) * kKeepSplit + i * 4 + (threadIdx.x >> 6);
+            bool odd = false;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) odd |= split_special(v[i][j >> 2][j & 3]);
+            bf8 x[3];
+            split8(v[i][0], v[i][1], x);
+            const uint64_t any = __ballot(odd);
+#pragma unroll
+            for (int part = 0; part < 3; ++part) {
+                const v4i from = __builtin_bit_cast(v4i, x[part]);
+                v4i w;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) w[j] = __shfl(from[j], i16 * 4 + g, 64);
+                if (q < nblk) *(v4i AQ_GLOBAL*)((char AQ_GLOBAL*)d + (int64_t)q * 3072 + part * 1024 + lane * 16) = w;
+            }
+            if (q < nblk && lane == 0) ((uint32_t AQ_GLOBAL*)d)[(int64_t)nblk * 768 + q] = any != 0;
         }
         return;
     }

@@ -132,6 +132,7 @@ struct RangeSlot {
 struct F32Ptrs {
     const float* w[AQ_MAX_LAYERS];    // row-major
     const float* wpk[AQ_MAX_LAYERS];  // in operand order
+    const float* wsp[AQ_MAX_LAYERS];  // split into bf16 parts (a convolution stack's layers)
     const float* b[AQ_MAX_LAYERS];
     const float* gamma[AQ_MAX_LAYERS];
     const float* beta[AQ_MAX_LAYERS];
@@ -160,14 +161,16 @@ struct F32Call {
 // where a set of fp32 parameters goes: each array starts at workgroup blk0 of the copy's grid, one workgroup per
 // kKeepPiece values
 constexpr int kKeepPiece = 4096;
+constexpr int kKeepSplit = 8;  // blocks of split weights (kind 5) per workgroup
 struct F32KeepTab {
     struct Entry {
         int64_t off;  // bytes from where the set begins
         int64_t count;
-        int kind, layer, N, K;  // kind: 0 weights, 1 bias, 2 gain, 3 offset, 4 packed weights
+        int kind, layer, N, K;  // kind: 0 weights, 1 bias, 2 gain, 3 offset, 4 packed weights,
+                                  // 5 weights split into bf16 parts (a convolution stack's)
     };
-    Entry e[5 * AQ_MAX_LAYERS];
-    int blk0[5 * AQ_MAX_LAYERS];
+    Entry e[5 * AQ_MAX_LAYERS + 4];  // (split weights: at most four layers)
+    int blk0[5 * AQ_MAX_LAYERS + 4];
     int n, blocks;
 };
 aq_status launch_fp32_layer(const Fp32Layer& L, const void* in, int in_u8, float* out, int64_t rows, RangeSlot* slots,
@@ -178,6 +181,12 @@ void fp32_layer_tile(const Fp32Layer& L, int64_t rows, int* features, int* tile_
 bool fp32_mlp_fits(const NetDev& n, int64_t batch, int* rt);
 aq_status launch_fp32_mlp(const NetDev& n, const NetDev* d_net, const F32Ptrs& ptrs, const F32Ptrs* d_ptrs, const void* obs,
                           int64_t batch, void* actions, RangeSlot* slots, int rt, hipStream_t st);
+// the leading convolutions of a frame policy in one launch (fp32_conv_stack.hip): how many layers (0: none of these shapes;
+// their weights are also kept split), and the launch, which writes the last one's map to `out`; with slots also the
+// ranges of the frames and of every map
+int fp32_conv_stack_layers(const NetDev& n);
+aq_status launch_fp32_conv_stack(const NetDev& n, const F32Ptrs& ptrs, const void* frames, int64_t batch, float* out, RangeSlot* slots,
+                                 hipStream_t st);
 aq_status launch_fp32_ln_tanh(float* x, int64_t rows, int N, const float* gamma, const float* beta, float eps,
                               RangeSlot* slots, hipStream_t st);
 aq_status launch_fp32_argmax(const float* y, int64_t rows, int N, int32_t* actions, hipStream_t st);
