@@ -69,8 +69,9 @@ __global__ __launch_bounds__(FT_) void k_fp32_layer(const Fp32Layer L, const voi
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     const int wk = wave % WK, wn = (wave / WK) % WN, wm = wave / (WK * WN);
-    const int64_t row0 = (int64_t)blockIdx.x * BM;
-    const int t0 = (blockIdx.y * WN + wn) * FT;  // this wave's first feature tile
+    const uint32_t bx = L.features_first ? blockIdx.y : blockIdx.x, by = L.features_first ? blockIdx.x : blockIdx.y;
+    const int64_t row0 = (int64_t)bx * BM;
+    const int t0 = (by * WN + wn) * FT;  // this wave's first feature tile
     const int K = L.K, N = L.N, nst = (K + 15) >> 4, tiles = (N + 15) >> 4;
 
     // where the rows this thread stages begin; rows past the end re-read the last one and are not stored
@@ -233,6 +234,130 @@ __global__ __launch_bounds__(FT_) void k_fp32_layer(const Fp32Layer L, const voi
             }
     }
     if (slots) range_note(slots, (uint32_t)((blockIdx.y * gridDim.x + blockIdx.x) * FW_ + wave), lo, hi);
+}
+
+// ------------------------------------------------------------------------------------- a fully connected layer at few rows
+// One workgroup owns FT tiles of 16 features x RT tiles of 16 rows and splits K over its eight waves: every byte of weights and
+// inputs passes the CU's vector memory path once, straight into operand registers, PF stages of 16 k in flight, no barrier
+// before the partial sums meet in LDS.  Inputs are requested along the rows (four lanes to 64 bytes; lanes down the rows
+// take 75 clocks a request instead of 16) and change lanes on the way.  Bound by the fp32 matrix cores, 32 clocks an MFMA,
+// and the vector memory path, 47 bytes a clock beside them at 16 x 32.  With a layer of 4 behind it, us on the tiles of the
+// kernel above (inputs through LDS, a barrier every 128 to 512 k) and so: 3136-512 at 128 rows 16.4, 13.0, at 256 19.9, 18.2;
+// 700-523 at 16 rows 9.9, 8.1, at 512 18.5, 16.5; 2048-2048 at 128 22.5, 20.8.
+template <int FT, int RT, bool U8>
+__global__ __launch_bounds__(FT_) void k_fp32_rows(const Fp32Layer L, const void* __restrict__ in, float* __restrict__ out,
+                                                   const int64_t rows, RangeSlot* __restrict__ slots) {
+    constexpr int PF = 4, NQ = FT * RT;
+    __shared__ v4f part[FW_][NQ][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i16 = lane & 15, g = lane >> 4;
+    const uint32_t bx = L.features_first ? blockIdx.y : blockIdx.x, by = L.features_first ? blockIdx.x : blockIdx.y;
+    const int64_t row0 = (int64_t)bx * (16 * RT);
+    const int K = L.K, N = L.N, nst = (K + 15) >> 4, tiles = (N + 15) >> 4, t0 = by * FT;
+    const int per = (nst + FW_ - 1) / FW_, s0 = wave * per, s1 = s0 + per < nst ? s0 + per : nst;
+    gf_ptr wbase[FT];
+#pragma unroll
+    for (int f = 0; f < FT; ++f) wbase[f] = (gf_ptr)L.wpk + (int64_t)(t0 + f < tiles ? t0 + f : tiles - 1) * nst * 256 + lane * 4;
+    int64_t xoff[RT];  // rows past the end re-read the last one and are not stored
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const int64_t row = row0 + r * 16 + (lane >> 2);
+        xoff[r] = (row < rows ? row : rows - 1) * K + 4 * (lane & 3);
+    }
+    const int swap = (i16 * 4 + g) * 4;
+    v4f acc[FT][RT];
+#pragma unroll
+    for (int f = 0; f < FT; ++f)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) acc[f][r] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    v4f w[PF][FT], x[PF][RT];
+    auto fetch = [&](auto p_c, int s) __attribute__((always_inline)) {
+        constexpr int p = decltype(p_c)::value;
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            const int64_t o = xoff[r] + 16 * s;
+            if (16 * s + 16 <= K) {
+                if (U8) {
+                    const uint32_t q = *(const u32_u*)((const uint8_t*)in + o);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[p][r][i] = (float)((q >> (8 * i)) & 255u);
+                } else {
+                    x[p][r] = *(const v4f_u AQ_GLOBAL*)((const float*)in + o);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool ok = 16 * s + 4 * (lane & 3) + i < K;
+                    x[p][r][i] = 0.0f;
+                    if (ok) x[p][r][i] = U8 ? (float)((const uint8_t*)in)[o + i] : ((const float*)in)[o + i];
+                }
+            }
+        }
+#pragma unroll
+        for (int f = 0; f < FT; ++f) w[p][f] = *(gv4f_ptr)(wbase[f] + (s << 8));
+    };
+    auto stage = [&](auto p_c) __attribute__((always_inline)) {
+        constexpr int p = decltype(p_c)::value;
+        v4f y[RT];
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[r][i] = __int_as_float(__builtin_amdgcn_ds_bpermute(swap, __float_as_int(x[p][r][i])));
+        mma_stage<FT, RT, FT>(w[p], y, acc);
+    };
+    if (s0 < s1) {
+        static_for<0, PF>([&](auto p_c) __attribute__((always_inline)) {
+            constexpr int p = decltype(p_c)::value;
+            fetch(p_c, s0 + p < s1 ? s0 + p : s1 - 1);
+        });
+        int s = s0;
+        for (; s + PF <= s1; s += PF) {
+            static_for<0, PF>([&](auto p_c) __attribute__((always_inline)) {
+                constexpr int p = decltype(p_c)::value;
+                stage(p_c);
+                fetch(p_c, s + p + PF < s1 ? s + p + PF : s1 - 1);
+                asm volatile("" ::: "memory");
+            });
+        }
+        static_for<0, PF - 1>([&](auto p_c) __attribute__((always_inline)) {
+            if (s + decltype(p_c)::value < s1) stage(p_c);
+        });
+    }
+#pragma unroll
+    for (int f = 0; f < FT; ++f)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) part[wave][f * RT + r][lane] = acc[f][r];
+    lds_barrier();
+    // quad q of the tile is summed and finished by wave q
+    float lo = INFINITY, hi = -INFINITY;
+    if (wave < NQ) {
+        const int f = wave / RT, r = wave - f * RT, n = (t0 + f) * 16 + 4 * g;
+        const int64_t row = row0 + r * 16 + i16;
+        v4f v = part[0][wave][lane];
+#pragma unroll
+        for (int k = 1; k < FW_; ++k) v += part[k][wave][lane];
+        if (row < rows && n < N) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (n + i < N) {
+                    if (L.b) v[i] += L.b[n + i];
+                    if (L.relu) v[i] = v[i] > 0.0f ? v[i] : 0.0f;
+                    lo = fminf(lo, v[i]);
+                    hi = fmaxf(hi, v[i]);
+                    if (L.head >= 0) v[i] = head_value(v[i], L.head);
+                }
+            }
+            float* o = out + row * N + n;
+            if ((N & 3) == 0) {
+                *(v4f_u*)o = v;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (n + i < N) o[i] = v[i];
+            }
+        }
+        if (slots) range_note(slots, (uint32_t)((blockIdx.y * gridDim.x + blockIdx.x) * NQ + wave), lo, hi);
+    }
 }
 
 // ---------------------------------------------------------------------------------------- a whole small MLP
@@ -711,11 +836,17 @@ int pick_tile(const Fp32Layer& L, int64_t rows) {
     }
     return best;
 }
+// Workgroups that follow each other go to the eight XCDs in turn, so the faster grid dimension decides what an XCD's L2 must
+// hold: all of the other dimension's operand and an eighth of its own.  The larger operand takes the faster one.
+dim3 layer_grid(Fp32Layer& L, int64_t nx, int64_t ny, int64_t rows) {
+    const double w = 4.0 * L.K * L.N, x = 4.0 * (double)rows * L.K;
+    L.features_first = w > x && nx <= 65535;
+    return L.features_first ? dim3((unsigned)ny, (unsigned)nx) : dim3((unsigned)nx, (unsigned)ny);
+}
 template <int I, bool CONV, bool U8>
-aq_status launch_tile(const Fp32Layer& L, const void* in, float* out, int64_t rows, RangeSlot* slots, hipStream_t st) {
+aq_status launch_tile(Fp32Layer L, const void* in, float* out, int64_t rows, RangeSlot* slots, hipStream_t st) {
     constexpr TileShape t = kTiles[I];
-    const dim3 grid((unsigned)((rows + 16 * t.rt * t.wm - 1) / (16 * t.rt * t.wm)),
-                    (unsigned)((L.N + 16 * t.ft * t.wn - 1) / (16 * t.ft * t.wn)));
+    const dim3 grid = layer_grid(L, (rows + 16 * t.rt * t.wm - 1) / (16 * t.rt * t.wm), (L.N + 16 * t.ft * t.wn - 1) / (16 * t.ft * t.wn), rows);
     auto* const kernel = k_fp32_layer<t.ft, t.rt, t.wn, t.wm, t.wk, t.ks, CONV, U8>;
     constexpr size_t lds = fp32_layer_lds(t.ft, t.rt, t.wm, t.wk, t.ks);
     static std::atomic<bool> attr_set{false};
@@ -728,6 +859,17 @@ aq_status launch_tile(const Fp32Layer& L, const void* in, float* out, int64_t ro
 }
 template <int I>
 aq_status launch_tile_kind(const Fp32Layer& L, bool fc, int in_u8, const void* in, float* out, int64_t rows, RangeSlot* slots, hipStream_t st) {
+    if constexpr (kTiles[I].wk == FW_) {
+        constexpr TileShape t = kTiles[I];
+        if (fc) {
+            Fp32Layer q = L;
+            const dim3 grid = layer_grid(q, (rows + 16 * t.rt - 1) / (16 * t.rt), (L.N + 16 * t.ft - 1) / (16 * t.ft), rows);
+            if (in_u8) hipLaunchKernelGGL((k_fp32_rows<t.ft, t.rt, true>), grid, dim3(FT_), 0, st, q, in, out, rows, slots);
+            else hipLaunchKernelGGL((k_fp32_rows<t.ft, t.rt, false>), grid, dim3(FT_), 0, st, q, in, out, rows, slots);
+            return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
+        }
+        return in_u8 ? launch_tile<I, true, true>(L, in, out, rows, slots, st) : launch_tile<I, true, false>(L, in, out, rows, slots, st);
+    }
     if (fc) return in_u8 ? launch_tile<I, false, true>(L, in, out, rows, slots, st) : launch_tile<I, false, false>(L, in, out, rows, slots, st);
     return in_u8 ? launch_tile<I, true, true>(L, in, out, rows, slots, st) : launch_tile<I, true, false>(L, in, out, rows, slots, st);
 }

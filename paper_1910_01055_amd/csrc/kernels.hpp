@@ -122,6 +122,7 @@ struct Fp32Layer {
     int relu;
     int head;  // last layer with an elementwise head applied to the outputs (aq_head), else -1
     int in_h, in_w, in_c, kh, kw, stride, oh, ow;
+    int features_first;  // the grid's faster dimension is the features' (set at the launch)
 };
 // (min, max) of an activation tensor as it is collected: kRangeSlots pairs per tensor, each an order-preserving key of
 // the float (the minimum's complemented, so that both are maxima and zero is neutral)
