@@ -549,6 +549,8 @@ static aq_status ensure_f16(aq_policy* p, int64_t batch, hipStream_t st) {
     }
     p->cap_f16 = 0;
     size_t n = ((size_t)batch * (size_t)p->max_out_elems + 64) * 2;
+    for (const LayerBuf& b : p->L)  // (fully connected layers' maps may lie in operand order)
+        if (b.fc) n = std::max(n, 2 * blocked_map_bytes(batch, b.N));
     for (int i = 0; i < 2; ++i)
         if (hipMalloc(&p->act_f16[i], n) != hipSuccess) return AQ_ENOMEM;
     p->cap_f16 = batch;
@@ -1521,6 +1523,7 @@ extern "C" aq_status aq_policy_forward_fp16(aq_policy* p, const void* d_obs, int
             AQ_HIP_CHECK(hipMemcpyAsync(taps_out[nc - 1], out, (size_t)batch * b.oh * b.ow * b.N * 2,
                                         hipMemcpyDeviceToDevice, st));
     }
+    int blocked = 0;
     for (int l = nc; l < nl; ++l) {
         const LayerBuf& b = p->L[l];
         const bool last = l == nl - 1;
@@ -1536,8 +1539,13 @@ extern "C" aq_status aq_policy_forward_fp16(aq_policy* p, const void* d_obs, int
         }
         // an argmax policy whose logits fit one tile of the few-row kernel: the action index leaves the same launch
         const bool fused_argmax = last && p->net.head == AQ_HEAD_ARGMAX && L.NT == 1 &&
-                                  fp16_layer_is_skinny(L, in, l == 0 ? in_mode0 : 0, rows_l);
+                                  fp16_layer_is_skinny(L, l == 0 ? in_mode0 : 0, rows_l);
         if (fused_argmax) L.head_argmax = (int32_t*)d_actions;
+        // between two layers of the few-row kernel the activations lie in its operand order
+        L.in_blocked = blocked;
+        blocked = !last && b.d.act != AQ_ACT_LN_TANH && !(taps_out && taps_out[l]) && Ls[l + 1].fc &&
+                  fp16_layer_is_skinny(L, l == 0 ? in_mode0 : 0, rows_l) && fp16_layer_is_skinny(Ls[l + 1], 0, rows_l);
+        L.out_blocked = blocked;
         s = launch_layer_fp16(L, in, l == 0 ? in_mode0 : 0, out, rows_l, st);
         if (s != AQ_OK) return s;
         if (!last && b.d.act == AQ_ACT_LN_TANH) {

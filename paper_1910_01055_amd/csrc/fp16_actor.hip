@@ -10,7 +10,7 @@
 //   k_fp16_ln_tanh        LayerNorm, rounded, then tanh, rounded, in place
 //   k_fp16_head           tanh / identity / argmax on the last layer's rows
 #include "fp16_device.hpp"
-#include "kernels.hpp"
+#include "int8_device.hpp"
 
 namespace aq {
 
@@ -364,144 +364,171 @@ __global__ __launch_bounds__(256, 2) void k_layer_fp16(const Fp16Layer L, const 
     }
 }
 
-// Fully connected hidden layer at few rows (the paper's actors run one observation at a time, Sec. 3.1,
-// on layers of 2048 units, Sec. 4.1): the time goes into streaming the binary16 weights once, so one
-// workgroup of 8 waves owns a single 32-row x 32-feature output tile and its waves split K.  Both MFMA
-// operands come straight from global memory, 16 bytes per lane and k-step (the activation rows are a
-// few KB and stay in cache), SKH_PF k-steps of each in flight; partial tiles meet in LDS, then the 512
-// threads reduce eight partial sums for two outputs each, add the bias, round once and store.
+// Fully connected layer at few rows (the paper's actors run one observation at a time, Sec. 3.1, on layers of 2048 units,
+// Sec. 4.1), the binary16 counterpart of the 8-bit few-row kernel: one workgroup of 8 waves owns FT tiles of 16 features x RT
+// tiles of 16 rows (v_mfma_f32_16x16x32_f16), its waves split K, both operands go straight from memory into operand
+// registers, up to PF k-steps in flight; partial tiles meet in LDS, then a thread sums eight partial sums of an output, adds the
+// bias, rounds once and stores.  Between two such layers the activations lie in operand order (value k of row m at
+// ((k / 8) * R + m) * 8 + k % 8, R = rows rounded up to 16, zeros behind K); row-major inputs are requested along the rows and
+// change lanes on the way.  The library's 32 x 16 weight tiles serve it unchanged: lane (i = lane % 16, g = lane / 16) of
+// feature half h and k-step s takes piece h * 16 + i + 32 * (g % 2) of tile 2 s + g / 2.
+// Bound by the launch and the round trips: 67-2048x3-21 at one row, four launches, 15.3 us with row-major activations, 200
+// bytes of arguments and the tiled kernel for the first layer, 13.4 so; 67-700-523-21, whose rows are no multiples of 8 values, at
+// 16 rows 43.9 (the tiled kernel's element-wise staging), 9.9.
 constexpr int SKH_W = 8;
-constexpr int SKH_PF = 8;
 constexpr int SKH_LD = 65;  // words per register row of a partial tile (conflict-free feature-major reads)
-
-__global__ __launch_bounds__(SKH_W * 64) void k_layer_fp16_skinny(const Fp16Layer L, const _Float16* __restrict__ in,
-                                                                   _Float16* __restrict__ out, const int64_t rows) {
-    __shared__ float part[SKH_W * 16 * SKH_LD];
+typedef float f4acc __attribute__((ext_vector_type(4)));
+typedef float f4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef _Float16 h8_u __attribute__((ext_vector_type(8), aligned(2)));
+enum { HIN_ROWS = 0, HIN_F32 = 1, HIN_BLOCKED = 2 };
+struct HalfRows {
+    const void* w;
+    const float* bias;
+    const void* in;
+    _Float16* out;
+    void* head;  // fp32 actions, or action indices, or NULL
+    int K, N, KS16, rows, flags;
+};
+enum { HF_RELU = 1, HF_TANH = 2, HF_ARGMAX = 4, HF_BLOCKED = 8 };
+template <int FT, int RT, int IN>
+__global__ __launch_bounds__(SKH_W * 64) void k_layer_fp16_rows(const HalfRows L) {
+    constexpr int NF = 16 * FT, NQ = FT * RT, PF = IN == HIN_F32 ? 2 : NQ == 4 ? 4 : 8;
+    __shared__ float part[SKH_W][NQ * 4][SKH_LD];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nt = blockIdx.x;
-    const int64_t row0 = (int64_t)blockIdx.y * 32;
-    const int KSr = (L.K + 15) / 16;                  // k-steps that hold real columns
-    const int kc = (KSr + SKH_W - 1) / SKH_W;
-    const int k0 = wave * kc, k1 = k0 + kc < KSr ? k0 + kc : KSr;
-    const int64_t xrow = row0 + (lane & 31) < rows ? row0 + (lane & 31) : rows - 1;  // (clamped, zeroed below)
-    const bool row_ok = row0 + (lane & 31) < rows;
-    const h8* wsrc = (const h8*)L.wp + (int64_t)nt * L.KS16 * 64 + lane;
-    const _Float16* xsrc = in + xrow * L.K + 8 * (lane >> 5);
-    const h8 z8 = {0, 0, 0, 0, 0, 0, 0, 0};
-    f16acc acc;
+    const int i16 = lane & 15, g = lane >> 4;
+    const int n0 = blockIdx.x * NF, row0 = blockIdx.y * (16 * RT);
+    const int K = L.K, N = L.N, rows = L.rows, rtiles = (rows + 15) >> 4;
+    const int KS = (K + 31) >> 5, kc = (KS + SKH_W - 1) / SKH_W;  // (the weight tiles are padded to 64 k)
+    const int k0 = wave * kc, k1 = k0 + kc < KS ? k0 + kc : KS;
+    const float bias = L.bias[n0 + (tid & (NF - 1))];  // (padded to whole tiles of 32)
+    f4acc acc[FT][RT];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-    for (int g0 = k0; g0 < k1; g0 += SKH_PF) {
-        h8 a[SKH_PF], b[SKH_PF];
+    for (int f = 0; f < FT; ++f)
 #pragma unroll
-        for (int u = 0; u < SKH_PF; ++u) {
-            const int ks = g0 + u < k1 ? g0 + u : k1 - 1;
-            a[u] = wsrc[(int64_t)ks * 64];
-            // K is a multiple of 8: a piece of 8 columns is whole or lies entirely in the zero padding
-            const int kcol = ks * 16 + 8 * (lane >> 5);
-            b[u] = *(const h8*)(xsrc + (kcol < L.K ? ks * 16 : 0));
-            if (!(row_ok && kcol < L.K && g0 + u < k1)) b[u] = z8;
+        for (int r = 0; r < RT; ++r) acc[f][r] = f4acc{0.0f, 0.0f, 0.0f, 0.0f};
+    int64_t roff[RT];  // rows past the batch re-read the last one; they only reach outputs that are not stored
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const int row = row0 + r * 16 + (lane >> 2);
+        roff[r] = (int64_t)(row < rows ? row : rows - 1) * K + 8 * (lane & 3);
+    }
+    auto load_x = [&](int r, int ks) __attribute__((always_inline)) {
+        h8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+        if constexpr (IN == HIN_BLOCKED) {
+            const int tile = (int)blockIdx.y * RT + r, k = ks * 32 + 8 * g;
+            const int64_t row = (tile < rtiles ? tile : rtiles - 1) * 16 + i16;
+            if (k < K) v = *(const h8 AQ_GLOBAL*)((const _Float16*)L.in + ((int64_t)(k >> 3) * rtiles * 16 + row) * 8);
+        } else if constexpr (IN == HIN_ROWS) {
+            const int k = ks * 32 + 8 * (lane & 3);
+            const _Float16* p = (const _Float16*)L.in + roff[r] + ks * 32;
+            if (k + 8 <= K) {
+                v = (h8)*(const h8_u*)p;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (k + j < K) v[j] = p[j];
+            }
+        } else {
+            const int k = ks * 32 + 8 * (lane & 3);
+            const float* p = (const float*)L.in + roff[r] + ks * 32;
+            f4acc x[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (k + 4 * q + 4 <= K) {
+                    x[q] = *(const f4_u*)(p + 4 * q);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[q][j] = k + 4 * q + j < K ? p[4 * q + j] : 0.0f;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = (_Float16)x[j >> 2][j & 3];
         }
+        return v;
+    };
+    const int swap = (i16 * 4 + g) * 4;  // where the row-major request left this lane's operand
+    const int nt = FT == 1 ? (int)blockIdx.x >> 1 : (int)blockIdx.x, h0 = FT == 1 ? (int)blockIdx.x & 1 : 0;
+    const h8 AQ_GLOBAL* wsrc = (const h8 AQ_GLOBAL*)L.w + (int64_t)nt * L.KS16 * 64 + (g >> 1) * 64 + h0 * 16 + i16 + 32 * (g & 1);
+    for (int g0 = k0; g0 < k1; g0 += PF) {
+        h8 w[PF][FT], x[PF][RT];
+        // (behind a scalar test each: none is requested that the share does not have)
+        static_for<0, PF>([&](auto u_c) __attribute__((always_inline)) {
+            constexpr int u = decltype(u_c)::value;
+            if (g0 + u < k1) {
 #pragma unroll
-        for (int u = 0; u < SKH_PF; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u], b[u], acc, 0, 0, 0);
-    }
-    {
-        float* mine = part + wave * 16 * SKH_LD + lane;
+                for (int r = 0; r < RT; ++r) x[u][r] = load_x(r, g0 + u);
+            }
+        });
+        static_for<0, PF>([&](auto u_c) __attribute__((always_inline)) {
+            constexpr int u = decltype(u_c)::value;
+            if (g0 + u < k1) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mine[r * SKH_LD] = acc[r];
+                for (int f = 0; f < FT; ++f) w[u][f] = wsrc[(int64_t)(g0 + u) * 128 + 16 * f];
+            }
+        });
+        static_for<0, PF>([&](auto u_c) __attribute__((always_inline)) {
+            constexpr int u = decltype(u_c)::value;
+            if (g0 + u < k1) {
+                if constexpr (IN != HIN_BLOCKED) {
+#pragma unroll
+                    for (int r = 0; r < RT; ++r) {
+                        v4i t = __builtin_bit_cast(v4i, x[u][r]);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) t[j] = __builtin_amdgcn_ds_bpermute(swap, t[j]);
+                        x[u][r] = __builtin_bit_cast(h8, t);
+                    }
+                }
+#pragma unroll
+                for (int f = 0; f < FT; ++f)
+#pragma unroll
+                    for (int r = 0; r < RT; ++r) acc[f][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[u][f], x[u][r], acc[f][r], 0, 0, 0);
+            }
+        });
     }
+#pragma unroll
+    for (int f = 0; f < FT; ++f)
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[wave][(f * RT + r) * 4 + i][lane] = acc[f][r][i];
     __syncthreads();
+    constexpr int MP = SKH_W * 64 / NF;  // rows per turn
 #pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const int m = (tid >> 5) + 16 * it, nl = tid & 31;
-        // accumulator register and lane that hold (feature nl, row m) of the tile
-        const int reg = 4 * (nl >> 3) + (nl & 3), lsrc = m + 32 * ((nl >> 2) & 1);
+    for (int it = 0; it < (16 * RT + MP - 1) / MP; ++it) {
+        const int m = tid / NF + MP * it, nl = tid & (NF - 1);
+        if (m >= 16 * RT) break;
+        const int reg = ((nl >> 4) * RT + (m >> 4)) * 4 + (nl & 3), lsrc = (m & 15) + 16 * ((nl >> 2) & 3);
         float v = 0.0f;
 #pragma unroll
-        for (int kp = 0; kp < SKH_W; ++kp) v += part[kp * 16 * SKH_LD + reg * SKH_LD + lsrc];
-        const int n = nt * 32 + nl;
-        const int64_t row = row0 + m;
-        const bool ok = row < rows && n < L.N;
-        _Float16 o = (_Float16)(v + L.bias[n]);  // (bias is padded to the tile)
-        if (L.relu) o = o > (_Float16)0.0f ? o : (_Float16)0.0f;
-        if (ok) {
-            out[row * L.N + n] = o;
-            if (L.head_actions)
-                L.head_actions[row * L.N + n] = L.head_tanh ? (float)(_Float16)tanh_rel((float)o) : (float)o;
+        for (int kp = 0; kp < SKH_W; ++kp) v += part[kp][reg][lsrc];
+        const int n = n0 + nl, row = row0 + m;
+        const bool ok = row < rows && n < N;
+        _Float16 o = (_Float16)(v + bias);
+        if (L.flags & HF_RELU) o = o > (_Float16)0.0f ? o : (_Float16)0.0f;
+        if (L.flags & HF_BLOCKED) {
+            if (row < rows && n < ((N + 15) & ~15)) L.out[((int64_t)(n >> 3) * rtiles * 16 + row) * 8 + (n & 7)] = ok ? o : (_Float16)0.0f;
+        } else if (ok) {
+            L.out[(int64_t)row * N + n] = o;
         }
-        if (L.head_argmax) {
-            // the whole output row sits in this tile, one feature per lane of a 32-lane group: the action
+        if (L.flags & HF_ARGMAX) {
+            // the whole output row sits in this workgroup, one feature per lane of an NF-lane group: the action
             // index (lowest index among equal values) is a shuffle reduction away
             float y = ok ? (float)o : -INFINITY;
             int best = n;
 #pragma unroll
-            for (int d = 16; d > 0; d >>= 1) {
-                const float yo = __shfl_xor(y, d, 32);
-                const int bo = __shfl_xor(best, d, 32);
+            for (int d = NF / 2; d > 0; d >>= 1) {
+                const float yo = __shfl_xor(y, d, NF);
+                const int bo = __shfl_xor(best, d, NF);
                 if (yo > y || (yo == y && bo < best)) {
                     y = yo;
                     best = bo;
                 }
             }
-            if (nl == 0 && row < rows) L.head_argmax[row] = best;
+            if (nl == 0 && row < rows) ((int32_t*)L.head)[row] = best;
+        } else if (L.head && ok) {
+            ((float*)L.head)[(int64_t)row * N + n] = L.flags & HF_TANH ? (float)(_Float16)tanh_rel((float)o) : (float)o;
         }
     }
-}
-
-// The same for at most 16 rows, on tiles of 16 rows x 16 features (v_mfma_f32_16x16x32_f16): no half of the tile that
-// belongs to nobody, twice the workgroups, and a wave's share of K up to 2048 is at most eight k-steps of 32, all in flight
-// at once (the kernel above needs two round trips of eight there).  Bound by those round trips and the launch: a layer of
-// 2048 x 2048 at one row has 8 MiB of weights on 128 CUs.  67-2048x3-21 at one row: 19.0 us with the kernel above, 15.3.
-// The library's 32 x 16 weight tiles serve it unchanged: lane (i = lane % 16, g = lane / 16) of feature half h and k-step s
-// takes piece h * 16 + i + 32 * (g % 2) of tile 2 s + g / 2.  PF: k-steps in flight, 4 for shares of up to four, else 8
-// (those past the share re-read its last).
-typedef float f4acc __attribute__((ext_vector_type(4)));
-template <int PF>
-__global__ __launch_bounds__(SKH_W * 64) void k_layer_fp16_rows16(const Fp16Layer L, const _Float16* __restrict__ in,
-                                                                 _Float16* __restrict__ out, const int rows) {
-    __shared__ float part[SKH_W * 4 * SKH_LD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int i = lane & 15, g = lane >> 4, h = blockIdx.x & 1;
-    const int KSr = (L.K + 31) / 32;  // (the tiles are padded to 64 k)
-    const int kc = (KSr + SKH_W - 1) / SKH_W;
-    const int k0 = wave * kc, k1 = k0 + kc < KSr ? k0 + kc : KSr;
-    const bool row_ok = i < rows;
-    const h8* wsrc = (const h8*)L.wp + (int64_t)(blockIdx.x >> 1) * L.KS16 * 64 + (g >> 1) * 64 + h * 16 + i + 32 * (g & 1);
-    const _Float16* xsrc = in + (int64_t)(row_ok ? i : rows - 1) * L.K;
-    // this thread's output: row m, feature n (bias is padded to the tile)
-    const int m = (tid >> 4) & 15, nl = tid & 15, n = blockIdx.x * 16 + nl;
-    const float bias = L.bias[n];
-    const h8 z8 = {0, 0, 0, 0, 0, 0, 0, 0};
-    f4acc acc = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int g0 = k0; g0 < k1; g0 += PF) {
-        h8 a[PF], b[PF];
-#pragma unroll
-        for (int u = 0; u < PF; ++u) {
-            const int ks = g0 + u < k1 ? g0 + u : k1 - 1;
-            a[u] = wsrc[(int64_t)ks * 128];
-            // K is a multiple of 8: a piece of 8 columns is whole or lies entirely in the zero padding
-            const int kcol = ks * 32 + 8 * g;
-            b[u] = *(const h8*)(xsrc + (kcol < L.K ? kcol : 0));
-            if (!(row_ok && kcol < L.K && g0 + u < k1)) b[u] = z8;
-            if (g0 + u >= k1) a[u] = z8;  // (scalar; a weight may be infinite)
-        }
-#pragma unroll
-        for (int u = 0; u < PF; ++u) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u], b[u], acc, 0, 0, 0);
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) part[(wave * 4 + r) * SKH_LD + lane] = acc[r];
-    __syncthreads();
-    if (tid >= 256 || m >= rows || n >= L.N) return;
-    // register and lane that hold (feature nl, row m)
-    const float* src = part + (nl & 3) * SKH_LD + m + 16 * (nl >> 2);
-    float v = 0.0f;
-#pragma unroll
-    for (int kp = 0; kp < SKH_W; ++kp) v += src[kp * 4 * SKH_LD];
-    _Float16 o = (_Float16)(v + bias);
-    if (L.relu) o = o > (_Float16)0.0f ? o : (_Float16)0.0f;
-    out[(int64_t)m * L.N + n] = o;
-    if (L.head_actions)
-        L.head_actions[(int64_t)m * L.N + n] = L.head_tanh ? (float)(_Float16)tanh_rel((float)o) : (float)o;
 }
 
 // LayerNorm (biased variance, eps inside the root) rounded to binary16, then tanh rounded to binary16,
@@ -670,11 +697,24 @@ void launch_layer_cfg(const Fp16Layer& L, const void* in, int in_mode, bool piec
 }
 }  // namespace
 
-bool fp16_layer_is_skinny(const Fp16Layer& L, const void* in, int in_mode, int64_t rows) {
+// Any layer with few workgroups on the tiled kernel (8-bit observations excepted), and rows that are no whole pieces of 8 values,
+// which that one stages one by one, for longer.  us at this kernel / the tiled one: 67-1024x3-21 at 512 rows 19.6 / 31.9, 1000
+// 28.9 / 33.3, 1500 35.3 / 36.7, 2000 44.2 / 38.5; 67-2048x3-21 at 256 rows 24.0 / 56.3, 700 45.7 / 57.5, 67-1100-900-21 at 700
+// 16.5 / 42.8, 2000 38.4 / 51.6.
+bool fp16_layer_is_skinny(const Fp16Layer& L, int in_mode, int64_t rows) {
     const int64_t tiled_wgs = ((rows + 31) / 32) * (int64_t)((L.NT + HW - 1) / HW);
-    return in_mode == 0 && L.fc && L.K % 8 == 0 && ((uintptr_t)in & 15) == 0 && L.K >= 128 && tiled_wgs < 128 &&
-           (rows + 31) / 32 <= 65535;
+    return in_mode != 2 && L.fc && tiled_wgs < (L.K % 8 ? 512 : 400) && (rows + 15) / 16 <= 65535;
 }
+
+namespace {
+template <int FT, int RT>
+void launch_rows(const HalfRows& q, int in, hipStream_t st) {
+    const dim3 grid((unsigned)((q.N + 16 * FT - 1) / (16 * FT)), (unsigned)((q.rows + 16 * RT - 1) / (16 * RT)));
+    if (in == HIN_F32) hipLaunchKernelGGL((k_layer_fp16_rows<FT, RT, HIN_F32>), grid, dim3(SKH_W * 64), 0, st, q);
+    else if (in == HIN_ROWS) hipLaunchKernelGGL((k_layer_fp16_rows<FT, RT, HIN_ROWS>), grid, dim3(SKH_W * 64), 0, st, q);
+    else hipLaunchKernelGGL((k_layer_fp16_rows<FT, RT, HIN_BLOCKED>), grid, dim3(SKH_W * 64), 0, st, q);
+}
+}  // namespace
 
 aq_status launch_layer_fp16(const Fp16Layer& L, const void* in, int in_mode, void* out, int64_t rows,
                             hipStream_t st) {
@@ -693,19 +733,18 @@ aq_status launch_layer_fp16(const Fp16Layer& L, const void* in, int in_mode, voi
     auto wgs = [&](int mt, int nb) {
         return ((rows + 32 * mt - 1) / (32 * mt)) * (int64_t)((L.NT + HW * nb - 1) / (HW * nb));
     };
-    // few rows: one workgroup per output tile with K split over its waves, whenever the tiled kernel would
-    // leave most CUs without a workgroup (binary16 rows of whole, aligned 16-byte pieces)
-    if (fp16_layer_is_skinny(L, in, in_mode, rows)) {
-        // (an argmax in the launch needs the whole row in one tile)
-        if (rows <= 16 && !L.head_argmax) {
-            if (L.K <= SKH_W * 4 * 32)
-                hipLaunchKernelGGL(k_layer_fp16_rows16<4>, dim3(2 * L.NT), dim3(SKH_W * 64), 0, st, L, (const _Float16*)in, o, (int)rows);
-            else
-                hipLaunchKernelGGL(k_layer_fp16_rows16<8>, dim3(2 * L.NT), dim3(SKH_W * 64), 0, st, L, (const _Float16*)in, o, (int)rows);
-            return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
-        }
-        const dim3 grid((unsigned)L.NT, (unsigned)((rows + 31) / 32));
-        hipLaunchKernelGGL(k_layer_fp16_skinny, grid, dim3(SKH_W * 64), 0, st, L, (const _Float16*)in, o, rows);
+    // few rows: small output tiles with K split over a workgroup's waves, whenever the tiled kernel would leave most CUs
+    // without a workgroup
+    if (fp16_layer_is_skinny(L, in_mode, rows)) {
+        int ft = 1, rt = 1;
+        few_row_tile(L.N, rows, L.head_argmax != nullptr, &ft, &rt);
+        const int flags = (L.relu ? HF_RELU : 0) | (L.head_tanh ? HF_TANH : 0) | (L.head_argmax ? HF_ARGMAX : 0) | (L.out_blocked ? HF_BLOCKED : 0);
+        const HalfRows q{L.wp, L.bias, in, o, L.head_argmax ? (void*)L.head_argmax : (void*)L.head_actions, L.K, L.N, L.KS16, (int)rows, flags};
+        const int mode = L.in_blocked ? HIN_BLOCKED : in_mode == 1 ? HIN_F32 : HIN_ROWS;
+        if (ft == 1 && rt == 1) launch_rows<1, 1>(q, mode, st);
+        else if (ft == 1) launch_rows<1, 2>(q, mode, st);
+        else if (rt == 1) launch_rows<2, 1>(q, mode, st);
+        else launch_rows<2, 2>(q, mode, st);
         return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
     }
     if (in_mode == 0 && L.NT > HW && wgs(4, 2) >= 512) launch_layer_cfg<4, 2>(L, in, in_mode, piece, o, rows, st);

@@ -95,7 +95,7 @@ aq_status launch_layer_int8(const FwdArgs& a, int layer, const LayerIO& io, hipS
 // FC layers at few rows: small output tiles, K split over a workgroup's waves (skinny_layer.hip)
 bool skinny_layer_supported(const LayerDev& L, int64_t rows);
 // 16-feature and 16-row tiles per workgroup that such a layer takes (argmax: all features in one workgroup)
-void skinny_layer_tile(const LayerDev& L, int64_t rows, bool argmax, int* ft, int* rt);
+void few_row_tile(int N, int64_t rows, bool argmax, int* ft, int* rt);
 bool skinny_layer_does_argmax(const FwdArgs& a, int l);
 // whether an MLP that fits the whole-network kernels is faster layer by layer at this batch (at most kFewMaxRows rows, a
 // hidden layer of at least kFewMinWidth); noise: exploration then takes a launch of its own
@@ -206,6 +206,7 @@ struct Fp16Layer {
     int head_tanh;
     int32_t* head_argmax;  // last layer of an argmax policy run by the few-row kernel with one feature tile:
                            // action indices [rows], else NULL
+    int in_blocked, out_blocked;  // input / output in the few-row kernel's operand order
 };
 // The learner's parameters -> binary16, every array of every layer in one launch: entry i starts at workgroup blk0[i].
 // Weights go into operand order (kind 0: 16 tiles of 32 features x 16 k per workgroup), biases, gains and offsets
@@ -262,7 +263,7 @@ aq_status launch_fp16_mlp(const Fp16Net& n, const Fp16Net* d_net, const void* ob
 aq_status launch_layer_fp16(const Fp16Layer& L, const void* in, int in_mode, void* out, int64_t rows,
                             hipStream_t st);
 // whether launch_layer_fp16 takes the few-row (K-split) kernel for this layer
-bool fp16_layer_is_skinny(const Fp16Layer& L, const void* in, int in_mode, int64_t rows);
+bool fp16_layer_is_skinny(const Fp16Layer& L, int in_mode, int64_t rows);
 aq_status launch_fp16_ln_tanh(void* x, int64_t rows, int N, const float* gamma, const float* beta, float eps,
                               hipStream_t st);
 aq_status launch_fp16_head(const void* y, int64_t rows, int N, int head, void* actions, hipStream_t st);

@@ -44,12 +44,12 @@ aq_status launch_pack_nibbles(const int8_t* wp, uint8_t* w4, int64_t pieces, hip
 // 1.4 times that where no second workgroup fills the waits of the first.  Layers of 2048 x 2048, four launches, us with
 // 1 x 1, 2 x 1 (features x rows), 1 x 2, 2 x 2: 16 rows 12.7 13.4 14.3 15.8, 64 rows 14.8 14.3 15.5 17.3, 128 rows 21.8
 // 16.6 18.7 17.9, 256 rows 32.9 24.9 27.7 24.5, 900 rows 83.7 66.5 77.5 66.1.
-void skinny_layer_tile(const LayerDev& L, int64_t rows, bool argmax, int* ft, int* rt) {
+void few_row_tile(int N, int64_t rows, bool argmax, int* ft, int* rt) {
     double best = 1e300;
     for (int f = 1; f <= 2; ++f) {
-        if (argmax && 16 * f < L.N) continue;
+        if (argmax && 16 * f < N) continue;
         for (int r = 1; r <= 2; ++r) {
-            const int64_t wgs = ((L.N + 16 * f - 1) / (16 * f)) * ((rows + 16 * r - 1) / (16 * r));
+            const int64_t wgs = ((N + 16 * f - 1) / (16 * f)) * ((rows + 16 * r - 1) / (16 * r));
             const double c = (wgs > 256 ? (double)((wgs + 255) / 256) : 1.4) * (f + 2 * r);
             if (c < best) {
                 best = c;
@@ -93,7 +93,7 @@ aq_status launch_layer_skinny(const FwdArgs& a, int l, const LayerIO& io, hipStr
     const int in = io.in_blocked ? IN_BLOCKED : first && !a.net.in_u8 ? IN_F32 : IN_ROWS;
     const bool argmax = skinny_layer_does_argmax(a, l);
     int ft = 1, rt = 1;
-    skinny_layer_tile(L, rows, argmax, &ft, &rt);
+    few_row_tile(L.N, rows, argmax, &ft, &rt);
     const bool asym = a.net.asym != 0;
     const uint8_t* w4 = asym ? nullptr : a.w4[l];
     void* out = !last ? (ln ? (void*)io.ln_x : (void*)io.out) : argmax || a.net.head != AQ_HEAD_ARGMAX ? a.c.actions : nullptr;

@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import gpu_util as U
+import test_gpu_fp16 as H
 from paper_1910_01055_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -41,6 +42,27 @@ def test_few_row_layers_against_the_oracle(aq, name, batches):
         plain, _ = U.gpu_forward(P, net, obs, taps=False)
         assert np.array_equal(plain, actions)
         P.close()
+
+
+@pytest.mark.parametrize("batch", [1, 16, 33, 270])
+@pytest.mark.parametrize("odd,head", [(True, "tanh"), (True, "argmax"), (False, "linear")])
+def test_fp16_few_row_layers_against_the_oracle(aq, odd, head, batch):
+    """The half-precision counterpart: rows of no whole pieces of eight values behind fp32 observations, an argmax over two tiles of
+    16, K beyond eight k-steps of 32 per wave.  (Without intermediate outputs, maps between the layers in operand order.)"""
+    print(f"[fp16 few rows] {odd} {head} batch={batch}", flush=True)
+    if odd:
+        layers = [fc(67, 1099, "relu"), fc(1099, 1037, "none"), fc(1037, 18 if head == "argmax" else 33, "none")]
+    else:
+        layers = [fc(300, 2400, "relu"), fc(2400, 136, "relu"), fc(136, 16, "none")]
+    net = synth.small_net(layers, head=head)
+    params = synth.make_params(net, nonzero_bias=True)
+    obs = synth.make_obs(net, batch)
+    P = aq.Policy(net)
+    P.convert_params_fp16(*U.upload_params(params))
+    assert P.policy_fp16_plan(batch) == 0  # a launch per layer
+    P.close()
+    actions, outs = H._run_gpu(aq, net, params, obs)
+    H._check(net, params, obs, actions, outs, end_to_end=False)
 
 
 def test_wide_policies_at_few_rows_take_the_layers_launches(aq):
