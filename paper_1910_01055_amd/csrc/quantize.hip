@@ -120,45 +120,59 @@ __global__ __launch_bounds__(256) void k_quant_asym_flat(const float4* __restric
     }
 }
 
-// per-channel symmetric codes, canonical order: one wavefront per row, the row lives in
-// registers (R float4 per lane) between the |w| reduction and the rounding.
-template <int R>
-__global__ __launch_bounds__(256) void k_quant_sym_rows_flat(const float4* __restrict__ w4, int64_t rows, int cols4, int qw,
-                                                             uint32_t* __restrict__ codes, float* __restrict__ scale,
-                                                             int32_t* __restrict__ zp, uint32_t* __restrict__ mm) {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= rows) return;
-    const float4* src = w4 + row * cols4;
-    float4 v[R];
-    float amax = 0.0f;
+// per-channel symmetric codes, canonical order, short rows: G lanes per row, V float4 of it each, in registers between the |w|
+// reduction and the rounding; U such sets of rows per wavefront, all requested at once, so that 64 bytes a thread are in flight
+// however short the rows.  Bound by memory: 100000 x 64 (26 MB in, 6 MB out) took 24.9 us with a wavefront per row (one float4
+// a thread, three quarters of the lanes idle), 8.3 so.
+template <int G, int V, int U>
+__global__ __launch_bounds__(256) void k_quant_sym_rows_short(const float4* __restrict__ w4, int64_t rows, int cols4, int qw,
+                                                              uint32_t* __restrict__ codes, float* __restrict__ scale,
+                                                              int32_t* __restrict__ zp, uint32_t* __restrict__ mm) {
+    constexpr int RW = 64 / G;
+    const int lane = threadIdx.x & 63, li = lane & (G - 1);
+    const int64_t row0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (RW * U) + lane / G;
+    f4v v[U][V];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const int c = li + G * i;
+            const int64_t row = row0 + u * RW;
+            v[u][i] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+            if (row < rows && c < cols4) v[u][i] = __builtin_nontemporal_load((const f4v*)w4 + row * cols4 + c);
+        }
     int bad = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        int c = lane + 64 * r;
-        v[r] = c < cols4 ? src[c] : make_float4(0.f, 0.f, 0.f, 0.f);
-        float a0 = fabsf(v[r].x), a1 = fabsf(v[r].y), a2 = fabsf(v[r].z), a3 = fabsf(v[r].w);
-        bad |= !(a0 <= FLT_MAX) | !(a1 <= FLT_MAX) | !(a2 <= FLT_MAX) | !(a3 <= FLT_MAX);
-        amax = fmaxf(fmaxf(amax, fmaxf(a0, a1)), fmaxf(a2, a3));
-    }
-    amax = wave_max(amax);
-    bad = wave_or_i32(bad);
-    float s = amax / (float)qw;
-    if (amax == 0.0f) s = 1.0f;
-    if (lane == 0) {
-        scale[row] = s;
-        zp[row] = 0;
-        if (bad) atomicOr(&mm[2], 1u);
-    }
-    uint32_t* dst = codes + row * cols4;
-    const QuantScale qs = make_quant_scale(s);
+    for (int u = 0; u < U; ++u) {
+        const int64_t row = row0 + u * RW;
+        float amax = 0.0f;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        int c = lane + 64 * r;
-        if (c < cols4) {
-            __builtin_nontemporal_store(quant_code4(v[r], qs, -qw, qw, 0), dst + c);
+        for (int i = 0; i < V; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float x = fabsf(v[u][i][j]);
+                bad |= !(x <= FLT_MAX);
+                amax = fmaxf(amax, x);
+            }
+#pragma unroll
+        for (int o = G / 2; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+        float s = amax / (float)qw;
+        if (amax == 0.0f) s = 1.0f;
+        if (row >= rows) continue;
+        if (li == 0) {
+            scale[row] = s;
+            zp[row] = 0;
+        }
+        const QuantScale qs = make_quant_scale(s);
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const int c = li + G * i;
+            if (c < cols4)
+                __builtin_nontemporal_store(quant_code4(make_float4(v[u][i][0], v[u][i][1], v[u][i][2], v[u][i][3]), qs, -qw, qw, 0),
+                                            codes + row * cols4 + c);
         }
     }
+    if (bad) atomicOr(&mm[2], 1u);
 }
 
 // Longer rows: one workgroup per row, R float4 per thread held in registers between the |w|
@@ -768,10 +782,20 @@ aq_status launch_quantize_tensor(const float* d_w, int64_t rows, int64_t cols, i
                            d_zp, d_ws + 2);
     } else {
         const int cols4 = (int)(cols / 4);
-        if (cols4 <= 64) {
-            hipLaunchKernelGGL(k_quant_sym_rows_flat<1>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, w4, rows,
-                               cols4, qw, c4, d_scale, d_zp, d_ws);
-        } else {
+#define AQ_SHORT(G, V, U)                                                                                                     \
+    hipLaunchKernelGGL((k_quant_sym_rows_short<G, V, U>), dim3((unsigned)((rows + 4 * (64 / G) * U - 1) / (4 * (64 / G) * U))), \
+                       dim3(256), 0, st, w4, rows, cols4, qw, c4, d_scale, d_zp, d_ws)
+        // Fewer, fuller wavefronts from the row counts on where they fill the chip, us so / with a wavefront or a workgroup per row:
+        // 500000 x 32 25.4 / 107, 20000 x 160 7.3 / 6.5, 60000 x 252 16.6 / 16.5, 2000 x 400 5.2 / 4.6, 20000 x 400 9.3 / 17.9,
+        // 2000 x 1000 4.8 / 4.5, 5000 x 700 5.4 / 6.7, 30000 x 1000 25.1 / 32.1.
+        if (cols4 <= 16) AQ_SHORT(16, 1, 4);
+        else if (cols4 <= 32) AQ_SHORT(16, 2, 2);
+        else if (cols4 <= 64 && rows < 40000) AQ_SHORT(64, 1, 1);
+        else if (cols4 <= 64) AQ_SHORT(64, 1, 4);
+        else if (cols4 <= 128 && rows >= 6000) AQ_SHORT(64, 2, 2);
+        else if (cols4 <= 256 && rows >= 4096) AQ_SHORT(64, 4, 1);
+#undef AQ_SHORT
+        else {
 #define AQ_ROW_WG(R) \
     hipLaunchKernelGGL(k_quant_sym_row_wg<R>, dim3((unsigned)rows), dim3(256), 0, st, w4, cols4, qw, c4, d_scale, d_zp, d_ws)
             if (cols4 <= 256) AQ_ROW_WG(1);
