@@ -459,24 +459,37 @@ __global__ __launch_bounds__(512) void k_qp_rows(const QTab* __restrict__ tab, c
 
     float s;
     int z = 0;
+    bool bounded = false;  // no value beyond the largest code
     if (SYM) {
-        float amax = 0.0f;
-        int bad = 0;
+        // the largest magnitude by its bits (in order for finite values; anything above them is not finite)
+        uint32_t most = 0;
         for (int k0 = 0; k0 < K; k0 += QR_CHUNK) {
             if (!held) load(k0);
 #pragma unroll
             for (int c = 0; c < R; ++c)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const float a = fabsf(v[c][j]);
-                    bad |= !(a <= FLT_MAX);
-                    amax = fmaxf(amax, a);
+                    const uint32_t u = __float_as_uint(v[c][j]) & 0x7fffffffu;
+                    most = most > u ? most : u;
                 }
         }
+        const bool bad = __ballot(most > 0x7f7fffffu) != 0;
+        float amax = __uint_as_float(most);
+        if (bad) {  // the same over what is no NaN
+            amax = 0.0f;
+            for (int k0 = 0; k0 < K; k0 += QR_CHUNK) {
+                if (!held) load(k0);
+#pragma unroll
+                for (int c = 0; c < R; ++c)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) amax = fmaxf(amax, fabsf(v[c][j]));
+            }
+        }
+        bounded = !bad;
         amax = wave_max(amax);
         s = amax / (float)t.w_qw;
         if (amax == 0.0f) s = 1.0f;
-        if (bad) atomicOr(o.status, kStatNonFinite);
+        if (bad && lane == 0) atomicOr(o.status, kStatNonFinite);
     } else {
         // the layer's range from its workgroups' partial ones (at most 256)
         float hi = 0.0f, nlo = 0.0f;
@@ -507,6 +520,7 @@ __global__ __launch_bounds__(512) void k_qp_rows(const QTab* __restrict__ tab, c
     }
 
     const QuantScale qs = make_quant_scale(s);
+    bounded = bounded && qs.rcp_ok;
     const float lo = SYM ? -(float)t.w_qw : -(float)z, hi = SYM ? (float)t.w_qw : (float)(t.w_qmax - z), add = SYM ? 128.0f : (float)z;
     int sum = 0;
     for (int k0 = 0; k0 < K; k0 += QR_CHUNK) {
@@ -515,8 +529,10 @@ __global__ __launch_bounds__(512) void k_qp_rows(const QTab* __restrict__ tab, c
         for (int c = 0; c < R; ++c) {
             if (k0 + 256 * c >= L.KS * 32) continue;  // (scalar)
             const int kk = 4 * (lane + 64 * c);
-            uint32_t q = quant_s8x4(make_float4(v[c][0], v[c][1], v[c][2], v[c][3]), qs, lo, hi, add);
-            // entries behind the end of K are zeros in the signed domain
+            const float4 x = make_float4(v[c][0], v[c][1], v[c][2], v[c][3]);
+            uint32_t q = SYM && bounded ? quant_s8x4_bounded(x, qs) : quant_s8x4(x, qs, lo, hi, add);
+            // entries behind the end of K are zeros in the signed domain (unconditionally: behind a scalar test for the pieces
+            // that reach it, the compiler took 95 registers instead of 64, two workgroups per CU instead of four)
             const int left = K - k0 - kk;
             if (left < 4) q = left <= 0 ? 0u : q & (0xffffffffu >> (8 * (4 - left)));
             sum = __builtin_amdgcn_sdot4((int)q, 0x01010101, sum, false);
