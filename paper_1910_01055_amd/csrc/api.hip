@@ -611,8 +611,10 @@ static bool few_alloc(aq_policy* p, int i) {
     return hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess && ok;
 }
 
-// the pair of maps that belongs to `st`; NULL: more streams than pairs, a capture, or no memory
+// the pair of maps that belongs to `st`; NULL: more streams than pairs, a capture, no memory, or the handle that names another
+// stream in every thread (a forward of the thread that had the policy before may still run on its own)
 static int8_t* few_maps_of(aq_policy* p, hipStream_t st) {
+    if (st == hipStreamPerThread) return nullptr;
     int i = 0;
     while (i < p->few_streams && p->few_stream[i] != st) ++i;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;

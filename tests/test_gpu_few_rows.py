@@ -94,6 +94,12 @@ def test_wide_policies_at_few_rows_take_the_layers_launches(aq):
                 outs.append(y)
     torch.cuda.synchronize()
     assert all(np.array_equal(y.cpu().numpy(), want) for y in outs)
+    # the handle that names another stream in every thread has no maps of its own: the whole-network kernel
+    with torch.cuda.stream(torch.cuda.ExternalStream(2)):
+        y = torch.zeros((250, 21), device="cuda:0")
+        P.policy_forward_int8(d_obs, y)
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy(), want)
     P.close()
     # per-tensor weights, an argmax head within one workgroup, exploration behind the layers
     net = synth.small_net([fc(40, 1024, "relu"), fc(1024, 1024, "relu"), fc(1024, 30, "none")], head="tanh", wscheme="tensor_asym_u8")
