@@ -168,8 +168,8 @@ __global__ __launch_bounds__(SK_W * 64) void k_layer_skinny(const SkinnyLayer L,
                 if (g0 + u < k1) {
 #pragma unroll
                     for (int r = 0; r < RT; ++r) {
-                        const int64_t tile = (int64_t)blockIdx.y * RT + r;
-                        const int64_t row = (tile < rtiles ? tile : rtiles - 1) * 16 + i16;
+                        // (rows past the batch re-read the last one: nobody writes theirs, and they would come from HBM)
+                        const int64_t row_r = row0 + r * 16 + i16, row = row_r < rows ? row_r : rows - 1;
                         const int k = (g0 + u) * 64 + g * 16;
                         x[u][r] = v4i{0, 0, 0, 0};
                         if (k < K) x[u][r] = *(gv4i_ptr)((const int8_t*)L.in + ((int64_t)(k >> 4) * rtiles * 16 + row) * 16);
