@@ -242,8 +242,8 @@ __global__ __launch_bounds__(FT_) void k_fp32_layer(const Fp32Layer L, const voi
 // before the partial sums meet in LDS.  Inputs are requested along the rows (four lanes to 64 bytes; lanes down the rows
 // take 75 clocks a request instead of 16) and change lanes on the way.  Bound by the fp32 matrix cores, 32 clocks an MFMA,
 // and the vector memory path, 47 bytes a clock beside them at 16 x 32.  With a layer of 4 behind it, us on the tiles of the
-// kernel above (inputs through LDS, a barrier every 128 to 512 k) and so: 3136-512 at 128 rows 16.4, 13.0, at 256 19.9, 18.2;
-// 700-523 at 16 rows 9.9, 8.1, at 512 18.5, 16.5; 2048-2048 at 128 22.5, 20.8.
+// kernel above (inputs through LDS, a barrier every 128 to 512 k) and so: 3136-512 at 128 rows 16.4, 12.3, at 256 19.9, 17.3;
+// 700-523 at 16 rows 9.9, 8.1, at 512 18.5, 16.5; 2048-2048 at 128 22.5, 19.6.
 template <int FT, int RT, bool U8>
 __global__ __launch_bounds__(FT_) void k_fp32_rows(const Fp32Layer L, const void* __restrict__ in, float* __restrict__ out,
                                                    const int64_t rows, RangeSlot* __restrict__ slots) {
@@ -311,13 +311,25 @@ __global__ __launch_bounds__(FT_) void k_fp32_rows(const Fp32Layer L, const void
             fetch(p_c, s0 + p < s1 ? s0 + p : s1 - 1);
         });
         int s = s0;
-        for (; s + PF <= s1; s += PF) {
+        for (; s + 2 * PF <= s1; s += PF) {
             static_for<0, PF>([&](auto p_c) __attribute__((always_inline)) {
                 constexpr int p = decltype(p_c)::value;
                 stage(p_c);
-                fetch(p_c, s + p + PF < s1 ? s + p + PF : s1 - 1);
+                fetch(p_c, s + p + PF);
                 asm volatile("" ::: "memory");
             });
+        }
+        // (the last requests of a share behind scalar tests: clamped to its end instead, up to PF of them were re-reads that
+        // took their turn on the vector memory path: 1024-1024 at 256 rows 13.5 us, 12.9 so, 2048-2048 at 128 20.5, 19.6; eight
+        // stages in flight instead of four are slower, 18.5 for 17.3 of 3136-512 at 256)
+        if (s + PF <= s1) {
+            static_for<0, PF>([&](auto p_c) __attribute__((always_inline)) {
+                constexpr int p = decltype(p_c)::value;
+                stage(p_c);
+                if (s + p + PF < s1) fetch(p_c, s + p + PF);
+                asm volatile("" ::: "memory");
+            });
+            s += PF;
         }
         static_for<0, PF - 1>([&](auto p_c) __attribute__((always_inline)) {
             if (s + decltype(p_c)::value < s1) stage(p_c);
