@@ -115,7 +115,8 @@ typedef struct {
 /* Creates a policy handle for `net` on the current HIP device.  Validates that the layers chain
  * (AQ_ESHAPE otherwise) and that every layer is within the size limits of the int32 accumulation:
  * K = kh * kw * in_c <= 65536, out_c <= 2^20, in_h and in_w <= 16384 (AQ_ESHAPE beyond them).
- * Allocates the per-layer device buffers (packed 8-bit weights, per-channel constants). */
+ * Allocates the per-layer device buffers (packed 8-bit weights, per-channel constants; for a policy whose few rows go
+ * layer by layer, see aq_policy_set_path, also their maps: 4 KiB per unit of its widest layer). */
 aq_status aq_policy_create(const aq_net* net, aq_policy** out);
 aq_status aq_policy_destroy(aq_policy* p);
 

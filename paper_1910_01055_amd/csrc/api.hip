@@ -99,10 +99,10 @@ struct aq_policy {
     int64_t cap_i8 = 0, cap_f32 = 0;
     // ... and the maps of a policy that fits the whole-network kernels but runs few rows layer by layer (few_rows_faster): a
     // pair of them for each of the first kFewStreams streams, since a forward that needs no scratch may overlap another
-    // on a second stream (allocated by aq_policy_reserve or the first such forward on a stream)
+    // on a second stream.  Made with the policy: such a forward allocates nothing, as on the whole-network kernels.
     size_t few_bytes = 0;  // of one map; 0: the policy never takes that route
+    int8_t* few_slab = nullptr;
     hipStream_t few_stream[kFewStreams] = {};
-    int8_t* few_maps[kFewStreams] = {};
     int few_streams = 0;
     int8_t* act_i8[2] = {nullptr, nullptr};
     float* ln_x = nullptr;
@@ -386,7 +386,15 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         int r = 0, few_n = 0;
         size_t lds = 0;
         for (int l = 0; l < net->n_layers - 1; ++l) few_n = std::max(few_n, p->L[l].N);
-        if (few_n >= kFewMinWidth && fused_mlp_supported(probe, &r, &lds)) p->few_bytes = (blocked_map_bytes(kFewMaxRows, few_n) + 255) & ~(size_t)255;
+        // (one row: if the layers' launches are not faster there, they are at no batch)
+        if (fused_mlp_supported(probe, &r, &lds) && few_rows_faster(probe, false)) {
+            p->few_bytes = (blocked_map_bytes(kFewMaxRows, few_n) + 255) & ~(size_t)255;
+            if (hipMalloc((void**)&p->few_slab, 2 * kFewStreams * p->few_bytes) != hipSuccess) {
+                (void)hipFree(p->slab);
+                delete p;
+                return AQ_ENOMEM;
+            }
+        }
     }
     {   // the quantizer's table: outputs per layer and each layer's first workgroup in the shared grids
         QTab& q = p->h_qtab;
@@ -446,6 +454,7 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     memcpy(up.data() + (off_ftab - off_net), &ftab, sizeof(F32KeepTab));
     if (hipMemcpy(p->d_net, up.data(), up.size(), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(p->slab);
+        if (p->few_slab) (void)hipFree(p->few_slab);
         delete p;
         return AQ_EHIP;
     }
@@ -453,6 +462,7 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         unsigned char* sc = nullptr;
         if (static_scratch(&sc) != AQ_OK) {
             (void)hipFree(p->slab);
+            if (p->few_slab) (void)hipFree(p->few_slab);
             delete p;
             return AQ_EHIP;
         }
@@ -466,8 +476,7 @@ extern "C" aq_status aq_policy_destroy(aq_policy* p) {
     (void)hipDeviceSynchronize();
     if (p->slab) (void)hipFree(p->slab);
     if (p->w4_slab) (void)hipFree(p->w4_slab);
-    for (int8_t* m : p->few_maps)
-        if (m) (void)hipFree(m);
+    if (p->few_slab) (void)hipFree(p->few_slab);
     for (int i = 0; i < 2; ++i) {
         if (p->act_i8[i]) (void)hipFree(p->act_i8[i]);
         if (p->act_f32[i]) (void)hipFree(p->act_f32[i]);
@@ -602,32 +611,22 @@ static aq_status ensure_f32_passed(aq_policy* p) {
     return AQ_OK;
 }
 
-static bool few_alloc(aq_policy* p, int i) {
-    if (p->few_maps[i]) return true;
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another thread may be capturing)
-    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
-    const bool ok = hipMalloc((void**)&p->few_maps[i], 2 * p->few_bytes) == hipSuccess;
-    if (!ok) p->few_maps[i] = nullptr;
-    return hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess && ok;
-}
-
-// the pair of maps that belongs to `st`; NULL: more streams than pairs, a capture, no memory, or the handle that names another
+// the pair of maps that belongs to `st`; NULL: more streams than pairs, a capture, or the handle that names another
 // stream in every thread (a forward of the thread that had the policy before may still run on its own)
 static int8_t* few_maps_of(aq_policy* p, hipStream_t st) {
     if (st == hipStreamPerThread) return nullptr;
     int i = 0;
     while (i < p->few_streams && p->few_stream[i] != st) ++i;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (i == kFewStreams || hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone || !few_alloc(p, i)) return nullptr;
+    if (i == kFewStreams || hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return nullptr;
     if (i == p->few_streams) p->few_stream[p->few_streams++] = st;
-    return p->few_maps[i];
+    return p->few_slab + (size_t)i * 2 * p->few_bytes;
 }
 
 extern "C" aq_status aq_policy_reserve(aq_policy* p, int64_t max_batch) {
     if (!p || max_batch < 0) return AQ_EINVAL;
     aq_status s = ensure_i8(p, max_batch, nullptr);
     if (s != AQ_OK) return s;
-    if (p->few_bytes) (void)few_alloc(p, 0);  // (without it the whole-network kernels run)
     if (p->h16_ready) {
         s = ensure_f16(p, max_batch, nullptr);
         if (s != AQ_OK) return s;

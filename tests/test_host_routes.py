@@ -1,0 +1,131 @@
+"""Host code of the library on a HIP runtime of host memory (fake_hip.c): which kernels a forward launches on which stream and
+buffers, what it allocates, and what it answers when a runtime call fails.  Each scenario runs in a process of its own, in
+which no other HIP runtime is loaded."""
+import ctypes as C
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+LAUNCH, MALLOC, WAIT, RECORD = range(4)
+
+
+class Entry(C.Structure):
+    _fields_ = [("kind", C.c_int), ("grid", C.c_uint * 3), ("stream", C.c_void_p), ("in_", C.c_void_p), ("out", C.c_void_p),
+                ("name", C.c_char * 160)]
+
+
+class Mem:
+    """What the binding asks of a tensor."""
+
+    def __init__(self, rows=1):
+        self._buf = C.create_string_buffer(4096)
+        self.shape = (rows,)
+
+    def data_ptr(self):
+        return (C.addressof(self._buf) + 255) & ~255
+
+
+class Host:
+    def __init__(self, fake_path):
+        sys.path.insert(0, ROOT)
+        self.hip = C.CDLL(fake_path, mode=C.RTLD_GLOBAL)
+        self.hip.fake_entry.restype = C.POINTER(Entry)
+        for f in ("fake_capture", "fake_set_busy"):
+            getattr(self.hip, f).argtypes = [C.c_void_p]
+        from paper_1910_01055_amd import binding, synth
+        self.aq, self.synth = binding, synth
+        binding._stream = lambda: self.stream
+        self.stream = 0
+
+    def policy(self, *widths, k=67, out=21, **kw):
+        fc, layers = self.synth.fc, []
+        for w in widths:
+            layers.append(fc(k, w, "relu"))
+            k = w
+        net = self.synth.small_net(layers + [fc(k, out, "none")], **kw)
+        P = self.aq.Policy(net)
+        n = len(net["layers"])
+        P.quantize_params([Mem()] * n, [Mem()] * n, None, None, [(0.0, 1.0)] * n)
+        return P
+
+    def logged(self, kind=None):
+        e = [self.hip.fake_entry(i).contents for i in range(self.hip.fake_entries())]
+        return [x for x in e if kind is None or x.kind == kind]
+
+    def forward(self, P, batch, stream=0):
+        """-> the entries of one forward on `stream`."""
+        self.stream = stream
+        self.hip.fake_clear()
+        P.policy_forward_int8(Mem(batch), Mem(batch))
+        return self.logged()
+
+    def maps(self, entries):
+        """Addresses of the maps between the layers of a few-row forward; empty for one whole-network launch."""
+        runs = [e for e in entries if e.kind == LAUNCH]
+        if len(runs) == 1:
+            assert b"mlp" in runs[0].name
+            return set()
+        assert all(b"k_layer_skinny" in e.name for e in runs)
+        for a, b in zip(runs, runs[1:]):
+            assert a.out == b.in_
+        return {e.out for e in runs[:-1]}
+
+
+def few_row_forwards_allocate_nothing(h):
+    """... with or without a reserve, on any stream: a wide policy at few rows needed no memory on the whole-network kernels."""
+    for reserve in (True, False):
+        P = h.policy(1024, 1024)
+        if reserve:
+            P.policy_reserve(64)
+        seen = []
+        for stream in (0, 64, 128, 192, 256, 0):
+            entries = h.forward(P, 16, stream)
+            assert not [e for e in entries if e.kind == MALLOC], (reserve, stream)
+            seen.append(h.maps(entries))
+        assert len(seen[0]) == 2 and seen[5] == seen[0]
+        assert len({m for s in seen[:4] for m in s}) == 8
+        P.close()
+    assert h.hip.fake_live() == 0
+
+
+def policies_that_never_take_few_rows_apart_keep_no_maps(h):
+    """One allocation for a policy, two where few rows run layer by layer."""
+    for widths, n in (((256, 256), 1), ((300, 280), 1), ((1024, 1024), 2), ((2048, 2048), 1)):
+        h.hip.fake_clear()
+        P = h.policy(*widths)
+        assert len(h.logged(MALLOC)) == n, widths
+        assert (P.policy_fused_plan(1)[0] == 0) == (n == 2 or widths[0] == 2048)
+        P.close()
+
+
+def a_few_row_forward_without_memory_to_have(h):
+    """... answers OK: it needs none."""
+    P = h.policy(1024, 1024)
+    h.hip.fake_fail_mallocs(1)
+    assert len(h.maps(h.forward(P, 16, 64))) == 2
+
+
+SCENARIOS = [few_row_forwards_allocate_nothing, policies_that_never_take_few_rows_apart_keep_no_maps,
+             a_few_row_forward_without_memory_to_have]
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("hip") / "libamdhip64.so.7")
+    subprocess.run(["gcc", "-O1", "-std=c11", "-Wall", "-shared", "-fPIC", "-Wl,-soname,libamdhip64.so.7", "-o", lib,
+                    os.path.join(HERE, "fake_hip.c")], check=True)
+    return lib
+
+
+@pytest.mark.parametrize("name", [s.__name__ for s in SCENARIOS])
+def test_host(fake, name):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), fake, name], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    {s.__name__: s for s in SCENARIOS}[sys.argv[2]](Host(sys.argv[1]))
