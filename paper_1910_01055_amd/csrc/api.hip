@@ -24,11 +24,11 @@ void* g_scratch_ptr[kMaxDevices];  // per device, filled on first use with that 
 // device address of `scratch` on the current device (AQ_EHIP when the lookup fails)
 aq_status static_scratch(unsigned char** out) {
     int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return AQ_EHIP;
+    if (hip_failed(hipGetDevice(&dev)) || dev < 0 || dev >= kMaxDevices) return AQ_EHIP;
     std::lock_guard<std::mutex> lock(g_scratch_mu);
     if (!g_scratch_ptr[dev]) {
         void* ptr = nullptr;
-        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return AQ_EHIP;
+        if (hip_failed(hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch))) || !ptr) return AQ_EHIP;
         g_scratch_ptr[dev] = ptr;
     }
     *out = (unsigned char*)g_scratch_ptr[dev];
@@ -239,7 +239,7 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     if (!(net->ln_eps > 0.0f)) return AQ_EINVAL;
     if (net->wbits != 0 && (net->wbits < 2 || net->wbits > 8)) return AQ_EINVAL;
     int dev_count = 0;
-    if (hipGetDeviceCount(&dev_count) != hipSuccess || dev_count < 1) return AQ_EHIP;
+    if (hip_failed(hipGetDeviceCount(&dev_count)) || dev_count < 1) return AQ_EHIP;
 
     aq_policy* p = new (std::nothrow) aq_policy();
     if (!p) return AQ_ENOMEM;
@@ -332,12 +332,12 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     size_t off_net = take(sizeof(NetDev));
     size_t off_qtab = take(sizeof(QTab));
     size_t off_ftab = take(sizeof(F32KeepTab));
-    if (hipMalloc(&p->slab, bytes) != hipSuccess) {
+    if (hip_failed(hipMalloc(&p->slab, bytes))) {
         delete p;
         return AQ_ENOMEM;
     }
     // zero once: padding rows / k-steps of the packed weights and padded constants stay zero for good
-    if (hipMemset(p->slab, 0, bytes) != hipSuccess) {
+    if (hip_failed(hipMemset(p->slab, 0, bytes))) {
         (void)hipFree(p->slab);
         delete p;
         return AQ_EHIP;
@@ -389,7 +389,7 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         // (one row: if the layers' launches are not faster there, they are at no batch)
         if (fused_mlp_supported(probe, &r, &lds) && few_rows_faster(probe, false)) {
             p->few_bytes = (blocked_map_bytes(kFewMaxRows, few_n) + 255) & ~(size_t)255;
-            if (hipMalloc((void**)&p->few_slab, 2 * kFewStreams * p->few_bytes) != hipSuccess) {
+            if (hip_failed(hipMalloc((void**)&p->few_slab, 2 * kFewStreams * p->few_bytes))) {
                 (void)hipFree(p->slab);
                 delete p;
                 return AQ_ENOMEM;
@@ -452,7 +452,7 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     memcpy(up.data(), &p->h_net, sizeof(NetDev));
     memcpy(up.data() + (off_qtab - off_net), &p->h_qtab, sizeof(QTab));
     memcpy(up.data() + (off_ftab - off_net), &ftab, sizeof(F32KeepTab));
-    if (hipMemcpy(p->d_net, up.data(), up.size(), hipMemcpyHostToDevice) != hipSuccess) {
+    if (hip_failed(hipMemcpy(p->d_net, up.data(), up.size(), hipMemcpyHostToDevice))) {
         (void)hipFree(p->slab);
         if (p->few_slab) (void)hipFree(p->few_slab);
         delete p;
@@ -496,7 +496,7 @@ extern "C" aq_status aq_policy_destroy(aq_policy* p) {
 // caller's stream is being captured into a graph, which the forward then reports instead of breaking the capture.
 static bool capturing(hipStream_t st) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+    return !hip_failed(hipStreamIsCapturing(st, &cs)) && cs != hipStreamCaptureStatusNone;
 }
 
 // bytes of one 8-bit activation map of the per-layer plan (a little slack behind the last row), and the same where
@@ -524,10 +524,10 @@ static aq_status ensure_i8(aq_policy* p, int64_t batch, hipStream_t st) {
     p->ln_x = p->y_rows = nullptr;
     p->cap_i8 = 0;
     for (int i = 0; i < 2; ++i)
-        if (hipMalloc((void**)&p->act_i8[i], i8_map_bytes_blocked(p, batch)) != hipSuccess) return AQ_ENOMEM;
+        if (hip_failed(hipMalloc((void**)&p->act_i8[i], i8_map_bytes_blocked(p, batch)))) return AQ_ENOMEM;
     // fp32 rows exist only where the 8-bit path needs them: LayerNorm inputs, argmax logits
-    if (p->ln_elems && hipMalloc((void**)&p->ln_x, (size_t)batch * p->ln_elems * 4 + 256) != hipSuccess) return AQ_ENOMEM;
-    if (p->y_elems && hipMalloc((void**)&p->y_rows, (size_t)batch * p->y_elems * 4 + 256) != hipSuccess) return AQ_ENOMEM;
+    if (p->ln_elems && hip_failed(hipMalloc((void**)&p->ln_x, (size_t)batch * p->ln_elems * 4 + 256))) return AQ_ENOMEM;
+    if (p->y_elems && hip_failed(hipMalloc((void**)&p->y_rows, (size_t)batch * p->y_elems * 4 + 256))) return AQ_ENOMEM;
     p->cap_i8 = batch;
     return AQ_OK;
 }
@@ -543,7 +543,7 @@ static aq_status ensure_f32(aq_policy* p, int64_t batch, hipStream_t st) {
     p->cap_f32 = 0;
     size_t n = ((size_t)batch * (size_t)p->max_out_elems + 64) * sizeof(float);
     for (int i = 0; i < 2; ++i)
-        if (hipMalloc((void**)&p->act_f32[i], n) != hipSuccess) return AQ_ENOMEM;
+        if (hip_failed(hipMalloc((void**)&p->act_f32[i], n))) return AQ_ENOMEM;
     p->cap_f32 = batch;
     return AQ_OK;
 }
@@ -561,7 +561,7 @@ static aq_status ensure_f16(aq_policy* p, int64_t batch, hipStream_t st) {
     for (const LayerBuf& b : p->L)  // (fully connected layers' maps may lie in operand order)
         if (b.fc) n = std::max(n, 2 * blocked_map_bytes(batch, b.N));
     for (int i = 0; i < 2; ++i)
-        if (hipMalloc(&p->act_f16[i], n) != hipSuccess) return AQ_ENOMEM;
+        if (hip_failed(hipMalloc(&p->act_f16[i], n))) return AQ_ENOMEM;
     p->cap_f16 = batch;
     return AQ_OK;
 }
@@ -577,9 +577,9 @@ static aq_status ensure_f32_kept(aq_policy* p, hipStream_t st) {
     } up{};
     const size_t bytes = f32_store_layout(p, true, up.tab);
     char* slab = nullptr;
-    if (hipMalloc((void**)&slab, bytes + sizeof(up)) != hipSuccess) return AQ_ENOMEM;
+    if (hip_failed(hipMalloc((void**)&slab, bytes + sizeof(up)))) return AQ_ENOMEM;
     up.ptrs = f32_store_ptrs(up.tab, slab);
-    if (hipMemcpy(slab + bytes, &up, sizeof(up), hipMemcpyHostToDevice) != hipSuccess) {
+    if (hip_failed(hipMemcpy(slab + bytes, &up, sizeof(up), hipMemcpyHostToDevice))) {
         (void)hipFree(slab);
         return AQ_EHIP;
     }
@@ -601,9 +601,9 @@ static aq_status ensure_f32_passed(aq_policy* p) {
     const size_t bytes = f32_store_layout(p, false, tab);
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     AQ_HIP_CHECK(hipThreadExchangeStreamCaptureMode(&mode));
-    const hipError_t e = hipMalloc(&S.slab, bytes);
+    const bool failed = hip_failed(hipMalloc(&S.slab, bytes));
     AQ_HIP_CHECK(hipThreadExchangeStreamCaptureMode(&mode));
-    if (e != hipSuccess) {
+    if (failed) {
         S.slab = nullptr;
         return AQ_ENOMEM;
     }
@@ -618,7 +618,7 @@ static int8_t* few_maps_of(aq_policy* p, hipStream_t st) {
     int i = 0;
     while (i < p->few_streams && p->few_stream[i] != st) ++i;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (i == kFewStreams || hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return nullptr;
+    if (i == kFewStreams || hip_failed(hipStreamIsCapturing(st, &cs)) || cs != hipStreamCaptureStatusNone) return nullptr;
     if (i == p->few_streams) p->few_stream[p->few_streams++] = st;
     return p->few_slab + (size_t)i * 2 * p->few_bytes;
 }
@@ -648,7 +648,7 @@ extern "C" aq_status aq_policy_set_path(aq_policy* p, int32_t path) {
             w4_bytes += need[l];
         }
         if (w4_bytes) {
-            if (hipMalloc(&p->w4_slab, w4_bytes) != hipSuccess) return AQ_ENOMEM;
+            if (hip_failed(hipMalloc(&p->w4_slab, w4_bytes))) return AQ_ENOMEM;
             size_t o4 = 0;
             for (size_t l = 0; l < p->L.size(); ++l) {
                 if (!need[l]) continue;
@@ -1339,7 +1339,7 @@ extern "C" aq_status aq_calibrate_fp32(aq_policy* p, const void* d_obs, int64_t 
     // The ranges come back through host memory that the last kernel writes and this thread watches: a copy to pageable
     // memory and a stream synchronization cost 23 us, a third of a frame policy's whole calibration.
     if (!p->calib) {
-        if (hipHostMalloc((void**)&p->calib, 64 + sizeof(float) * 2 * AQ_MAX_LAYERS, hipHostMallocDefault) != hipSuccess) {
+        if (hip_failed(hipHostMalloc((void**)&p->calib, 64 + sizeof(float) * 2 * AQ_MAX_LAYERS, hipHostMallocDefault))) {
             p->calib = nullptr;
             return AQ_ENOMEM;
         }
@@ -1359,7 +1359,7 @@ extern "C" aq_status aq_calibrate_fp32(aq_policy* p, const void* d_obs, int64_t 
             continue;
         }
         const hipError_t e = hipStreamQuery(st);
-        if (e == hipErrorNotReady) continue;
+        if (hip_failed(e) && e == hipErrorNotReady) continue;
         if (e != hipSuccess || __atomic_load_n(p->calib, __ATOMIC_ACQUIRE) != ticket) return AQ_EHIP;
     }
     const float* h = (const float*)((const char*)p->calib + 64);
@@ -1398,7 +1398,7 @@ static aq_status ensure_h16(aq_policy* p, hipStream_t st) {
     } up{};
     const size_t off_h = take((size_t)cst * 2), off_up = take(sizeof(up));
     void* slab = nullptr;
-    if (hipMalloc(&slab, bytes) != hipSuccess) return AQ_ENOMEM;
+    if (hip_failed(hipMalloc(&slab, bytes))) return AQ_ENOMEM;
     char* base = (char*)slab;
     Fp16Net& net = up.net;
     Fp16ConvTab& tab = up.tab;
@@ -1422,7 +1422,7 @@ static aq_status ensure_h16(aq_policy* p, hipStream_t st) {
         }
     }
     tab.blocks = blk;
-    if (hipMemcpy(base + off_up, &up, sizeof(up), hipMemcpyHostToDevice) != hipSuccess) {
+    if (hip_failed(hipMemcpy(base + off_up, &up, sizeof(up), hipMemcpyHostToDevice))) {
         (void)hipFree(slab);
         return AQ_EHIP;
     }

@@ -348,10 +348,17 @@ struct LayerTaps {
     float* ln;
 };
 
+// Whether a runtime call failed.  Its error ends here: the runtime keeps the last one of any call until it is asked, and a
+// launch asks (a forward launched behind an allocation that failed would answer AQ_EHIP for work that is done).
+inline bool hip_failed(hipError_t e) {
+    if (e == hipSuccess) return false;
+    (void)hipGetLastError();
+    return true;
+}
+
 }  // namespace aq
 
-#define AQ_HIP_CHECK(expr)                        \
-    do {                                          \
-        hipError_t e_ = (expr);                   \
-        if (e_ != hipSuccess) return AQ_EHIP;     \
+#define AQ_HIP_CHECK(expr)                            \
+    do {                                              \
+        if (aq::hip_failed(expr)) return AQ_EHIP;     \
     } while (0)

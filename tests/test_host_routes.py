@@ -41,12 +41,12 @@ class Host:
         binding._stream = lambda: self.stream
         self.stream = 0
 
-    def policy(self, *widths, k=67, out=21, **kw):
+    def policy(self, *widths, k=67, out=21, wbits=0, **kw):
         fc, layers = self.synth.fc, []
         for w in widths:
             layers.append(fc(k, w, "relu"))
             k = w
-        net = self.synth.small_net(layers + [fc(k, out, "none")], **kw)
+        net = dict(self.synth.small_net(layers + [fc(k, out, "none")], **kw), wbits=wbits)
         P = self.aq.Policy(net)
         n = len(net["layers"])
         P.quantize_params([Mem()] * n, [Mem()] * n, None, None, [(0.0, 1.0)] * n)
@@ -109,8 +109,38 @@ def a_few_row_forward_without_memory_to_have(h):
     assert len(h.maps(h.forward(P, 16, 64))) == 2
 
 
+def a_failed_call_leaves_no_error_behind(h):
+    """What the caller was told once is not told again by the next call, which works."""
+    aq, hip = h.aq, h.hip
+
+    def fails(status, f, *args):
+        hip.fake_fail_mallocs(1)
+        with pytest.raises(aq.AqError) as e:
+            f(*args)
+        assert e.value.status == status
+        hip.fake_fail_mallocs(0)
+
+    fails(aq.ENOMEM, h.policy, 1024, 1024)
+    assert hip.fake_live() == 0
+    P = h.policy(2048, 2048, wbits=4)  # a launch per layer: the forward needs memory
+    P.policy_reserve(4)
+    obs, out, pars = Mem(64), Mem(64), ([Mem()] * 3, [Mem()] * 3, None, None)
+    for f, args in ((P.policy_reserve, (64,)), (P.policy_forward_int8, (obs, out)), (P.policy_set_path, (4,)), (P.convert_params_fp16, pars),
+                    (P.policy_set_params_fp32, pars), (P.policy_forward_fp32_params, pars + (obs, out))):
+        fails(aq.ENOMEM, f, *args)
+        P.policy_forward_int8(Mem(4), Mem(4))
+    P.policy_set_params_fp32(*pars)
+    fails(aq.ENOMEM, P.calibrate_fp32, Mem(4))
+    P.policy_forward_int8(Mem(4), Mem(4))
+    # a stream that cannot be asked whether it is being captured: the whole network in one launch, and done
+    Q = h.policy(1024, 1024)
+    hip.fake_fail_capture_query(1)
+    assert not h.maps(h.forward(Q, 16, 64)) and len(h.logged(LAUNCH)) == 1
+    hip.fake_fail_capture_query(0)
+
+
 SCENARIOS = [few_row_forwards_allocate_nothing, policies_that_never_take_few_rows_apart_keep_no_maps,
-             a_few_row_forward_without_memory_to_have]
+             a_few_row_forward_without_memory_to_have, a_failed_call_leaves_no_error_behind]
 
 
 @pytest.fixture(scope="module")
