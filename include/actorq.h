@@ -127,8 +127,9 @@ aq_status aq_policy_destroy(aq_policy* p);
 aq_status aq_policy_reserve(aq_policy* p, int64_t max_batch);
 
 /* Chooses the 8-bit forward's launch plan: 0 = automatic (whole-network fused kernel when the
- * network is an MLP that fits it -- but for few rows on layers wider than 256, which go one launch per layer outside of
- * graph captures and on the first four streams the handle sees --, else one launch per layer, with the leading convolutions of a
+ * network is an MLP that fits it -- but for few rows on layers wider than 256, which go one launch per layer where that is
+ * faster, outside of graph captures: on the default stream, and on others while no more than three of them have such
+ * forwards of the handle in flight (an event behind each guards the maps) --, else one launch per layer, with the leading convolutions of a
  * frame policy in a single launch where their shapes allow it), 1 = fused only (AQ_ESHAPE from the
  * forward if it does not fit), 2 = one launch per layer (convolutions as in 0), 3 = one launch per
  * layer for every layer, 4 = plan 2 with sub-byte weight streaming where the policy allows it (see
@@ -149,7 +150,7 @@ aq_status aq_policy_fp16_conv_stack_layers(const aq_policy* p, int32_t* n_layers
 /* Which compiled variant of the whole-network kernels a forward of `batch` >= 1 rows launches under the
  * current launch plan: *rows = batch rows per workgroup (16, 32, 64 or 128), *tiles = 32-feature tiles per
  * wavefront and pass (1 or 2); both 0 when the forward runs one launch per layer instead (a network the
- * kernels do not take, few rows on wide layers under plan 0, or launch plan 2 / 3).  *kind is the kernel: 0 = the general kernel; 1 = the
+ * kernels do not take, few rows on wide layers under plan 0 -- told for the default stream, without exploration --, or launch plan 2 / 3).  *kind is the kernel: 0 = the general kernel; 1 = the
  * software-pipelined kernel for wide layers (64 rows, two tiles; per-channel weights, fp32 observations, hidden
  * widths multiples of 64 without LayerNorm, every K a multiple of 128, at most 64 outputs); 2 = the kernel for
  * small networks (16, 32 or 64 rows by batch size; either weight scheme, fp32 or 8-bit observations, at most four

@@ -72,7 +72,7 @@ struct F32Store {
     int blocks = 0;            // of the launch that fills it
 };
 
-constexpr int kFewStreams = 4;
+constexpr int kFewPairs = 4;
 
 struct aq_policy {
     aq_net net;
@@ -97,13 +97,15 @@ struct aq_policy {
     // activation scratch of the per-layer path (8-bit maps, the fp32 rows a LayerNorm layer hands to its row
     // kernel, the logits of an argmax head) and of the fp32 actor, grown on demand
     int64_t cap_i8 = 0, cap_f32 = 0;
-    // ... and the maps of a policy that fits the whole-network kernels but runs few rows layer by layer (few_rows_faster): a
-    // pair of them for each of the first kFewStreams streams, since a forward that needs no scratch may overlap another
-    // on a second stream.  Made with the policy: such a forward allocates nothing, as on the whole-network kernels.
+    // ... and the maps of a policy that fits the whole-network kernels but runs few rows layer by layer (few_rows_faster):
+    // kFewPairs pairs of them, since a forward that needs no scratch may overlap another on a second stream.  Made with the
+    // policy: such a forward allocates nothing, as on the whole-network kernels.  Pair 0 belongs to the default stream,
+    // which is the same one for good.  Any other handle may name a new stream once its own is destroyed, perhaps with work
+    // in flight: those pairs are guarded by an event behind their last forward, whatever stream it was on.
     size_t few_bytes = 0;  // of one map; 0: the policy never takes that route
     int8_t* few_slab = nullptr;
-    hipStream_t few_stream[kFewStreams] = {};
-    int few_streams = 0;
+    hipStream_t few_stream[kFewPairs] = {};  // of the pair's last forward
+    hipEvent_t few_done[kFewPairs] = {};
     int8_t* act_i8[2] = {nullptr, nullptr};
     float* ln_x = nullptr;
     float* y_rows = nullptr;
@@ -227,6 +229,12 @@ static F32Ptrs f32_store_ptrs(const F32KeepTab& tab, char* base) {
             (float*)(base + e.off);
     }
     return ptrs;
+}
+
+static void few_free(aq_policy* p) {
+    if (p->few_slab) (void)hipFree(p->few_slab);
+    for (hipEvent_t e : p->few_done)
+        if (e) (void)hipEventDestroy(e);
 }
 
 extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
@@ -387,12 +395,21 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         size_t lds = 0;
         for (int l = 0; l < net->n_layers - 1; ++l) few_n = std::max(few_n, p->L[l].N);
         // (one row: if the layers' launches are not faster there, they are at no batch)
-        if (fused_mlp_supported(probe, &r, &lds) && few_rows_faster(probe, false)) {
+        if (fused_mlp_supported(probe, &r, &lds) && few_rows_faster(probe, false, false)) {
             p->few_bytes = (blocked_map_bytes(kFewMaxRows, few_n) + 255) & ~(size_t)255;
-            if (hip_failed(hipMalloc((void**)&p->few_slab, 2 * kFewStreams * p->few_bytes))) {
+            if (hip_failed(hipMalloc((void**)&p->few_slab, 2 * kFewPairs * p->few_bytes))) {
                 (void)hipFree(p->slab);
                 delete p;
                 return AQ_ENOMEM;
+            }
+            for (int i = 1; i < kFewPairs; ++i) {
+                if (hip_failed(hipEventCreateWithFlags(&p->few_done[i], hipEventDisableTiming))) {
+                    p->few_done[i] = nullptr;
+                    few_free(p);
+                    (void)hipFree(p->slab);
+                    delete p;
+                    return AQ_ENOMEM;
+                }
             }
         }
     }
@@ -454,7 +471,7 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     memcpy(up.data() + (off_ftab - off_net), &ftab, sizeof(F32KeepTab));
     if (hip_failed(hipMemcpy(p->d_net, up.data(), up.size(), hipMemcpyHostToDevice))) {
         (void)hipFree(p->slab);
-        if (p->few_slab) (void)hipFree(p->few_slab);
+        few_free(p);
         delete p;
         return AQ_EHIP;
     }
@@ -462,7 +479,7 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         unsigned char* sc = nullptr;
         if (static_scratch(&sc) != AQ_OK) {
             (void)hipFree(p->slab);
-            if (p->few_slab) (void)hipFree(p->few_slab);
+            few_free(p);
             delete p;
             return AQ_EHIP;
         }
@@ -476,7 +493,7 @@ extern "C" aq_status aq_policy_destroy(aq_policy* p) {
     (void)hipDeviceSynchronize();
     if (p->slab) (void)hipFree(p->slab);
     if (p->w4_slab) (void)hipFree(p->w4_slab);
-    if (p->few_slab) (void)hipFree(p->few_slab);
+    few_free(p);
     for (int i = 0; i < 2; ++i) {
         if (p->act_i8[i]) (void)hipFree(p->act_i8[i]);
         if (p->act_f32[i]) (void)hipFree(p->act_f32[i]);
@@ -611,16 +628,29 @@ static aq_status ensure_f32_passed(aq_policy* p) {
     return AQ_OK;
 }
 
-// the pair of maps that belongs to `st`; NULL: more streams than pairs, a capture, or the handle that names another
-// stream in every thread (a forward of the thread that had the policy before may still run on its own)
-static int8_t* few_maps_of(aq_policy* p, hipStream_t st) {
-    if (st == hipStreamPerThread) return nullptr;
-    int i = 0;
-    while (i < p->few_streams && p->few_stream[i] != st) ++i;
+// The pair of maps for a forward on `st`, which waits for what may still use it; -1: `st` is being captured (or cannot say so),
+// or every pair is at work on another stream.
+static int few_pair_of(aq_policy* p, hipStream_t st) {
+    if (!st) return 0;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (i == kFewStreams || hip_failed(hipStreamIsCapturing(st, &cs)) || cs != hipStreamCaptureStatusNone) return nullptr;
-    if (i == p->few_streams) p->few_stream[p->few_streams++] = st;
-    return p->few_slab + (size_t)i * 2 * p->few_bytes;
+    if (hip_failed(hipStreamIsCapturing(st, &cs)) || cs != hipStreamCaptureStatusNone) return -1;
+    int mine = -1, idle = -1;
+    for (int i = 1; i < kFewPairs && mine < 0; ++i) {
+        if (p->few_stream[i] == st) mine = i;
+        else if (!p->few_stream[i] && idle < 0) idle = i;
+    }
+    // (on the stream of the pair's last forward there is nothing to wait for and the runtime sees that, 0.1 us; the handle
+    // may name a new one)
+    if (mine > 0) return hip_failed(hipStreamWaitEvent(st, p->few_done[mine], 0)) ? -1 : mine;
+    if (idle < 0) {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another thread may be capturing)
+        if (hip_failed(hipThreadExchangeStreamCaptureMode(&mode))) return -1;
+        for (int i = 1; i < kFewPairs && idle < 0; ++i)
+            if (!hip_failed(hipEventQuery(p->few_done[i]))) idle = i;
+        if (hip_failed(hipThreadExchangeStreamCaptureMode(&mode))) return -1;
+    }
+    if (idle > 0) p->few_stream[idle] = st;
+    return idle;
 }
 
 extern "C" aq_status aq_policy_reserve(aq_policy* p, int64_t max_batch) {
@@ -679,7 +709,7 @@ extern "C" aq_status aq_policy_fused_plan(const aq_policy* p, int64_t batch, int
     a.c.batch = batch;
     int r = 0, t = 0;
     size_t lds = 0;
-    if (p->path == 2 || !fused_mlp_supported(a, &r, &lds, &t) || (p->path == 0 && p->few_bytes && few_rows_faster(a, false))) r = t = 0;
+    if (p->path == 2 || !fused_mlp_supported(a, &r, &lds, &t) || (p->path == 0 && p->few_bytes && few_rows_faster(a, false, false))) r = t = 0;
     *rows = r;
     *tiles = t;
     *kind = r != 0 ? fused_mlp_kernel_kind(a) : 0;
@@ -1074,9 +1104,17 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
     // the allocation-free entry point: what is captured may be replayed on any stream beside any other, and needs no
     // scratch with the whole-network kernels.)
     const bool noise = ex && p->net.head != AQ_HEAD_ARGMAX;
-    int8_t* few = nullptr;
-    if (can_fuse && p->path == 0 && p->few_bytes && !fixed && few_rows_faster(a, noise) && (few = few_maps_of(p, st)) != nullptr)
-        can_fuse = false;
+    int pair = -1;
+    if (can_fuse && p->path == 0 && p->few_bytes && !fixed && few_rows_faster(a, noise, st != nullptr)) pair = few_pair_of(p, st);
+    if (pair >= 0) can_fuse = false;
+    // on every way out: the event behind this forward's last use of the pair
+    struct Done {
+        hipEvent_t e;
+        hipStream_t st;
+        ~Done() {
+            if (e && hip_failed(hipEventRecord(e, st))) (void)hip_failed(hipStreamSynchronize(st));
+        }
+    } const done{pair > 0 ? p->few_done[pair] : nullptr, st};
     const int A = p->L.back().N * p->L.back().oh * p->L.back().ow;
     if (can_fuse) {
         // Gaussian noise rides in the kernel where it writes the actions itself (an elementwise head on
@@ -1099,8 +1137,9 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
     FwdScratch sc;
     if (fixed) {
         sc = *fixed;
-    } else if (few) {
-        sc = FwdScratch{{few, few + p->few_bytes}, true, nullptr, nullptr};
+    } else if (pair >= 0) {
+        int8_t* const maps = p->few_slab + (size_t)(2 * pair) * p->few_bytes;
+        sc = FwdScratch{{maps, maps + p->few_bytes}, true, nullptr, nullptr};
     } else {
         s = ensure_i8(p, batch, st);
         if (s != AQ_OK) return s;

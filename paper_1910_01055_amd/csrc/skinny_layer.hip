@@ -64,8 +64,9 @@ void few_row_tile(int N, int64_t rows, bool argmax, int* ft, int* rt) {
 // own launches spread them over the chip.  Measured, us (whole network / layers), one to 256 rows: 67-512x2-21 10.6 / 9.4,
 // 67-512x3-21 14.5 / 12.2, 67-1024x2-21 19.8 / 9.3 (256 rows 10.6), 256-1024x3-64 31.3 / 12.0 (256 rows 14.7),
 // 111-400-300-8 10.0 / 9.6; 512 rows: 67-1024x2-21 20.3 / 15.9, 111-800-600-8 15.4 / 16.8; per-tensor weights 67-512x2-21
-// 12.2 / 9.7, 67-1024x2-21 24.1 / 9.5.
-bool few_rows_faster(const FwdArgs& a, bool noise) {
+// 12.2 / 9.7, 67-1024x2-21 24.1 / 9.5.  An event behind the forward (streams other than the default one) costs 2.8 to 3.5: 67-512x2-21
+// at one row 8.7 without, 11.6 with it, 256-1024x3-64 11.4 and 14.9.
+bool few_rows_faster(const FwdArgs& a, bool noise, bool guarded) {
     const int nl = a.net.n_layers;
     if (a.c.batch > kFewMaxRows || nl < 2) return false;
     double weights = 0.0;  // millions
@@ -82,7 +83,7 @@ bool few_rows_faster(const FwdArgs& a, bool noise) {
     for (int l = 0; l < nl; ++l)
         if (!layer_uses_skinny(a, l)) return false;
     const double whole = a.net.asym ? 8.3 + 13.0 * weights : 7.5 + 10.0 * weights;
-    const double layers = nl * (a.c.batch > 256 ? 5.0 : a.c.batch > 128 ? 3.5 : 3.1) + (noise ? 3.1 : 0.0);
+    const double layers = nl * (a.c.batch > 256 ? 5.0 : a.c.batch > 128 ? 3.5 : 3.1) + (noise ? 3.1 : 0.0) + (guarded ? 3.3 : 0.0);
     return layers < whole;
 }
 

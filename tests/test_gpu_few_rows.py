@@ -94,7 +94,7 @@ def test_wide_policies_at_few_rows_take_the_layers_launches(aq):
                 outs.append(y)
     torch.cuda.synchronize()
     assert all(np.array_equal(y.cpu().numpy(), want) for y in outs)
-    # the handle that names another stream in every thread has no maps of its own: the whole-network kernel
+    # the handle that names another stream in every thread
     with torch.cuda.stream(torch.cuda.ExternalStream(2)):
         y = torch.zeros((250, 21), device="cuda:0")
         P.policy_forward_int8(d_obs, y)

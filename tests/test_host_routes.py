@@ -82,7 +82,7 @@ def few_row_forwards_allocate_nothing(h):
         if reserve:
             P.policy_reserve(64)
         seen = []
-        for stream in (0, 64, 128, 192, 256, 0):
+        for stream in (0, 64, 128, 192, 320, 0):
             entries = h.forward(P, 16, stream)
             assert not [e for e in entries if e.kind == MALLOC], (reserve, stream)
             seen.append(h.maps(entries))
@@ -100,6 +100,38 @@ def policies_that_never_take_few_rows_apart_keep_no_maps(h):
         assert len(h.logged(MALLOC)) == n, widths
         assert (P.policy_fused_plan(1)[0] == 0) == (n == 2 or widths[0] == 2048)
         P.close()
+
+
+def streams_come_and_go(h):
+    """Pairs of maps are given back by streams that are done, and only by those; the default stream keeps its own without an
+    event; a handle that names a new stream waits for what the old one left in flight."""
+    P = h.policy(1024, 1024)
+    default = h.maps(h.forward(P, 16))
+    assert [e.kind for e in h.logged()] == [LAUNCH] * 3
+    used = set(default)
+    for n in range(1, 4):  # three streams at once, their work in flight
+        h.hip.fake_set_busy(64 * n)
+        entries = h.forward(P, 16, 64 * n)
+        assert [e.kind for e in entries] == [LAUNCH] * 3 + [RECORD] and {e.stream for e in entries} == {64 * n}
+        assert len(h.maps(entries)) == 2 and not used & h.maps(entries)
+        used |= h.maps(entries)
+    assert not h.maps(h.forward(P, 16, 1000))  # a fourth: the whole network in one launch
+    mine = h.forward(P, 16, 128)  # a handle seen before, of a new stream perhaps
+    assert [e.kind for e in mine] == [WAIT] + [LAUNCH] * 3 + [RECORD] and mine[0].in_ == mine[-1].in_
+    h.hip.fake_finish_all()
+    for n in range(20):  # a stream per episode
+        entries = h.forward(P, 16, 2000 + 64 * n)
+        assert len(h.maps(entries)) == 2 and not h.maps(entries) & default and entries[-1].kind == RECORD
+    assert h.maps(h.forward(P, 16)) == default
+    # the handle of each thread's own default stream is one like the others; a captured stream takes one launch
+    assert len(h.maps(h.forward(P, 16, 2))) == 2
+    h.hip.fake_capture(64)
+    assert not h.maps(h.forward(P, 16, 64))
+    P.close()
+    assert h.hip.fake_live() == 0
+    # where the event costs what the layers' launches gain
+    Q = h.policy(512, 512)
+    assert h.maps(h.forward(Q, 16)) and not h.maps(h.forward(Q, 16, 128))
 
 
 def a_few_row_forward_without_memory_to_have(h):
@@ -139,7 +171,7 @@ def a_failed_call_leaves_no_error_behind(h):
     hip.fake_fail_capture_query(0)
 
 
-SCENARIOS = [few_row_forwards_allocate_nothing, policies_that_never_take_few_rows_apart_keep_no_maps,
+SCENARIOS = [few_row_forwards_allocate_nothing, streams_come_and_go, policies_that_never_take_few_rows_apart_keep_no_maps,
              a_few_row_forward_without_memory_to_have, a_failed_call_leaves_no_error_behind]
 
 
