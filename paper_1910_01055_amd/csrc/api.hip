@@ -130,6 +130,7 @@ struct aq_policy {
     F32Store f32_passed;  // made by the first aq_policy_forward_fp32_params (its table with the policy)
     bool f32_ready = false;
     int f32_stack = 0;    // leading convolutions that the fp32 actor runs in one launch
+    Fp32StackWork f32_work;
     // policies of at most 4 bits, per-channel symmetric, under launch plan 4: the fully connected layers' weights
     // once more as nibbles, for the few-row kernel (one allocation when the plan is first chosen; rewritten by
     // the first forward pass after every quantize / import)
@@ -385,7 +386,7 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
     p->h_net.in_u8 = net->in_type == AQ_IN_U8;
     p->h_net.asym = net->wscheme == AQ_W_TENSOR_ASYM_U8;
     p->h_net.ln_eps = net->ln_eps;
-    p->f32_stack = fp32_conv_stack_layers(p->h_net);
+    p->f32_stack = fp32_conv_stack_layers(p->h_net, &p->f32_work);
     F32KeepTab ftab{};  // of parameters passed with a call
     (void)f32_store_layout(p, false, ftab);
     {
@@ -732,14 +733,9 @@ extern "C" aq_status aq_policy_subbyte_layers(const aq_policy* p, int64_t batch,
     return AQ_OK;
 }
 
-// A frame policy's convolutions in one launch, an image per CU, where that fills the chip; a few images, or the last ones of
-// a second round, are faster in the layers' own launches, which spread an image over several CUs.  fp32 forward, us (one
-// launch / the layers'): 84 x 84 x 4 through 32, 64, 64 at 32 images 41.6 / 36.0, 48 43.5 / 41.9, 64 43.5 / 46.9, 256
-// 52.0 / 92.3, 300 87 / 100, 600 124 / 168; 61 x 61 x 3 through 16, 32, 32 at 32 images 26.0 / 25.2, 48 25.8 / 27.2, 256
-// 27.3 / 37.3, 300 42.1 / 39.0, 600 60.5 / 61.6.
+// how many convolutions of a frame policy run in one launch at this batch
 static int f32_stack_layers(const aq_policy* p, int64_t batch) {
-    const int64_t rounds = (batch + 255) / 256;
-    return p->conv_stack && batch * 100 >= rounds * 256 * (rounds == 1 ? 19 : 60) ? p->f32_stack : 0;
+    return p->conv_stack && p->f32_stack && fp32_conv_stack_faster(p->f32_work, p->f32_stack, batch) ? p->f32_stack : 0;
 }
 
 extern "C" aq_status aq_policy_fp32_plan(const aq_policy* p, int64_t batch, int32_t* rows, int32_t* tiles) {

@@ -421,8 +421,9 @@ __global__ __launch_bounds__(CF_T) void k_fp32_conv_stack(const CfArgs A, const 
 // Feature tiles of a wavefront, position groups and parts of K of a layer: so that the slowest of the matrix cores (16 clocks
 // an MFMA, two wavefronts on each SIMD), the splitting (48 instructions of 4 clocks for an operand) and the weights' way through the
 // vector memory path (52 bytes a clock, once per position group) takes least; `spare` bytes of LDS hold parts of K.  (Two
-// wavefronts on a SIMD hide about a quarter of matrix and vector instructions behind each other: measured.)
-bool plan_layer(CfLayer& q, bool u8, int64_t spare) {
+// wavefronts on a SIMD hide about a quarter of matrix and vector instructions behind each other: measured.)  Returns those
+// clocks, 0 where nothing fits.
+double plan_layer(CfLayer& q, bool u8, int64_t spare) {
     double best = 1e300;
     const int tiles = (q.R + 15) / 16;
     const int64_t map = (int64_t)q.R * q.out_ld * 4;
@@ -448,10 +449,10 @@ bool plan_layer(CfLayer& q, bool u8, int64_t spare) {
             }
         }
     }
-    return best < 1e300;
+    return best < 1e300 ? best : 0.0;
 }
 
-bool plan_cf(const NetDev& net, CfArgs* A, size_t* lds) {
+bool plan_cf(const NetDev& net, CfArgs* A, size_t* lds, double* clocks) {
     if (!net.in_u8) return false;
     int nc = 0;
     while (nc < net.n_layers && !(net.L[nc].kh == 1 && net.L[nc].kw == 1 && net.L[nc].in_h == 1 && net.L[nc].in_w == 1)) ++nc;
@@ -504,7 +505,9 @@ bool plan_cf(const NetDev& net, CfArgs* A, size_t* lds) {
     for (int l = 0; l < nc; ++l) {
         CfLayer& q = A->L[l];
         const int64_t out = (int64_t)q.R * q.out_ld * 4, spare = (int64_t)CF_MAX_LDS - (int64_t)at - in - out;
-        if (spare < 0 || !plan_layer(q, l == 0, spare)) return false;
+        const double c = spare < 0 ? 0.0 : plan_layer(q, l == 0, spare);
+        if (c == 0.0) return false;
+        *clocks += c;
         q.in_off = l & 1 ? (int)(CF_MAX_LDS - in) : (int)at;
         q.out_off = l & 1 ? (int)at : (int)(CF_MAX_LDS - out);
         q.part_off = (int)at + (int)(l & 1 ? out : in);
@@ -515,17 +518,42 @@ bool plan_cf(const NetDev& net, CfArgs* A, size_t* lds) {
 }
 }  // namespace
 
-int fp32_conv_stack_layers(const NetDev& net) {
+int fp32_conv_stack_layers(const NetDev& net, Fp32StackWork* w) {
     CfArgs A{};
     size_t lds = 0;
-    return plan_cf(net, &A, &lds) ? A.nc : 0;
+    double clocks = 0.0;
+    if (!plan_cf(net, &A, &lds, &clocks)) return 0;
+    *w = Fp32StackWork{};
+    w->round = clocks / 2400.0;
+    w->ragged = 1e-3 * (double)A.frame_bytes * (A.row_bytes & 3 ? 2 : A.row_bytes & 7 ? 1 : 0);
+    for (int l = 0; l < A.nc; ++l) {
+        w->operands += 1e-6 * A.L[l].R * A.L[l].K;
+        w->products += 1e-6 * A.L[l].R * A.L[l].K * A.L[l].N;
+    }
+    return A.nc;
+}
+
+// One launch, an image per CU and a round of 256 images after the other, or the layers' own launches, which spread a few images
+// over several CUs, keep the chip full between rounds and, on many small frames, run at a rate that one image per CU does not
+// reach.  fp32 forward, us (one launch / the layers'): 84 x 84 x 4 through 32, 64, 64 at 32 images 41.4 / 35.6, 49 41.4 / 40.9, 64
+// 41.7 / 48.0, 256 45.9 / 86.4, 257 78.1 / 93.2, 768 113 / 181; 61 x 61 x 3 through 16, 32, 32 at 256 25.4 / 35.5, 512 42.0 / 64.1,
+// 900 79.7 / 70.0, 2048 155 / 122; 52 x 52 x 1 through the same at 256 20.2 / 27.5, 513 42.5 / 37.2, 768 42.5 / 43.1, 2048 96.7 / 72.2.
+// The estimates are fitted to 1639 measured pairs, 56 stacks of one to four layers on frames of 20 to 100 pixels a side and 1 to 4
+// channels at 8 to 4096 images; what the rule takes is within 4 % of the faster one in 1588 of them and at most 13 % behind the layers'
+// launches (tiny frames of a second round just begun).
+bool fp32_conv_stack_faster(const Fp32StackWork& w, int nc, int64_t batch) {
+    const double n = (double)batch, rounds = (double)((batch + 255) / 256);
+    // (in the first round the layers' launches do not fill the chip and hide less behind each other)
+    if (batch <= 256) return 3.15 * nc + n * (0.41 * w.operands + 0.0235 * w.products) > 3.4 + 1.5 * w.round + 0.07 * w.ragged;
+    return 5.0 * nc + n * (0.556 * w.operands + 0.009 * w.products) > rounds * (4.07 + 1.36 * w.round + 0.24 * w.ragged);
 }
 
 aq_status launch_fp32_conv_stack(const NetDev& net, const F32Ptrs& ptrs, const void* frames, int64_t batch, float* out, RangeSlot* slots,
                                  hipStream_t st) {
     CfArgs A{};
     size_t lds = 0;
-    if (!plan_cf(net, &A, &lds)) return AQ_ESHAPE;
+    double clocks = 0.0;
+    if (!plan_cf(net, &A, &lds, &clocks)) return AQ_ESHAPE;
     for (int l = 0; l < A.nc; ++l) {
         A.L[l].w = (const char*)ptrs.wsp[l];
         A.L[l].wrow = ptrs.w[l];

@@ -185,7 +185,14 @@ aq_status launch_fp32_mlp(const NetDev& n, const NetDev* d_net, const F32Ptrs& p
 // the leading convolutions of a frame policy in one launch (fp32_conv_stack.hip): how many layers (0: none of these shapes;
 // their weights are also kept split), and the launch, which writes the last one's map to `out`; with slots also the
 // ranges of the frames and of every map
-int fp32_conv_stack_layers(const NetDev& n);
+// What the choice between it and the layers' own launches goes by: the launch's time for a round of 256 images by its plan, us;
+// kilobytes of a frame whose rows are no whole pieces of 8 bytes, twice where they are none of 4; of the layers, millions of operand
+// values and of products an image
+struct Fp32StackWork {
+    double round = 0.0, ragged = 0.0, operands = 0.0, products = 0.0;
+};
+bool fp32_conv_stack_faster(const Fp32StackWork& w, int nc, int64_t batch);
+int fp32_conv_stack_layers(const NetDev& n, Fp32StackWork* w);
 aq_status launch_fp32_conv_stack(const NetDev& n, const F32Ptrs& ptrs, const void* frames, int64_t batch, float* out, RangeSlot* slots,
                                  hipStream_t st);
 aq_status launch_fp32_ln_tanh(float* x, int64_t rows, int N, const float* gamma, const float* beta, float eps,

@@ -134,6 +134,29 @@ def streams_come_and_go(h):
     assert h.maps(h.forward(Q, 16)) and not h.maps(h.forward(Q, 16, 128))
 
 
+def fp32_convolutions_of_small_frames(h):
+    """One launch for the convolutions while that is faster: not for rounds of images without number, each of which gives a CU one
+    small frame."""
+    conv, fc = h.synth.conv, h.synth.fc
+    for side, stack, ch, one, many in ((84, 4, 32, (64, 256, 257, 300, 1000, 2048), ()), (52, 1, 16, (49, 256, 512), (1300, 2048, 4096)),
+                                       (61, 3, 16, (100, 256, 512), (900, 1500, 2048)), (52, 3, 32, (100, 256, 512), (1300, 3000, 4096))):
+        layers, n, c = [], side, stack
+        for out, k, s in ((ch, 8, 4), (2 * ch, 4, 2), (2 * ch, 3, 1)):
+            layers.append(conv(n, n, c, out, k, k, s, "relu"))
+            n, c = (n - k) // s + 1, out
+        net = h.synth.small_net(layers + [fc(n * n * c, 256, "relu"), fc(256, 6, "none")], head="linear", in_type="u8")
+        P = h.aq.Policy(net)
+        P.policy_set_params_fp32([Mem()] * 5, [Mem()] * 5, None, None)
+        for batch in one + many:
+            P.policy_reserve(batch)
+            assert (P.policy_fp32_plan(batch)[1][0][0] == 0) == (batch in one), (side, stack, ch, batch)
+            h.hip.fake_clear()
+            P.policy_forward_fp32(Mem(batch), Mem(batch))
+            names = [e.name for e in h.logged(LAUNCH)]
+            assert len(names) == (3 if batch in one else 5) and any(b"conv_stack" in x for x in names) == (batch in one)
+        P.close()
+
+
 def a_few_row_forward_without_memory_to_have(h):
     """... answers OK: it needs none."""
     P = h.policy(1024, 1024)
@@ -171,7 +194,7 @@ def a_failed_call_leaves_no_error_behind(h):
     hip.fake_fail_capture_query(0)
 
 
-SCENARIOS = [few_row_forwards_allocate_nothing, streams_come_and_go, policies_that_never_take_few_rows_apart_keep_no_maps,
+SCENARIOS = [few_row_forwards_allocate_nothing, streams_come_and_go, fp32_convolutions_of_small_frames, policies_that_never_take_few_rows_apart_keep_no_maps,
              a_few_row_forward_without_memory_to_have, a_failed_call_leaves_no_error_behind]
 
 
