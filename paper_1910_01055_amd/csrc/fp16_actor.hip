@@ -699,13 +699,18 @@ void launch_layer_cfg(const Fp16Layer& L, const void* in, int in_mode, bool piec
 }
 }  // namespace
 
-// Any layer with few workgroups on the tiled kernel (8-bit observations excepted), and rows that are no whole pieces of 8 values,
-// which that one stages one by one, for longer.  us at this kernel / the tiled one: 67-1024x3-21 at 512 rows 19.6 / 31.9, 1000
-// 28.9 / 33.3, 1500 35.3 / 36.7, 2000 44.2 / 38.5; 67-2048x3-21 at 256 rows 24.0 / 56.3, 700 45.7 / 57.5, 67-1100-900-21 at 700
-// 16.5 / 42.8, 2000 38.4 / 51.6.
+// The few-row kernel spreads a layer of few output tiles (32 rows x 32 features) over the chip; the tiled kernel moves fewer bytes
+// from many tiles on: sooner where K is short or the features are few and the activations weigh most, later where it stages rows
+// of no whole 8 values one by one, which takes it longer from 16-bit rows than from fp32 ones.  8-bit observations take the tiled
+// kernel.  Measured on 1743 layers of 8 to 2048 features, K 17 to 3136, 60 to 25600 rows: what the rule takes is within 4 % of the
+// faster kernel in 1603 of them and 1 % behind it on average (by up to 50 %: ragged rows at many tiles).  Policies of such layers, us
+// on the few-row / the tiled kernel: 16-512-128-9 at 2048 rows 14.3 / 16.3, 6400 21.8 / 17.0; 384-256-9 at 1024 7.0 / 8.3, 3200
+// 12.9 / 9.7; 16-1024-1500-9 at 800 21.6 / 26.5, 2133 35.8 / 31.5; 67-2048x3-21 at 256 24.0 / 56.3, 700 45.7 / 57.5.
 bool fp16_layer_is_skinny(const Fp16Layer& L, int in_mode, int64_t rows) {
-    const int64_t tiled_wgs = ((rows + 31) / 32) * (int64_t)((L.NT + HW - 1) / HW);
-    return in_mode != 2 && L.fc && tiled_wgs < (L.K % 8 ? 512 : 400) && (rows + 15) / 16 <= 65535;
+    if (in_mode == 2 || !L.fc || (rows + 15) / 16 > 65535) return false;
+    double most = L.K < 200 || L.NT <= 8 ? 600.0 : 1000.0;
+    if (L.K % 8) most *= in_mode == 1 ? 1.5 : 2.7;
+    return (double)((rows + 31) / 32) * L.NT < most;
 }
 
 namespace {

@@ -65,6 +65,20 @@ def test_fp16_few_row_layers_against_the_oracle(aq, odd, head, batch):
     H._check(net, params, obs, actions, outs, end_to_end=False)
 
 
+@pytest.mark.parametrize("channels,batches", [(8, (4768, 4769)), (9, (12928, 12929))])
+def test_fp16_layers_at_the_last_rows_of_the_few_row_kernel(aq, channels, batches):
+    """... and the first of the tiled one: a hidden layer of 200 inputs, and of 225, behind a convolution."""
+    net = synth.small_net([synth.conv(12, 12, 2, channels, 4, 4, 2, "relu"), fc(25 * channels, 100, "relu"), fc(100, 11, "none")],
+                          head="argmax", in_type="u8", init="he_normal")
+    params = synth.make_params(net, nonzero_bias=True)
+    for batch in batches:
+        print(f"[fp16 few rows] {channels} batch={batch}", flush=True)
+        obs = synth.make_obs(net, batch)
+        actions, outs = H._run_gpu(aq, net, params, obs)
+        rows = np.unique(np.concatenate([[0, 15, 16, 31, 32, batch - 2, batch - 1], np.random.default_rng(3).integers(0, batch, 40)]))
+        H._check(net, params, obs[rows], actions[rows], [o.reshape(batch, -1)[rows] for o in outs], end_to_end=False)
+
+
 def test_wide_policies_at_few_rows_take_the_layers_launches(aq):
     """Which plan an MLP that fits the whole-network kernels takes on either side of the rule, and the same integers from both
     plans, from a second stream while the first is busy, and from more streams than there are pairs of maps."""

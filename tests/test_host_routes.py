@@ -157,6 +157,28 @@ def fp32_convolutions_of_small_frames(h):
         P.close()
 
 
+def half_precision_layers_by_their_output_tiles(h):
+    """The last batch of the few-row kernel and the first of the tiled one, for each side of the rule: short and long K, few and many
+    features, rows of whole 8 values and not, fp32 and 16-bit inputs.  (A layer of 6000 keeps the policy from one launch.)"""
+    fc = h.synth.fc
+    for layers, at, last in (([fc(16, 6000, "relu"), fc(6000, 128, "relu"), fc(128, 9, "none")], 1, 4768),
+                             ([fc(16, 6000, "relu"), fc(6000, 128, "relu"), fc(128, 9, "none")], 2, 19168),
+                             ([fc(16, 6000, "relu"), fc(6000, 300, "relu"), fc(300, 9, "none")], 1, 3168),
+                             ([fc(16, 6001, "relu"), fc(6001, 128, "relu"), fc(128, 9, "none")], 1, 12928),
+                             ([fc(200, 6000, "relu"), fc(6000, 9, "none")], 0, 160),
+                             ([fc(203, 6000, "relu"), fc(6000, 9, "none")], 0, 224)):
+        net = h.synth.small_net(layers, head="linear")
+        P, n = h.aq.Policy(net), len(layers)
+        P.convert_params_fp16([Mem()] * n, [Mem()] * n, None, None)
+        for batch in (last, last + 1):
+            P.policy_reserve(batch)
+            h.hip.fake_clear()
+            P.policy_forward_fp16(Mem(batch), Mem(batch))
+            names = [e.name for e in h.logged(LAUNCH)]
+            assert len(names) == n and (b"k_layer_fp16_rows" in names[at]) == (batch == last), (layers, batch, names)
+        P.close()
+
+
 def a_few_row_forward_without_memory_to_have(h):
     """... answers OK: it needs none."""
     P = h.policy(1024, 1024)
@@ -194,7 +216,7 @@ def a_failed_call_leaves_no_error_behind(h):
     hip.fake_fail_capture_query(0)
 
 
-SCENARIOS = [few_row_forwards_allocate_nothing, streams_come_and_go, fp32_convolutions_of_small_frames, policies_that_never_take_few_rows_apart_keep_no_maps,
+SCENARIOS = [few_row_forwards_allocate_nothing, streams_come_and_go, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
              a_few_row_forward_without_memory_to_have, a_failed_call_leaves_no_error_behind]
 
 
