@@ -419,7 +419,7 @@ aq_status launch_stack_t(const FwdArgs& a, const StackPlan& p, const StackArgs& 
     auto* const kernel = k_conv_stack<TAPS, WLDS, W>;
     static std::atomic<bool> attr_set{false};
     if (!attr_set) {
-        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)CS_MAX_LDS) != hipSuccess) return AQ_EHIP;
+        if (hip_failed(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)CS_MAX_LDS))) return AQ_EHIP;
         attr_set = true;
     }
     const int64_t most = 256 * (CS_W / W);

@@ -936,7 +936,7 @@ aq_status launch_tile(Fp32Layer L, const void* in, float* out, int64_t rows, Ran
     constexpr size_t lds = fp32_layer_lds(t.ft, t.rt, t.wm, t.wk, t.ks);
     static std::atomic<bool> attr_set{false};
     if (!attr_set) {
-        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return AQ_EHIP;
+        if (hip_failed(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds))) return AQ_EHIP;
         attr_set = true;
     }
     hipLaunchKernelGGL(kernel, grid, dim3(FT_), lds, st, L, in, out, rows, slots);
@@ -1031,8 +1031,8 @@ aq_status launch_fp32_mlp(const NetDev& n, const NetDev* d_net, const F32Ptrs& p
     do {                                                                                                                \
         static std::atomic<bool> attr_set{false};                                                                       \
         if (!attr_set) {                                                                                                \
-            if (hipFuncSetAttribute((const void*)k_fp32_mlp<RTV, U, BV>, hipFuncAttributeMaxDynamicSharedMemorySize,     \
-                                    160 * 1024) != hipSuccess)                                                          \
+            if (hip_failed(hipFuncSetAttribute((const void*)k_fp32_mlp<RTV, U, BV>,                                     \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)))                \
                 return AQ_EHIP;                                                                                         \
             attr_set = true;                                                                                            \
         }                                                                                                               \

@@ -210,8 +210,8 @@ aq_status launch_fp16_conv_stack(const Fp16Layer* L, int n_layers, const void* o
     S.off_bias = p.off_bias;
     static std::atomic<bool> attr_set{false};
     if (!attr_set) {
-        if (hipFuncSetAttribute((const void*)k_fp16_conv_stack, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)FS_MAX_LDS) != hipSuccess)
+        if (hip_failed(hipFuncSetAttribute((const void*)k_fp16_conv_stack, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)FS_MAX_LDS)))
             return AQ_EHIP;
         attr_set = true;
     }

@@ -432,8 +432,8 @@ aq_status launch_fp16_mlp(const Fp16Net& n, const Fp16Net* d_net, const void* ob
     do {                                                                                                                      \
         static std::atomic<bool> attr_set{false};                                                                             \
         if (!attr_set) {                                                                                                      \
-            if (hipFuncSetAttribute((const void*)k_fp16_mlp<RT, U, TP>, hipFuncAttributeMaxDynamicSharedMemorySize,           \
-                                    160 * 1024) != hipSuccess)                                                                \
+            if (hip_failed(hipFuncSetAttribute((const void*)k_fp16_mlp<RT, U, TP>,                                            \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)))                      \
                 return AQ_EHIP;                                                                                               \
             attr_set = true;                                                                                                  \
         }                                                                                                                     \

@@ -561,7 +561,7 @@ aq_status launch_fp32_conv_stack(const NetDev& net, const F32Ptrs& ptrs, const v
     }
     static std::atomic<bool> attr_set{false};
     if (!attr_set) {
-        if (hipFuncSetAttribute((const void*)k_fp32_conv_stack, hipFuncAttributeMaxDynamicSharedMemorySize, (int)CF_MAX_LDS) != hipSuccess)
+        if (hip_failed(hipFuncSetAttribute((const void*)k_fp32_conv_stack, hipFuncAttributeMaxDynamicSharedMemorySize, (int)CF_MAX_LDS)))
             return AQ_EHIP;
         attr_set = true;
     }

@@ -718,8 +718,8 @@ template <int MT, int NB, bool ASYM, bool TAPS, bool HALF>
 aq_status launch_fused_t(const FwdArgs& a, size_t lds, hipStream_t st) {
     static std::atomic<bool> attr_set{false};
     if (!attr_set) {
-        if (hipFuncSetAttribute((const void*)k_mlp_fused<MT, NB, ASYM, TAPS, HALF>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+        if (hip_failed(hipFuncSetAttribute((const void*)k_mlp_fused<MT, NB, ASYM, TAPS, HALF>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)))
             return AQ_EHIP;
         attr_set = true;
     }

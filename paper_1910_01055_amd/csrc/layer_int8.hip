@@ -395,8 +395,8 @@ static aq_status launch_layer_t(const FwdArgs& a, int l, const LayerIO& io, int6
     do {                                                                                                            \
         static std::atomic<bool> attr_set{false};                                                                          \
         if (!attr_set) {                                                                                            \
-            if (hipFuncSetAttribute((const void*)k_layer_int8<W, MT, NB, AS, TP, DEEP>,                                   \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)          \
+            if (hip_failed(hipFuncSetAttribute((const void*)k_layer_int8<W, MT, NB, AS, TP, DEEP>,                  \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)))            \
                 return AQ_EHIP;                                                                                     \
             attr_set = true;                                                                                        \
         }                                                                                                           \

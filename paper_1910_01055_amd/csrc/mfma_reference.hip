@@ -9,7 +9,7 @@
 // matrix cores (8192 op/clock) are both saturated.  No epilogue, no barrier, no output but the accumulators of
 // workgroup 0, which a test checks.  The matrix cores' clock under load depends on the operands (a loop on
 // zeros runs about a third faster than one on random bytes), which is why the operands are arguments.
-#include <mutex>
+#include <atomic>
 
 #include "kernels.hpp"
 
@@ -93,14 +93,13 @@ __global__ __launch_bounds__(512) void k_mfma_reference(const char* __restrict__
 
 aq_status launch_mfma_reference(const void* d_weights, const void* d_acts, int ksteps, bool stream_weights, int workgroups,
                                 int32_t* d_acc, hipStream_t st) {
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute((const void*)k_mfma_reference<true>, hipFuncAttributeMaxDynamicSharedMemorySize, RLDS);
-        if (attr_err == hipSuccess)
-            attr_err = hipFuncSetAttribute((const void*)k_mfma_reference<false>, hipFuncAttributeMaxDynamicSharedMemorySize, RLDS);
-    });
-    if (attr_err != hipSuccess) return AQ_EHIP;
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set) {
+        if (hip_failed(hipFuncSetAttribute((const void*)k_mfma_reference<true>, hipFuncAttributeMaxDynamicSharedMemorySize, RLDS)) ||
+            hip_failed(hipFuncSetAttribute((const void*)k_mfma_reference<false>, hipFuncAttributeMaxDynamicSharedMemorySize, RLDS)))
+            return AQ_EHIP;
+        attr_set = true;
+    }
     if (stream_weights)
         hipLaunchKernelGGL((k_mfma_reference<true>), dim3((unsigned)workgroups), dim3(512), RLDS, st, (const char*)d_weights,
                            (const int8_t*)d_acts, ksteps, d_acc);

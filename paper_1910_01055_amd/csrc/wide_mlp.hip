@@ -16,7 +16,7 @@
 // Shapes: per-channel symmetric weights, fp32 observations at a 16-byte aligned address, every hidden layer
 // ReLU / none (no LayerNorm) with a width that is a multiple of 64, every layer's K a multiple of 128, a
 // last layer of at most 64 outputs.  Everything else takes the general fused kernel.
-#include <mutex>
+#include <atomic>
 
 #include "fused_mlp.hpp"
 
@@ -415,12 +415,12 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
 
 template <bool TAPS>
 aq_status launch_wide_t(const FwdArgs& a, size_t lds, hipStream_t st) {
-    static std::once_flag once;
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(once, [] {
-        attr_err = hipFuncSetAttribute((const void*)k_mlp_wide<TAPS>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    });
-    if (attr_err != hipSuccess) return AQ_EHIP;
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set) {
+        if (hip_failed(hipFuncSetAttribute((const void*)k_mlp_wide<TAPS>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)))
+            return AQ_EHIP;
+        attr_set = true;
+    }
     const unsigned grid = (unsigned)((a.c.batch + WROWS - 1) / WROWS);
     hipLaunchKernelGGL((k_mlp_wide<TAPS>), dim3(grid), dim3(FT), lds, st, a.d_net, a.c, TapParam<TAPS>(a.t));
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;

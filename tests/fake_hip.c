@@ -24,7 +24,7 @@ typedef struct {
 } Dim3;
 
 static _Thread_local int last_error;
-static int fail_mallocs, fail_capture_query, live;
+static int fail_mallocs, fail_capture_query, fail_attributes, live;
 static Entry logged[4096];
 static int entries;
 static uintptr_t capturing_stream = ~(uintptr_t)0, busy[64];
@@ -58,6 +58,7 @@ static int is_busy(void* s) {
 /* ---- what the test sets and reads */
 void fake_fail_mallocs(int on) { fail_mallocs = on; }
 void fake_fail_capture_query(int on) { fail_capture_query = on; }
+void fake_fail_attributes(int on) { fail_attributes = on; }
 void fake_capture(uintptr_t s) { capturing_stream = s; }
 void fake_set_busy(uintptr_t s) { busy[n_busy++ & 63] = s; }
 void fake_finish_all(void) {
@@ -115,7 +116,10 @@ int hipStreamSynchronize(void* s) { (void)s; return OK; }
 int hipStreamQuery(void* s) { (void)s; return OK; }
 int hipGetDevice(int* d) { *d = 0; return OK; }
 int hipGetDeviceCount(int* n) { *n = 1; return OK; }
-int hipFuncSetAttribute(const void* f, int a, int v) { (void)f; (void)a; (void)v; return OK; }
+int hipFuncSetAttribute(const void* f, int a, int v) {
+    (void)f; (void)a; (void)v;
+    return ret(fail_attributes ? INVALID : OK);
+}
 int hipGetSymbolAddress(void** p, const void* sym) {
     static char mem[17 << 20] __attribute__((aligned(256)));
     (void)sym;

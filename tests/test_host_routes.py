@@ -216,8 +216,36 @@ def a_failed_call_leaves_no_error_behind(h):
     hip.fake_fail_capture_query(0)
 
 
+def a_refused_amount_of_lds_is_told_once(h):
+    """... by the call whose kernel asked for it; the same call later, where it is granted, works."""
+    fc, conv, small = h.synth.fc, h.synth.conv, h.synth.small_net
+    frames = small([conv(84, 84, 4, 32, 8, 8, 4, "relu"), conv(20, 20, 32, 64, 4, 4, 2, "relu"), conv(9, 9, 64, 64, 3, 3, 1, "relu"),
+                    fc(3136, 512, "relu"), fc(512, 18, "none")], head="linear", in_type="u8")
+    mlp = lambda *w: small([fc(a, b, "relu") for a, b in zip(w, w[1:])] + [fc(w[-1], 21, "none")])
+    for net, batch, bits, kernel in ((mlp(67, 400, 300), 4096, 8, b"k_mlp_fused"), (mlp(256, 1024, 1024), 16384, 8, b"k_mlp_wide"),
+                                     (mlp(67, 2048, 2048), 16384, 8, b"k_layer_int8"), (frames, 256, 8, b"k_conv_stack"),
+                                     (mlp(67, 256), 4096, 16, b"k_fp16_mlp"), (frames, 256, 16, b"k_fp16_conv_stack"),
+                                     (mlp(67, 256), 4096, 32, b"k_fp32_mlp"), (mlp(67, 2048), 4096, 32, b"k_fp32_layer"),
+                                     (frames, 256, 32, b"k_fp32_conv_stack")):
+        P, n = h.aq.Policy(net), len(net["layers"])
+        P.quantize_params([Mem()] * n, [Mem()] * n, None, None, [(0.0, 1.0)] * n)
+        P.convert_params_fp16([Mem()] * n, [Mem()] * n, None, None)
+        P.policy_set_params_fp32([Mem()] * n, [Mem()] * n, None, None)
+        P.policy_reserve(batch)
+        call = {8: P.policy_forward_int8, 16: P.policy_forward_fp16, 32: P.policy_forward_fp32}[bits]
+        h.hip.fake_fail_attributes(1)
+        with pytest.raises(h.aq.AqError) as e:
+            call(Mem(batch), Mem(batch))
+        assert e.value.status == h.aq.EHIP
+        h.hip.fake_fail_attributes(0)
+        h.hip.fake_clear()
+        call(Mem(batch), Mem(batch))
+        assert any(kernel in x.name for x in h.logged(LAUNCH)), (kernel, [x.name for x in h.logged(LAUNCH)])
+        P.close()
+
+
 SCENARIOS = [few_row_forwards_allocate_nothing, streams_come_and_go, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
-             a_few_row_forward_without_memory_to_have, a_failed_call_leaves_no_error_behind]
+             a_few_row_forward_without_memory_to_have, a_failed_call_leaves_no_error_behind, a_refused_amount_of_lds_is_told_once]
 
 
 @pytest.fixture(scope="module")
