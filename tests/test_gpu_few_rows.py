@@ -115,7 +115,7 @@ def test_wide_policies_at_few_rows_take_the_layers_launches(aq):
     torch.cuda.synchronize()
     assert np.array_equal(y.cpu().numpy(), want)
     P.close()
-    # per-tensor weights, an argmax head within one workgroup, exploration behind the layers
+    # per-tensor weights, exploration behind the layers
     net = synth.small_net([fc(40, 1024, "relu"), fc(1024, 1024, "relu"), fc(1024, 30, "none")], head="tanh", wscheme="tensor_asym_u8")
     params = synth.make_params(net, nonzero_bias=True)
     obs = synth.make_obs(net, 200)
@@ -130,4 +130,70 @@ def test_wide_policies_at_few_rows_take_the_layers_launches(aq):
         P.policy_step_int8(d_obs, y, 5, 3, sigma=sigma)
         got.append(y.cpu().numpy())
     assert np.array_equal(got[0], got[1])
+    P.close()
+
+
+@pytest.mark.parametrize("actions", [16, 17, 32, 33])
+def test_wide_argmax_policies_at_few_rows(aq, actions):
+    """The layers' launches find the index in the last of them, without logits in memory: up to 32 outputs, which one workgroup
+    holds; 33 keep the whole-network kernel.  The same integers from both plans, with the logits too, and with exploration."""
+    import torch
+    net = synth.small_net([fc(40, 1024, "relu"), fc(1024, 1024, "none"), fc(1024, actions, "none")], head="argmax")
+    params = synth.make_params(net, nonzero_bias=True)
+    obs = synth.make_obs(net, 200)
+    pol, ranges = U.make_oracle(net, params, obs)
+    P, _ = U.gpu_quantize(aq, net, params, ranges)
+    for batch in (1, 33, 200):
+        print(f"few_rows argmax {actions} batch={batch}", flush=True)
+        d_obs, got = aq.to_dev(obs[:batch]), []
+        P.policy_set_path(0)
+        assert (P.policy_fused_plan(batch)[0] == 0) == (actions <= 32)
+        for path in (0, 1):
+            P.policy_set_path(path)
+            plain, _ = U.gpu_forward(P, net, obs[:batch], taps=False)
+            with_taps, taps = U.gpu_forward(P, net, obs[:batch])
+            assert np.array_equal(plain, with_taps)
+            only_y = torch.zeros((batch, actions), device=U.DEV)
+            act = torch.full((batch,), -7, dtype=torch.int32, device=U.DEV)
+            P.policy_forward_int8(d_obs, act, {"y": only_y})
+            explored = torch.full((batch,), -7, dtype=torch.int32, device=U.DEV)
+            P.policy_step_int8(d_obs, explored, 11, 4, epsilon=0.4)
+            got.append([plain, act.cpu().numpy(), only_y.cpu().numpy(), explored.cpu().numpy()])
+            U.compare_forward(net, pol, obs[:batch], with_taps, taps)
+        for a, b in zip(*got):
+            assert np.array_equal(a, b)
+        assert batch == 1 or (got[0][3] != got[0][0]).any()
+    P.close()
+
+
+def test_captured_and_allocation_free_forwards_of_a_wide_policy(aq):
+    """Both keep the whole-network kernel: a graph's replays and the static entry point beside eager forwards on the layers'
+    launches, on the same stream and another, give the same actions."""
+    import torch
+    net = synth.small_net([fc(67, 1024, "relu"), fc(1024, 1024, "relu"), fc(1024, 21, "none")], head="tanh")
+    params = synth.make_params(net, nonzero_bias=True)
+    obs = synth.make_obs(net, 96)
+    pol, ranges = U.make_oracle(net, params, obs)
+    P, _ = U.gpu_quantize(aq, net, params, ranges)
+    assert P.policy_fused_plan(96)[0] == 0
+    d_obs, side = aq.to_dev(obs), torch.cuda.Stream()
+    want = torch.zeros((96, 21), device=U.DEV)
+    P.policy_forward_int8(d_obs, want)
+    assert U.close(want.cpu().numpy(), pol.forward_int8(obs)["actions"]).all()
+    graph, y = torch.cuda.CUDAGraph(), torch.zeros((96, 21), device=U.DEV)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        P.policy_forward_int8(d_obs, y)
+    for _ in range(4):
+        y.zero_()
+        eager, static, other = (torch.zeros((96, 21), device=U.DEV) for _ in range(3))
+        torch.cuda.synchronize()
+        graph.replay()
+        P.policy_forward_int8(d_obs, eager)
+        P.policy_forward_int8_static(d_obs, static)
+        with torch.cuda.stream(side):
+            P.policy_forward_int8(d_obs, other)
+        torch.cuda.synchronize()
+        for got in (y, eager, static, other):
+            assert torch.equal(got, want)
     P.close()

@@ -52,18 +52,21 @@ def _run(aq, net, params, obs, one_launch=True):
 
 
 def _exact(net, params, obs):
-    """The actions in 64 bits."""
-    x = obs.astype(np.float64)
+    """The actions in 64 bits, and the range of every layer's input."""
+    x, ranges = obs.astype(np.float64), []
     for l, p in zip(net["layers"], params):
+        ranges.append((x.min(), x.max()))
         w = p["w"].astype(np.float64)
         if l["kind"] == "conv":
             v = np.lib.stride_tricks.sliding_window_view(x, (l["kh"], l["kw"]), (1, 2))[:, ::l["stride"], ::l["stride"]]
-            x = np.einsum("nyxcij,oijc->nyxo", v, w.reshape(l["out_c"], l["kh"], l["kw"], -1)) + p["b"]
+            n, oh, ow = v.shape[:3]
+            w = w.reshape(l["out_c"], l["kh"], l["kw"], -1).transpose(0, 3, 1, 2).reshape(l["out_c"], -1)
+            x = (v.reshape(n * oh * ow, -1) @ w.T + p["b"]).reshape(n, oh, ow, -1)
         else:
             x = x.reshape(len(x), -1) @ w.T + p["b"]
         if l["act"] == "relu":
             x = np.where(x > 0.0, x, 0.0)  # (a NaN becomes 0, as in the library)
-    return x
+    return x, np.array(ranges)
 
 
 # one image: the layers' own launches but for the smallest frames; then one launch, the second time with a second round of images
@@ -75,18 +78,17 @@ def test_fp32_convolutions_in_one_launch(aq, name, batch):
     params = synth.make_params(net, nonzero_bias=True)
     params[0]["w"] /= 255.0
     obs = synth.make_obs(net, batch)
-    rows = np.unique([0, 1 % batch, batch // 2, batch - 1])
     out, ranges = _run(aq, net, params, obs, batch > 1 or name in ("odd_3_channels", "one_channel", "ragged_features"))
-    want = _exact(net, params, obs[rows])
+    want, ref = _exact(net, params, obs)
     # fp32: 2^-24 a rounding, some 5 to 20 of them along a path, in random directions
-    assert np.abs(out[rows] - want).max() <= 2e-6 * np.abs(want).max()
-    _, ref = O.OraclePolicy(net).forward_fp32(params, obs[rows])
-    ref = np.array(ref)
+    assert np.abs(out - want).max() <= 2e-6 * np.abs(want).max()
     assert (ranges[0] == [obs.min(), obs.max()]).all()
-    slack = 1e-5 * np.abs(ref) + 1e-6  # a subset's range lies within the batch's, and is the same for all rows
-    assert (ranges[:, 0] <= ref[:, 0] + slack[:, 0]).all() and (ranges[:, 1] >= ref[:, 1] - slack[:, 1]).all()
-    if len(rows) == batch:
-        assert (np.abs(ranges - ref) <= slack).all()
+    assert (np.abs(ranges - ref) <= 1e-5 * np.abs(ref) + 1e-6).all()
+    # a subset's range lies within the batch's
+    _, few = O.OraclePolicy(net).forward_fp32(params, obs[[0, batch - 1]])
+    few = np.array(few)
+    slack = 1e-5 * np.abs(few) + 1e-6
+    assert (ranges[:, 0] <= few[:, 0] + slack[:, 0]).all() and (ranges[:, 1] >= few[:, 1] - slack[:, 1]).all()
 
 
 @pytest.mark.parametrize("layer,value", [(0, np.inf), (1, np.inf), (2, -np.inf), (1, np.nan), (0, 3.4e38), (2, 1e-38)])
@@ -107,7 +109,7 @@ def test_weights_outside_of_the_split_range(aq, layer, value):
         params[1]["w"] *= np.float32(1e-20)
     out, ranges = _run(aq, net, params, obs)
     with np.errstate(invalid="ignore"):
-        want = _exact(net, params, obs)
+        want, _ = _exact(net, params, obs)
     f = np.isfinite(want)
     assert np.array_equal(np.isnan(out), np.isnan(want)) and np.array_equal(out[~f & ~np.isnan(want)], want[~f & ~np.isnan(want)])
     assert np.allclose(out[f], want[f], rtol=1e-5)
