@@ -352,8 +352,8 @@ aq_status aq_policy_forward_int8_static(aq_policy* p, const void* d_obs, int64_t
  *   activation -- the ranges aq_quantize_params takes.  Waits for `stream` (AQ_EINVAL while it is being
  *   captured).  AQ_ENOTQUANT before aq_policy_set_params_fp32.
  * aq_policy_forward_fp32_params: the same actor on parameter arrays passed with the call (nothing is kept of
- *   them: every call packs them anew, into memory of the handle, 4 bytes per weight, that the first call
- *   allocates, under capture too), with the calibration as an optional device-side output and no wait: d_ranges_out (may be NULL)
+ *   them: every call packs them anew, into memory of the handle, 4 bytes per weight -- 10 for the convolutions
+ *   that may run in one launch --, that the first call allocates, under capture too), with the calibration as an optional device-side output and no wait: d_ranges_out (may be NULL)
  *   receives 2 * n_layers floats, (min, max) per activation tensor as above. */
 aq_status aq_policy_set_params_fp32(aq_policy* p, const float* const* h_d_w, const float* const* h_d_b,
                                     const float* const* h_d_gamma, const float* const* h_d_beta, void* stream);

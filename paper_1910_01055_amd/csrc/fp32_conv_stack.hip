@@ -8,8 +8,8 @@
 // products, exact in fp32; the three smallest (together below 2^-23 of |w x|, 2^-25 of it typically) are left out and six
 // v_mfma_f32_16x16x32_bf16 take the place of eight v_mfma_f32_16x16x4_f32 of twice their time, 3 for the first layer, whose
 // codes are bf16 values as they are.  Sums stay in fp32, with one rounding per 32 products and term instead of one per 4.
-// Error against 64 bits (2-norm, whole fp32 forwards on 84 x 84 x 4, 61 x 61 x 3, 99 x 99 x 4 and 53 x 53 x 1 frames): 4.0, 3.5,
-// 7.4 and 4.3e-7; with the fp32 instructions throughout 4.3, 4.1, 7.3 and 4.3e-7.
+// Error against 64 bits (2-norm, whole fp32 forwards of 150 random frame policies: 52 to 100 pixels a side, 1 to 4 channels): 3.36e-7
+// on average, with the fp32 instructions throughout 3.53e-7; 0.95 times theirs by the geometric mean, 0.8 to 1.2 times on single ones.
 // A layer with weights or inputs whose parts would leave bf16's range (not finite, rounding to infinity, or below 2^-100 and
 // not zero) takes the fp32 instructions on the values themselves: no part of an infinite value meets a zero.
 //
@@ -18,10 +18,10 @@
 // feature tiles.  The parts of K lie side by side in LDS; then all threads add them up and finish the map (bias, ReLU, range).
 // Layer sizes and what LDS is left set groups and parts (plan_layer).
 //
-// Bound by the matrix cores and, beside them, by the splitting: 84 x 84 x 4 through 32, 64 and 64 channels is 36.5 M bf16
-// products an image = 7.5 us of a CU.  Measured at 256 images: 37 us, of which
-// the phases' matrix and vector instructions, hardly overlapping, make some 30; as three launches of the per-layer fp32 kernel with
-// the input's range in front 5 + 35 + 29.5 + 20 us.
+// Bound by the splitting and the matrix cores in turn: 84 x 84 x 4 through 32, 64 and 64 channels at 256 images takes 35 us, vector
+// instructions 46 % and matrix instructions 30 % of it, hardly at once (the two wavefronts of a SIMD reach the same phase together);
+// a third of the LDS time is bank conflicts (3.6 k of 71 k clocks), 11 registers are spilled.  As three launches of the per-layer
+// fp32 kernel with the input's range in front 5 + 35 + 29.5 + 20 us.
 #include "fp32_split.hpp"
 
 namespace aq {
