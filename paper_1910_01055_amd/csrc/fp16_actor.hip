@@ -699,18 +699,23 @@ void launch_layer_cfg(const Fp16Layer& L, const void* in, int in_mode, bool piec
 }
 }  // namespace
 
-// The few-row kernel spreads a layer of few output tiles (32 rows x 32 features) over the chip; the tiled kernel moves fewer bytes
-// from many tiles on: sooner where K is short or the features are few and the activations weigh most, later where it stages rows
-// of no whole 8 values one by one, which takes it longer from 16-bit rows than from fp32 ones.  8-bit observations take the tiled
-// kernel.  Measured on 1743 layers of 8 to 2048 features, K 17 to 3136, 60 to 25600 rows: what the rule takes is within 4 % of the
-// faster kernel in 1603 of them and 1 % behind it on average (by up to 50 %: ragged rows at many tiles).  Policies of such layers, us
-// on the few-row / the tiled kernel: 16-512-128-9 at 2048 rows 14.3 / 16.3, 6400 21.8 / 17.0; 384-256-9 at 1024 7.0 / 8.3, 3200
-// 12.9 / 9.7; 16-1024-1500-9 at 800 21.6 / 26.5, 2133 35.8 / 31.5; 67-2048x3-21 at 256 24.0 / 56.3, 700 45.7 / 57.5.
+// The few-row kernel spreads a layer of few workgroups of the tiled one (32 rows x 128 features) over the chip, for longer where that
+// one stages rows of no whole 8 values one by one.  Narrow layers, of at most eight 32-feature tiles, count those instead: the
+// tiled kernel is the faster one sooner where K is short, and not in the measured range where a single tile leaves three of its
+// four wavefronts without one, unless 16-bit rows are short.  8-bit observations take the tiled kernel.  us on the few-row / the tiled
+// kernel, wide: 67-1024x3-21 at 512 rows 19.6 / 31.9, 1500 35.3 / 36.7, 2000 44.2 / 38.5; 67-2048x3-21 at 700 45.7 / 57.5;
+// 67-1100-900-21 at 2000 38.4 / 51.6.  Narrow, over 6676 layers of K 16 to 3136 and 60 to 66000 rows: the rule is 1.1 % behind the faster
+// kernel on average, 6.3 with the workgroups' line: 16-512-128-9 at 2048 rows 14.3 / 16.3, 6400 21.8 / 17.0; 384-256-9 at 1024 7.0 / 8.3,
+// 3200 12.9 / 9.7.  (Layers wider than that by their tiles too: 7200 whole policies 4 % slower on average than so, since a layer's
+// neighbours then lose the maps in operand order.)
 bool fp16_layer_is_skinny(const Fp16Layer& L, int in_mode, int64_t rows) {
     if (in_mode == 2 || !L.fc || (rows + 15) / 16 > 65535) return false;
-    double most = L.K < 200 || L.NT <= 8 ? 600.0 : 1000.0;
-    if (L.K % 8) most *= in_mode == 1 ? 1.5 : 2.7;
-    return (double)((rows + 31) / 32) * L.NT < most;
+    const int64_t row_tiles = (rows + 31) / 32;
+    if (L.NT > 8) return row_tiles * ((L.NT + HW - 1) / HW) < (L.K % 8 ? 512 : 400);
+    double most = L.K >= 1000 ? 1000.0 : 500.0;
+    if (L.K % 8) most *= L.K < 150 ? 1.4 : 2.5;
+    if (L.NT == 1 && (L.K >= 200 || in_mode == 1)) most = 2100.0;
+    return (double)row_tiles * L.NT < most;
 }
 
 namespace {

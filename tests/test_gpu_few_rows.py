@@ -65,7 +65,7 @@ def test_fp16_few_row_layers_against_the_oracle(aq, odd, head, batch):
     H._check(net, params, obs, actions, outs, end_to_end=False)
 
 
-@pytest.mark.parametrize("channels,batches", [(8, (4768, 4769)), (9, (12928, 12929))])
+@pytest.mark.parametrize("channels,batches", [(8, (3968, 3969)), (9, (9984, 9985))])
 def test_fp16_layers_at_the_last_rows_of_the_few_row_kernel(aq, channels, batches):
     """... and the first of the tiled one: a hidden layer of 200 inputs, and of 225, behind a convolution."""
     net = synth.small_net([synth.conv(12, 12, 2, channels, 4, 4, 2, "relu"), fc(25 * channels, 100, "relu"), fc(100, 11, "none")],

@@ -161,12 +161,16 @@ def half_precision_layers_by_their_output_tiles(h):
     """The last batch of the few-row kernel and the first of the tiled one, for each side of the rule: short and long K, few and many
     features, rows of whole 8 values and not, fp32 and 16-bit inputs.  (A layer of 6000 keeps the policy from one launch.)"""
     fc = h.synth.fc
-    for layers, at, last in (([fc(16, 6000, "relu"), fc(6000, 128, "relu"), fc(128, 9, "none")], 1, 4768),
-                             ([fc(16, 6000, "relu"), fc(6000, 128, "relu"), fc(128, 9, "none")], 2, 19168),
-                             ([fc(16, 6000, "relu"), fc(6000, 300, "relu"), fc(300, 9, "none")], 1, 3168),
-                             ([fc(16, 6001, "relu"), fc(6001, 128, "relu"), fc(128, 9, "none")], 1, 12928),
-                             ([fc(200, 6000, "relu"), fc(6000, 9, "none")], 0, 160),
-                             ([fc(203, 6000, "relu"), fc(6000, 9, "none")], 0, 224)):
+    for layers, at, last in (([fc(16, 6000, "relu"), fc(6000, 128, "relu"), fc(128, 9, "none")], 1, 7968),
+                             ([fc(16, 6000, "relu"), fc(6000, 128, "relu"), fc(128, 9, "none")], 2, 15968),
+                             ([fc(16, 6000, "relu"), fc(6000, 200, "relu"), fc(200, 9, "none")], 2, 67168),
+                             ([fc(16, 6000, "relu"), fc(6000, 200, "relu"), fc(200, 300, "relu"), fc(300, 9, "none")], 2, 4256),
+                             ([fc(16, 6000, "relu"), fc(6000, 200, "relu"), fc(200, 128, "relu"), fc(128, 9, "none")], 2, 3968),
+                             ([fc(16, 6001, "relu"), fc(6001, 128, "relu"), fc(128, 9, "none")], 1, 19968),
+                             ([fc(16, 6000, "relu"), fc(6000, 100, "relu"), fc(100, 40, "none")], 2, 11168),
+                             ([fc(200, 6000, "relu"), fc(6000, 9, "none")], 0, 256),
+                             ([fc(203, 6000, "relu"), fc(6000, 9, "none")], 0, 320),
+                             ([fc(16, 9, "relu"), fc(9, 6000, "relu"), fc(6000, 9, "none")], 0, 67168)):
         net = h.synth.small_net(layers, head="linear")
         P, n = h.aq.Policy(net), len(layers)
         P.convert_params_fp16([Mem()] * n, [Mem()] * n, None, None)
