@@ -802,12 +802,12 @@ aq_status launch_quantize_tensor(const float* d_w, int64_t rows, int64_t cols, i
     hipLaunchKernelGGL((k_quant_sym_rows_short<G, V, U>), dim3((unsigned)((rows + 4 * (64 / G) * U - 1) / (4 * (64 / G) * U))), \
                        dim3(256), 0, st, w4, rows, cols4, qw, c4, d_scale, d_zp, d_ws)
         // Fewer, fuller wavefronts from the row counts on where they fill the chip, us so / with a wavefront or a workgroup per row:
-        // 500000 x 32 25.4 / 107, 20000 x 160 7.3 / 6.5, 60000 x 252 16.6 / 16.5, 2000 x 400 5.2 / 4.6, 20000 x 400 9.3 / 17.9,
-        // 2000 x 1000 4.8 / 4.5, 5000 x 700 5.4 / 6.7, 30000 x 1000 25.1 / 32.1.
+        // 500000 x 32 25.4 / 107, 2000 x 400 5.2 / 4.6, 20000 x 400 9.3 / 17.9, 2000 x 1000 4.8 / 4.5, 5000 x 700 5.4 / 6.7, 30000 x 1000
+        // 25.1 / 32.1.  Rows of 132 to 256 at any count, two to a wavefront / one to a wavefront / four of one each in flight:
+        // 25000 x 212 from HBM 7.7 / 8.9 / 10.0, in cache 7.1 / 7.4 / 9.0; 100000 x 160 18.2 / 25.7 / 22.2.
         if (cols4 <= 16) AQ_SHORT(16, 1, 4);
         else if (cols4 <= 32) AQ_SHORT(16, 2, 2);
-        else if (cols4 <= 64 && rows < 40000) AQ_SHORT(64, 1, 1);
-        else if (cols4 <= 64) AQ_SHORT(64, 1, 4);
+        else if (cols4 <= 64) AQ_SHORT(32, 2, 1);
         else if (cols4 <= 128 && rows >= 6000) AQ_SHORT(64, 2, 2);
         else if (cols4 <= 256 && rows >= 4096) AQ_SHORT(64, 4, 1);
 #undef AQ_SHORT

@@ -1,4 +1,4 @@
-"""The tensor quantizer's per-channel scheme on either side of every rule on rows and columns: lane groups of 16 and 64 per row,
+"""The tensor quantizer's per-channel scheme on either side of every rule on rows and columns: lane groups of 16, 32 and 64 per row,
 ragged rows, row counts that end inside a wavefront's set."""
 import numpy as np
 import pytest
