@@ -551,11 +551,12 @@ __global__ __launch_bounds__(MT_) void k_fp32_mlp(const NetDev* __restrict__ net
 #pragma unroll
                 for (int r = 0; r < RT; ++r) store(acc[0][r], b0, t, r);
             }
-            // LayerNorm of up to 64 LNV features: gains, offsets and the row in registers, the former requested in front of the
+            // LayerNorm of 129 to 64 LNV features: gains, offsets and the row in registers, the former requested in front of the
             // barrier (in the loop over features behind it, each of its turns waited for its own two).  111-400-300-8 on
-            // 3001 rows, biases and LayerNorm together: 24.0 -> 23.5 us.
+            // 3001 rows, biases and LayerNorm together: 24.0 -> 23.5 us.  Fewer features are one or two turns of that loop: held, a
+            // whole policy took up to 4 % longer with 64 of them, 2 % with 128.
             constexpr int LNV = 8;
-            const bool held = ln && N <= 64 * LNV;
+            const bool held = ln && N > 128 && N <= 64 * LNV;
             float gv[LNV], bv[LNV];
             if (held) {
                 const gf_ptr gam = (gf_ptr)P.gamma[l], bet = (gf_ptr)P.beta[l];
@@ -1004,7 +1005,9 @@ bool fp32_mlp_fits(const NetDev& n, int64_t batch, int* rt_out) {
     }
     const int ld = mlp_ld(n);
     if (mlp_lds(1, ld) > 160 * 1024) return false;
-    const int rt = batch > 16 * 512 && mlp_lds(2, ld) <= 80 * 1024 ? 2 : 1;
+    // (two row tiles from the second round of single ones on: 256-wide policies at 4100 to 8192 rows take 0.76 of the time, up to 4096
+    // 1.5 times as long)
+    const int rt = batch > 16 * 256 && mlp_lds(2, ld) <= 80 * 1024 ? 2 : 1;
     *rt_out = rt;
     const int64_t workgroups = (batch + 16 * rt - 1) / (16 * rt);
     if (!grid_ok(workgroups, MT_)) return false;

@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256) void k_quant_asym_flat(const float4* __restric
 }
 
 // per-channel symmetric codes, canonical order, short rows: G lanes per row, V float4 of it each, in registers between the |w|
-// reduction and the rounding; U such sets of rows per wavefront, all requested at once, so that 64 bytes a thread are in flight
+// reduction and the rounding; U such sets of rows per wavefront, all requested at once, so that 32 to 64 bytes a thread are in flight
 // however short the rows.  Bound by memory: 100000 x 64 (26 MB in, 6 MB out) took 24.9 us with a wavefront per row (one float4
 // a thread, three quarters of the lanes idle), 8.3 so.
 template <int G, int V, int U>

@@ -25,6 +25,9 @@ def _cases():
         "mlp_u8": (small([fc(48, 65, "relu"), fc(65, 5, "none")], head="linear", in_type="u8"), [3, 64]),
         "mlp_single": (small([fc(50, 37, "none")]), [19]),
         "mlp_two_tiles": (small([fc(20, 256, "relu"), fc(256, 21, "none")]), [8193 + 16]),  # 32 rows per workgroup
+        # LayerNorms on either side of the widths that a wavefront holds in registers, one and two row tiles per workgroup
+        **{"mlp_ln_%d" % n: (small([fc(20, n, "ln_tanh"), fc(n, 7, "none")]), bs)
+           for n, bs in ((128, [40]), (129, [40, 4097]), (300, [4096, 4097]), (512, [40]), (513, [40]))},
         # a launch per layer: wide layers, few and many rows
         "layers_few_rows": (small([fc(67, 1300, "ln_tanh"), fc(1300, 1300, "relu"), fc(1300, 21, "none")]), [1, 16, 17, 70]),
         "layers_many_rows": (small([fc(70, 1300, "relu"), fc(1300, 130, "none"), fc(130, 66, "none")], head="argmax"), [513, 2100]),
@@ -84,6 +87,12 @@ def test_the_cases_reach_every_tile(aq):
         P.close()
     assert rows == {0, 16, 32}
     assert tiles == {(64, 128), (32, 128), (64, 64), (32, 32), (16, 32), (16, 16)}
+
+
+def test_two_row_tiles_per_workgroup_from_the_second_round_on(aq):
+    P = aq.Policy(synth.small_net([fc(20, 256, "relu"), fc(256, 21, "none")]))
+    assert [P.policy_fp32_plan(b)[0] for b in (1, 4096, 4097, 8193)] == [16, 16, 32, 32]
+    P.close()
 
 
 def test_batches_beyond_a_grid_of_whole_policy_workgroups_go_layer_by_layer(aq):
