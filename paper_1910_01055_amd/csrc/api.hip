@@ -137,6 +137,7 @@ struct aq_policy {
     void* w4_slab = nullptr;
     std::vector<uint8_t*> w4;
     bool w4_stale = true;
+    bool cold = false;  // the 8-bit weights were quantized or imported since the last forward
     // aq_calibrate_fp32's answer, in host memory that the GPU writes (made by its first call): the number of the
     // calibration that is ready, then (min, max) per activation tensor
     uint32_t* calib = nullptr;
@@ -396,7 +397,7 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         size_t lds = 0;
         for (int l = 0; l < net->n_layers - 1; ++l) few_n = std::max(few_n, p->L[l].N);
         // (one row: if the layers' launches are not faster there, they are at no batch)
-        if (fused_mlp_supported(probe, &r, &lds) && few_rows_faster(probe, false, false)) {
+        if (fused_mlp_supported(probe, &r, &lds) && few_rows_faster(probe, false, false, false)) {
             p->few_bytes = (blocked_map_bytes(kFewMaxRows, few_n) + 255) & ~(size_t)255;
             if (hip_failed(hipMalloc((void**)&p->few_slab, 2 * kFewPairs * p->few_bytes))) {
                 (void)hipFree(p->slab);
@@ -710,7 +711,7 @@ extern "C" aq_status aq_policy_fused_plan(const aq_policy* p, int64_t batch, int
     a.c.batch = batch;
     int r = 0, t = 0;
     size_t lds = 0;
-    if (p->path == 2 || !fused_mlp_supported(a, &r, &lds, &t) || (p->path == 0 && p->few_bytes && few_rows_faster(a, false, false))) r = t = 0;
+    if (p->path == 2 || !fused_mlp_supported(a, &r, &lds, &t) || (p->path == 0 && p->few_bytes && few_rows_faster(a, false, false, false))) r = t = 0;
     *rows = r;
     *tiles = t;
     *kind = r != 0 ? fused_mlp_kernel_kind(a) : 0;
@@ -836,7 +837,7 @@ extern "C" aq_status aq_policy_import_blob(aq_policy* p, const void* d_blob, uin
     const aq_status s = launch_blob_import(blob_head(w), p->d_net->actq, p->slab, (int64_t)p->layer_bytes, d_blob, p->status,
                                            as_stream(stream));
     if (s != AQ_OK) return s;
-    p->w4_stale = true;
+    p->w4_stale = p->cold = true;
     p->quantized = true;
     return AQ_OK;
 }
@@ -917,6 +918,7 @@ extern "C" aq_status aq_policy_import_packed_blob(aq_policy* p, const void* d_bl
     const aq_status s = launch_packed_import(blob_head(w), a, p->d_net->actq, p->slab, d_blob, p->status, as_stream(stream));
     if (s != AQ_OK) return s;
     p->w4_stale = true;
+    p->cold = false;  // (the codes' expansion takes long enough: what follows it is launched by then)
     p->quantized = true;
     return AQ_OK;
 }
@@ -1001,7 +1003,7 @@ extern "C" aq_status aq_quantize_params(aq_policy* p, const float* const* h_d_w,
     }
     aq_status s = launch_quantize_policy(p->d_qtab, p->h_qtab, ptrs, r, p->qout, st);
     if (s != AQ_OK) return s;
-    p->w4_stale = true;
+    p->w4_stale = p->cold = true;
     p->quantized = true;
     return AQ_OK;
 }
@@ -1100,8 +1102,10 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
     // the allocation-free entry point: what is captured may be replayed on any stream beside any other, and needs no
     // scratch with the whole-network kernels.)
     const bool noise = ex && p->net.head != AQ_HEAD_ARGMAX;
+    const bool cold = p->cold;
+    p->cold = false;
     int pair = -1;
-    if (can_fuse && p->path == 0 && p->few_bytes && !fixed && few_rows_faster(a, noise, st != nullptr)) pair = few_pair_of(p, st);
+    if (can_fuse && p->path == 0 && p->few_bytes && !fixed && few_rows_faster(a, noise, st != nullptr, cold)) pair = few_pair_of(p, st);
     if (pair >= 0) can_fuse = false;
     // on every way out: the event behind this forward's last use of the pair
     struct Done {

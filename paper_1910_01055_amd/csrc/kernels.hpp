@@ -98,9 +98,10 @@ bool skinny_layer_supported(const LayerDev& L, int64_t rows);
 void few_row_tile(int N, int64_t rows, bool argmax, int* ft, int* rt);
 bool skinny_layer_does_argmax(const FwdArgs& a, int l);
 // whether an MLP that fits the whole-network kernels is faster layer by layer at this batch (at most kFewMaxRows rows, a
-// hidden layer of at least kFewMinWidth); noise: exploration then takes a launch of its own; guarded: an event behind the forward
+// hidden layer of at least kFewMinWidth); noise: exploration then takes a launch of its own; guarded: an event behind the forward;
+// cold: the weights were just written
 constexpr int kFewMaxRows = 512, kFewMinWidth = 257;
-bool few_rows_faster(const FwdArgs& a, bool noise, bool guarded);
+bool few_rows_faster(const FwdArgs& a, bool noise, bool guarded, bool cold);
 // whether launch_layer_int8 hands layer l at this batch to the K-split kernel
 // the leading convolution layers in one launch (0 layers = shapes it does not take); writes the last
 // convolution's signed codes to `out` ([batch * oh * ow][N])

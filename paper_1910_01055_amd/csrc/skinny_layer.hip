@@ -65,8 +65,9 @@ void few_row_tile(int N, int64_t rows, bool argmax, int* ft, int* rt) {
 // 67-512x3-21 14.5 / 12.2, 67-1024x2-21 19.8 / 9.3 (256 rows 10.6), 256-1024x3-64 31.3 / 12.0 (256 rows 14.7),
 // 111-400-300-8 10.0 / 9.6; 512 rows: 67-1024x2-21 20.3 / 15.9, 111-800-600-8 15.4 / 16.8; per-tensor weights 67-512x2-21
 // 12.2 / 9.7, 67-1024x2-21 24.1 / 9.5.  An event behind the forward (streams other than the default one) costs 2.8 to 3.5: 67-512x2-21
-// at one row 8.7 without, 11.6 with it, 256-1024x3-64 11.4 and 14.9.
-bool few_rows_faster(const FwdArgs& a, bool noise, bool guarded) {
+// at one row 8.7 without, 11.6 with it, 256-1024x3-64 11.4 and 14.9.  The first forward behind a quantize or an import finds its weights
+// in no L2, and each launch waits for its own: a whole pull of 28-512x2-1 24.8 us in one launch, 27.8 layer by layer.
+bool few_rows_faster(const FwdArgs& a, bool noise, bool guarded, bool cold) {
     const int nl = a.net.n_layers;
     if (a.c.batch > kFewMaxRows || nl < 2) return false;
     double weights = 0.0;  // millions
@@ -82,8 +83,8 @@ bool few_rows_faster(const FwdArgs& a, bool noise, bool guarded) {
     if (a.net.head == AQ_HEAD_ARGMAX && !skinny_layer_does_argmax(a, nl - 1)) return false;
     for (int l = 0; l < nl; ++l)
         if (!layer_uses_skinny(a, l)) return false;
-    const double whole = a.net.asym ? 8.3 + 13.0 * weights : 7.5 + 10.0 * weights;
-    const double layers = nl * (a.c.batch > 256 ? 5.0 : a.c.batch > 128 ? 3.5 : 3.1) + (noise ? 3.1 : 0.0) + (guarded ? 3.3 : 0.0);
+    const double whole = a.net.asym ? 7.8 + 15.0 * weights : 7.5 + 10.0 * weights;
+    const double layers = nl * (a.c.batch > 256 ? 5.0 : a.c.batch > 128 ? 3.5 : 3.1) + (noise ? 3.1 : 0.0) + (guarded ? 3.3 : cold ? 1.6 : 0.0);
     return layers < whole;
 }
 

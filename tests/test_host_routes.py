@@ -131,7 +131,18 @@ def streams_come_and_go(h):
     assert h.hip.fake_live() == 0
     # where the event costs what the layers' launches gain
     Q = h.policy(512, 512)
+    h.forward(Q, 16)
     assert h.maps(h.forward(Q, 16)) and not h.maps(h.forward(Q, 16, 128))
+
+
+def the_first_forward_of_new_weights(h):
+    """One launch where the layers' gain is what their round trips for cold weights cost; layers of 1024 gain more."""
+    for widths, first in (((512, 512), False), ((1024, 1024), True)):
+        P = h.policy(*widths)
+        for renew in (lambda: None, lambda: P.quantize_params([Mem()] * 3, [Mem()] * 3, None, None, [(0.0, 1.0)] * 3)):
+            renew()
+            assert [bool(h.maps(h.forward(P, 16))) for _ in range(3)] == [first, True, True], widths
+        P.close()
 
 
 def fp32_convolutions_of_small_frames(h):
@@ -248,7 +259,7 @@ def a_refused_amount_of_lds_is_told_once(h):
         P.close()
 
 
-SCENARIOS = [few_row_forwards_allocate_nothing, streams_come_and_go, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
+SCENARIOS = [few_row_forwards_allocate_nothing, streams_come_and_go, the_first_forward_of_new_weights, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
              a_few_row_forward_without_memory_to_have, a_failed_call_leaves_no_error_behind, a_refused_amount_of_lds_is_told_once]
 
 
