@@ -385,8 +385,8 @@ bool plan_rows(const Fp16Net& n, int rt, MlpPlan* p) {
 // workgroup per CU.  Fitted to 67-w-w-w-21: w = 128, 256, 512 at batch 4096 7.0, 9.2, 16.6 us; at 16384 12.9, 16.6,
 // 27.7 us; 256-1024x3-64 at 16384 75.8 us.  Against a launch per layer, which spreads a layer's weights over the
 // chip: 4 us each, then 371 k flop per clock.  That is what the widest layers reach; narrower ones and rows of no whole 8 values are
-// slower than so (110-1024x2-37 at 4544 rows 43.8 us, here 28.9; 131-871-794-5 at 4277 89, here 21.6).  At few rows the launches
-// are the faster ones (67-512x3-21 at 100 rows 11.4, here 14.8) but write maps that two streams would share.
+// slower than so (187-1024x2-35 at 4570 rows 51.2 us, here 29.8; 131-871-794-5 at 4277 89, here 21.6).  At few rows the launches
+// are the faster ones (121-512x3-30 at 99 rows 11.4, here 14.9) but write maps that two streams would share.
 bool plan_mlp(const Fp16Net& n, int64_t batch, MlpPlan* best) {
     double best_c = 0.0;
     bool found = false;
