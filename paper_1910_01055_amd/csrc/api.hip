@@ -1165,16 +1165,17 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
         const int64_t rows_l = batch * b.oh * b.ow;
         LayerIO io;
         io.in_blocked = blocked;
-        blocked = sc.blocked && l < nl - 1 && b.fc && b.d.act != AQ_ACT_LN_TANH && layer_uses_skinny(a, l) && layer_uses_skinny(a, l + 1);
-        io.out_blocked = blocked;
+        const bool ln = l < nl - 1 && b.d.act == AQ_ACT_LN_TANH;  // (its rows' kernel writes either order)
+        blocked = sc.blocked && l < nl - 1 && b.fc && (ln || layer_uses_skinny(a, l)) && layer_uses_skinny(a, l + 1);
+        io.out_blocked = ln ? 0 : blocked;
         io.in = l == 0 ? d_obs : (const void*)sc.i8[(l - 1) & 1];
         io.out = sc.i8[l & 1];
         io.ln_x = sc.ln_x;
         io.y = ybuf;
         s = launch_layer_int8(a, l, io, st);
         if (s != AQ_OK) return s;
-        if (l < nl - 1 && b.d.act == AQ_ACT_LN_TANH) {
-            s = launch_ln_tanh_rows(a, l, io.ln_x, io.out, rows_l, st);
+        if (ln) {
+            s = launch_ln_tanh_rows(a, l, io.ln_x, io.out, rows_l, blocked, st);
             if (s != AQ_OK) return s;
         }
         if (l == nl - 1 && p->net.head == AQ_HEAD_ARGMAX && !(layer_uses_skinny(a, l) && skinny_layer_does_argmax(a, l))) {

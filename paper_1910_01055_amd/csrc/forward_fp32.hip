@@ -15,6 +15,7 @@
 // k_fp32_layer: one layer (fully connected or implicit-GEMM convolution) from and to global memory, inputs staged in
 //   LDS.  k_fp32_mlp: a whole small MLP in one launch, activations in LDS.
 #include "fp32_split.hpp"
+#include "ln_rows.hpp"
 
 namespace aq {
 
@@ -667,8 +668,49 @@ __global__ __launch_bounds__(MT_) void k_fp32_mlp(const NetDev* __restrict__ net
     }
 }
 
-// LayerNorm (biased variance, eps inside the root) + tanh in place, one wavefront per row (layers that run on their own)
+// LayerNorm (biased variance, eps inside the root) + tanh in place (layers that run on their own), rows in registers (ln_rows.hpp)
+template <int W, int P, bool VEC>
 __global__ __launch_bounds__(256) void k_fp32_ln_tanh(float* __restrict__ x, int64_t rows, int N,
+                                                      const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                      float eps, RangeSlot* __restrict__ slots) {
+    using Row = LnRow<W, P>;
+    __shared__ float red[2][4];
+    const int t = threadIdx.x & (Row::T - 1);
+    const int64_t row = W == 1 ? (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6) : (int64_t)blockIdx.x;
+    if (row >= rows) return;  // (a whole wavefront, or nobody)
+    float* const xr = x + row * N;
+    Row r;
+    float gg[P][4], bb[P][4];
+#pragma unroll
+    for (int i = 0; i < P; ++i) Row::template load<VEC>(xr, t, i, N, 0.0f, r.v[i]);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        Row::template load<VEC>(gamma, t, i, N, 1.0f, gg[i]);
+        Row::template load<VEC>(beta, t, i, N, 0.0f, bb[i]);
+    }
+    float mean, inv;
+    r.template stats<VEC>(t, N, eps, red, mean, inv);
+    float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        float o[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            o[j] = tanhf((r.v[i][j] - mean) * inv * gg[i][j] + bb[i][j]);
+            const int n = Row::template at<VEC>(t, i, j);
+            if (n < N) {
+                lo = fminf(lo, o[j]);
+                hi = fmaxf(hi, o[j]);
+                if (!VEC) xr[n] = o[j];
+            }
+        }
+        if (VEC && Row::template at<true>(t, i, 0) < N) *(float4*)(xr + Row::template at<true>(t, i, 0)) = make_float4(o[0], o[1], o[2], o[3]);
+    }
+    if (slots) range_note(slots, W == 1 ? (uint32_t)row : (uint32_t)row * 4 + (threadIdx.x >> 6), lo, hi);
+}
+
+// rows longer than those hold: one wavefront per row, which is read three times
+__global__ __launch_bounds__(256) void k_fp32_ln_tanh_long(float* __restrict__ x, int64_t rows, int N,
                                                       const float* __restrict__ gamma, const float* __restrict__ beta,
                                                       float eps, RangeSlot* __restrict__ slots) {
     const int lane = threadIdx.x & 63;
@@ -1060,8 +1102,19 @@ aq_status launch_fp32_mlp(const NetDev& n, const NetDev* d_net, const F32Ptrs& p
 
 aq_status launch_fp32_ln_tanh(float* x, int64_t rows, int N, const float* gamma, const float* beta, float eps,
                               RangeSlot* slots, hipStream_t st) {
-    hipLaunchKernelGGL(k_fp32_ln_tanh, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, x, rows, N, gamma, beta,
-                       eps, slots);
+    LnForm f;
+    if (!ln_form(rows, N, &f)) {
+        hipLaunchKernelGGL(k_fp32_ln_tanh_long, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, x, rows, N, gamma, beta, eps, slots);
+        return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
+    }
+    const bool vec = N % 4 == 0 && (((uintptr_t)x | (uintptr_t)gamma | (uintptr_t)beta) & 15) == 0;
+    const dim3 grid((unsigned)(f.w == 1 ? (rows + 3) / 4 : rows));
+    ln_dispatch(f, [&](auto w, auto p) {
+        constexpr int W = decltype(w)::value, P = decltype(p)::value;
+        auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(256), 0, st, x, rows, N, gamma, beta, eps, slots); };
+        if (vec) go(k_fp32_ln_tanh<W, P, true>);
+        else go(k_fp32_ln_tanh<W, P, false>);
+    });
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
 

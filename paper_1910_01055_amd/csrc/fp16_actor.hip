@@ -11,6 +11,7 @@
 //   k_fp16_head           tanh / identity / argmax on the last layer's rows
 #include "fp16_device.hpp"
 #include "int8_device.hpp"
+#include "ln_rows.hpp"
 
 namespace aq {
 
@@ -533,91 +534,65 @@ __global__ __launch_bounds__(SKH_W * 64) void k_layer_fp16_rows(const HalfRows L
     }
 }
 
-// LayerNorm (biased variance, eps inside the root) rounded to binary16, then tanh rounded to binary16,
-// in place.  One wavefront per LN_R rows, the rows in registers between the statistics and the result,
-// all of a wave's loads requested before the first is used (8-byte pieces when N is a multiple of 4).
-constexpr int LN_R = 4;     // rows per wavefront
-constexpr int LN_MAXV = 16; // elements per lane and row held in registers (N <= 1024)
-template <bool VEC4>
+// LayerNorm (biased variance, eps inside the root) rounded to binary16, then tanh rounded to binary16, in place, rows in
+// registers (ln_rows.hpp)
+template <int W, int P, bool VEC>
 __global__ __launch_bounds__(256) void k_fp16_ln_tanh(_Float16* __restrict__ x, int64_t rows, int N,
                                                       const float* __restrict__ gamma, const float* __restrict__ beta,
                                                       float eps) {
-    const int lane = threadIdx.x & 63;
-    const int64_t r0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * LN_R;
-    if (r0 >= rows) return;
-    float v[LN_R][LN_MAXV];
-    // element index of register i: VEC4: 4 * lane + 256 * (i / 4) + i % 4, else lane + 64 * i
+    using Row = LnRow<W, P>;
+    __shared__ float red[2][4];
+    const int t = threadIdx.x & (Row::T - 1);
+    const int64_t row = W == 1 ? (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6) : (int64_t)blockIdx.x;
+    if (row >= rows) return;  // (a whole wavefront, or nobody)
+    _Float16* const xr = x + row * N;
+    Row r;
+    float gg[P][4], bb[P][4];
 #pragma unroll
-    for (int r = 0; r < LN_R; ++r) {
-        const int64_t row = r0 + r < rows ? r0 + r : rows - 1;
-        const _Float16* xr = x + row * N;
-        if (VEC4) {
+    for (int i = 0; i < P; ++i) {
+        if (VEC) {
+            const int n = Row::template at<true>(t, i, 0);
+            h4 q = {0, 0, 0, 0};
+            if (n < N) q = *(const h4*)(xr + n);
 #pragma unroll
-            for (int i = 0; i < LN_MAXV / 4; ++i) {
-                const int n = 4 * lane + 256 * i;
-                h4 t = {0, 0, 0, 0};
-                if (n < N) t = *(const h4*)(xr + n);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[r][4 * i + j] = (float)t[j];
-            }
+            for (int j = 0; j < 4; ++j) r.v[i][j] = (float)q[j];
         } else {
 #pragma unroll
-            for (int i = 0; i < LN_MAXV; ++i) {
-                const int n = lane + 64 * i;
-                v[r][i] = n < N ? (float)xr[n] : 0.0f;
+            for (int j = 0; j < 4; ++j) {
+                const int n = Row::template at<false>(t, i, j);
+                r.v[i][j] = n < N ? (float)xr[n] : 0.0f;
             }
         }
     }
 #pragma unroll
-    for (int r = 0; r < LN_R; ++r) {
-        if (r0 + r >= rows) break;
-        _Float16* xr = x + (r0 + r) * N;
-        float s = 0.0f;
+    for (int i = 0; i < P; ++i) {
+        Row::template load<VEC>(gamma, t, i, N, 1.0f, gg[i]);
+        Row::template load<VEC>(beta, t, i, N, 0.0f, bb[i]);
+    }
+    float mean, inv;
+    r.template stats<VEC>(t, N, eps, red, mean, inv);
 #pragma unroll
-        for (int i = 0; i < LN_MAXV; ++i) s += v[r][i];
+    for (int i = 0; i < P; ++i) {
+        h4 o;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-        const float mean = s / (float)N;
-        float ss = 0.0f;
-#pragma unroll
-        for (int i = 0; i < LN_MAXV; ++i) {
-            const int n = VEC4 ? 4 * lane + 256 * (i / 4) + i % 4 : lane + 64 * i;
-            const float d = n < N ? v[r][i] - mean : 0.0f;
-            ss += d * d;
+        for (int j = 0; j < 4; ++j) {
+            const _Float16 ln = (_Float16)((r.v[i][j] - mean) * inv * gg[i][j] + bb[i][j]);
+            o[j] = (_Float16)tanh_rel((float)ln);
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-        const float inv = 1.0f / sqrtf(ss / (float)N + eps);
-        if (VEC4) {
-#pragma unroll
-            for (int i = 0; i < LN_MAXV / 4; ++i) {
-                const int n = 4 * lane + 256 * i;
-                if (n < N) {
-                    const float4 g4 = *(const float4*)(gamma + n), b4 = *(const float4*)(beta + n);
-                    const float gg[4] = {g4.x, g4.y, g4.z, g4.w}, bb[4] = {b4.x, b4.y, b4.z, b4.w};
-                    h4 o;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const _Float16 ln = (_Float16)((v[r][4 * i + j] - mean) * inv * gg[j] + bb[j]);
-                        o[j] = (_Float16)tanh_rel((float)ln);
-                    }
-                    *(h4*)(xr + n) = o;
-                }
-            }
+        if (VEC) {
+            const int n = Row::template at<true>(t, i, 0);
+            if (n < N) *(h4*)(xr + n) = o;
         } else {
 #pragma unroll
-            for (int i = 0; i < LN_MAXV; ++i) {
-                const int n = lane + 64 * i;
-                if (n < N) {
-                    const _Float16 ln = (_Float16)((v[r][i] - mean) * inv * gamma[n] + beta[n]);
-                    xr[n] = (_Float16)tanh_rel((float)ln);
-                }
+            for (int j = 0; j < 4; ++j) {
+                const int n = Row::template at<false>(t, i, j);
+                if (n < N) xr[n] = o[j];
             }
         }
     }
 }
 
-// rows wider than 64 * LN_MAXV: one wavefront per row, the row is read three times
+// rows longer than those hold: one wavefront per row, which is read three times
 __global__ __launch_bounds__(256) void k_fp16_ln_tanh_long(_Float16* __restrict__ x, int64_t rows, int N,
                                                            const float* __restrict__ gamma,
                                                            const float* __restrict__ beta, float eps) {
@@ -769,16 +744,19 @@ aq_status launch_fp16_ln_tanh(void* x, int64_t rows, int N, const float* gamma, 
                               hipStream_t st) {
     if (rows < 1) return AQ_OK;
     _Float16* xh = (_Float16*)x;
-    if (N > 64 * LN_MAXV) {
-        hipLaunchKernelGGL(k_fp16_ln_tanh_long, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, xh, rows, N, gamma,
-                           beta, eps);
-    } else {
-        const dim3 grid((unsigned)((rows + 4 * LN_R - 1) / (4 * LN_R)));
-        if (N % 4 == 0 && ((uintptr_t)x & 7) == 0)
-            hipLaunchKernelGGL(k_fp16_ln_tanh<true>, grid, dim3(256), 0, st, xh, rows, N, gamma, beta, eps);
-        else
-            hipLaunchKernelGGL(k_fp16_ln_tanh<false>, grid, dim3(256), 0, st, xh, rows, N, gamma, beta, eps);
+    LnForm f;
+    if (!ln_form(rows, N, &f)) {
+        hipLaunchKernelGGL(k_fp16_ln_tanh_long, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, xh, rows, N, gamma, beta, eps);
+        return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
     }
+    const bool vec = N % 4 == 0 && ((uintptr_t)x & 7) == 0 && (((uintptr_t)gamma | (uintptr_t)beta) & 15) == 0;
+    const dim3 grid((unsigned)(f.w == 1 ? (rows + 3) / 4 : rows));
+    ln_dispatch(f, [&](auto w, auto p) {
+        constexpr int W = decltype(w)::value, P = decltype(p)::value;
+        auto go = [&](auto k) { hipLaunchKernelGGL(k, grid, dim3(256), 0, st, xh, rows, N, gamma, beta, eps); };
+        if (vec) go(k_fp16_ln_tanh<W, P, true>);
+        else go(k_fp16_ln_tanh<W, P, false>);
+    });
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
 

@@ -111,7 +111,8 @@ bool layer_uses_skinny(const FwdArgs& a, int l);
 aq_status launch_layer_skinny(const FwdArgs& a, int l, const LayerIO& io, hipStream_t st);
 // the few-row kernel's nibble weights from a layer's packed 8-bit operands: `pieces` = NT * KS * 64 (16 bytes -> 8)
 aq_status launch_pack_nibbles(const int8_t* wp, uint8_t* w4, int64_t pieces, hipStream_t st);
-aq_status launch_ln_tanh_rows(const FwdArgs& a, int layer, const float* x, int8_t* out, int64_t rows, hipStream_t st);
+// blocked: `out` in the few-row kernel's operand order
+aq_status launch_ln_tanh_rows(const FwdArgs& a, int layer, const float* x, int8_t* out, int64_t rows, bool blocked, hipStream_t st);
 aq_status launch_head_rows(const float* y, int64_t rows, int N, int head, void* actions, hipStream_t st);
 
 // ---- fp32 actor (forward_fp32.hip)

@@ -8,6 +8,7 @@
 // keeps the L2 -> register stream of a wide layer under a quarter KiB per MFMA; two waves per SIMD
 // let one wave's epilogue overlap the other's MFMAs.
 #include "int8_device.hpp"
+#include "ln_rows.hpp"
 
 namespace aq {
 
@@ -299,11 +300,71 @@ __global__ __launch_bounds__(W * 64, (W <= 2 && !DEEP) ? 4 : 1) void k_layer_int
     }
 }
 
-// LayerNorm + tanh + re-quantize of fp32 rows (per-layer path): one wavefront per row.
+// LayerNorm + tanh + re-quantize of fp32 rows (per-layer path), rows in registers (ln_rows.hpp).  `rtiles`: 0, or the 16-row tiles
+// of a map in the few-row kernel's operand order, whose features past N are zeros.
+template <int W, int P, bool VEC>
 __global__ __launch_bounds__(256) void k_ln_tanh_rows(const float* __restrict__ x, int64_t rows, int N,
                                                       const float* __restrict__ gamma, const float* __restrict__ beta,
                                                       float eps, const ActQ* __restrict__ actq, int out_idx,
-                                                      int8_t* __restrict__ out, float* __restrict__ tap_ln,
+                                                      int8_t* __restrict__ out, int64_t rtiles, float* __restrict__ tap_ln,
+                                                      uint8_t* __restrict__ tap_act) {
+    using Row = LnRow<W, P>;
+    __shared__ float red[2][4];
+    const int t = threadIdx.x & (Row::T - 1);
+    const int64_t row = W == 1 ? (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6) : (int64_t)blockIdx.x;
+    if (row >= rows) return;  // (a whole wavefront, or nobody)
+    Row r;
+    float gg[P][4], bb[P][4];
+#pragma unroll
+    for (int i = 0; i < P; ++i) Row::template load<VEC>(x + row * N, t, i, N, 0.0f, r.v[i]);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        Row::template load<VEC>(gamma, t, i, N, 1.0f, gg[i]);
+        Row::template load<VEC>(beta, t, i, N, 0.0f, bb[i]);
+    }
+    const float s_out = actq[out_idx].s;
+    const int z_out = actq[out_idx].z;
+    const QuantScale qs_out = make_quant_scale(s_out);
+    float mean, inv;
+    r.template stats<VEC>(t, N, eps, red, mean, inv);
+    auto place = [&](int n) { return rtiles ? ((int64_t)(n >> 4) * rtiles * 16 + row) * 16 + (n & 15) : row * N + n; };
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+        float tv[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) tv[j] = tanh_fast((r.v[i][j] - mean) * inv * gg[i][j] + bb[i][j]);
+        if (VEC) {
+            const int n = Row::template at<true>(t, i, 0);
+            if (n < N) {
+                const uint32_t q = quant_u8x4(make_float4(tv[0], tv[1], tv[2], tv[3]), qs_out, (float)z_out);
+                *(uint32_t*)(out + place(n)) = q ^ 0x80808080u;
+                if (tap_ln) *(float4*)(tap_ln + row * N + n) = make_float4(tv[0], tv[1], tv[2], tv[3]);
+                if (tap_act) *(uint32_t*)(tap_act + row * N + n) = q;
+            } else if (rtiles && n < ((N + 15) & ~15)) {
+                *(uint32_t*)(out + place(n)) = 0;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int n = Row::template at<false>(t, i, j);
+                if (n < N) {
+                    const int code = quant_code(tv[j], qs_out, -z_out, 255 - z_out) + z_out;
+                    out[place(n)] = (int8_t)(code - 128);
+                    if (tap_ln) tap_ln[row * N + n] = tv[j];
+                    if (tap_act) tap_act[row * N + n] = (uint8_t)code;
+                } else if (rtiles && n < ((N + 15) & ~15)) {
+                    out[place(n)] = 0;
+                }
+            }
+        }
+    }
+}
+
+// rows longer than those hold: one wavefront per row, which is read three times
+__global__ __launch_bounds__(256) void k_ln_tanh_long(const float* __restrict__ x, int64_t rows, int N,
+                                                      const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                      float eps, const ActQ* __restrict__ actq, int out_idx,
+                                                      int8_t* __restrict__ out, int64_t rtiles, float* __restrict__ tap_ln,
                                                       uint8_t* __restrict__ tap_act) {
     const int lane = threadIdx.x & 63;
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -331,8 +392,9 @@ __global__ __launch_bounds__(256) void k_ln_tanh_rows(const float* __restrict__ 
         if (tap_ln) tap_ln[row * N + n] = tv;
         int code = quant_code(tv, qs_out, -z_out, 255 - z_out) + z_out;
         if (tap_act) tap_act[row * N + n] = (uint8_t)code;
-        out[row * N + n] = (int8_t)(code - 128);
+        out[rtiles ? ((int64_t)(n >> 4) * rtiles * 16 + row) * 16 + (n & 15) : row * N + n] = (int8_t)(code - 128);
     }
+    if (rtiles && N + lane < ((N + 15) & ~15)) out[((int64_t)(N >> 4) * rtiles * 16 + row) * 16 + ((N + lane) & 15)] = 0;
 }
 
 // argmax head on the dequantized last-layer rows (per-layer path; lowest index wins ties)
@@ -448,10 +510,27 @@ aq_status launch_layer_int8(const FwdArgs& a, int l, const LayerIO& io, hipStrea
     return launch_layer_t<4, 2, 2>(a, l, io, rows, stage_mode, actions, st);
 }
 
-aq_status launch_ln_tanh_rows(const FwdArgs& a, int l, const float* x, int8_t* out, int64_t rows, hipStream_t st) {
+aq_status launch_ln_tanh_rows(const FwdArgs& a, int l, const float* x, int8_t* out, int64_t rows, bool blocked, hipStream_t st) {
     const LayerDev& L = a.net.L[l];
-    hipLaunchKernelGGL(k_ln_tanh_rows, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, x, rows, L.N, L.gamma,
-                       L.beta, a.net.ln_eps, a.d_net->actq, l + 1, out, a.t.ln[l], a.t.act[l]);
+    const int64_t rtiles = blocked ? (rows + 15) / 16 : 0;
+    LnForm f;
+    if (!ln_form(rows, L.N, &f)) {
+        hipLaunchKernelGGL(k_ln_tanh_long, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, x, rows, L.N, L.gamma,
+                           L.beta, a.net.ln_eps, a.d_net->actq, l + 1, out, rtiles, a.t.ln[l], a.t.act[l]);
+        return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
+    }
+    const bool vec = L.N % 4 == 0 && (((uintptr_t)x | (uintptr_t)L.gamma | (uintptr_t)L.beta | (uintptr_t)a.t.ln[l]) & 15) == 0 &&
+                     (((uintptr_t)out | (uintptr_t)a.t.act[l]) & 3) == 0;
+    const dim3 grid((unsigned)(f.w == 1 ? (rows + 3) / 4 : rows));
+    ln_dispatch(f, [&](auto w, auto p) {
+        constexpr int W = decltype(w)::value, P = decltype(p)::value;
+        auto go = [&](auto k) {
+            hipLaunchKernelGGL(k, grid, dim3(256), 0, st, x, rows, L.N, L.gamma, L.beta, a.net.ln_eps, a.d_net->actq, l + 1, out,
+                               rtiles, a.t.ln[l], a.t.act[l]);
+        };
+        if (vec) go(k_ln_tanh_rows<W, P, true>);
+        else go(k_ln_tanh_rows<W, P, false>);
+    });
     return hipGetLastError() == hipSuccess ? AQ_OK : AQ_EHIP;
 }
 
