@@ -148,8 +148,9 @@ aq_status aq_policy_conv_stack_layers(const aq_policy* p, int32_t* n_layers);
 aq_status aq_policy_fp16_conv_stack_layers(const aq_policy* p, int32_t* n_layers);
 
 /* Which compiled variant of the whole-network kernels a forward of `batch` >= 1 rows launches under the
- * current launch plan: *rows = batch rows per workgroup (16, 32, 64 or 128), *tiles = 32-feature tiles per
- * wavefront and pass (1 or 2); both 0 when the forward runs one launch per layer instead (a network the
+ * current launch plan: *rows = batch rows per workgroup (16, 32, 64 or 128), *tiles = 1 or 2, 32-feature tiles
+ * per wavefront and pass (kinds 1 to 3) or half the most tiles a wavefront can own (kind 0: 1 for hidden layers up to 512 wide,
+ * 2 up to 1024); both 0 when the forward runs one launch per layer instead (a network the
  * kernels do not take, few rows on wide layers under plan 0 -- told for the default stream, without exploration, weights in use --, or launch plan 2 / 3).  *kind is the kernel: 0 = the general kernel; 1 = the
  * software-pipelined kernel for wide layers (64 rows, two tiles; per-channel weights, fp32 observations, hidden
  * widths multiples of 64 without LayerNorm, every K a multiple of 128, at most 64 outputs); 2 = the kernel for

@@ -103,6 +103,7 @@ struct aq_policy {
     // which is the same one for good.  Any other handle may name a new stream once its own is destroyed, perhaps with work
     // in flight: those pairs are guarded by an event behind their last forward, whatever stream it was on.
     size_t few_bytes = 0;  // of one map; 0: the policy never takes that route
+    size_t few_ln_bytes = 0;  // of a pair's fp32 rows into a LayerNorm
     int8_t* few_slab = nullptr;
     hipStream_t few_stream[kFewPairs] = {};  // of the pair's last forward
     hipEvent_t few_done[kFewPairs] = {};
@@ -394,12 +395,12 @@ extern "C" aq_status aq_policy_create(const aq_net* net, aq_policy** out) {
         FwdArgs probe(p->h_net);
         probe.c.batch = 1;
         int r = 0, few_n = 0;
-        size_t lds = 0;
         for (int l = 0; l < net->n_layers - 1; ++l) few_n = std::max(few_n, p->L[l].N);
         // (one row: if the layers' launches are not faster there, they are at no batch)
-        if (fused_mlp_supported(probe, &r, &lds) && few_rows_faster(probe, false, false, false)) {
+        if (fused_mlp_supported(probe, &r) && few_rows_faster(probe, false, false, false)) {
             p->few_bytes = (blocked_map_bytes(kFewMaxRows, few_n) + 255) & ~(size_t)255;
-            if (hip_failed(hipMalloc((void**)&p->few_slab, 2 * kFewPairs * p->few_bytes))) {
+            p->few_ln_bytes = ((size_t)kFewMaxRows * (size_t)p->ln_elems * 4 + 255) & ~(size_t)255;
+            if (hip_failed(hipMalloc((void**)&p->few_slab, kFewPairs * (2 * p->few_bytes + p->few_ln_bytes)))) {
                 (void)hipFree(p->slab);
                 delete p;
                 return AQ_ENOMEM;
@@ -710,8 +711,7 @@ extern "C" aq_status aq_policy_fused_plan(const aq_policy* p, int64_t batch, int
     FwdArgs a(p->h_net);
     a.c.batch = batch;
     int r = 0, t = 0;
-    size_t lds = 0;
-    if (p->path == 2 || !fused_mlp_supported(a, &r, &lds, &t) || (p->path == 0 && p->few_bytes && few_rows_faster(a, false, false, false))) r = t = 0;
+    if (p->path == 2 || !fused_mlp_supported(a, &r, &t) || (p->path == 0 && p->few_bytes && few_rows_faster(a, false, false, false))) r = t = 0;
     *rows = r;
     *tiles = t;
     *kind = r != 0 ? fused_mlp_kernel_kind(a) : 0;
@@ -723,9 +723,8 @@ extern "C" aq_status aq_policy_subbyte_layers(const aq_policy* p, int64_t batch,
     FwdArgs a(p->h_net);
     a.c.batch = batch;
     int r = 0;
-    size_t lds = 0;
     int n = 0;
-    if (p->path == 2 || !fused_mlp_supported(a, &r, &lds)) {
+    if (p->path == 2 || !fused_mlp_supported(a, &r)) {
         const int nc = p->conv_stack ? conv_stack_layers(a) : 0;
         for (int l = nc; l < (int)p->L.size(); ++l)
             n += p->subbyte && p->w4[l] && !p->h_net.asym && layer_uses_skinny(a, l);
@@ -1076,7 +1075,6 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
     a.c.actions = d_actions;
     a.c.batch = batch;
     a.c.K0 = p->L[0].K;
-    a.c.Kp0 = p->L[0].K_pad;
     a.c.in_u8 = p->h_net.in_u8;
     if (p->subbyte && p->w4_slab && p->w4_stale) {
         const aq_status ws = refresh_w4(p, st);
@@ -1095,8 +1093,7 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
     }
 
     int rows;
-    size_t lds;
-    bool can_fuse = p->path != 2 && fused_mlp_supported(a, &rows, &lds);
+    bool can_fuse = p->path != 2 && fused_mlp_supported(a, &rows);
     if (p->path == 1 && !can_fuse) return AQ_ESHAPE;
     // An MLP that fits a whole-network kernel runs there, but for few rows on wide layers.  (Not under capture, nor for
     // the allocation-free entry point: what is captured may be replayed on any stream beside any other, and needs no
@@ -1138,8 +1135,8 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
     if (fixed) {
         sc = *fixed;
     } else if (pair >= 0) {
-        int8_t* const maps = p->few_slab + (size_t)(2 * pair) * p->few_bytes;
-        sc = FwdScratch{{maps, maps + p->few_bytes}, true, nullptr, nullptr};
+        int8_t* const maps = p->few_slab + (size_t)pair * (2 * p->few_bytes + p->few_ln_bytes);
+        sc = FwdScratch{{maps, maps + p->few_bytes}, true, (float*)(maps + 2 * p->few_bytes), nullptr};
     } else {
         s = ensure_i8(p, batch, st);
         if (s != AQ_OK) return s;
@@ -1211,8 +1208,7 @@ extern "C" aq_status aq_policy_forward_int8_static(aq_policy* p, const void* d_o
     FwdArgs probe(p->h_net);
     probe.c.batch = batch > 0 ? batch : 1;
     int rows = 0;
-    size_t lds = 0;
-    const bool fused = p->path != 2 && fused_mlp_supported(probe, &rows, &lds);
+    const bool fused = p->path != 2 && fused_mlp_supported(probe, &rows);
     FwdScratch sc{{nullptr, nullptr}, false, nullptr, nullptr};
     if (!fused) {  // (the whole-network kernel keeps everything in LDS and needs none of it)
         if ((double)batch * (double)(p->max_hidden_elems + 4 * (p->ln_elems + p->y_elems)) > 1e12 ||

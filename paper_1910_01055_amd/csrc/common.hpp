@@ -300,21 +300,13 @@ struct CallArgs {
     const void* obs;
     void* actions;
     int64_t batch;
-    int ld;     // fused kernel: LDS row stride, bytes
-    int cst_n;  // fused kernel: words per constant array in the LDS staging area
-    int K0, Kp0, in_u8;  // first layer's input width (real, padded) and input type, so the observation
-                         // loads can be issued before anything else has been read
-    // fused kernel: the first layer's packed weights and constant pack, so that their loads do not
-    // wait for the network description either
+    int K0, in_u8;  // first layer's input width and input type
+    // pipelined wide kernel: LDS row stride in bytes; the first layer's packed weights, so that their loads do not wait for
+    // the network description
+    int ld;
     const int8_t* wp0;
-    const int32_t* pack0;
-    int NT0, KS0, pieces0;
-    int cst_dbl;   // fused kernel: the LDS constant area is doubled (next layer's constants parked early)
-    int ln0;       // fused kernel: the first layer is followed by LayerNorm (its parked gain / offset are pre-scaled)
-    int narrow0;   // fused kernel: the first layer is also the last and narrow (its weights are split over K)
-    int part_off;  // fused kernel: LDS offset of the partial-sum area of a narrow last layer, or -1 when it
-                   // fits the idle activation buffer
-    // fused kernel: Gaussian exploration noise added where the actions are written (ex_sigma != NULL)
+    int NT0, KS0;
+    // whole-network kernels: Gaussian exploration noise added where the actions are written (ex_sigma != NULL)
     const float* ex_sigma;
     uint32_t ex_k0, ex_k1, ex_s0, ex_s1;
 };

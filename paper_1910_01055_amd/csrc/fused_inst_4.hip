@@ -1,5 +1,4 @@
-// Explicit instantiation of one fused-MLP kernel variant (rows = 32 * 2, 2 feature tile(s) per wave,
-// symmetric weights), with and without intermediate taps.
+// Explicit instantiation of general whole-network kernel variants, with and without intermediate taps.
 #include "fused_mlp.hpp"
 
 namespace aq {

@@ -1,8 +1,7 @@
-// Explicit instantiation of one fused-MLP kernel variant (16 rows per workgroup, per-tensor asymmetric
-// weights), with and without intermediate taps.
+// Explicit instantiation of general whole-network kernel variants, with and without intermediate taps.
 #include "fused_mlp.hpp"
 
 namespace aq {
-AQ_FUSED_INST(1, 1, true, false, true);
-AQ_FUSED_INST(1, 1, true, true, true);
+AQ_FUSED_INST(2, 2, true, false, false);
+AQ_FUSED_INST(2, 2, true, true, false);
 }  // namespace aq

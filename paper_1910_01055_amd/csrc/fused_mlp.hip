@@ -1,9 +1,11 @@
-// Host side of the whole-network fused int8 MLP: decides whether a network fits the kernel, picks
-// rows per workgroup and feature tiles per wave, and dispatches to the compiled variant.
+// Host side of the whole-network int8 MLP kernels: decides whether a network fits the general one, picks its rows per workgroup,
+// and hands each call to the kernel that takes its shape.
 #include "fused_mlp.hpp"
 
 namespace aq {
 
+AQ_FUSED_DECL(1, 1, false, false, true);
+AQ_FUSED_DECL(1, 1, false, true, true);
 AQ_FUSED_DECL(1, 1, false, false, false);
 AQ_FUSED_DECL(1, 1, false, true, false);
 AQ_FUSED_DECL(2, 1, false, false, false);
@@ -14,86 +16,82 @@ AQ_FUSED_DECL(1, 2, false, false, false);
 AQ_FUSED_DECL(1, 2, false, true, false);
 AQ_FUSED_DECL(2, 2, false, false, false);
 AQ_FUSED_DECL(2, 2, false, true, false);
+AQ_FUSED_DECL(1, 1, true, false, true);
+AQ_FUSED_DECL(1, 1, true, true, true);
 AQ_FUSED_DECL(1, 1, true, false, false);
 AQ_FUSED_DECL(1, 1, true, true, false);
 AQ_FUSED_DECL(2, 1, true, false, false);
 AQ_FUSED_DECL(2, 1, true, true, false);
-AQ_FUSED_DECL(1, 1, false, false, true);
-AQ_FUSED_DECL(1, 1, false, true, true);
-AQ_FUSED_DECL(1, 1, true, false, true);
-AQ_FUSED_DECL(1, 1, true, true, true);
+// hidden layers wider than 512: 16 rows per workgroup, and per-tensor weights
+extern AQ_FUSED_INST(1, 2, false, false, true);
+extern AQ_FUSED_INST(1, 2, false, true, true);
+extern AQ_FUSED_INST(1, 2, true, false, true);
+extern AQ_FUSED_INST(1, 2, true, true, true);
+extern AQ_FUSED_INST(1, 2, true, false, false);
+extern AQ_FUSED_INST(1, 2, true, true, false);
+extern AQ_FUSED_INST(2, 2, true, false, false);
+extern AQ_FUSED_INST(2, 2, true, true, false);
 
 namespace {
 struct Plan {
-    int mt, nb, ld, cst_n, part_off, cst_dbl;
-    bool half;  // 16 rows per workgroup
+    int rt, nb, ld, off_red, off_sum, off_cst, off_y;
     size_t lds;
 };
 
+// LDS of a workgroup of 16 rt rows; false where the network is none of this kernel's.
+bool layout(const NetDev& n, int rt, Plan* p) {
+    int w = 0, nt = 0;
+    const LayerDev& last = n.L[n.n_layers - 1];
+    for (int l = 0; l < n.n_layers; ++l) {
+        const LayerDev& L = n.L[l];
+        if (L.kh != 1 || L.kw != 1 || L.in_h != 1 || L.in_w != 1 || L.NT * 32 > fused::IMAXN || L.K > fused::IMAXK) return false;
+        const int k = (L.K + 63) & ~63;
+        w = w > k ? w : k;
+        if (l < n.n_layers - 1) nt = nt > L.NT ? nt : L.NT;
+    }
+    p->rt = rt;
+    p->nb = nt > 2 * fused::IW ? 2 : 1;
+    p->ld = w + 16;  // (16-byte reads of consecutive rows are 4 banks further each)
+    size_t bytes = (size_t)16 * rt * p->ld;
+    const size_t part = (size_t)fused::IW * rt * 1024;  // a narrow last layer's partial sums
+    if (bytes < part) bytes = part;
+    auto take = [&](size_t more) {
+        const int at = (int)bytes;
+        bytes += more;
+        return at;
+    };
+    p->off_red = take((size_t)16 * rt * fused::IW * 8);
+    p->off_sum = take(n.asym ? (size_t)2 * 16 * rt * 4 : 0);
+    p->off_cst = take(2 * fused::INARROW * 4);
+    p->off_y = take(n.head == AQ_HEAD_ARGMAX && last.N <= fused::INARROW ? (size_t)16 * rt * (fused::INARROW + 1) * 4 : 0);
+    p->lds = bytes;
+    return p->lds <= 160 * 1024;
+}
+
+// Rows per workgroup, by measurement (us at 16 / 32 / 64 / 128 rows).  More rows pass fewer weight bytes per row through the CU's
+// vector memory path, fewer leave fewer CUs idle.  Above 512 wide one workgroup fills a CU: 61-1024x3-40 at 4096 rows
+// 27 / 30 / 42, at 8000 50 / 30 / 37, at 16379 97 / 58 / 41.  Up to 512, where two share one: 61-512x3-17 at 8000 17.1 / 14.4 / 18.1,
+// at 16379 29.8 / 19.6 / 20.0, at 24000 28.3 (32) / 26.5 / 26.2, at 65536 65.8 / 54.6 / 52.4; 111-400-300-8 at 16379 16.7 / 10.9 / 14.5,
+// at 24000 17.0 / 18.6 / 17.6, at 65536 37.8 / 37.7 / 34.4.  With per-tensor weights, which have no variant of 128 rows,
+// 111-400-300-8 at 65536 42.2 / 41.4 (64), 512x3 70.6 / 65.9.
 bool make_plan(const FwdArgs& a, Plan* p) {
-    int maxw = 0, max_np = 0, max_nt = 0;
-    for (int l = 0; l < a.net.n_layers; ++l) {
-        const LayerDev& L = a.net.L[l];
-        if (L.kh != 1 || L.kw != 1 || L.in_h != 1 || L.in_w != 1) return false;
-        maxw = maxw > L.KS * 32 ? maxw : L.KS * 32;
-        if (l < a.net.n_layers - 1) maxw = maxw > L.NT * 32 ? maxw : L.NT * 32;
-        max_np = max_np > L.NT * 32 ? max_np : L.NT * 32;
-        max_nt = max_nt > L.NT ? max_nt : L.NT;
-    }
-    if (max_np > CST_MAXN) return false;
-    // the last layer's fp32 rows (NT * 32 floats) reuse an activation buffer
-    const int lastw = a.net.L[a.net.n_layers - 1].NT * 32 * 4;
-    maxw = maxw > lastw ? maxw : lastw;
-    p->ld = maxw + 16;
-    p->cst_n = max_np;
-    // feature tiles per wave: wide layers take 2 (two passes of the 8 waves cover 32 tiles); more would
-    // not leave registers for the operand pipeline at two waves per SIMD
-    p->nb = (max_nt >= 32 && !a.net.asym) ? 2 : 1;
-    auto ln_fits = [&](int nb) {  // LayerNorm needs its whole row resident in one pass
-        for (int l = 0; l < a.net.n_layers - 1; ++l)
-            if (a.net.L[l].act == AQ_ACT_LN_TANH && (a.net.L[l].NT + nb - 1) / nb > FW) return false;
-        return true;
-    };
-    const bool narrow_last = a.net.L[a.net.n_layers - 1].NT <= NARROW_NT;
-    const int nb_full = p->nb;
-    // Rows per workgroup: 16 (one tile per wave only), 32, 64 or 128 (the latter with one tile per wave
-    // only).  A workgroup's time grows roughly like 1 + rows/32 (a fixed latency chain plus epilogue work
-    // per row), the 256 CUs take one workgroup each per round: take the cheapest rounds x time.
-    struct Cand {
-        int rows, mt, nb;
-        bool half;
-    };
-    const Cand cands[4] = {{16, 1, 1, true}, {32, 1, nb_full, false}, {64, 2, nb_full, false}, {128, 4, 1, false}};
-    double best = 0.0;
-    bool found = false;
-    for (const Cand& cd : cands) {
-        if (cd.mt == 4 && (nb_full != 1 || a.net.asym)) continue;  // (the asymmetric 128-row variant does not fit the registers)
-        if (!ln_fits(cd.nb)) continue;
-        Plan q = *p;
-        q.mt = cd.mt;
-        q.nb = cd.nb;
-        q.half = cd.half;
-        // (a doubled constant area when everything still fits in 64 KB: small networks, where the
-        // barrier it saves per layer is a visible share of the time)
-        q.cst_dbl = cd.nb != 2 && cd.mt != 4 && fused_lds_bytes(32 * cd.mt, q.ld, q.cst_n, true) + PART_BYTES <= 64 * 1024;
-        q.lds = fused_lds_bytes(32 * cd.mt, q.ld, q.cst_n, q.cst_dbl != 0);
-        q.part_off = -1;
-        // partial sums of a narrow last layer: in the idle activation buffer if it is large enough,
-        // else in an area of their own behind everything else
-        if (narrow_last && (size_t)32 * cd.mt * q.ld < (size_t)PART_BYTES) {
-            q.part_off = (int)q.lds;
-            q.lds += PART_BYTES;
-        }
-        if (q.lds > 160 * 1024) continue;
-        const int64_t wgs = (a.c.batch + cd.rows - 1) / cd.rows;
-        const double cost = (double)((wgs + 255) / 256) * (1.0 + cd.rows / 32.0);
-        if (!found || cost < best) {
-            best = cost;
-            found = true;
-            *p = q;
-        }
-    }
-    return found;
+    const NetDev& n = a.net;
+    const int64_t b = a.c.batch;
+    Plan q;
+    if (!layout(n, 1, &q)) return false;
+    int widest = 0;
+    for (int l = 0; l < n.n_layers - 1; ++l) widest = widest > n.L[l].N ? widest : n.L[l].N;
+    int rt;
+    if (b <= 16 * 256) rt = 1;
+    else if (q.nb == 2) rt = b <= 32 * 256 ? 2 : 4;
+    else if (b <= (widest > 480 ? 32 * 511 : 32 * 768)) rt = 2;
+    else if (b <= 32 * 768) rt = 4;
+    else rt = !n.asym ? 8 : widest > 480 ? 4 : 2;
+    while (rt > 1 && !layout(n, rt, &q)) rt /= 2;
+    if (rt == 1) (void)layout(n, 1, &q);
+    if (!grid_ok((b + 16 * rt - 1) / (16 * rt), fused::IT)) return false;
+    *p = q;
+    return true;
 }
 }  // namespace
 
@@ -105,17 +103,15 @@ bool any_taps(const FwdArgs& a) {
     return false;
 }
 
-bool fused_mlp_supported(const FwdArgs& a, int* rows_out, size_t* lds_out, int* tiles_out) {
+bool fused_mlp_supported(const FwdArgs& a, int* rows_out, int* tiles_out) {
     if (rows16_mlp_supported(a)) {  // (given a 16-byte aligned observation buffer; every such network also has a plan)
         *rows_out = 16 * rows16_mlp_row_tiles(a.c.batch);
-        *lds_out = 0;
         if (tiles_out) *tiles_out = 1;
         return true;
     }
     Plan p;
     if (!make_plan(a, &p)) return false;
-    *rows_out = p.half ? 16 : 32 * p.mt;
-    *lds_out = p.lds;
+    *rows_out = 16 * p.rt;
     if (tiles_out) *tiles_out = p.nb;
     return true;
 }
@@ -125,54 +121,44 @@ int fused_mlp_kernel_kind(const FwdArgs& a) {
     Plan p;
     int ld;
     if (!make_plan(a, &p)) return 0;
-    if (p.half) return 0;
-    if (p.nb == 2 && p.mt == 2 && wide_mlp_supported(a, &ld)) return 1;
+    if (p.nb == 2 && p.rt == 4 && wide_mlp_supported(a, &ld)) return 1;
     return 0;
 }
 
-aq_status launch_fused_mlp(const FwdArgs& a_in, hipStream_t st) {
+aq_status launch_fused_mlp(const FwdArgs& a, hipStream_t st) {
     // 16-row workgroups on small networks: the kernel built for that case (asked first, before any planning: at
     // these sizes the call's host time is what a launch costs)
-    const bool aligned = ((uintptr_t)a_in.c.obs & 15) == 0;
-    if (aligned && rows16_mlp_supported(a_in)) return launch_rows16_mlp(a_in, st);
+    const bool aligned = ((uintptr_t)a.c.obs & 15) == 0;
+    if (aligned && rows16_mlp_supported(a)) return launch_rows16_mlp(a, st);
     Plan p;
-    if (!make_plan(a_in, &p)) return AQ_ESHAPE;
+    if (!make_plan(a, &p)) return AQ_ESHAPE;
     // 64-row workgroups on wide layers: the pipelined kernel where the shapes and the address allow it
     int wide_ld;
-    if (aligned && !p.half && p.nb == 2 && p.mt == 2 && wide_mlp_supported(a_in, &wide_ld)) return launch_wide_mlp(a_in, st);
-    FwdArgs a = a_in;
-    a.c.ld = p.ld;
-    a.c.cst_n = p.cst_n;
-    a.c.wp0 = a.net.L[0].wp;
-    a.c.pack0 = a.net.L[0].bias_fold;
-    a.c.NT0 = a.net.L[0].NT;
-    a.c.KS0 = a.net.L[0].KS;
-    a.c.pieces0 = (a.net.n_layers == 1 ? 2 : 4) * a.net.L[0].NT * 8;
-    a.c.part_off = p.part_off;
-    a.c.cst_dbl = p.cst_dbl;
-    a.c.ln0 = a.net.n_layers > 1 && a.net.L[0].act == AQ_ACT_LN_TANH;
-    a.c.narrow0 = a.net.n_layers == 1 && a.net.L[0].NT <= NARROW_NT;
-    const bool tp = any_taps(a);
-    const bool as = a.net.asym != 0;
-#define AQ_GO(MT, NB, AS, HF)                                                   \
-    return tp ? launch_fused_t<MT, NB, AS, true, HF>(a, p.lds, st) \
-              : launch_fused_t<MT, NB, AS, false, HF>(a, p.lds, st)
-    if (p.half) {
-        if (as) AQ_GO(1, 1, true, true);
-        AQ_GO(1, 1, false, true);
-    }
+    if (aligned && p.nb == 2 && p.rt == 4 && wide_mlp_supported(a, &wide_ld)) return launch_wide_mlp(a, st);
+    const fused::Call c{a.c.obs, a.c.actions, a.c.batch, a.c.ex_sigma, a.c.ex_k0, a.c.ex_k1, a.c.ex_s0, a.c.ex_s1,
+                        p.ld, p.off_red, p.off_sum, p.off_cst, p.off_y};
+    const bool taps = any_taps(a), as = a.net.asym != 0;
+#define AQ_GO(MT, NB, AS, HF)                                                            \
+    return taps ? launch_fused_t<MT, NB, AS, true, HF>(a.d_net, c, a.t, p.lds, st)       \
+                : launch_fused_t<MT, NB, AS, false, HF>(a.d_net, c, a.t, p.lds, st)
+#define AQ_GO_ROWS(NB, AS)                 \
+    do {                                   \
+        if (p.rt == 1) AQ_GO(1, NB, AS, true);  \
+        if (p.rt == 2) AQ_GO(1, NB, AS, false); \
+        if (p.rt == 4) AQ_GO(2, NB, AS, false); \
+    } while (0)
     if (p.nb == 2) {
-        if (p.mt == 1) AQ_GO(1, 2, false, false);
-        AQ_GO(2, 2, false, false);
+        if (as) AQ_GO_ROWS(2, true);
+        else AQ_GO_ROWS(2, false);
+        return AQ_ESHAPE;
     }
     if (as) {
-        if (p.mt == 1) AQ_GO(1, 1, true, false);
-        if (p.mt == 2) AQ_GO(2, 1, true, false);
-        return AQ_ESHAPE;  // (no 128-row asymmetric variant: make_plan never picks it)
+        AQ_GO_ROWS(1, true);
+        return AQ_ESHAPE;
     }
-    if (p.mt == 1) AQ_GO(1, 1, false, false);
-    if (p.mt == 2) AQ_GO(2, 1, false, false);
+    AQ_GO_ROWS(1, false);
     AQ_GO(4, 1, false, false);
+#undef AQ_GO_ROWS
 #undef AQ_GO
 }
 

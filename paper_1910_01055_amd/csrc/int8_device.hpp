@@ -255,22 +255,6 @@ __device__ __forceinline__ void quad_acc(const int N, const LayerTaps& T, const 
     }
 }
 
-// 16-row workgroups still run 32x32x32 MFMAs (rows 16..31 of the operand are don't-care), then fold
-// the tile: lanes that hold rows 16..31 take over feature quads 2 and 3 of the row 16 below them.
-// Afterwards lane l owns row l & 15, half h = (l >> 4) & 1, and registers 4j+i (j = 0, 1) hold feature
-// 8 (j + 2h) + 4 (l >> 5) + i of the tile: every lane does useful epilogue work on half the registers.
-// v_permlane16_swap exchanges the odd 16-lane rows of its first operand with the even rows of its
-// second: (c[r], c[r+8]) -> c[r] = [own row 0 | c[r+8] row 0 | own row 2 | c[r+8] row 2], which is the fold.
-__device__ __forceinline__ void fold_rows16(v16i& c, int lane) {
-    (void)lane;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) c[r] = (int)__builtin_amdgcn_permlane16_swap((unsigned)c[r], (unsigned)c[r + 8], false, false)[0];
-}
-__device__ __forceinline__ int fold_rows16_scalar(int v, int lane) {
-    (void)lane;
-    return (int)__builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false)[0];
-}
-
 // Hidden-layer epilogue of a wave's whole tile set (NB feature tiles x MT row tiles).  The
 // per-channel constants of a feature quad are loaded once and shared by the MT row tiles, and the
 // next quad's constants are requested before the current quad is processed, so the (global or LDS)
@@ -296,7 +280,6 @@ __device__ __forceinline__ QuadConsts load_quad_consts(const CPtrs& C, int n0) {
 }
 // FAST: every channel has 33 <= r <= 54, so (acc*M0 + 2^(r-1)) >> r + z_out collapses to
 // (mulhi(acc, M0) + rz) >> sh with rz = 2^(r-33) + (z_out << sh), sh = r - 32 (same integers).
-// HALF: the tiles were folded by fold_rows16 (two quads per tile, `hh` = this lane's half).
 // clamp(x, lo, hi) for lo <= hi as one instruction: the median of the three
 __device__ __forceinline__ int clamp_code(int x, int lo_v, int hi_s) {
     int r;
@@ -304,15 +287,14 @@ __device__ __forceinline__ int clamp_code(int x, int lo_v, int hi_s) {
     return r;
 }
 
-template <int MT, int NB, bool ASYM, bool TAPS, bool FAST, bool HALF = false>
+template <int MT, int NB, bool ASYM, bool TAPS, bool FAST>
 __device__ __forceinline__ void epi_hidden_wave(const int N, const int NT, const LayerTaps& T, const CPtrs& C,
                                                 v16i (&acc)[NB][MT], v16i (&rs)[MT], int zw_s, int grp, int g,
                                                 int64_t row_first, int64_t rows, bool guard_rows, int z_out, int lo,
-                                                int8_t* out0, int64_t out_mt_stride, bool packed, int n_store,
-                                                int hh = 0) {
-    constexpr int QT = HALF ? 2 : 4;  // quads per tile
+                                                int8_t* out0, int64_t out_mt_stride, bool packed, int n_store) {
+    constexpr int QT = 4;  // quads per tile
     constexpr int NQ = NB * QT;
-    auto n0_of = [&](int q) { return (grp * NB + q / QT) * 32 + 8 * (q % QT + (HALF ? 2 * hh : 0)) + 4 * g; };
+    auto n0_of = [&](int q) { return (grp * NB + q / QT) * 32 + 8 * (q % QT) + 4 * g; };
     auto valid = [&](int q) { return grp * NB + q / QT < NT; };
     QuadConsts cur = load_quad_consts<FAST>(C, valid(0) ? n0_of(0) : 0);
     // clamp bounds as operands of the three-input median: one vector register, one scalar (the
@@ -372,13 +354,13 @@ __device__ __forceinline__ void epi_hidden_wave(const int N, const int NT, const
 
 // Last layer: y = (float)acc * m[n] for one tile, stored to y_row[n] (n < n_store) when y_row is
 // given; when act_row is given the elementwise head (tanh or identity) is applied and stored too.
-template <bool ASYM, bool TAPS, bool HALF = false>
+template <bool ASYM, bool TAPS>
 __device__ __forceinline__ void epi_last_tile(const int N, const LayerTaps& T, const CPtrs& C, const v16i& c, int rs0,
                                               int zw_s, int nt, int g, int64_t row, bool row_ok, float* y_row,
-                                              int n_store, float* act_row, int head, int hh = 0) {
+                                              int n_store, float* act_row, int head) {
 #pragma unroll
-    for (int j = 0; j < (HALF ? 2 : 4); ++j) {
-        const int n0 = nt * 32 + 8 * (j + (HALF ? 2 * hh : 0)) + 4 * g;
+    for (int j = 0; j < 4; ++j) {
+        const int n0 = nt * 32 + 8 * j + 4 * g;
         int val[4];
         quad_acc<ASYM, TAPS>(N, T, C, c, j, n0, rs0, zw_s, row, row_ok, val);
         const float4 mm = *(const float4*)(C.m + n0);

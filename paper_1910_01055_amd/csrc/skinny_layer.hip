@@ -61,30 +61,30 @@ void few_row_tile(int N, int64_t rows, bool argmax, int* ft, int* rt) {
 }
 
 // A whole-network kernel passes every weight through the vector memory path of one CU, however few the rows; the layers'
-// own launches spread them over the chip.  Measured, us (whole network / layers), one to 256 rows: 67-512x2-21 10.6 / 9.4,
-// 67-512x3-21 14.5 / 12.2, 67-1024x2-21 19.8 / 9.3 (256 rows 10.6), 256-1024x3-64 31.3 / 12.0 (256 rows 14.7),
-// 111-400-300-8 10.0 / 9.6; 512 rows: 67-1024x2-21 20.3 / 15.9, 111-800-600-8 15.4 / 16.8; per-tensor weights 67-512x2-21
-// 12.2 / 9.7, 67-1024x2-21 24.1 / 9.5.  An event behind the forward (streams other than the default one) costs 2.8 to 3.5: 67-512x2-21
-// at one row 8.7 without, 11.6 with it, 256-1024x3-64 11.4 and 14.9.  The first forward behind a quantize or an import finds its weights
-// in no L2, and each launch waits for its own: a whole pull of 28-512x2-1 24.8 us in one launch, 27.8 layer by layer.
+// own launches spread them over the chip.  Measured, us (whole network / layers), 16 rows, 61 inputs: 512x3 10.4 / 11.9, with a
+// LayerNorm 11.2 / 15.0; 1024x2 15.2 / 9.8, with a LayerNorm 15.8 / 12.6; 1024x3 23.6 / 12.3, with a LayerNorm 24.3 / 15.3; 300 rows
+// 1024x3 23.8 / 18.3, with a LayerNorm 24.8 / 21.7; 400-300 6.3 / 9.5; per-tensor weights 1024x3 24.2 / 12.4, 512x3 11.2 / 12.0.
+// An event behind the forward (streams other than the default one) costs 2.8 to 3.5.  The first forward behind a quantize or an
+// import finds its weights in no L2, and each launch waits for its own: a whole pull of 28-512x2-1 24.8 us in one launch, 27.8 layer
+// by layer.
 bool few_rows_faster(const FwdArgs& a, bool noise, bool guarded, bool cold) {
     const int nl = a.net.n_layers;
     if (a.c.batch > kFewMaxRows || nl < 2) return false;
     double weights = 0.0;  // millions
-    int widest = 0;
+    int widest = 0, lns = 0;
     for (int l = 0; l < nl; ++l) {
         const LayerDev& L = a.net.L[l];
         weights += 1e-6 * L.K * L.N;
         if (l == nl - 1) break;
-        if (L.act == AQ_ACT_LN_TANH) return false;  // (a launch and fp32 rows of its own)
+        if (L.act == AQ_ACT_LN_TANH) ++lns;
         widest = widest > L.N ? widest : L.N;
     }
     if (widest < kFewMinWidth) return false;
     if (a.net.head == AQ_HEAD_ARGMAX && !skinny_layer_does_argmax(a, nl - 1)) return false;
     for (int l = 0; l < nl; ++l)
         if (!layer_uses_skinny(a, l)) return false;
-    const double whole = a.net.asym ? 7.8 + 15.0 * weights : 7.5 + 10.0 * weights;
-    const double layers = nl * (a.c.batch > 256 ? 5.0 : a.c.batch > 128 ? 3.5 : 3.1) + (noise ? 3.1 : 0.0) + (guarded ? 3.3 : cold ? 1.6 : 0.0);
+    const double whole = 7.0 + 8.2 * weights + 0.9 * lns;  // (an upper bound: between 512x2 and 512x3 the two are within 1 us)
+    const double layers = nl * (a.c.batch > 256 ? 5.0 : a.c.batch > 128 ? 3.5 : 3.1) + 3.0 * lns + (noise ? 3.1 : 0.0) + (guarded ? 3.3 : cold ? 1.6 : 0.0);
     return layers < whole;
 }
 

@@ -18,10 +18,147 @@
 // last layer of at most 64 outputs.  Everything else takes the general fused kernel.
 #include <atomic>
 
-#include "fused_mlp.hpp"
+#include "explore_device.hpp"
+#include "int8_device.hpp"
 
 namespace aq {
 namespace {
+
+constexpr int FW = 8;            // wavefronts per workgroup
+constexpr int FT = FW * 64;      // threads per workgroup
+constexpr int CST_MAXN = 1024;   // widest layer
+
+
+// The network description is read through the kernel's pointer argument with uniform indices, i.e. by
+// scalar loads into scalar registers (measured faster than a copy in LDS read back through vector
+// registers: 2 % on the headline workload).  readfirstlane keeps a value scalar wherever the compiler
+// cannot prove it uniform, so that loop bounds and branches stay scalar.
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float unif(float v) { return __int_as_float(uni(__float_as_int(v))); }
+template <class T>
+__device__ __forceinline__ T* uni_ptr(T* p) {
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (T*)(((uint64_t)hi << 32) | lo);
+}
+
+// One layer as the kernel needs it: plain scalars, built field by field from the LDS copy.
+struct LayerView {
+    const int8_t* wp;
+    gv4i_ptr pack;        // the layer's epilogue constants: four contiguous [Np] arrays, as 16-byte pieces
+    const int32_t* rshift;
+    gint_ptr z_w;
+    int N, NT, KS, act, pieces, fast, z_out;
+    float s_out;
+    bool last, ln;
+};
+// The pack holds bias_fold, then by layer type: requantized M0, rz, sh (the general requantization
+// form reads its shifts from global memory); LayerNorm m, gamma, beta; last m (two arrays staged).
+__device__ __forceinline__ LayerView layer_view(const NetDev& n, int l, int n_layers) {
+    const LayerDev& s = n.L[l];
+    LayerView v;
+    v.last = l == n_layers - 1;
+    v.act = uni(s.act);
+    v.ln = !v.last && v.act == AQ_ACT_LN_TANH;
+    v.wp = uni_ptr(s.wp);
+    v.pack = (gv4i_ptr)uni_ptr(s.bias_fold);
+    v.rshift = uni_ptr(s.rshift);
+    v.z_w = (gint_ptr)uni_ptr(s.z_w);
+    v.N = uni(s.N);
+    v.NT = uni(s.NT);
+    v.KS = uni(s.KS);
+    v.pieces = (v.last ? 2 : 4) * v.NT * 8;
+    v.s_out = 1.0f;
+    v.z_out = 0;
+    v.fast = 0;
+    if (!v.last) {
+        v.s_out = unif(n.actq[l + 1].s);
+        v.z_out = uni(n.actq[l + 1].z);
+        v.fast = uni(n.fast[l]);
+    }
+    return v;
+}
+// this thread's share of a layer's constants: up to two 16-byte pieces (Np <= CST_MAXN)
+__device__ __forceinline__ void load_consts(const LayerView& v, int tid, v4i& c0, v4i& c1) {
+    if (tid < v.pieces) c0 = v.pack[tid];
+    if (tid + FT < v.pieces) c1 = v.pack[tid + FT];
+}
+__device__ __forceinline__ void park_consts(int pieces, int tid, int32_t* cst, const v4i& c0, const v4i& c1) {
+    if (tid < pieces) ((v4i*)cst)[tid] = c0;
+    if (tid + FT < pieces) ((v4i*)cst)[tid + FT] = c1;
+}
+
+// A last layer of at most two feature tiles would leave most waves idle.  It is spread over all
+// eight instead: its (feature tile, row tile) pairs go to different waves, and the waves left over
+// split K.  Partial accumulators meet in LDS (PART_WORDS ints per wave: 16 accumulator registers
+// and the row sums of the activations, lane-major).
+constexpr int NARROW_NT = 2;
+constexpr int PART_WORDS = 17 * 64;
+constexpr int PART_BYTES = FW * PART_WORDS * 4;
+struct NarrowMap {
+    int pairs, ksplit, pair, nt, mt, k0, k1;
+};
+template <int MT>
+__device__ __forceinline__ NarrowMap narrow_map(int NT, int KS, int wave) {
+    NarrowMap x;
+    x.pairs = NT * MT;                        // 1, 2, 4 or 8
+    const int lg = 31 - __builtin_clz(x.pairs);
+    x.ksplit = FW >> lg;
+    x.pair = wave & (x.pairs - 1);
+    const int kpart = wave >> lg;
+    x.nt = x.pair & (NT - 1);
+    x.mt = x.pair >> (NT - 1);                // NT is 1 or 2
+    const int kchunk = (KS + x.ksplit - 1) >> (3 - lg);
+    x.k0 = kpart * kchunk;
+    x.k1 = x.k0 + kchunk < KS ? x.k0 + kchunk : KS;
+    return x;
+}
+
+// Sums the K-split partial accumulators of a narrow last layer and dequantizes: every thread owns
+// 2 * NT * MT outputs (lane-major, so its LDS reads are conflict-free) and reads the KSPLIT partial
+// sums of each; all reads of one output are independent and issued together.
+template <int MT, int NT, bool TAPS>
+__device__ __forceinline__ void narrow_reduce(const int32_t* part, const CPtrs& C, const LayerTaps& T, int N,
+                                              int64_t row0, int64_t batch, float* yrow, int ldy, int tid, int head,
+                                              float* actions, float* tap_y, const CallArgs& c) {
+    constexpr int PAIRS = NT * MT, KSPLIT = FW / PAIRS;
+#pragma unroll
+    for (int it = 0; it < 2 * PAIRS; ++it) {
+        const int e = tid + it * FT, pr = it >> 1;  // FT = 512 outputs per step, 1024 per pair
+        const int reg = (e >> 6) & 15, ln = tid & 63;
+        int v = 0;
+#pragma unroll
+        for (int kp = 0; kp < KSPLIT; ++kp) {
+            const int32_t* src = part + (kp * PAIRS + pr) * PART_WORDS + ln;
+            v += src[reg * 64];
+        }
+        const int nt = pr & (NT - 1), mt = pr / NT;
+        const int n = nt * 32 + 8 * (reg >> 2) + 4 * (ln >> 5) + (reg & 3);
+        const int m = mt * 32 + (ln & 31);
+        v += C.bias_fold[n];
+        const int64_t row = row0 + m;
+        const bool ok = row < batch && n < N;
+        if (TAPS) {
+            if (T.acc && ok) T.acc[row * N + n] = v;
+        }
+        const float y = (float)v * C.m[n];
+        if (actions) {
+            // elementwise heads leave from here; only argmax needs the whole row in one place
+            if (ok) {
+                if (TAPS) {
+                    if (tap_y) tap_y[row * N + n] = y;
+                }
+                float act = head == AQ_HEAD_TANH ? tanh_head(y) : y;
+                if (c.ex_sigma)  // exploration noise of Sec. 4.1, sigma per actor (= per batch row)
+                    act = act + c.ex_sigma[row] * gaussian_draw((uint32_t)row, n, c.ex_k0, c.ex_k1, c.ex_s0, c.ex_s1);
+                actions[row * N + n] = act;
+            }
+        } else {
+            yrow[m * ldy + n] = y;
+        }
+    }
+}
+
 
 constexpr int WROWS = 64;    // batch rows per workgroup: two row tiles per wavefront
 constexpr int WPF = 4;       // weight k-steps in flight per wavefront
@@ -391,9 +528,9 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
         float* direct = head != AQ_HEAD_ARGMAX ? (float*)c.actions : nullptr;
         float* tap_y = TAPS ? t.y : nullptr;
         if (L.NT == 1)
-            narrow_reduce<2, 1, false, TAPS, false>(part, C, T, L.N, 0, row0, c.batch, yrow, ldy, tid, head, direct, tap_y, c);
+            narrow_reduce<2, 1, TAPS>(part, C, T, L.N, row0, c.batch, yrow, ldy, tid, head, direct, tap_y, c);
         else
-            narrow_reduce<2, 2, false, TAPS, false>(part, C, T, L.N, 0, row0, c.batch, yrow, ldy, tid, head, direct, tap_y, c);
+            narrow_reduce<2, 2, TAPS>(part, C, T, L.N, row0, c.batch, yrow, ldy, tid, head, direct, tap_y, c);
         if (direct) return;
         lds_barrier();
         // argmax over the dequantized rows (lowest index wins ties)
