@@ -5,13 +5,17 @@
 //
 // A layer's output features are split into passes of 512 (8 wavefronts x 2 feature tiles x 32); a wavefront
 // keeps two sets of accumulators, the pass being multiplied and the pass before it.  While the matrix cores
-// run the MFMAs of pass i, the vector ALU requantizes the accumulators of pass i - 1, one register quad per
+// run the MFMAs of pass i, the vector ALU requantizes the accumulators of pass i - 1, one register quads two per
 // k-step, written between the MFMAs of that k-step.  Across a layer boundary this still works: the first
 // k-steps of layer l + 1 read the features that layer l's earlier passes wrote, so the epilogue of layer l's
 // last pass runs under them; one workgroup barrier in the middle of that pass then publishes the remaining
-// features, and the k-steps that read them follow it.  Weights stream L2 -> registers in operand order, four
-// k-steps in flight per wavefront, and the stream does not stop at a pass boundary: the last k-steps of a
+// features, and the k-steps that read them follow it.  Weights stream L2 -> registers in operand order, two
+// k-steps of 64 in flight per wavefront, and the stream does not stop at a pass boundary: the last k-steps of a
 // pass already request the first k-steps of the next one.
+//
+// v_mfma_i32_16x16x64_i8 on the 32 x 32 operand tiles, as in the general kernel: the chip holds a higher clock under it than under
+// 32x32x32 (256-1024x3-64 at 16384 rows 46.5 -> 43.7 us, everything else the same).  Four quads of the epilogue in a k-step
+// instead of two, so that layers of K = 256 hide theirs too, spilled 41 registers and took 47.
 //
 // Shapes: per-channel symmetric weights, fp32 observations at a 16-byte aligned address, every hidden layer
 // ReLU / none (no LayerNorm) with a width that is a multiple of 64, every layer's K a multiple of 128, a
@@ -161,9 +165,9 @@ __device__ __forceinline__ void narrow_reduce(const int32_t* part, const CPtrs& 
 
 
 constexpr int WROWS = 64;    // batch rows per workgroup: two row tiles per wavefront
-constexpr int WPF = 4;       // weight k-steps in flight per wavefront
+constexpr int WPF = 2;       // weight k-steps (of 64) in flight per wavefront
 constexpr int WSLOT = 256;   // words of one wave-private constant slot: four arrays of 64 features
-constexpr int WGROUP = 16;   // k-steps of a pass that carry the epilogue of the pass before (one quad each)
+constexpr int WGROUP = 8;    // k-steps of a pass that carry the epilogue of the pass before (two quads each)
 
 typedef const char AQ_GLOBAL* gbytes;
 
@@ -176,7 +180,8 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
     const TapArgs t = taps_of(tp);
     extern __shared__ __align__(16) int8_t smem[];
     const NetDev& a = *netp;
-    const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6), g = lane >> 5, mrow = lane & 31;
+    const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+    const int b16 = lane & 15, g = lane >> 4;  // this lane's batch row and k-group (operands) / feature quad (results)
     const int64_t row0 = (int64_t)blockIdx.x * WROWS;
     const int ld = c.ld;
     int32_t* const cst_all = (int32_t*)(smem + 2 * WROWS * ld);
@@ -185,31 +190,28 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
     auto buf = [&](int i) { return smem + (i & 1) * WROWS * ld; };
     const int n_layers = uni(a.n_layers), nh = n_layers - 1;
 
-    // the weight stream of one pass of this wavefront: its two feature tiles, KS k-steps of 1 KiB each
+    // the weight stream of one pass of this wavefront: its two feature tiles, KS k-steps of 2 KiB each
     struct Stream {
         gbytes b0, b1;
         int KS;
     };
-    auto stream_of = [&](int l, int grp) {
-        const int KS = uni(a.L[l].KS);
-        gbytes wp = (gbytes)uni_ptr(a.L[l].wp);
-        return Stream{wp + (int64_t)(2 * grp) * KS * 1024, wp + (int64_t)(2 * grp + 1) * KS * 1024, KS};
+    const uint32_t lane_off = (uint32_t)((g >> 1) * 1024 + (b16 + 32 * (g & 1)) * 16);
+    // half h of the stream's tiles at k-step ks
+    auto wload = [&](gbytes t0, gbytes t1, int h, int ks) {
+        return *(gv4i_ptr)((h >> 1 ? t1 : t0) + (int64_t)ks * 2048 + (lane_off + 256 * (h & 1)));
     };
-    const uint32_t lane_off = (uint32_t)lane * 16u;
-    auto wload = [&](gbytes b, int ks) { return *(gv4i_ptr)(b + (int64_t)ks * 1024 + lane_off); };
 
     // first pass's first weights: requested before the observations are touched
-    v4i wreg[WPF][2];
+    v4i wreg[WPF][4];
     {
         const int KS0 = c.KS0;
         gbytes wp = (gbytes)c.wp0;
         const int grp0 = 2 * wave < c.NT0 ? wave : 0;
 #pragma unroll
-        for (int p = 0; p < WPF; ++p) {
-            const int k = p < KS0 ? p : KS0 - 1;
-            wreg[p][0] = wload(wp + (int64_t)(2 * grp0) * KS0 * 1024, k);
-            wreg[p][1] = wload(wp + (int64_t)(2 * grp0 + 1) * KS0 * 1024, k);
-        }
+        for (int p = 0; p < WPF; ++p)
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+                wreg[p][h] = wload(wp + (int64_t)(2 * grp0) * KS0 * 1024, wp + (int64_t)(2 * grp0 + 1) * KS0 * 1024, h, p);
     }
 
     // observation quantize: a0 = clamp(round(x / s0) + z0, 0, 255), kept in the signed domain.  The block's
@@ -253,11 +255,11 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
     }
     lds_barrier();
 
-    v16i cur[2][2], prev[2][2];
+    v4i cur[4][4], prev[4][4];  // [16-feature half][16-row tile]
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int h = 0; h < 4; ++h)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) cur[i][j] = prev[i][j] = zero16();
+        for (int r = 0; r < 4; ++r) cur[h][r] = prev[h][r] = v4i{0, 0, 0, 0};
 
     // what the epilogue of the previous pass needs (all uniform)
     bool have_prev = false, prev_active = false;
@@ -267,13 +269,12 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
     int32_t* prev_tacc = nullptr;  // intermediate outputs asked for by a test (TAPS only)
     uint8_t* prev_tact = nullptr;
 
-    // ---- epilogue of the previous pass, in pieces: quad Q = (feature tile nb, register quad j, row tile mt),
-    // piece i = output i of the quad.  Constants of a (nb, j) pair are read from the wave's LDS slot one pair
-    // ahead of their use.
+    // ---- epilogue of the previous pass, in pieces: quad Q = (half h, row tile r), piece i = output i of the quad.
+    // Constants of a half are read from the wave's LDS slot one half ahead of their use.
     QuadConsts qc{}, qn{};
     uint32_t pack = 0;
-    auto quad_consts = [&](int pair) {  // pair = nb * 4 + j
-        const int32_t* s = my_cst + prev_slot * WSLOT + (pair >> 2) * 32 + 8 * (pair & 3) + 4 * g;
+    auto quad_consts = [&](int h) {
+        const int32_t* s = my_cst + prev_slot * WSLOT + 16 * h + 4 * g;
         QuadConsts q;
         q.bf = *(const int4*)(s);
         q.M = *(const int4*)(s + 64);
@@ -285,29 +286,29 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
     auto epi_piece = [&](auto q_c, auto i_c, auto fast_c) __attribute__((always_inline)) {
         constexpr int Q = decltype(q_c)::value, i = decltype(i_c)::value;
         constexpr bool FAST = decltype(fast_c)::value;
-        constexpr int pair = Q >> 1, mt = Q & 1, nb = pair >> 2, j = pair & 3;
-        if (i == 0 && mt == 0) {
+        constexpr int h = Q >> 2, r = Q & 3;
+        if (i == 0 && r == 0) {
             qc = qn;
-            if (pair + 1 < 8) qn = quad_consts(pair + 1);
+            if (h + 1 < 4) qn = quad_consts(h + 1);
         }
         const int bfv = i == 0 ? qc.bf.x : i == 1 ? qc.bf.y : i == 2 ? qc.bf.z : qc.bf.w;
         const int Mv = i == 0 ? qc.M.x : i == 1 ? qc.M.y : i == 2 ? qc.M.z : qc.M.w;
         const int Zv = i == 0 ? qc.Z.x : i == 1 ? qc.Z.y : i == 2 ? qc.Z.z : qc.Z.w;
         const int Sv = i == 0 ? qc.S.x : i == 1 ? qc.S.y : i == 2 ? qc.S.z : qc.S.w;
-        const int val = prev[nb][mt][4 * j + i] + bfv;
-        const int n = (2 * prev_grp + nb) * 32 + 8 * j + 4 * g + i;
+        const int val = prev[h][r][i] + bfv;
+        const int n = 64 * prev_grp + 16 * h + 4 * g + i;
         int code;
         if (FAST) code = clamp_code((__mulhi(val, Mv) + Zv) >> Sv, lo_v, 255);
         else code = requant_code(val, Mv, prev_rshift[n], prev_zout, prev_lo);
         if (TAPS) {
-            const int64_t row = row0 + mt * 32 + mrow;
+            const int64_t row = row0 + r * 16 + b16;
             if (row < c.batch) {
                 if (prev_tacc) prev_tacc[row * prev_N + n] = val;
                 if (prev_tact) prev_tact[row * prev_N + n] = (uint8_t)code;
             }
         }
         pack = i == 0 ? (uint32_t)code : pack | ((uint32_t)code << (8 * i));
-        if (i == 3) *(uint32_t*)(prev_out + (mt * 32 + mrow) * ld + n - 3) = pack ^ 0x80808080u;
+        if (i == 3) *(uint32_t*)(prev_out + (r * 16 + b16) * ld + n - 3) = pack ^ 0x80808080u;
     };
     auto epi_begin = [&]() __attribute__((always_inline)) {
         qn = quad_consts(0);
@@ -322,48 +323,42 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
         });
     };
 
-    // ---- one k-step of this wavefront's 2 x 2 tiles; Q >= 0: with one quad of the previous pass's epilogue
-    // between its MFMAs.  Then the activation operands of k-step k + 2 and the weight slot's refill: k-step
-    // k + WPF of this pass, or, past its end, of the next pass (clamped to an address that exists when there
-    // is nothing left to request; those registers are then never used).
+    // ---- one k-step (of 64) of this wavefront's 4 x 4 tiles of 16 x 16; Q >= 0: with quads Q and Q + 1 of the previous
+    // pass's epilogue between its MFMAs.  A row tile's operand of the next k-step is read as soon as this one's MFMAs with it
+    // are issued; then the weight slot's refill: k-step k + WPF of this pass, or, past its end, of the next pass (clamped to an
+    // address that exists when there is nothing left to request; those registers are then never used).
     Stream sc{nullptr, nullptr, 1}, sn{nullptr, nullptr, 1};
     const int8_t* xrow = nullptr;
-    v4i xf[2][2];
+    v4i xf[4];
     auto kstep = [&](int k, auto p_c, auto q_c) __attribute__((always_inline)) {
         constexpr int p = decltype(p_c)::value, Q = decltype(q_c)::value;
-        constexpr int xs = p & 1;
-        using T = std::true_type;
-        cur[0][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[p][0], xf[xs][0], cur[0][0], 0, 0, 0);
-        if (Q >= 0) epi_piece(std::integral_constant<int, (Q >= 0 ? Q : 0)>{}, std::integral_constant<int, 0>{}, T{});
-        cur[0][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[p][0], xf[xs][1], cur[0][1], 0, 0, 0);
-        if (Q >= 0) epi_piece(std::integral_constant<int, (Q >= 0 ? Q : 0)>{}, std::integral_constant<int, 1>{}, T{});
-        cur[1][0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[p][1], xf[xs][0], cur[1][0], 0, 0, 0);
-        if (Q >= 0) epi_piece(std::integral_constant<int, (Q >= 0 ? Q : 0)>{}, std::integral_constant<int, 2>{}, T{});
-        cur[1][1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wreg[p][1], xf[xs][1], cur[1][1], 0, 0, 0);
-        if (Q >= 0) epi_piece(std::integral_constant<int, (Q >= 0 ? Q : 0)>{}, std::integral_constant<int, 3>{}, T{});
-        const int kk = k + 2 < sc.KS ? k + 2 : sc.KS - 1;
-        xf[xs][0] = *(const v4i*)(xrow + kk * 32);
-        xf[xs][1] = *(const v4i*)(xrow + 32 * ld + kk * 32);
+        const int8_t* const nx = xrow + (k + 1 < sc.KS ? k + 1 : sc.KS - 1) * 64;
+        static_for<0, 4>([&](auto r_c) __attribute__((always_inline)) {
+            constexpr int r = decltype(r_c)::value;
+            static_for<0, 4>([&](auto h_c) __attribute__((always_inline)) {
+                constexpr int h = decltype(h_c)::value;
+                cur[h][r] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wreg[p][h], xf[r], cur[h][r], 0, 0, 0);
+                if constexpr (Q >= 0 && (h & 1) == 1)  // eight pieces a k-step
+                    epi_piece(std::integral_constant<int, Q + r / 2>{}, std::integral_constant<int, 2 * (r & 1) + h / 2>{}, std::true_type{});
+            });
+            xf[r] = *(const v4i*)(nx + r * 16 * ld);
+        });
         const int idx = k + WPF;
         const bool in = idx < sc.KS;
         const int past = idx - sc.KS < sn.KS ? idx - sc.KS : sn.KS - 1;
         const int ks = in ? idx : past;
-        wreg[p][0] = wload(in ? sc.b0 : sn.b0, ks);
-        wreg[p][1] = wload(in ? sc.b1 : sn.b1, ks);
+#pragma unroll
+        for (int h = 0; h < 4; ++h) wreg[p][h] = wload(in ? sc.b0 : sn.b0, in ? sc.b1 : sn.b1, h, ks);
         __builtin_amdgcn_sched_barrier(0);
     };
     using NoQ = std::integral_constant<int, -1>;
     auto group = [&](int k) __attribute__((always_inline)) {
         static_for<0, WPF>([&](auto p_c) __attribute__((always_inline)) { kstep(k + decltype(p_c)::value, p_c, NoQ{}); });
     };
-
-    // the activation operand ring of the k-steps from k on (k even): k and k + 1
+    // the activation operands of k-step k
     auto start_ring = [&](int k) __attribute__((always_inline)) {
-        const int k1 = k + 1 < sc.KS ? k + 1 : sc.KS - 1;
-        xf[0][0] = *(const v4i*)(xrow + k * 32);
-        xf[0][1] = *(const v4i*)(xrow + 32 * ld + k * 32);
-        xf[1][0] = *(const v4i*)(xrow + k1 * 32);
-        xf[1][1] = *(const v4i*)(xrow + 32 * ld + k1 * 32);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) xf[r] = *(const v4i*)(xrow + r * 16 * ld + k * 64);
     };
     // Everything uniform a pass needs.  It is read from the network description one pass ahead of its use, so
     // that the scalar loads' round trips run under the previous pass's k-steps.
@@ -387,14 +382,14 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
             q.active = q.grp < ngroups;
             q.N = uni(L.N);
             q.Np = NT * 32;
-            q.KS = uni(L.KS);
+            q.KS = uni(L.KS) >> 1;
             q.act = uni(L.act);
             q.z_out = uni(a.actq[l + 1].z);
             q.fast = uni(a.fast[l]);
             gbytes wp = (gbytes)uni_ptr(L.wp);
             const int grp = q.active ? q.grp : 0;
-            q.b0 = wp + (int64_t)(2 * grp) * q.KS * 1024;
-            q.b1 = wp + (int64_t)(2 * grp + 1) * q.KS * 1024;
+            q.b0 = wp + (int64_t)(2 * grp) * q.KS * 2048;
+            q.b1 = wp + (int64_t)(2 * grp + 1) * q.KS * 2048;
             q.pack = (gv4i_ptr)uni_ptr(L.bias_fold);
             q.rshift = uni_ptr(L.rshift);
         }
@@ -412,19 +407,18 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
         sc = Stream{P.b0, P.b1, P.KS};
         // the pass after this one, for the weight stream (nothing to request: this pass's last tile again)
         if (Nx.valid && Nx.active) sn = Stream{Nx.b0, Nx.b1, Nx.KS};
-        else sn = Stream{sc.b0 + (int64_t)(sc.KS - 1) * 1024, sc.b1 + (int64_t)(sc.KS - 1) * 1024, 1};
+        else sn = Stream{sc.b0 + (int64_t)(sc.KS - 1) * 2048, sc.b1 + (int64_t)(sc.KS - 1) * 2048, 1};
         // this pass's per-channel constants: one 16-byte piece per lane (four arrays x 64 features), parked in
         // the wave's slot at the end of the pass
         v4i cw = {0, 0, 0, 0};
         const int cw_word = (lane >> 4) * P.Np + 64 * P.grp + 4 * (lane & 15);
         if (active) cw = P.pack[cw_word >> 2];
-        xrow = buf(l) + mrow * ld + g * 16;
+        xrow = buf(l) + b16 * ld + g * 16;
         if (active && !w_ready) {  // (the pass before this one was not this wavefront's, or requested nothing)
 #pragma unroll
-            for (int q = 0; q < WPF; ++q) {
-                wreg[q][0] = wload(sc.b0, q);
-                wreg[q][1] = wload(sc.b1, q);
-            }
+            for (int q = 0; q < WPF; ++q)
+#pragma unroll
+                for (int h = 0; h < 4; ++h) wreg[q][h] = wload(sc.b0, sc.b1, h, q);
         }
         // k-steps that may run before the previous pass's outputs are visible to every wavefront: all of them
         // within a layer; in a layer's first pass those that read what the previous layer's earlier passes wrote
@@ -437,7 +431,7 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
                     epi_begin();
                     static_for<0, WGROUP>([&](auto q_c) __attribute__((always_inline)) {
                         constexpr int q = decltype(q_c)::value;
-                        kstep(q, std::integral_constant<int, q % WPF>{}, q_c);
+                        kstep(q, std::integral_constant<int, q % WPF>{}, std::integral_constant<int, 2 * q>{});
                     });
                     k0 = WGROUP;
                 } else if (prev_fast) {
@@ -456,7 +450,7 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
             // park the constants: [bias_fold | M0 | rz | sh] x 64 features
             *(v4i*)(my_cst + (pass_no & 1) * WSLOT + (lane >> 4) * 64 + 4 * (lane & 15)) = cw;
         }
-        w_ready = active && sn.KS > 1;  // (KS is at least 4: a one-step stream is the placeholder)
+        w_ready = active && sn.KS > 1;  // (KS is at least 2: a one-step stream is the placeholder)
         // hand the accumulators to the next pass's epilogue
         have_prev = true;
         prev_active = active;
@@ -473,11 +467,11 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
             prev_tact = t.act[l];
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int h = 0; h < 4; ++h)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                prev[i][j] = cur[i][j];
-                cur[i][j] = zero16();
+            for (int r = 0; r < 4; ++r) {
+                prev[h][r] = cur[h][r];
+                cur[h][r] = v4i{0, 0, 0, 0};
             }
         if (!more) npass_prev_layer = P.npass;
         P = Nx;
