@@ -37,6 +37,14 @@ __device__ __forceinline__ h8 load_operand(__amdgpu_buffer_rsrc_t w, int lane_of
     return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(w, lane_off, off, 0));
 }
 
+// sum over the four 16-lane rows of a wavefront, the same value in every lane
+__device__ __forceinline__ float sum_rows4(float s) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    s = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
+    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+
 constexpr int MLW = 8;               // wavefronts per workgroup
 constexpr int MLT = MLW * 64;
 constexpr int MLMAXW = 1024;         // widest layer input / output
@@ -63,6 +71,7 @@ __global__ __launch_bounds__(MLT) void k_fp16_mlp(const Fp16Net* __restrict__ ne
     const int vrows = left < ROWS ? (int)left : ROWS;
     _Float16* const xs = sm;                 // the activations
     _Float16* const cs = sm + c.off_const;   // every layer's bias, gain and offset
+    float* const red = (float*)(sm + c.off_red);  // a LayerNorm's partial statistics
 
     // tiles of this wavefront in a layer, and where a tile's weights begin
     auto tiles_of = [&](int l) { return a.L[l].NT > wave ? (a.L[l].NT - wave + MLW - 1) / MLW : 0; };
@@ -179,23 +188,103 @@ __global__ __launch_bounds__(MLT) void k_fp16_mlp(const Fp16Net* __restrict__ ne
         static_for<0, PF>([&](auto p_c) __attribute__((always_inline)) {
             if (s + decltype(p_c)::value < ks) one(p_c, s);
         });
-        lds_barrier();  // all inputs read: the outputs take their place
-        const bool relu = l < nl - 1 && a.L[l].act == AQ_ACT_RELU;
+        const int N = uni(a.L[l].N), act = l < nl - 1 ? uni(a.L[l].act) : AQ_ACT_NONE;
         const _Float16* const bias = cs + a.L[l].c_off;
+        auto n0_of = [&](int i) { return (wave + MLW * (i >> 1)) * 32 + 16 * (i & 1) + 4 * g; };
+        if (__builtin_expect(act != AQ_ACT_LN_TANH, 1)) {
+            lds_barrier();  // all inputs read: the outputs take their place
+            const bool relu = act == AQ_ACT_RELU;
+#pragma unroll
+            for (int i = 0; i < 2 * NB; ++i) {
+                const h4 b4 = *(const h4*)(bias + n0_of(i));
+#pragma unroll
+                for (int r = 0; r < RT; ++r) {
+                    h4 o;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        _Float16 v = (_Float16)(acc[i][r][j] + (float)b4[j]);
+                        if (relu) v = v > (_Float16)0.0f ? v : (_Float16)0.0f;
+                        o[j] = v;
+                    }
+                    *(h4*)(xs + (r * 16 + i16) * ld + n0_of(i)) = o;
+                }
+            }
+            return;
+        }
+        // LayerNorm (biased variance, eps inside the root) of the rounded outputs, rounded, then tanh, rounded.  The values stay in
+        // the accumulators; a wavefront's features give (sum, squared deviations from their own mean) per row, and the wavefronts'
+        // pairs meet by the pairwise update (Chan, Golub, LeVeque) over the barrier that frees the inputs.  (Through LDS, a wavefront
+        // a row at a time with twelve lane exchanges each: 19-125-102-34 at 9785 rows 21.9 us.)
+        const int NT = uni(a.L[l].NT);
+        auto count_of = [&](int w) {
+            const int tiles = NT > w ? (NT - w + MLW - 1) / MLW : 0;
+            return 32 * tiles - (((NT - 1) & (MLW - 1)) == w ? NT * 32 - N : 0);
+        };
+        const float inv_nw = 1.0f / (float)count_of(wave);  // (of a wavefront with a tile: at least one feature)
 #pragma unroll
         for (int i = 0; i < 2 * NB; ++i) {
-            const int n0 = (wave + MLW * (i >> 1)) * 32 + 16 * (i & 1) + 4 * g;
-            const h4 b4 = *(const h4*)(bias + n0);
+            const h4 b4 = *(const h4*)(bias + n0_of(i));
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][r][j] = (float)(_Float16)(acc[i][r][j] + (float)b4[j]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            float s = 0.0f, q = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 2 * NB; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (i < 2 * NB - 2 || n0_of(i) + j < N) s += acc[i][r][j];  // (only a wavefront's last tile has padding)
+            s = sum_rows4(s);
+            const float mean_w = s * inv_nw;
+#pragma unroll
+            for (int i = 0; i < 2 * NB; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float d = acc[i][r][j] - mean_w;
+                    if (i < 2 * NB - 2 || n0_of(i) + j < N) q += d * d;
+                }
+            q = sum_rows4(q);
+            if (g == 0) *(float2*)(red + ((16 * r + i16) * MLW + wave) * 2) = float2{s, q};
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // the row's four lanes take two wavefronts' pairs each
+        float cnt[2], inv_cnt[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int n = count_of(2 * g + k);
+            cnt[k] = (float)n;
+            inv_cnt[k] = 1.0f / (float)(n > 0 ? n : 1);
+        }
+        lds_barrier();  // statistics of all wavefronts; all inputs read: the outputs take their place
+        float mean[RT], inv[RT];
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            const float4 v = *(const float4*)(red + (16 * r + i16) * MLW * 2 + 4 * g);
+            const float sw[2] = {cnt[0] > 0.0f ? v.x : 0.0f, cnt[1] > 0.0f ? v.z : 0.0f};
+            const float qw[2] = {cnt[0] > 0.0f ? v.y : 0.0f, cnt[1] > 0.0f ? v.w : 0.0f};
+            mean[r] = sum_rows4(sw[0] + sw[1]) / (float)N;
+            const float d0 = sw[0] * inv_cnt[0] - mean[r], d1 = sw[1] * inv_cnt[1] - mean[r];
+            const float m2 = sum_rows4((cnt[0] * d0 * d0 + qw[0]) + (cnt[1] * d1 * d1 + qw[1]));
+            inv[r] = 1.0f / sqrtf(m2 / (float)N + a.eps);
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * NB; ++i) {
+            const h4 g4 = *(const h4*)(bias + NT * 32 + n0_of(i)), o4 = *(const h4*)(bias + 2 * NT * 32 + n0_of(i));
 #pragma unroll
             for (int r = 0; r < RT; ++r) {
                 h4 o;
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    _Float16 v = (_Float16)(acc[i][r][j] + (float)b4[j]);
-                    if (relu) v = v > (_Float16)0.0f ? v : (_Float16)0.0f;
-                    o[j] = v;
+                    const _Float16 t = (_Float16)((acc[i][r][j] - mean[r]) * inv[r] * (float)g4[j] + (float)o4[j]);
+                    o[j] = (_Float16)tanh_rel((float)t);
                 }
-                *(h4*)(xs + (r * 16 + i16) * ld + n0) = o;
+                *(h4*)(xs + (r * 16 + i16) * ld + n0_of(i)) = o;
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
@@ -293,43 +382,6 @@ __global__ __launch_bounds__(MLT) void k_fp16_mlp(const Fp16Net* __restrict__ ne
         // (Selected in the epilogue above, it cost the wide case 8 us in spilled registers.)
         if (!last && (N & 31) && wave == ((NT - 1) & (MLW - 1)) && lane < ROWS)
             for (int n = N; n < NT * 32; ++n) xs[lane * ld + n] = (_Float16)0.0f;
-        if (!last && a.L[l].act == AQ_ACT_LN_TANH) {
-            // LayerNorm (biased variance, eps inside the root) of the rounded outputs, rounded, then tanh, rounded; a
-            // wavefront per row, the row in registers
-            lds_barrier();
-            const _Float16 *gam = cs + a.L[l].c_off + NT * 32, *bet = gam + NT * 32;
-            constexpr int LV = MLMAXW / 64;
-            for (int m = wave; m < vrows; m += MLW) {
-                _Float16* xr = xs + m * ld;
-                float v[LV], s = 0.0f;
-#pragma unroll
-                for (int i = 0; i < LV; ++i) {
-                    v[i] = 0.0f;
-                    if (64 * i < N && lane + 64 * i < N) v[i] = (float)xr[lane + 64 * i];
-                    s += v[i];
-                }
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-                const float mean = s / (float)N;
-                float ss = 0.0f;
-#pragma unroll
-                for (int i = 0; i < LV; ++i) {
-                    const float d = lane + 64 * i < N ? v[i] - mean : 0.0f;
-                    ss += d * d;
-                }
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-                const float inv = 1.0f / sqrtf(ss / (float)N + a.eps);
-#pragma unroll
-                for (int i = 0; i < LV; ++i) {
-                    const int n = lane + 64 * i;
-                    if (64 * i < N && n < N) {
-                        const _Float16 t = (_Float16)((v[i] - mean) * inv * (float)gam[n] + (float)bet[n]);
-                        xr[n] = (_Float16)tanh_rel((float)t);
-                    }
-                }
-            }
-        }
         if (TAPS || last) lds_barrier();
         tap(l);
         if (last) {
@@ -354,7 +406,7 @@ __global__ __launch_bounds__(MLT) void k_fp16_mlp(const Fp16Net* __restrict__ ne
 
 namespace {
 struct MlpPlan {
-    int rt, ld, off_const, off_y;
+    int rt, ld, off_const, off_red, off_y;
     size_t lds;
 };
 bool plan_rows(const Fp16Net& n, int rt, MlpPlan* p) {
@@ -374,6 +426,12 @@ bool plan_rows(const Fp16Net& n, int rt, MlpPlan* p) {
     halfs = (halfs + 7) & ~(size_t)7;
     p->off_const = (int)halfs;
     halfs += (size_t)n.cst;
+    p->off_red = (int)halfs;
+    for (int l = 0; l < n.n_layers - 1; ++l)
+        if (n.L[l].act == AQ_ACT_LN_TANH) {
+            halfs += (size_t)16 * rt * MLW * 4;
+            break;
+        }
     p->off_y = (int)halfs;
     if (n.L[n.n_layers - 1].NT <= 2 && n.head == AQ_HEAD_ARGMAX) halfs += (size_t)16 * rt * MLY_LD;
     p->lds = halfs * 2;
@@ -381,12 +439,16 @@ bool plan_rows(const Fp16Net& n, int rt, MlpPlan* p) {
 }
 // Rows per workgroup, or none.  Clocks of a workgroup: its weights through the CU's vector memory path at 58 B per clock
 // and its MFMAs (20 clocks each at the clock the chip holds, on four SIMDs), half of the shorter of the two hidden
-// behind the longer; barriers and epilogue per layer; 10 clocks per row tile and feature of a LayerNorm; rounds of one
+// behind the longer; barriers and epilogue per layer; a LayerNorm's statistics and tanh; rounds of one
 // workgroup per CU.  Fitted to 67-w-w-w-21: w = 128, 256, 512 at batch 4096 7.0, 9.2, 16.6 us; at 16384 12.9, 16.6,
-// 27.7 us; 256-1024x3-64 at 16384 75.8 us.  Against a launch per layer, which spreads a layer's weights over the
-// chip: 4 us each, then 371 k flop per clock.  That is what the widest layers reach; narrower ones and rows of no whole 8 values are
-// slower than so (187-1024x2-35 at 4570 rows 51.2 us, here 29.8; 131-871-794-5 at 4277 89, here 21.6).  At few rows the launches
-// are the faster ones (121-512x3-30 at 99 rows 11.4, here 14.9) but write maps that two streams would share.
+// 27.7 us; 256-1024x3-64 at 16384 75.8 us; LayerNorms of 64, 256, 512, 1024 features in front add 2.8, 4.6, 7.9, 12.9 us at 64 rows.
+// Against a launch per layer, which spreads a layer's weights over the chip.  Two estimates of that, of which the larger counts
+// (the launches write maps that two streams would share): 4 us each and 371 k flop per clock, what the widest layers reach; and three
+// quarters of 3.96 us each, per 10^6 of output tiles x K 12 us on the few-row kernel, 4 on the tiled one, 20 there for rows of no
+// whole 8 values, 4 us per 10^6 values of a LayerNorm, fitted to 16000 pairs (one to five hidden layers of 50 to 1300, 320 to
+// 27600 rows; whole, 104-1024x3-19 at 4096 rows takes 54 us, 49.8 by layers, and would be called faster).  With the first alone
+// 19-125-102-34 took 40.0 us at 28000 rows and 80 at 65536 (18.4 and 33.7 here), 111-400-300-8 134 at 65536 (58); it still
+// stands where a last round of workgroups is nearly empty.
 bool plan_mlp(const Fp16Net& n, int64_t batch, MlpPlan* best) {
     double best_c = 0.0;
     bool found = false;
@@ -398,7 +460,7 @@ bool plan_mlp(const Fp16Net& n, int64_t batch, MlpPlan* best) {
             const double tiles = n.L[l].NT, ks = (n.L[l].K + 31) / 32;
             const double mem = tiles * ks * 2048.0 / 58.0, mm = tiles * ks * rt * 2 * 20.0 / 4.0;
             per += (mem > mm ? mem + 0.5 * mm : mm + 0.5 * mem) + 2000.0 * (1.0 + 0.15 * rt);
-            if (l < n.n_layers - 1 && n.L[l].act == AQ_ACT_LN_TANH) per += 1500.0 + 10.0 * rt * n.L[l].N;
+            if (l < n.n_layers - 1 && n.L[l].act == AQ_ACT_LN_TANH) per += 1200.0 + rt * (1100.0 + 6.0 * n.L[l].N);
         }
         const int64_t wgs = (batch + 16 * rt - 1) / (16 * rt);
         if (!grid_ok(wgs, MLT)) continue;
@@ -410,11 +472,25 @@ bool plan_mlp(const Fp16Net& n, int64_t batch, MlpPlan* best) {
         }
     }
     if (!found) return false;
-    double layers = 0.0;
+    double flop = 0.0, us = 0.0;
     for (int l = 0; l < n.n_layers; ++l) {
-        layers += 9500.0 + 2.0 * n.L[l].NT * 32.0 * n.L[l].K * (double)batch / 371e3;
-        if (l < n.n_layers - 1 && n.L[l].act == AQ_ACT_LN_TANH) layers += 8000.0 + 10.0 * n.L[l].N * (double)batch / 4096.0;
+        const Fp16LayerDev& D = n.L[l];
+        flop += 9500.0 + 2.0 * D.NT * 32.0 * D.K * (double)batch / 371e3;
+        Fp16Layer L{};
+        L.fc = 1;
+        L.K = D.K;
+        L.N = D.N;
+        L.NT = D.NT;
+        const double tiles = (double)((batch + 31) / 32) * D.NT * D.K * 1e-6;
+        us += 3.96 + tiles * (fp16_layer_is_skinny(L, l == 0 ? 1 : 0, batch) ? 12.0 : D.K % 8 ? 20.0 : 4.0);
+        if (l < n.n_layers - 1 && D.act == AQ_ACT_LN_TANH) {
+            flop += 8000.0 + 10.0 * D.N * (double)batch / 4096.0;
+            us += 3.96 + 4e-6 * D.N * (double)batch;
+        }
     }
+    const int64_t wgs = (batch + 16 * best->rt - 1) / (16 * best->rt), in_last = (wgs - 1) % 256 + 1;
+    const double second = 0.75 * 2375.0 * us;
+    const double layers = flop > second || (wgs > 256 && in_last < 32) ? flop : second;
     return best_c <= layers;
 }
 }  // namespace
@@ -428,7 +504,7 @@ aq_status launch_fp16_mlp(const Fp16Net& n, const Fp16Net* d_net, const void* ob
                           void* const* taps, hipStream_t st) {
     MlpPlan p;
     if (!plan_mlp(n, batch, &p)) return AQ_ESHAPE;
-    const Fp16Call c{obs, actions, batch, p.ld, p.off_const, p.off_y};
+    const Fp16Call c{obs, actions, batch, p.ld, p.off_const, p.off_red, p.off_y};
     const dim3 grid((unsigned)((batch + 16 * p.rt - 1) / (16 * p.rt)));
 #define AQ_MLP16(RT, U, TP)                                                                                                   \
     do {                                                                                                                      \

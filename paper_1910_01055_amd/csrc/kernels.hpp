@@ -250,7 +250,8 @@ struct Fp16Call {
     const void* obs;
     void* actions;
     int64_t batch;
-    int ld, off_const, off_y;  // LDS, in halfs: row stride of the activations, the constants, a narrow argmax head's logits
+    // LDS, in halfs: row stride of the activations, the constants, a LayerNorm's statistics, a narrow argmax head's logits
+    int ld, off_const, off_red, off_y;
 };
 template <bool TAPS>
 struct Fp16Taps {

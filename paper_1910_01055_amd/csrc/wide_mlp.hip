@@ -5,7 +5,7 @@
 //
 // A layer's output features are split into passes of 512 (8 wavefronts x 2 feature tiles x 32); a wavefront
 // keeps two sets of accumulators, the pass being multiplied and the pass before it.  While the matrix cores
-// run the MFMAs of pass i, the vector ALU requantizes the accumulators of pass i - 1, one register quads two per
+// run the MFMAs of pass i, the vector ALU requantizes the accumulators of pass i - 1, two register quads a
 // k-step, written between the MFMAs of that k-step.  Across a layer boundary this still works: the first
 // k-steps of layer l + 1 read the features that layer l's earlier passes wrote, so the epilogue of layer l's
 // last pass runs under them; one workgroup barrier in the middle of that pass then publishes the remaining
