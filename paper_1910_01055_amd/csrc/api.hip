@@ -1157,19 +1157,26 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
         if (s != AQ_OK) return s;
     }
     int blocked = 0;  // how the layer before left its output
+    // Wide layers at many rows take a kernel that reads and writes maps in operand order only: from the first layer on, as long as
+    // the next one reads such a map.
+    bool many = nc == 0;
+    auto takes_many = [&](int l) {
+        return sc.blocked && pair < 0 && layer_uses_rows(a, l) && (l + 1 == nl - 1 ? layer_uses_skinny(a, l + 1) : layer_uses_rows(a, l + 1));
+    };
     for (int l = nc; l < nl; ++l) {
         const LayerBuf& b = p->L[l];
         const int64_t rows_l = batch * b.oh * b.ow;
         LayerIO io;
         io.in_blocked = blocked;
         const bool ln = l < nl - 1 && b.d.act == AQ_ACT_LN_TANH;  // (its rows' kernel writes either order)
-        blocked = sc.blocked && l < nl - 1 && b.fc && (ln || layer_uses_skinny(a, l)) && layer_uses_skinny(a, l + 1);
+        many = many && takes_many(l);
+        blocked = many || (sc.blocked && l < nl - 1 && b.fc && (ln || layer_uses_skinny(a, l)) && layer_uses_skinny(a, l + 1));
         io.out_blocked = ln ? 0 : blocked;
         io.in = l == 0 ? d_obs : (const void*)sc.i8[(l - 1) & 1];
         io.out = sc.i8[l & 1];
         io.ln_x = sc.ln_x;
         io.y = ybuf;
-        s = launch_layer_int8(a, l, io, st);
+        s = many ? launch_layer_rows(a, l, io, st) : launch_layer_int8(a, l, io, st);
         if (s != AQ_OK) return s;
         if (ln) {
             s = launch_ln_tanh_rows(a, l, io.ln_x, io.out, rows_l, blocked, st);

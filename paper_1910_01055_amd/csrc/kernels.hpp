@@ -108,6 +108,9 @@ bool few_rows_faster(const FwdArgs& a, bool noise, bool guarded, bool cold);
 int conv_stack_layers(const FwdArgs& a);
 aq_status launch_conv_stack(const FwdArgs& a, int8_t* out, hipStream_t st);
 bool layer_uses_skinny(const FwdArgs& a, int l);
+// fully connected layers at many rows (rows_layer.hip): input fp32 observations or a map in operand order, output such a map or fp32 rows
+bool layer_uses_rows(const FwdArgs& a, int l);
+aq_status launch_layer_rows(const FwdArgs& a, int l, const LayerIO& io, hipStream_t st);
 aq_status launch_layer_skinny(const FwdArgs& a, int l, const LayerIO& io, hipStream_t st);
 // the few-row kernel's nibble weights from a layer's packed 8-bit operands: `pieces` = NT * KS * 64 (16 bytes -> 8)
 aq_status launch_pack_nibbles(const int8_t* wp, uint8_t* w4, int64_t pieces, hipStream_t st);
