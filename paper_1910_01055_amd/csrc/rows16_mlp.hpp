@@ -135,6 +135,7 @@ __global__ __launch_bounds__(RT, MT == 1 ? 2 : 4) void k_mlp_rows16(const NetDev
                                                                      const TapParam<TAPS> tp) {
     const TapArgs t = taps_of(tp);
     constexpr int ROWS = 16 * MT;
+    constexpr bool BIAS_FIRST = MT > 1 && !(ASYM && MT == 4 && NH < 3);  // (see where the sums begin)
     constexpr int NQ = 2 * MT;  // observation quads per thread at most (64 quads per row)
     __shared__ __align__(16) int8_t s_buf[2][ROWS * RLD];
     __shared__ __align__(16) float s_red[ROWS * RW * 2];
@@ -398,8 +399,24 @@ __global__ __launch_bounds__(RT, MT == 1 ? 2 : 4) void k_mlp_rows16(const NetDev
         auto request_next = [&]() __attribute__((always_inline)) { request_layer(std::integral_constant<int, l + 1>{}); };
         const v4i(&wcur)[RSTEPS][2] = w[WDBL ? l & 1 : 0];
         v4i acc[MT][2], rsa[MT];  // (rsa: every register of it ends up holding sum_k a_s of this lane's batch row)
+        // Several row tiles: the integer bias is where their sums begin, four broadcasts a tile in place of an addition for
+        // each output (67-256x3-21 with a LayerNorm at 65536 rows 33.0 -> 31.9 us); a single one adds it in the epilogue, where the
+        // broadcast rides on the addition.  Four row tiles of per-tensor weights spill registers so, which costs policies of up to
+        // two hidden layers more than it gains (20-128x2-9 at 30000 rows 9.6 -> 10.9; 67-256x3-21 19.4 -> 18.2).
+        v4i bias_q[2] = {v4i{0, 0, 0, 0}, v4i{0, 0, 0, 0}};
+        if constexpr (BIAS_FIRST) {
+            static_for<0, 2>([&](auto tl_c) __attribute__((always_inline)) {
+                constexpr int tl = decltype(tl_c)::value;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt][0] = acc[mt][1] = rsa[mt] = v4i{0, 0, 0, 0};
+                for (int i = 0; i < 4; ++i) bias_q[tl][i] = AQ_R16_CSH(cst[l & 1], 0, tl, i);
+            });
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            acc[mt][0] = bias_q[0];
+            acc[mt][1] = bias_q[1];
+            rsa[mt] = v4i{0, 0, 0, 0};
+        }
         {
             const int8_t* xrow = in + b * RLD + 16 * g4;
             if constexpr (MT == 1) {
@@ -483,8 +500,8 @@ __global__ __launch_bounds__(RT, MT == 1 ? 2 : 4) void k_mlp_rows16(const NetDev
                             const int64_t row = row0 + 16 * mt + b;
                             const bool row_ok = row < c.batch;
                             const int a4[4] = {acc[mt][tl][0], acc[mt][tl][1], acc[mt][tl][2], acc[mt][tl][3]};
-                            int val[4];
-                            add_row_bcast4<tl>(val, cm, a4);
+                            int val[4] = {a4[0], a4[1], a4[2], a4[3]};
+                            if constexpr (!BIAS_FIRST) add_row_bcast4<tl>(val, cm, a4);
 #pragma unroll
                             for (int i = 0; i < 4; ++i) {
                                 if (ASYM) val[i] += rowterm[mt];
@@ -541,8 +558,8 @@ __global__ __launch_bounds__(RT, MT == 1 ? 2 : 4) void k_mlp_rows16(const NetDev
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
                     const int a4[4] = {acc[mt][tl][0], acc[mt][tl][1], acc[mt][tl][2], acc[mt][tl][3]};
-                    int val[4];
-                    add_row_bcast4<tl>(val, cm, a4);
+                    int val[4] = {a4[0], a4[1], a4[2], a4[3]};
+                    if constexpr (!BIAS_FIRST) add_row_bcast4<tl>(val, cm, a4);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         if (ASYM) val[i] += rowterm[mt];
