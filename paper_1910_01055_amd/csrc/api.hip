@@ -1156,20 +1156,26 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
         s = launch_conv_stack(a, sc.i8[(nc - 1) & 1], st);
         if (s != AQ_OK) return s;
     }
+    // Wide layers at many rows take a kernel that writes operand order only (and reads it, behind the first layer).  Settled from the
+    // last layer backwards: a layer takes it if the next one reads that order, as one of its kind or of the few-row kernel's;
+    // and forwards from the first layer on, up to the first that does not.
+    bool takes_many[AQ_MAX_LAYERS] = {};
+    if (nc == 0 && sc.blocked && pair < 0) {
+        bool reads = false;
+        for (int l = nl - 1; l >= 0; --l) {
+            takes_many[l] = reads && layer_uses_rows(a, l);
+            reads = takes_many[l] || layer_uses_skinny(a, l);
+        }
+    }
+    bool many = true;
     int blocked = 0;  // how the layer before left its output
-    // Wide layers at many rows take a kernel that reads and writes maps in operand order only: from the first layer on, as long as
-    // the next one reads such a map.
-    bool many = nc == 0;
-    auto takes_many = [&](int l) {
-        return sc.blocked && pair < 0 && layer_uses_rows(a, l) && (l + 1 == nl - 1 ? layer_uses_skinny(a, l + 1) : layer_uses_rows(a, l + 1));
-    };
     for (int l = nc; l < nl; ++l) {
         const LayerBuf& b = p->L[l];
         const int64_t rows_l = batch * b.oh * b.ow;
         LayerIO io;
         io.in_blocked = blocked;
         const bool ln = l < nl - 1 && b.d.act == AQ_ACT_LN_TANH;  // (its rows' kernel writes either order)
-        many = many && takes_many(l);
+        many = many && takes_many[l];
         blocked = many || (sc.blocked && l < nl - 1 && b.fc && (ln || layer_uses_skinny(a, l)) && layer_uses_skinny(a, l + 1));
         io.out_blocked = ln ? 0 : blocked;
         io.in = l == 0 ? d_obs : (const void*)sc.i8[(l - 1) & 1];

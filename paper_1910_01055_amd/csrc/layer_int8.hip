@@ -503,6 +503,7 @@ aq_status launch_layer_int8(const FwdArgs& a, int l, const LayerIO& io, hipStrea
     const LayerPlan p = plan_layer(L, rows, a.net.asym != 0);
     // few workgroups and a fully connected layer: the K-split kernel makes one weight stream per wave
     if (layer_uses_skinny(a, l)) return launch_layer_skinny(a, l, io, st);
+    if (io.in_blocked || io.out_blocked) return AQ_ESHAPE;  // (the tiled kernel reads and writes rows: an error rather than an answer)
     if (p.w == 8) return launch_layer_t<8, 4, 2>(a, l, io, rows, stage_mode, actions, st);
     if (p.w == 1) return launch_layer_t<1, 1, 1>(a, l, io, rows, stage_mode, actions, st);
     if (p.w == 2 && p.deep) return launch_layer_t<2, 1, 1, true>(a, l, io, rows, stage_mode, actions, st);

@@ -23,7 +23,7 @@ using fused::sum_rows4;
 constexpr int RL_W = 8, RL_T = RL_W * 64, RL_RT = 4;  // wavefronts, threads, 16-row tiles of a workgroup
 constexpr int RL_KC = 16;                // pieces of 16 bytes of K per chunk
 constexpr int RL_MAXK0 = 512;            // longest observation row
-enum { RL_RELU = 1, RL_LN = 2, RL_BLOCKED = 4 };
+enum { RL_RELU = 1, RL_LN = 2 };
 
 struct RowsLayer {
     const NetDev* net;
@@ -271,13 +271,13 @@ aq_status go(const RowsLayer& q, const TapArgs& t, hipStream_t st) {
 }  // namespace
 
 // From 450 rows on: us on the few-row kernel / here, 67-2048x3-21 at 300 rows 30.3 / 33.0, 450 37.2 / 33.8; 67-1300-1500-21 at 300 16.1 /
-// 18.8, 450 21.5 / 19.1.  Up to 8191, where the last layer's few-row kernel still reads such maps.  512 features are two workgroups
-// a row block.
+// 18.8, 450 21.5 / 19.1.  The caller ends it where no layer behind reads its maps any more: layers narrower than 512, the last one
+// among them, read them on the few-row kernel (layer_uses_skinny), at up to eight feature tiles for 8128 rows.
 bool layer_uses_rows(const FwdArgs& a, int l) {
     const NetDev& n = a.net;
     const LayerDev& L = n.L[l];
     auto fc = [](const LayerDev& X) { return X.kh == 1 && X.kw == 1 && X.in_h == 1 && X.in_w == 1; };
-    if (l >= n.n_layers - 1 || !fc(L) || L.NT < 16 || a.c.batch < 450 || a.c.batch >= 8192 || a.w4[l]) return false;
+    if (l >= n.n_layers - 1 || !fc(L) || L.NT < 16 || a.c.batch < 450 || a.w4[l]) return false;
     if ((int64_t)L.NT * L.KS * 1024 >= 0x7fffffff) return false;
     return l == 0 ? !n.in_u8 && L.K <= RL_MAXK0 : fc(n.L[l - 1]);
 }

@@ -13,7 +13,8 @@ typedef struct {
     int kind;
     unsigned grid[3];
     void* stream;
-    const void *in, *out;  /* launches: words 5 and 6 of the first argument (the few-row kernel's input and output) */
+    const void *in, *out;  /* launches of one layer: its input and output */
+    int flags;             /* ... and how these lie: the kernel's own flags (test_host_routes.py) */
     char name[160];
 } Entry;
 typedef struct {
@@ -183,9 +184,18 @@ int hipLaunchKernel(const void* f, Dim3 g, Dim3 b, void** args, size_t shared, v
     e->grid[2] = g.z;
     for (int i = 0; i < n_kernels; ++i)
         if (kernels[i].host == f) strcpy(e->name, kernels[i].name);
-    if (strstr(e->name, "k_layer_skinny")) {
+    if (strstr(e->name, "k_layer_skinny") || strstr(e->name, "k_layer_rows")) { /* one struct: words 5 and 6, the last int */
         e->in = ((const void* const*)args[0])[5];
         e->out = ((const void* const*)args[0])[6];
+        e->flags = ((const int*)args[0])[strstr(e->name, "k_layer_rows") ? 21 : 19];
+    } else if (strstr(e->name, "k_layer_int8")) { /* LayerIO: in, out, LayerNorm rows, last layer's rows, two flags */
+        e->in = ((const void* const*)args[3])[0];
+        e->out = ((const void* const*)args[3])[1];
+        e->flags = ((const int*)args[3])[8] | ((const int*)args[3])[9];
+    } else if (strstr(e->name, "k_ln_tanh_rows") || strstr(e->name, "k_ln_tanh_long")) {
+        e->in = *(const void* const*)args[0];
+        e->out = *(const void* const*)args[8];
+        e->flags = *(const long long*)args[9] != 0; /* 16-row tiles of a map in operand order */
     }
     return OK;
 }

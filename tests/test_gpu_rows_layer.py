@@ -1,6 +1,6 @@
 """Wide 8-bit layers at many rows (policies wider than the whole-network kernels hold): ragged K and N, LayerNorm rows, a last row
-block of one row and of all, both weight schemes, misaligned observations, on both sides of where that kernel begins; every stage
-against the oracle."""
+block of one row and of all, both weight schemes, misaligned observations, on both sides of where that kernel begins and ends, also
+in front of layers it does not take; every stage against the oracle.  (Which kernel each layer takes: test_host_routes.py.)"""
 import numpy as np
 import pytest
 
@@ -13,13 +13,20 @@ NETS = {
     "whole": ([fc(128, 2048, "relu"), fc(2048, 1024, "none"), fc(1024, 21, "none")], "tanh"),
     "ragged": ([fc(67, 1300, "relu"), fc(1300, 1043, "ln_tanh"), fc(1043, 37, "none")], "argmax"),
     "ln_first": ([fc(381, 1100, "ln_tanh"), fc(1100, 1031, "relu"), fc(1031, 512, "ln_tanh"), fc(512, 40, "none")], "linear"),
+    "2048x3": ([fc(67, 2048, "relu"), fc(2048, 2048, "relu"), fc(2048, 2048, "relu"), fc(2048, 21, "none")], "tanh"),
+    "narrow_third": ([fc(67, 2048, "ln_tanh"), fc(2048, 2048, "relu"), fc(2048, 256, "relu"), fc(256, 21, "none")], "tanh"),
+    "wide_last": ([fc(67, 2048, "relu"), fc(2048, 1100, "ln_tanh"), fc(1100, 512, "none")], "linear"),
     "narrow_between": ([fc(20, 1100, "relu"), fc(1100, 200, "relu"), fc(200, 1030, "relu"), fc(1030, 5, "none")], "tanh"),
 }
 
 
-@pytest.mark.parametrize("name", list(NETS))
+CASES = [(name, batch) for name in ("whole", "ragged", "ln_first", "narrow_between") for batch in (449, 450, 513, 1024)] + [
+    ("2048x3", 8128), ("2048x3", 8150), ("narrow_third", 960), ("narrow_third", 961), ("narrow_third", 1300), ("wide_last", 1300),
+    ("wide_last", 4500), ("narrow_between", 3000)]
+
+
+@pytest.mark.parametrize("name,batch", CASES)
 @pytest.mark.parametrize("scheme", ["channel_sym_s8", "tensor_asym_u8"])
-@pytest.mark.parametrize("batch", [449, 450, 513, 1024])
 def test_wide_layers_at_many_rows(aq, name, scheme, batch):
     print(f"[rows layer] {name} {scheme} batch={batch}", flush=True)
     net = synth.small_net(NETS[name][0], head=NETS[name][1], wscheme=scheme)

@@ -2,7 +2,9 @@
 buffers, what it allocates, and what it answers when a runtime call fails.  Each scenario runs in a process of its own, in
 which no other HIP runtime is loaded."""
 import ctypes as C
+import itertools
 import os
+import re
 import subprocess
 import sys
 
@@ -15,7 +17,7 @@ LAUNCH, MALLOC, WAIT, RECORD = range(4)
 
 class Entry(C.Structure):
     _fields_ = [("kind", C.c_int), ("grid", C.c_uint * 3), ("stream", C.c_void_p), ("in_", C.c_void_p), ("out", C.c_void_p),
-                ("name", C.c_char * 160)]
+                ("flags", C.c_int), ("name", C.c_char * 160)]
 
 
 class Mem:
@@ -41,15 +43,16 @@ class Host:
         binding._stream = lambda: self.stream
         self.stream = 0
 
-    def policy(self, *widths, k=67, out=21, wbits=0, **kw):
+    def policy(self, *widths, k=67, out=21, wbits=0, ln=(), **kw):
         fc, layers = self.synth.fc, []
-        for w in widths:
-            layers.append(fc(k, w, "relu"))
+        for i, w in enumerate(widths):
+            layers.append(fc(k, w, "ln_tanh" if i in ln else "relu"))
             k = w
         net = dict(self.synth.small_net(layers + [fc(k, out, "none")], **kw), wbits=wbits)
         P = self.aq.Policy(net)
         n = len(net["layers"])
-        P.quantize_params([Mem()] * n, [Mem()] * n, None, None, [(0.0, 1.0)] * n)
+        lns = [Mem() if i in ln else None for i in range(n)]
+        P.quantize_params([Mem()] * n, [Mem()] * n, lns, lns, [(0.0, 1.0)] * n)
         return P
 
     def logged(self, kind=None):
@@ -259,7 +262,74 @@ def a_refused_amount_of_lds_is_told_once(h):
         P.close()
 
 
-SCENARIOS = [few_row_forwards_allocate_nothing, streams_come_and_go, the_first_forward_of_new_weights, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
+def layer_launch(e):
+    """-> (kernel, how it reads its input, how it leaves its output); "own" is an order nobody else reads or writes."""
+    name, flags = e.name.decode(), e.flags
+    if "k_layer_rows" in name:
+        return "rows", "own" if "k_layer_rowsILb1E" in name else "operands", "own" if flags & 2 else "operands"
+    if "k_layer_skinny" in name:
+        reads = ("own", "rows", "operands")[int(re.search(r"Li(\d)EEEv", name).group(1))]
+        return "skinny", reads, "own" if flags & (2 | 4) else "operands" if flags & 64 else "rows"
+    if "k_layer_int8" in name:
+        assert not flags, "the tiled kernel knows row-major maps only"
+        return "tiled", "rows", "rows"
+    if "k_ln_tanh" in name:
+        return "ln", "own", "operands" if flags else "rows"
+    return name, "own", "own"
+
+
+WIDE = {  # hidden widths, outputs, layers with a LayerNorm
+    "2048x3": ((2048, 2048, 2048), 21, ()), "2048x3 ln": ((2048, 2048, 2048), 21, (0,)), "2048x2-256": ((2048, 2048, 256), 21, ()),
+    "2048x2-256 ln": ((2048, 2048, 256), 21, (0, 1)), "1300x2-400": ((1300, 1300, 400), 21, ()), "1300x2-400 ln": ((1300, 1300, 400), 21, (2,)),
+    "2048x2, wide last": ((2048, 2048), 512, ()), "2048x2, wide last ln": ((2048, 2048), 512, (1,)), "1100-700": ((1100, 700), 21, ()),
+    "1100-200-1030": ((1100, 200, 1030), 21, ()), "1100-200-1030 ln": ((1100, 200, 1030), 21, (0, 2)), "200-1300-1300": ((200, 1300, 1300), 21, ()),
+    "1100-1000-1030-30": ((1100, 1000, 1030, 30), 5, (1, 3)), "1300": ((1300,), 300, ()),
+    "1024x2-300": ((1024, 1024, 300), 9, (1,)), "800-600": ((800, 600), 9, ())}
+WIDE_BATCHES = (1, 449, 450, 900, 960, 961, 1300, 3000, 4500, 8000, 8128, 8129, 8150, 8191, 8192, 9000)
+
+
+def wide_layers_read_the_order_their_input_was_written_in(h):
+    """A kernel that writes operand order is only followed by one that reads it, for every mixture of widths, on both sides of where
+    each of the three kernels begins and ends, from every entry point; narrower policies, too, where a plan makes them go by layers."""
+    seen = set()
+
+    def static(P, batch):
+        h.hip.fake_clear()
+        try:
+            P.policy_forward_int8_static(Mem(batch), Mem(batch))
+        except h.aq.AqError as e:
+            assert e.status == h.aq.ETOOBIG
+        return h.logged()
+
+    def step(P, batch):
+        h.hip.fake_clear()
+        P.policy_step_int8(Mem(batch), Mem(batch), 1, 1, sigma=Mem(batch))
+        return h.logged()
+
+    for name, (widths, out, ln) in WIDE.items():
+        for scheme, head in itertools.product(("channel_sym_s8", "tensor_asym_u8"), ("linear", "argmax")):
+            P = h.policy(*widths, out=out, ln=ln, wscheme=scheme, head=head)
+            P.policy_set_path(2)
+            for batch in WIDE_BATCHES:
+                for call in (h.forward, static, step)[:2 if head == "argmax" else 3]:
+                    case, runs = (name, scheme, head, batch), [layer_launch(e) for e in call(P, batch) if e.kind == LAUNCH]
+                    assert not runs or sum(r[0] in ("rows", "skinny", "tiled") for r in runs) == len(widths) + 1, (case, runs)
+                    order = None  # of the last map written
+                    for kernel, reads, writes in runs:
+                        if order is not None and kernel in ("rows", "skinny", "tiled"):
+                            assert reads == order, (case, runs)
+                        if kernel in ("rows", "skinny", "tiled", "ln"):
+                            order = writes if writes != "own" else order
+                    seen.update((name, batch, r[0]) for r in runs)
+            P.close()
+    # where the many-row kernel serves and where it does not, because its reader could not follow
+    for name, batch, many in (("2048x3", 449, False), ("2048x3", 450, True), ("2048x3", 8128, True), ("2048x3", 8129, False),
+                              ("2048x2-256", 1300, True), ("2048x2-256 ln", 1300, True), ("1300x2-400", 3000, True), ("2048x2, wide last", 4500, False),
+                              ("1100-200-1030", 450, True), ("200-1300-1300", 900, False), ("1300", 900, True)):
+        assert ((name, batch, "rows") in seen) == many, (name, batch)
+
+
+SCENARIOS = [wide_layers_read_the_order_their_input_was_written_in, few_row_forwards_allocate_nothing, streams_come_and_go, the_first_forward_of_new_weights, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
              a_few_row_forward_without_memory_to_have, a_failed_call_leaves_no_error_behind, a_refused_amount_of_lds_is_told_once]
 
 
