@@ -270,16 +270,24 @@ aq_status go(const RowsLayer& q, const TapArgs& t, hipStream_t st) {
 }
 }  // namespace
 
-// From 450 rows on: us on the few-row kernel / here, 67-2048x3-21 at 300 rows 30.3 / 33.0, 450 37.2 / 33.8; 67-1300-1500-21 at 300 16.1 /
-// 18.8, 450 21.5 / 19.1.  The caller ends it where no layer behind reads its maps any more: layers narrower than 512, the last one
-// among them, read them on the few-row kernel (layer_uses_skinny), at up to eight feature tiles for 8128 rows.
+// From 450 rows on: us on the few-row kernel / here, the first layer of 67-2048-2048-256-21 at 470 rows 31.5 / 23.3 for the policy.  A
+// layer behind the first, which the few-row kernel reads in the same order, comes here where the grid holds enough workgroups; for
+// whole policies us there / here, per-channel weights: N = 512 at 1800 rows 18.6 / 19.1, 2200 20.6 / 19.2; 700 at 1400 18.0 / 18.9, 1600
+// 19.9 / 19.3; 900 at 1100 17.6 / 18.5, 1300 19.3 / 18.8; two of 1100 at 900 25.1 / 28.4, 1200 30.0 / 29.3; two of 2048 at 512 29.8 / 34.2,
+// 700 36.7 / 35.4.  Per-tensor weights, whose row sums all wavefronts add up here: two of 2048 at 768 38.9 / 43.3; 700 at 1600 21.1 / 22.1,
+// 2000 23.3 / 22.9.  Rows of more than 2048 values always come here (2500 of 2500 at 512 rows 29.6 / 24.4).  The caller ends it where no
+// layer behind reads its maps any more: layers of fewer than 16 feature tiles, the last one among them, read them on the few-row kernel
+// (layer_uses_skinny), at up to eight tiles for 8128 rows.
 bool layer_uses_rows(const FwdArgs& a, int l) {
     const NetDev& n = a.net;
     const LayerDev& L = n.L[l];
     auto fc = [](const LayerDev& X) { return X.kh == 1 && X.kw == 1 && X.in_h == 1 && X.in_w == 1; };
     if (l >= n.n_layers - 1 || !fc(L) || L.NT < 16 || a.c.batch < 450 || a.w4[l]) return false;
     if ((int64_t)L.NT * L.KS * 1024 >= 0x7fffffff) return false;
-    return l == 0 ? !n.in_u8 && L.K <= RL_MAXK0 : fc(n.L[l - 1]);
+    if (l == 0) return !n.in_u8 && L.K <= RL_MAXK0;
+    const int64_t groups = (L.NT + RL_W - 1) / RL_W, blocks = (a.c.batch + 16 * RL_RT - 1) / (16 * RL_RT);
+    if (L.K <= 2048 && groups * blocks < 60 + 5 * groups + (n.asym ? 20 : 0) && layer_uses_skinny(a, l)) return false;
+    return fc(n.L[l - 1]);
 }
 
 aq_status launch_layer_rows(const FwdArgs& a, int l, const LayerIO& io, hipStream_t st) {

@@ -329,7 +329,19 @@ def wide_layers_read_the_order_their_input_was_written_in(h):
         assert ((name, batch, "rows") in seen) == many, (name, batch)
 
 
-SCENARIOS = [wide_layers_read_the_order_their_input_was_written_in, few_row_forwards_allocate_nothing, streams_come_and_go, the_first_forward_of_new_weights, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
+def wide_layers_behind_the_first_at_some_hundred_rows(h):
+    """They go to the many-row kernel where its grid holds enough workgroups, or their rows are long, else to the few-row one."""
+    sym, asym = "channel_sym_s8", "tensor_asym_u8"
+    for widths, scheme, at in (((2048,) * 3, sym, 769), ((2048,) * 3, asym, 897), ((1100,) * 3, sym, 1025), ((1100,) * 3, asym, 1281),
+                               ((1100, 700), sym, 1537), ((1100, 512), sym, 2177), ((2500,) * 2, sym, 450), ((2500,) * 2, asym, 450)):
+        P = h.policy(*widths, wscheme=scheme)
+        for batch in (max(at - 1, 450), at):
+            want = ["rows"] + ["rows" if batch >= at else "skinny"] * (len(widths) - 1) + ["skinny"]
+            assert [layer_launch(e)[0] for e in h.forward(P, batch) if e.kind == LAUNCH] == want, (widths, scheme, batch)
+        P.close()
+
+
+SCENARIOS = [wide_layers_behind_the_first_at_some_hundred_rows, wide_layers_read_the_order_their_input_was_written_in, few_row_forwards_allocate_nothing, streams_come_and_go, the_first_forward_of_new_weights, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
              a_few_row_forward_without_memory_to_have, a_failed_call_leaves_no_error_behind, a_refused_amount_of_lds_is_told_once]
 
 
