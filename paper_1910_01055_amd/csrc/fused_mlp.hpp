@@ -57,6 +57,18 @@ __device__ __forceinline__ int sum_rows4(int s) {
     return (int)(q[0] + q[1]);
 }
 
+// 1 / n for n >= 1 and 1 / sqrt(v), the units' results (1 ulp) with one Newton step: as near as the correctly rounded operations, for
+// a fifth of their instructions
+__device__ __forceinline__ float recip(float n) {
+    const float r = __builtin_amdgcn_rcpf(n);
+    return fmaf(fmaf(-n, r, 1.0f), r, r);
+}
+__device__ __forceinline__ float rsqrt_near(float v) {
+    if (!(v >= 1e-36f)) return 1.0f / sqrtf(v);  // (a constant row without an eps)
+    const float r = __builtin_amdgcn_rsqf(v);
+    return fmaf(0.5f * r, fmaf(-v * r, r, 1.0f), r);
+}
+
 struct Call {
     const void* obs;
     void* actions;
@@ -382,7 +394,7 @@ __global__ __launch_bounds__(IT, NBM == 2 && RT <= 4 ? 4 : 2) void k_mlp_fused(c
                 return 32 * tiles - (((NT - 1) & (IW - 1)) == w ? Np - N : 0);
             };
             const int n_w = count_of(wave);
-            const float inv_nw = __builtin_amdgcn_rcpf((float)(n_w > 0 ? n_w : 1));
+            const float inv_nw = recip((float)(n_w > 0 ? n_w : 1));
             static_for<0, 2 * NB>([&](auto h_c) __attribute__((always_inline)) {
                 constexpr int h = decltype(h_c)::value;
                 int bias[4], ms[4];
@@ -430,7 +442,7 @@ __global__ __launch_bounds__(IT, NBM == 2 && RT <= 4 ? 4 : 2) void k_mlp_fused(c
             for (int j = 0; j < 2; ++j) {
                 const int n = count_of(2 * g + j);
                 cnt[j] = (float)n;
-                inv_cnt[j] = __builtin_amdgcn_rcpf((float)(n > 0 ? n : 1));
+                inv_cnt[j] = recip((float)(n > 0 ? n : 1));
             }
             lds_barrier();  // statistics of all wavefronts; all inputs read
             float sc[RT], mean[RT];
@@ -443,53 +455,66 @@ __global__ __launch_bounds__(IT, NBM == 2 && RT <= 4 ? 4 : 2) void k_mlp_fused(c
                 const float d0 = sw[0] * inv_cnt[0] - mean[r], d1 = sw[1] * inv_cnt[1] - mean[r];
                 const float m2 = sum_rows4(fmaf(cnt[0] * d0, d0, qw[0]) + fmaf(cnt[1] * d1, d1, qw[1]));
                 // (2 log2 e rides on the row's scale and on the offset: exp2 then yields e^{2y})
-                sc[r] = __builtin_amdgcn_rsqf(m2 / (float)N + eps) * K2_LOG2E;
+                sc[r] = rsqrt_near(m2 / (float)N + eps) * K2_LOG2E;
             }
-            static_for<0, 2 * NB>([&](auto h_c) __attribute__((always_inline)) {
-                constexpr int h = decltype(h_c)::value;
-                int gi[4], bi[4];
-                consts4(h_c, A2{}, gi);
-                consts4(h_c, A3{}, bi);
-                float gv[4], bv[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    gv[i] = __int_as_float(gi[i]);
-                    bv[i] = __int_as_float(bi[i]) * K2_LOG2E;
-                }
-                const int n0 = n0_of(h);
-#pragma unroll
-                for (int r = 0; r < RT; ++r) {
-                    float rv[4];
+            // Up to 256 features: code = round(t / s + z) with t = 1 - 2 / (e^{2y} + 1), straight from the reciprocal: 9 codes in a million off
+            // the 64-bit ones.  More, what rows in memory get (ln_rows.hpp, 5 in a million): tanh from |y|, and t (1 / s) rounded once,
+            // straight to an integer (in MAGIC's last place), before z is added: 4 in a million, tanh's error 3.5e-8 instead of 5.3e-8.
+            // It is three more instructions a value: 61-1024x2-36 at 16379 rows 34.3 -> 36.1 us, 61-263-163-2 at 32768 18.0 -> 19.0.
+            auto codes = [&](auto wide_c) __attribute__((always_inline)) {
+                constexpr bool WIDE = decltype(wide_c)::value;
+                constexpr float MAGIC = 12582912.0f;  // 1.5 * 2^23
+                const float unmagic = MAGIC - (float)z_out;
+                static_for<0, 2 * NB>([&](auto h_c) __attribute__((always_inline)) {
+                    constexpr int h = decltype(h_c)::value;
+                    int gi[4], bi[4];
+                    consts4(h_c, A2{}, gi);
+                    consts4(h_c, A3{}, bi);
+                    float gv[4], bv[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const float e = __builtin_amdgcn_exp2f(fmaf((__int_as_float(acc[h][r][i]) - mean[r]) * sc[r], gv[i], bv[i]));
-                        rv[i] = __builtin_amdgcn_rcpf(e + 1.0f);
+                        gv[i] = __int_as_float(gi[i]);
+                        bv[i] = __int_as_float(bi[i]) * K2_LOG2E;
                     }
-                    uint32_t pack = 0;
-                    if (qs_out.rcp_ok) {
-                        // code = round(t / s + z) with t = 1 - 2 r; the conversion rounds half to even and saturates
+                    const int n0 = n0_of(h);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) pack = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(rv[i], -c1, c0), i, pack);
-                    } else {
-                        pack = quant_code4(float4{fmaf(rv[0], -2.0f, 1.0f), fmaf(rv[1], -2.0f, 1.0f), fmaf(rv[2], -2.0f, 1.0f),
-                                                  fmaf(rv[3], -2.0f, 1.0f)}, qs_out, -z_out, 255 - z_out, z_out);
-                    }
-                    if (TAPS) {
-                        const int64_t row = row0 + 16 * r + b;
+                    for (int r = 0; r < RT; ++r) {
+                        float rv[4], tv[4];
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            if (row < c.batch && n0 + i < N) {
-                                if (T.ln) T.ln[row * N + n0 + i] = fmaf(rv[i], -2.0f, 1.0f);
-                                if (T.act) T.act[row * N + n0 + i] = (uint8_t)(pack >> (8 * i));
+                            const float y = fmaf((__int_as_float(acc[h][r][i]) - mean[r]) * sc[r], gv[i], bv[i]);
+                            rv[i] = __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(WIDE ? fabsf(y) : y) + 1.0f);
+                            tv[i] = fmaf(rv[i], -2.0f, 1.0f);
+                            if (WIDE) tv[i] = copysignf(tv[i], y);
+                        }
+                        uint32_t pack = 0;
+                        if (!qs_out.rcp_ok) {
+                            pack = quant_u8x4(make_float4(tv[0], tv[1], tv[2], tv[3]), qs_out, (float)z_out);
+                        } else {  // the conversion rounds half to even and saturates
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                pack = __builtin_amdgcn_cvt_pk_u8_f32(
+                                    WIDE ? fmaf(tv[i], qs_out.inv, MAGIC) - unmagic : fmaf(rv[i], -c1, c0), i, pack);
+                        }
+                        if (TAPS) {
+                            const int64_t row = row0 + 16 * r + b;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                if (row < c.batch && n0 + i < N) {
+                                    if (T.ln) T.ln[row * N + n0 + i] = tv[i];
+                                    if (T.act) T.act[row * N + n0 + i] = (uint8_t)(pack >> (8 * i));
+                                }
                             }
                         }
+                        const uint32_t word = mask_padding(h_c, nb_c, n0, N, pack ^ 0x80808080u);
+                        *(uint32_t*)(xs + (16 * r + b) * ld + n0) = word;
+                        if (ASYM) rs[r] = __builtin_amdgcn_sdot4((int)word, 0x01010101, h == 0 ? 0 : rs[r], false);
+                        __builtin_amdgcn_sched_barrier(0);
                     }
-                    const uint32_t word = mask_padding(h_c, nb_c, n0, N, pack ^ 0x80808080u);
-                    *(uint32_t*)(xs + (16 * r + b) * ld + n0) = word;
-                    if (ASYM) rs[r] = __builtin_amdgcn_sdot4((int)word, 0x01010101, h == 0 ? 0 : rs[r], false);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            });
+                });
+            };
+            if (N > 256) codes(std::true_type{});
+            else if (NB <= 1) codes(std::false_type{});  // (a second tile of a wavefront's is past 256)
             if (ASYM && NB > 0)
 #pragma unroll
                 for (int r = 0; r < RT; ++r) add_row_sum(l, r, rs[r]);

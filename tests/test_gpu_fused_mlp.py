@@ -3,6 +3,7 @@ and one short of it, layers that leave wavefronts without a tile, wide last laye
 observations, at row counts on both sides of its workgroups' sizes; every stage against the oracle."""
 import numpy as np
 import pytest
+import torch
 
 import gpu_util as U
 from paper_1910_01055_amd import synth
@@ -53,4 +54,36 @@ def test_general_kernel_against_the_oracle(aq, name, scheme, batch):
         U.compare_forward(net, pol, obs, actions, t, pick)
         plain, _ = U.gpu_forward(P, net, obs, taps=False, misalign=misalign)
         assert np.array_equal(plain, actions, equal_nan=True)
+    P.close()
+
+
+@pytest.mark.parametrize("scheme", ["channel_sym_s8", "tensor_asym_u8"])
+@pytest.mark.parametrize("n", [263, 512, 1024])
+def test_wide_layernorm_loses_nothing_to_the_layers_launches(aq, n, scheme):
+    """LayerNorms of more than 256 features: the tanh values and the codes are no further from the 64-bit ones than those of rows that
+    lie in memory (one launch per layer).  Bounds: the values' root mean square error, over 10^7 of them, within 3 %; the number of
+    codes off, a count of rare events, within four of its standard deviations."""
+    batch = (1 << 24) // n
+    net = synth.small_net([fc(61, n, "ln_tanh"), fc(n, 300, "relu"), fc(300, 7, "none")], wscheme=scheme)
+    params = synth.make_params(net, nonzero_bias=True)
+    obs = synth.make_obs(net, batch)
+    _, ranges = U.make_oracle(net, params, obs[:256])
+    P, d = U.gpu_quantize(aq, net, params, ranges)
+    m = torch.empty(n, device=U.DEV)
+    P.policy_export_layer(0, mult=None, m=m)
+    s, z = torch.empty(3, device=U.DEV), torch.empty(3, dtype=torch.int32, device=U.DEV)
+    P.policy_export_act_qparams(s, z)
+    got = {}
+    for path in (1, 2):
+        P.policy_set_path(path)
+        _, t = U.gpu_forward(P, net, obs)
+        x = (t["acc"][0].float() * m).double()
+        x -= x.mean(1, keepdim=True)
+        x /= torch.sqrt((x * x).mean(1, keepdim=True) + net["ln_eps"])
+        want = torch.tanh(x * d[2][0].double() + d[3][0].double())
+        code = (torch.round(want / s[1].double()) + z[1]).clamp(0, 255).to(torch.uint8)
+        got[path] = float((t["ln_t"][0].double() - want).square().mean().sqrt()), int((code != t["act"][0]).sum())
+    print(f"general kernel, LayerNorm of {n}, {scheme}: (rms error, codes off) whole {got[1]}, by layers {got[2]}", flush=True)
+    assert got[1][0] <= 1.03 * got[2][0]
+    assert got[1][1] <= got[2][1] + 4 * got[2][1] ** 0.5
     P.close()
