@@ -709,7 +709,7 @@ __global__ __launch_bounds__(256) void k_fp32_ln_tanh(float* __restrict__ x, int
     if (slots) range_note(slots, W == 1 ? (uint32_t)row : (uint32_t)row * 4 + (threadIdx.x >> 6), lo, hi);
 }
 
-// rows longer than those hold: one wavefront per row, which is read three times
+// rows longer than those hold, or too many for them (ln_form): one wavefront per row, which is read three times
 __global__ __launch_bounds__(256) void k_fp32_ln_tanh_long(float* __restrict__ x, int64_t rows, int N,
                                                       const float* __restrict__ gamma, const float* __restrict__ beta,
                                                       float eps, RangeSlot* __restrict__ slots) {

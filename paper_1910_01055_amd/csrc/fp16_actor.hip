@@ -592,7 +592,7 @@ __global__ __launch_bounds__(256) void k_fp16_ln_tanh(_Float16* __restrict__ x, 
     }
 }
 
-// rows longer than those hold: one wavefront per row, which is read three times
+// rows longer than those hold, or too many for them (ln_form): one wavefront per row, which is read three times
 __global__ __launch_bounds__(256) void k_fp16_ln_tanh_long(_Float16* __restrict__ x, int64_t rows, int N,
                                                            const float* __restrict__ gamma,
                                                            const float* __restrict__ beta, float eps) {

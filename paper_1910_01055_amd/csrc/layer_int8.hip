@@ -360,7 +360,7 @@ __global__ __launch_bounds__(256) void k_ln_tanh_rows(const float* __restrict__ 
     }
 }
 
-// rows longer than those hold: one wavefront per row, which is read three times
+// rows longer than those hold, or too many for them (ln_form): one wavefront per row, which is read three times
 __global__ __launch_bounds__(256) void k_ln_tanh_long(const float* __restrict__ x, int64_t rows, int N,
                                                       const float* __restrict__ gamma, const float* __restrict__ beta,
                                                       float eps, const ActQ* __restrict__ actq, int out_idx,

@@ -2,7 +2,7 @@
 #pragma once
 #include <type_traits>
 
-#include "common.hpp"
+#include "kernels.hpp"
 
 namespace aq {
 
@@ -72,7 +72,8 @@ struct LnRow {
 };
 
 // Which form a launch takes: four wavefronts to a row where a row is longer than 1024 or where one each would leave most of the
-// chip's 1024 SIMDs without one, and the fewest pieces.  False: the row is longer than any holds.
+// chip's 1024 SIMDs without one, and the fewest pieces.  False: the row is longer than any holds, or a workgroup for each would be more
+// threads than a launch holds.
 struct LnForm {
     int w, p;
 };
@@ -80,7 +81,7 @@ inline bool ln_form(int64_t rows, int N, LnForm* f) {
     f->w = N > 1024 || rows < 1024 ? 4 : 1;
     const int per = (N + 256 * f->w - 1) / (256 * f->w);
     f->p = per <= 1 ? 1 : per <= 2 ? 2 : 4;
-    return per <= 4;
+    return per <= 4 && (f->w == 1 || grid_ok(rows, 256));
 }
 // calls go(W, P) as constants
 template <class Go>

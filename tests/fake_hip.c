@@ -2,11 +2,14 @@
  * which kernels a call launches on which stream and buffers, what it allocates, and what it answers when a runtime call
  * fails.  Loaded under the runtime's own library name in a process of its own (test_host_routes.py).  hipGetLastError
  * returns the last error of any call of this thread and clears it; calls that succeed leave it alone. */
+#define _GNU_SOURCE
 #include <stddef.h>
 #include <stdint.h>
 #include <stdlib.h>
 #include <string.h>
+#include <sys/mman.h>
 
+#define BIG ((size_t)1 << 30)
 enum { OK = 0, INVALID = 1, NOMEM = 2, IMPLICIT = 906 /* hipErrorStreamCaptureImplicit */, NOTREADY = 600 };
 enum { K_LAUNCH = 0, K_MALLOC = 1, K_WAIT = 2, K_RECORD = 3 };
 typedef struct {
@@ -37,6 +40,11 @@ static struct {
     char name[160];
 } kernels[1024];
 static int n_kernels;
+static struct {
+    void* at;
+    size_t size;
+} maps[256];
+static int n_maps;
 
 static int ret(int e) {
     if (e) last_error = e;
@@ -80,7 +88,13 @@ int hipGetLastError(void) {
 int hipMalloc(void** p, size_t n) {
     add(K_MALLOC, NULL);
     if (fail_mallocs) return ret(NOMEM);
-    *p = aligned_alloc(256, (n + 255) / 256 * 256);
+    if (n > BIG) { /* addresses without memory behind them: nothing runs that would touch it */
+        *p = mmap(NULL, n, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+        if (*p == MAP_FAILED) return ret(NOMEM);
+        if (n_maps < 256) maps[n_maps].at = *p, maps[n_maps++].size = n;
+    } else {
+        *p = aligned_alloc(256, (n + 255) / 256 * 256);
+    }
     ++live;
     return ret(*p ? OK : NOMEM);
 }
@@ -90,6 +104,12 @@ int hipHostMalloc(void** p, size_t n, unsigned f) {
 }
 int hipFree(void* p) {
     if (p) --live;
+    for (int i = 0; i < n_maps; ++i)
+        if (maps[i].at == p) {
+            munmap(p, maps[i].size);
+            maps[i] = maps[--n_maps];
+            return OK;
+        }
     free(p);
     return OK;
 }
@@ -176,8 +196,8 @@ int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* shared, void** s) {
     return OK;
 }
 int hipLaunchKernel(const void* f, Dim3 g, Dim3 b, void** args, size_t shared, void* s) {
-    (void)b;
     (void)shared;
+    if ((unsigned long long)g.x * b.x > 0xffffffffull) return ret(INVALID); /* as the runtime: 2^32 threads along x */
     Entry* e = add(K_LAUNCH, s);
     e->grid[0] = g.x;
     e->grid[1] = g.y;

@@ -341,7 +341,25 @@ def wide_layers_behind_the_first_at_some_hundred_rows(h):
         P.close()
 
 
-SCENARIOS = [wide_layers_behind_the_first_at_some_hundred_rows, wide_layers_read_the_order_their_input_was_written_in, few_row_forwards_allocate_nothing, streams_come_and_go, the_first_forward_of_new_weights, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
+def long_layernorm_rows_without_number(h):
+    """Rows of more than 1024 values: four wavefronts each as long as a launch holds so many, then the kernel of one wavefront a row, which
+    takes four times as many rows."""
+    fc = h.synth.fc
+    net = h.synth.small_net([fc(37, 1100, "ln_tanh"), fc(1100, 1300, "relu"), fc(1300, 5, "none")])  # (too wide for one launch)
+    P, ln = h.aq.Policy(net), [Mem(), None, None]
+    P.quantize_params([Mem()] * 3, [Mem()] * 3, ln, ln, [(0.0, 1.0)] * 3)
+    P.convert_params_fp16([Mem()] * 3, [Mem()] * 3, ln, ln)
+    P.policy_set_params_fp32([Mem()] * 3, [Mem()] * 3, ln, ln)
+    for forward, name in ((P.policy_forward_int8, b"k_ln_tanh"), (P.policy_forward_fp16, b"k_fp16_ln_tanh"), (P.policy_forward_fp32, b"k_fp32_ln_tanh")):
+        for batch in ((1 << 24) - 1, 1 << 24, (1 << 26) - 4):
+            h.hip.fake_clear()
+            forward(Mem(batch), Mem(batch))
+            names = [e.name for e in h.logged(LAUNCH) if name in e.name]
+            assert len(names) == 1 and (b"_long" in names[0]) == (batch >= 1 << 24), (batch, names)
+    P.close()
+
+
+SCENARIOS = [long_layernorm_rows_without_number, wide_layers_behind_the_first_at_some_hundred_rows, wide_layers_read_the_order_their_input_was_written_in, few_row_forwards_allocate_nothing, streams_come_and_go, the_first_forward_of_new_weights, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
              a_few_row_forward_without_memory_to_have, a_failed_call_leaves_no_error_behind, a_refused_amount_of_lds_is_told_once]
 
 
