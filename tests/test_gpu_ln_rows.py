@@ -11,9 +11,10 @@ from paper_1910_01055_amd import synth
 
 pytestmark = pytest.mark.gpu
 fc = synth.fc
-# one row to four wavefronts up to 1023 rows of up to 1024 values, one wavefront each behind that, four for longer ones
-SHAPES = [(1, 3), (256, 3), (257, 17), (1024, 1023), (1024, 1024), (1021, 1025), (255, 1030), (512, 1100), (1025, 5), (1028, 1100),
-          (2048, 16), (2047, 16), (2052, 7), (4096, 5), (4097, 5)]
+# one row to four wavefronts up to 1023 rows of up to 1024 values (short ones leave wavefronts without a value), one wavefront each
+# behind that, four for longer ones
+SHAPES = [(1, 3), (100, 9), (193, 5), (256, 3), (257, 17), (1024, 1023), (1024, 1024), (1021, 1025), (255, 1030), (512, 1100), (1025, 5),
+          (1028, 1100), (2048, 16), (2047, 16), (2052, 7), (4096, 5), (4097, 5)]
 
 
 def _net(n):
@@ -47,7 +48,7 @@ def test_fp16(aq, n, batch):
     H._check(net, params, obs, actions, outs, end_to_end=False)
 
 
-@pytest.mark.parametrize("hidden", [1400, 1022])  # four wavefronts to a row, in whole pieces and not, and one
+@pytest.mark.parametrize("hidden", [1400, 1022, 100, 1])  # four wavefronts to a row, in whole pieces and not, with idle ones, and one
 @pytest.mark.parametrize("batch", [900, 1030])
 def test_fp16_behind_a_wide_layer(aq, hidden, batch):
     net = synth.small_net([fc(20, 1400, "relu"), fc(1400, hidden, "ln_tanh"), fc(hidden, 9, "none")])
@@ -57,7 +58,7 @@ def test_fp16_behind_a_wide_layer(aq, hidden, batch):
     H._check(net, params, obs, actions, outs, end_to_end=False)
 
 
-@pytest.mark.parametrize("n,batch", SHAPES[3:])
+@pytest.mark.parametrize("n,batch", SHAPES)
 def test_fp32(aq, n, batch):
     print(f"[ln rows] fp32 {n} x {batch}", flush=True)
     net = synth.small_net([fc(37, n, "ln_tanh"), fc(n, 1300, "relu"), fc(1300, 5, "none")])  # (a layer too wide for one launch)
