@@ -64,9 +64,10 @@ __device__ __forceinline__ float recip(float n) {
     return fmaf(fmaf(-n, r, 1.0f), r, r);
 }
 __device__ __forceinline__ float rsqrt_near(float v) {
-    if (!(v >= 1e-36f)) return 1.0f / sqrtf(v);  // (a constant row without an eps)
+    const bool tiny = v < 1e-30f;  // (a constant row and next to no eps: below, the unit takes v for zero)
+    v = tiny ? v * 0x1p64f : v;
     const float r = __builtin_amdgcn_rsqf(v);
-    return fmaf(0.5f * r, fmaf(-v * r, r, 1.0f), r);
+    return fmaf(0.5f * r, fmaf(-v * r, r, 1.0f), r) * (tiny ? 0x1p32f : 1.0f);
 }
 
 struct Call {
