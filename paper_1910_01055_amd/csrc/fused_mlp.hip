@@ -68,24 +68,34 @@ bool layout(const NetDev& n, int rt, Plan* p) {
     return p->lds <= 160 * 1024;
 }
 
-// Rows per workgroup, by measurement (us at 16 / 32 / 64 / 128 rows).  More rows pass fewer weight bytes per row through the CU's
-// vector memory path, fewer leave fewer CUs idle.  Above 512 wide one workgroup fills a CU: 61-1024x3-40 at 4096 rows
-// 27 / 30 / 42, at 8000 50 / 30 / 37, at 16379 97 / 58 / 41.  Up to 512, where two share one: 61-512x3-17 at 8000 17.1 / 14.4 / 18.1,
-// at 16379 29.8 / 19.6 / 20.0, at 24000 28.3 (32) / 26.5 / 26.2, at 65536 65.8 / 54.6 / 52.4; 111-400-300-8 at 16379 16.7 / 10.9 / 14.5,
-// at 24000 17.0 / 18.6 / 17.6, at 65536 37.8 / 37.7 / 34.4.  With per-tensor weights, which have no variant of 128 rows,
-// 111-400-300-8 at 65536 42.2 / 41.4 (64), 512x3 70.6 / 65.9.
+// Rows per workgroup, by measurement (us at 16 / 32 / 64 / 128 rows; -: not measured, or no such variant).  More rows pass fewer weight
+// bytes per row through the CU's vector memory path, fewer leave fewer CUs idle.
+// Above 512 wide one workgroup fills a CU: 61-1024x3-40 at 4096 rows 27 / 30 / 42, at 8000 50 / 30 / 37, at 16379 97 / 58 / 41.
+// Up to 512, where two of up to 64 rows share one: 61-512x3-17 at 8000 17.1 / 14.4 / 18.1, at 16384 - / 19.5 / 19.4 / 26.2, at 20000 - / 27.9 /
+// 25.4 / 26.2, at 65536 - / 65.8 / 54.6 / 52.4; 200-512-256-17 at 16384 - / 12.5 / 17.7 / 21.1, at 20000 - / 19.2 / 21.9 / 21.3; 111-400-300-8 at
+// 16379 16.7 / 10.9 / 14.5, at 24000 - / 17.0 / 18.6 / 17.6, at 65536 - / 37.8 / 37.7 / 34.4.  Between one and one and a half rounds of 32
+// rows (16385 to 24576) 64 serve policies of 512 with a quarter of a million weights behind the first layer: 61-512x2-17 at 20000
+// 19.9 (32) / 18.7, 256 inputs 22.9 / 23.2; 61-512-512-256-17 24.3 / 22.4; but 61-480x2-17 19.7 / 19.9, 256 inputs 22.8 / 25.2; 61-480x3-17
+// 27.5 / 27.2, 256 inputs 30.9 / 32.0; with a LayerNorm 61-512x3-17 31.9 / 34.3; per-tensor 29.9 / 30.3.  128 rows are the best at whole rounds
+// of 32768; a second round that is nearly empty loses to 32 rows (61-512x3-17 at 40000 - / 42.9 / 46.7 / 51.5).
+// Per-tensor weights, which have no variant of 128 rows: 512x3 at 65536 - / 70.6 / 65.9; 111-400-300-8 at 65536 - / 42.2 / 41.4.
 bool make_plan(const FwdArgs& a, Plan* p) {
     const NetDev& n = a.net;
     const int64_t b = a.c.batch;
     Plan q;
     if (!layout(n, 1, &q)) return false;
-    int widest = 0;
-    for (int l = 0; l < n.n_layers - 1; ++l) widest = widest > n.L[l].N ? widest : n.L[l].N;
+    int widest = 0, lns = 0;
+    int64_t weights = 0;
+    for (int l = 0; l < n.n_layers; ++l) {
+        if (l > 0) weights += (int64_t)n.L[l].K * n.L[l].N;
+        if (l == n.n_layers - 1) break;
+        widest = widest > n.L[l].N ? widest : n.L[l].N;
+        lns += n.L[l].act == AQ_ACT_LN_TANH;
+    }
     int rt;
     if (b <= 16 * 256) rt = 1;
     else if (q.nb == 2) rt = b <= 32 * 256 ? 2 : 4;
-    else if (b <= (widest > 480 ? 32 * 511 : 32 * 768)) rt = 2;
-    else if (b <= 32 * 768) rt = 4;
+    else if (b <= 32 * 768) rt = b > 32 * 512 && widest > 480 && weights > 250000 && !lns && !n.asym ? 4 : 2;
     else rt = !n.asym ? 8 : widest > 480 ? 4 : 2;
     while (rt > 1 && !layout(n, rt, &q)) rt /= 2;
     if (rt == 1) (void)layout(n, 1, &q);

@@ -14,6 +14,7 @@ fc = synth.fc
 NETS = {
     "ln263": ([fc(17, 263, "ln_tanh"), fc(263, 163, "relu"), fc(163, 2, "none")], "tanh", "f32"),
     "ln512": ([fc(41, 512, "ln_tanh"), fc(512, 257, "relu"), fc(257, 512, "ln_tanh"), fc(512, 17, "none")], "linear", "f32"),
+    "large": ([fc(61, 512, "relu"), fc(512, 511, "none"), fc(511, 490, "relu"), fc(490, 17, "none")], "tanh", "f32"),
     "ln1000": ([fc(65, 1000, "ln_tanh"), fc(1000, 513, "none"), fc(513, 64, "none")], "argmax", "f32"),
     "ln1024": ([fc(3, 1024, "ln_tanh"), fc(1024, 1, "relu"), fc(1, 1024, "relu"), fc(1024, 33, "none")], "tanh", "f32"),
     "ln_one": ([fc(300, 1, "ln_tanh"), fc(1, 700, "ln_tanh"), fc(700, 9, "none")], "tanh", "f32"),
@@ -24,8 +25,9 @@ NETS = {
 }
 # rows per workgroup and feature tiles per wavefront (in pairs) that the plan gives; (rows, 1): up to 512 wide
 VARIANTS = [(name, scheme, batch) for name in NETS for scheme in ("channel_sym_s8", "tensor_asym_u8") for batch in (1, 33)] + [
-    ("ln263", "channel_sym_s8", 24577), ("ln263", "tensor_asym_u8", 24577), ("ln512", "channel_sym_s8", 16353),
-    ("ln512", "channel_sym_s8", 24700), ("ln512", "tensor_asym_u8", 16353), ("ln512", "tensor_asym_u8", 4097),
+    ("ln263", "channel_sym_s8", 24577), ("ln263", "tensor_asym_u8", 24577), ("ln512", "channel_sym_s8", 16385),
+    ("ln512", "channel_sym_s8", 24700), ("ln512", "tensor_asym_u8", 24577), ("ln512", "tensor_asym_u8", 4097),
+    ("large", "channel_sym_s8", 16384), ("large", "channel_sym_s8", 16385), ("large", "tensor_asym_u8", 16385),
     ("ln1000", "channel_sym_s8", 8193), ("ln1000", "tensor_asym_u8", 8193), ("ln1000", "channel_sym_s8", 4097),
     ("ln1000", "tensor_asym_u8", 4097), ("wide_last", "tensor_asym_u8", 8200), ("wide_argmax", "channel_sym_s8", 24600)]
 
@@ -44,7 +46,7 @@ def test_general_kernel_against_the_oracle(aq, name, scheme, batch):
     assert kind == 0 and tiles == (2 if widest > 512 else 1)
     sym = scheme == "channel_sym_s8"
     want = 16 if batch <= 4096 else (32 if batch <= 8192 else 64) if widest > 512 else \
-        32 if batch <= (16352 if widest > 480 else 24576) else 64 if batch <= 24576 else 128 if sym else 64 if widest > 480 else 32
+        (64 if batch > 16384 and sym and name == "large" else 32) if batch <= 24576 else 128 if sym else 64 if widest > 480 else 32
     assert rows == want
     print(f"general kernel {name} {scheme} batch={batch} rows={rows}", flush=True)
     pick = None if batch < 64 else np.unique(np.concatenate([[0, 15, 16, 127, 128, batch - 2, batch - 1],

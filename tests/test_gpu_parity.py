@@ -345,14 +345,14 @@ FUSED_VARIANTS = {
     # the general kernel
     (16, 1, False, 0): [("mid_wide", 4096)],
     (16, 1, True, 0): [("mid_wide_asym", 4096)],
-    (32, 1, False, 0): [("mid_wide", 8192)],
-    (64, 1, False, 0): [("mid_wide", 16379)],
+    (32, 1, False, 0): [("mid_wide", 8192), ("mid_wide", 16379)],
+    (64, 1, False, 0): [("mid_deep", 16391), ("mid_deep", 24570)],
     (128, 1, False, 0): [("mid_wide", 32763), ("mid_wide_ln", 32700)],
     (32, 2, False, 0): [("cfg5", 8192), ("odd_wide", 8185)],
     (64, 2, False, 0): [("odd_wide", 16379)],
     (64, 2, False, 1): [("cfg5", 16384)],
-    (32, 1, True, 0): [("mid_wide_asym", 8192)],
-    (64, 1, True, 0): [("mid_wide_asym", 16379)],
+    (32, 1, True, 0): [("mid_wide_asym", 8192), ("mid_wide_asym", 16379)],
+    (64, 1, True, 0): [("mid_wide_asym", 24580)],
 }
 
 
@@ -367,6 +367,9 @@ def _variant_net(name):
     if name == "mid_wide_ln":  # ... with LayerNorm over a 256-wide layer behind it
         return synth.small_net([synth.fc(67, 512, "relu"), synth.fc(512, 256, "ln_tanh"), synth.fc(256, 21, "none")],
                                head="tanh")
+    if name == "mid_deep":  # 64 rows a workgroup: large layers of 512
+        return synth.small_net([synth.fc(67, 512, "relu"), synth.fc(512, 512, "relu"), synth.fc(512, 512, "none"),
+                                synth.fc(512, 21, "none")], head="tanh")
     if name == "mid_wide_asym":  # per-tensor weights with a layer too wide for the small-network kernel
         return synth.small_net([synth.fc(67, 512, "relu"), synth.fc(512, 256, "relu"), synth.fc(256, 21, "none")],
                                head="tanh", wscheme="tensor_asym_u8")

@@ -359,7 +359,19 @@ def long_layernorm_rows_without_number(h):
     P.close()
 
 
-SCENARIOS = [long_layernorm_rows_without_number, wide_layers_behind_the_first_at_some_hundred_rows, wide_layers_read_the_order_their_input_was_written_in, few_row_forwards_allocate_nothing, streams_come_and_go, the_first_forward_of_new_weights, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
+def rows_per_workgroup_of_the_general_kernel(h):
+    """Whole rounds of two workgroups of 32 rows per CU are never given up for 64 rows; behind them only large policies take 64."""
+    sym, asym = "channel_sym_s8", "tensor_asym_u8"
+    for widths, ln, scheme, want in (((512, 256), (), sym, 32), ((512, 512), (), sym, 64), ((512, 400), (), sym, 32), ((512,) * 3, (), sym, 64), ((512,) * 3, (0,), sym, 32),
+                                     ((512,) * 3, (), asym, 32), ((480,) * 3, (), sym, 32), ((490,) * 3, (), sym, 64)):
+        P = h.policy(*widths, ln=ln, wscheme=scheme)
+        rows = {b: P.policy_fused_plan(b)[0] for b in (4096, 4097, 16353, 16384, 16385, 24576, 24577)}
+        assert rows == {4096: 16, 4097: 32, 16353: 32, 16384: 32, 16385: want, 24576: want,
+                        24577: 128 if scheme == sym else 64}, (widths, ln, scheme, rows)
+        P.close()
+
+
+SCENARIOS = [rows_per_workgroup_of_the_general_kernel, long_layernorm_rows_without_number, wide_layers_behind_the_first_at_some_hundred_rows, wide_layers_read_the_order_their_input_was_written_in, few_row_forwards_allocate_nothing, streams_come_and_go, the_first_forward_of_new_weights, fp32_convolutions_of_small_frames, half_precision_layers_by_their_output_tiles, policies_that_never_take_few_rows_apart_keep_no_maps,
              a_few_row_forward_without_memory_to_have, a_failed_call_leaves_no_error_behind, a_refused_amount_of_lds_is_told_once]
 
 
