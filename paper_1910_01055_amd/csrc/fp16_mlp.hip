@@ -446,9 +446,11 @@ bool plan_rows(const Fp16Net& n, int rt, MlpPlan* p) {
 // (the launches write maps that two streams would share): 4 us each and 371 k flop per clock, what the widest layers reach; and three
 // quarters of 3.96 us each, per 10^6 of output tiles x K 12 us on the few-row kernel, 4 on the tiled one, 20 there for rows of no
 // whole 8 values, 4 us per 10^6 values of a LayerNorm, fitted to 16000 pairs (one to five hidden layers of 50 to 1300, 320 to
-// 27600 rows; whole, 104-1024x3-19 at 4096 rows takes 54 us, 49.8 by layers, and would be called faster).  With the first alone
-// 19-125-102-34 took 40.0 us at 28000 rows and 80 at 65536 (18.4 and 33.7 here), 111-400-300-8 134 at 65536 (58); it still
-// stands where a last round of workgroups is nearly empty.
+// 27600 rows).  Three quarters, because it is up to 1.4 times too long for layers of 1024 at some hundred to 2400 rows: 36-1024x3-30 at
+// 1067 rows takes 46.0 us whole and 32.6 by layers, 55-1024x2-9 at 974 22.4 and 19.5, 104-1024x3-19 at 4096 54 and 49.8, which the whole of
+// it calls faster here.  Elsewhere it costs: 396 drawn policies are 1.3 % from the better way (the whole estimate 0.8 %), 500 at row
+// counts just above whole rounds of workgroups 3.2 % (0.6 %).  With the first estimate alone 13.6 and 29 %: 19-125-102-34 took 40.0 us
+// at 28000 rows and 80 at 65536 (18.4 and 33.7 here), 111-400-300-8 134 at 65536 (58).
 bool plan_mlp(const Fp16Net& n, int64_t batch, MlpPlan* best) {
     double best_c = 0.0;
     bool found = false;
@@ -488,10 +490,8 @@ bool plan_mlp(const Fp16Net& n, int64_t batch, MlpPlan* best) {
             us += 3.96 + 4e-6 * D.N * (double)batch;
         }
     }
-    const int64_t wgs = (batch + 16 * best->rt - 1) / (16 * best->rt), in_last = (wgs - 1) % 256 + 1;
     const double second = 0.75 * 2375.0 * us;
-    const double layers = flop > second || (wgs > 256 && in_last < 32) ? flop : second;
-    return best_c <= layers;
+    return best_c <= (flop > second ? flop : second);
 }
 }  // namespace
 

@@ -24,7 +24,8 @@ def _nets():
     }
 
 
-# 16, 32 and 64 rows per workgroup at 2101, 4099 and 12005; the launch per layer at 16391, and of some at fewer rows
+# 16, 32 and 64 rows per workgroup at 2101, 4099 and 12005; at 16391 a second round for a few rows, or a launch per layer, which some
+# take at fewer rows too
 BATCHES = [1, 49, 2101, 4099, 8200, 12005, 16391]
 
 
@@ -34,7 +35,8 @@ def test_the_batches_reach_every_row_count(aq, name):
     P = aq.Policy(net)
     P.convert_params_fp16(*U.upload_params(synth.make_params(net)))
     plan = {batch: P.policy_fp16_plan(batch) for batch in BATCHES}
-    assert (plan[2101], plan[4099], plan[12005], plan[16391]) == (16, 32, 64, 0), plan
+    second_round = {"narrow_argmax": 0, "u8_wide_head": 0, "aligned": 0, "ln_wide": 32}
+    assert (plan[2101], plan[4099], plan[12005], plan[16391]) == (16, 32, 64, second_round.get(name, 64)), plan
     P.close()
 
 
