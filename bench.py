@@ -213,8 +213,8 @@ def quantize_workload(torch, aq, synth, scheme, iters=30, n_buf=40, repeat=1, re
 
 def mfma_loop_workload(torch, aq, operands, stream_weights=True, ksteps=2048):
     """What the matrix cores sustain in the wide whole-network kernel's k-step loop with nothing around it (no
-    observation load, no epilogue, no barrier): one workgroup per CU, per CU and k-step 32 MFMAs on 16 KiB of
-    streamed weights.  The clock under matrix load depends on the operand bits, so three operand sets: zeros,
+    observation load, no epilogue, no barrier): one workgroup per CU, per CU and k-step (of 32) 2.1 MOP on 16 KiB of
+    streamed weights, in 16x16x64 instructions.  The clock under matrix load depends on the operand bits, so three operand sets: zeros,
     codes distributed like cfg5's (Gaussian weight codes, post-ReLU activations), uniformly random bytes."""
     import numpy as np
     rng = np.random.default_rng(41)

@@ -268,7 +268,7 @@ aq_status aq_stream_reference(const float* d_in, int64_t n, void* d_out, void* s
 
 /* Measurement aid for aq_policy_forward_int8 on wide layers at large batch: the inner loop of the whole-network
  * kernel that serves them and nothing else -- per workgroup (8 wavefronts, one workgroup per CU) 64 activation
- * rows of K = 1024 held in LDS, per wavefront and k-step four 32x32x32 int8 MFMAs on 2 x 1 KiB of weight operands
+ * rows of K = 1024 held in LDS, per wavefront and two k-steps (of 32) sixteen 16x16x64 int8 MFMAs on 4 KiB of weight operands
  * read from device memory in operand order (stream_weights != 0) or kept in registers (stream_weights = 0: the first
  * four k-steps' operands again and again), no
  * epilogue and no barrier -- so that a benchmark can report the int8 rate the matrix cores sustain in that loop
@@ -281,7 +281,7 @@ aq_status aq_stream_reference(const float* d_in, int64_t n, void* d_out, void* s
  * d_acc: 32768 int32 the call overwrites with workgroup 0's accumulators, index
  * (((w * 2 + feature tile) * 2 + row tile) * 16 + r) * 64 + lane, where register r of lane l is feature
  * 8 * (r / 4) + 4 * (l / 32) + r % 4 and row l mod 32 of the 32 x 32 tile.  Work per call: workgroups * ksteps *
- * 32 MFMAs of 65536 op.  NULL pointers: AQ_EINVAL.  Enqueues on `stream`. */
+ * 2097152 op.  NULL pointers: AQ_EINVAL.  Enqueues on `stream`. */
 aq_status aq_mfma_loop_reference(const void* d_weights, const void* d_acts, int32_t ksteps, int32_t stream_weights,
                                  int32_t workgroups, int32_t* d_acc, void* stream);
 
