@@ -17,6 +17,7 @@
 // workgroup.
 #include "fp16_device.hpp"
 #include "int8_device.hpp"
+#include "lanes.hpp"
 
 namespace aq {
 
@@ -27,22 +28,8 @@ typedef const h8 AQ_GLOBAL* gh8_ptr;
 
 namespace {
 
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ void* uni_ptr(const void* p) {
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return (void*)(((uint64_t)hi << 32) | lo);
-}
 __device__ __forceinline__ h8 load_operand(__amdgpu_buffer_rsrc_t w, int lane_off, int off) {
     return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(w, lane_off, off, 0));
-}
-
-// sum over the four 16-lane rows of a wavefront, the same value in every lane
-__device__ __forceinline__ float sum_rows4(float s) {
-    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
-    s = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
-    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
 constexpr int MLW = 8;               // wavefronts per workgroup
@@ -81,7 +68,7 @@ __global__ __launch_bounds__(MLT) void k_fp16_mlp(const Fp16Net* __restrict__ ne
     // registers for two k-steps in flight instead of four.)
     auto weights_of = [&](int l) {
         const int bytes = uni(a.L[l].NT) * uni(a.L[l].KS16) * 1024;
-        return __builtin_amdgcn_make_buffer_rsrc(uni_ptr(a.L[l].wp), 0, bytes, 0x00020000);
+        return __builtin_amdgcn_make_buffer_rsrc((void*)uni_ptr(a.L[l].wp), 0, bytes, 0x00020000);
     };
     const int lane_off = (g >> 1) * 1024 + (i16 + 32 * (g & 1)) * 16;
 
@@ -129,8 +116,8 @@ __global__ __launch_bounds__(MLT) void k_fp16_mlp(const Fp16Net* __restrict__ ne
     const _Float16* const xrow = xs + i16 * ld + 8 * g;
 
     // One layer for a wavefront with NB tiles.  (The accumulators live inside this one block: with the k-loop and the
-    // epilogue in separate switches over NB the compiler spilled hundreds of registers.  At 64 rows it still spills 33 to
-    // 37: 128 accumulators, the ring and the LayerNorm row's values share 256.)
+    // epilogue in separate switches over NB the compiler spilled hundreds of registers.  At 64 rows it still spills 36 or
+    // 37: 128 accumulators, the ring of operands and the rows' operands share 256.)
     auto layer_nb = [&](auto nb_c, int l) __attribute__((always_inline)) {
         constexpr int NB = decltype(nb_c)::value, PF = ring_depth<NB>();
         const int ks = (uni(a.L[l].K) + 31) >> 5;

@@ -18,6 +18,7 @@
 #pragma once
 #include "explore_device.hpp"
 #include "int8_device.hpp"
+#include "lanes.hpp"
 
 namespace aq {
 namespace fused {
@@ -28,34 +29,6 @@ constexpr int IMAXN = 1024;        // widest layer
 constexpr int IMAXK = 2496;        // longest input row
 constexpr int INARROW = 64;        // most outputs of a last layer that is split over K
 constexpr float K2_LOG2E = 2.885390081777927f;  // 2 log2(e): tanh(y) = 1 - 2 / (2^(K2 y) + 1)
-
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ float unif(float v) { return __int_as_float(uni(__float_as_int(v))); }
-template <class T>
-__device__ __forceinline__ T* uni_ptr(T* p) {
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return (T*)(((uint64_t)hi << 32) | lo);
-}
-// lane N of every 16-lane row, broadcast to that row (through an instruction of its own, so that no consumer folds it)
-template <int N>
-__device__ __forceinline__ int row_bcast(int v) {
-    int r = __builtin_amdgcn_mov_dpp(v, 0x150 + N, 0xF, 0xF, true);
-    asm volatile("" : "+v"(r));
-    return r;
-}
-__device__ __forceinline__ float sum_rows4(float s) {
-    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
-    s = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
-    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
-}
-__device__ __forceinline__ int sum_rows4(int s) {
-    const auto p = __builtin_amdgcn_permlane16_swap((uint32_t)s, (uint32_t)s, false, false);
-    s = (int)(p[0] + p[1]);
-    const auto q = __builtin_amdgcn_permlane32_swap((uint32_t)s, (uint32_t)s, false, false);
-    return (int)(q[0] + q[1]);
-}
 
 // 1 / n for n >= 1 and 1 / sqrt(v), the units' results (1 ulp) with one Newton step: as near as the correctly rounded operations, for
 // a fifth of their instructions
@@ -327,7 +300,7 @@ __global__ __launch_bounds__(IT, NBM == 2 && RT <= 4 ? 4 : 2) void k_mlp_fused(c
         auto consts4 = [&](auto h_c, auto arr_c, int (&o)[4]) __attribute__((always_inline)) {
             constexpr int h = decltype(h_c)::value, arr = decltype(arr_c)::value;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = row_bcast<4 * arr + (h & 3)>(cm[h >> 2][i]);
+            for (int i = 0; i < 4; ++i) o[i] = row_bcast_mov<4 * arr + (h & 3)>(cm[h >> 2][i]);
         };
         using A0 = std::integral_constant<int, 0>;
         using A1 = std::integral_constant<int, 1>;

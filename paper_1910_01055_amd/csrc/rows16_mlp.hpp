@@ -42,6 +42,7 @@
 #pragma once
 #include "explore_device.hpp"
 #include "int8_device.hpp"
+#include "lanes.hpp"
 
 namespace aq {
 namespace r16 {
@@ -52,15 +53,6 @@ constexpr int RLD = 272;       // LDS row stride, bytes: 256 codes + 16 (16-byte
 constexpr int RMAXL = 4;       // layers
 constexpr int RMAXK = 256;     // widest layer input / hidden layer
 constexpr int RSTEPS = 4;      // k-steps of 64 per layer at most
-
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ float unif(float v) { return __int_as_float(uni(__float_as_int(v))); }
-template <class T>
-__device__ __forceinline__ T* uni_ptr(T* p) {
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return (T*)(((uint64_t)hi << 32) | lo);
-}
 
 constexpr float K2_LOG2E = 2.885390081777927f;  // 2 log2(e): tanh(y) = 1 - 2 / (2^(K2 y) + 1)
 
@@ -83,12 +75,6 @@ struct R16Args {
 };
 static_assert(sizeof(R16Args) == 56, "the kernel arguments must stay within one 64-byte line");
 
-// lane N of every 16-lane row, broadcast to that row.  The old value is left undefined (a row broadcast writes
-// every lane): no move that clears the destination first.
-template <int N>
-__device__ __forceinline__ int row_bcast(int v) {
-    return __builtin_amdgcn_mov_dpp(v, 0x150 + N, 0xF, 0xF, true);
-}
 // r[i] = (lane N of the row's c[i]) + v[i] for a quad: the broadcast rides on the addition (v_add_u32_dpp, the
 // form the compiler itself emits for some of these additions, but not for all), so a constant that is only
 // ever added costs no instruction of its own.  The leading two wait states are the ones a DPP read needs after a
@@ -103,26 +89,9 @@ __device__ __forceinline__ void add_row_bcast4(int (&r)[4], const v4i& c, const 
         : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
         : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "n"(N));
 }
-// The same as an operand of its own instruction.  Needed for shift amounts: the compiler folds a row broadcast
-// into the shift (v_ashrrev_i32_dpp), and that instruction came back from the hardware with the broadcast
-// applied to the shifted value instead of the amount (additions and plain moves are right).
-template <int N>
-__device__ __forceinline__ int row_bcast_mov(int v) {
-    int r = row_bcast<N>(v);
-    asm volatile("" : "+v"(r));
-    return r;
-}
 // piece 2 * A + TL of this lane's row of constants (see load_c below)
 #define AQ_R16_C(cm, A, TL, i) row_bcast<2 * (A) + (TL)>((cm)[i])
 #define AQ_R16_CSH(cm, A, TL, i) row_bcast_mov<2 * (A) + (TL)>((cm)[i])
-
-// sum over the four 16-lane rows of a wavefront (lane ^ 16, then lane ^ 32), the same value in every lane
-__device__ __forceinline__ float sum_rows4(float s) {
-    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(s), __float_as_uint(s), false, false);
-    s = __uint_as_float(p[0]) + __uint_as_float(p[1]);
-    const auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(s), __float_as_uint(s), false, false);
-    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
-}
 
 // MT = row tiles of 16 batch rows per workgroup.  NH = number of hidden layers (the network has NH + 1 layers):
 // a compile-time fact, so that every global load sits in straight-line code and the compiler can count exactly

@@ -12,13 +12,13 @@
 // The few-row kernel re-reads both operands for each 32 x 32 tile, the tiled one stages all of K before the first product with one
 // wavefront per SIMD, byte by byte where rows are no whole pieces.  us before / now: 67-2048x3-21 at 600 rows 45.3 / 34.8, 1300
 // 72.3 / 36.5, 4500 173 / 78; with a LayerNorm at 2000 97 / 55; 67-1300-1500-21 at 900 33.0 / 20.3, at 3000 336 / 30.
-#include "fused_mlp.hpp"
+#include <atomic>
+
+#include "int8_device.hpp"
+#include "lanes.hpp"
 
 namespace aq {
 namespace {
-
-using fused::row_bcast;
-using fused::sum_rows4;
 
 constexpr int RL_W = 8, RL_T = RL_W * 64, RL_RT = 4;  // wavefronts, threads, 16-row tiles of a workgroup
 constexpr int RL_KC = 16;                // pieces of 16 bytes of K per chunk
@@ -208,10 +208,10 @@ __global__ __launch_bounds__(RL_T) void k_layer_rows(const RowsLayer L, const Ta
         int bias[4], mul[4], rz[4], sh[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            bias[i] = row_bcast<h>(cm[i]);
-            mul[i] = row_bcast<4 + h>(cm[i]);
-            rz[i] = row_bcast<8 + h>(cm[i]);
-            sh[i] = row_bcast<12 + h>(cm[i]);
+            bias[i] = row_bcast_mov<h>(cm[i]);
+            mul[i] = row_bcast_mov<4 + h>(cm[i]);
+            rz[i] = row_bcast_mov<8 + h>(cm[i]);
+            sh[i] = row_bcast_mov<12 + h>(cm[i]);
         }
 #pragma unroll
         for (int r = 0; r < RT; ++r) {

@@ -13,8 +13,9 @@
 // k-steps of 64 in flight per wavefront, and the stream does not stop at a pass boundary: the last k-steps of a
 // pass already request the first k-steps of the next one.
 //
-// v_mfma_i32_16x16x64_i8 on the 32 x 32 operand tiles, as in the general kernel: the chip holds a higher clock under it than under
-// 32x32x32 (256-1024x3-64 at 16384 rows 46.5 -> 43.7 us, everything else the same).  Four quads of the epilogue in a k-step
+// v_mfma_i32_16x16x64_i8 on the 32 x 32 operand tiles, as in the general kernel: a weight stream beside it keeps the matrix pipe waiting
+// less than beside 32x32x32 (the loop alone: busy 80 % of the cycles instead of 72; this kernel 102.6 k cycles -> 97.0 k at the same
+// clock, 256-1024x3-64 at 16384 rows 46.5 -> 43.7 us).  Four quads of the epilogue in a k-step
 // instead of two, so that layers of K = 256 hide theirs too, spilled 41 registers and took 47.
 //
 // Shapes: per-channel symmetric weights, fp32 observations at a 16-byte aligned address, every hidden layer
@@ -24,6 +25,7 @@
 
 #include "explore_device.hpp"
 #include "int8_device.hpp"
+#include "lanes.hpp"
 
 namespace aq {
 namespace {
@@ -33,71 +35,23 @@ constexpr int FT = FW * 64;      // threads per workgroup
 constexpr int CST_MAXN = 1024;   // widest layer
 
 
-// The network description is read through the kernel's pointer argument with uniform indices, i.e. by
-// scalar loads into scalar registers (measured faster than a copy in LDS read back through vector
-// registers: 2 % on the headline workload).  readfirstlane keeps a value scalar wherever the compiler
-// cannot prove it uniform, so that loop bounds and branches stay scalar.
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ float unif(float v) { return __int_as_float(uni(__float_as_int(v))); }
-template <class T>
-__device__ __forceinline__ T* uni_ptr(T* p) {
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return (T*)(((uint64_t)hi << 32) | lo);
-}
-
-// One layer as the kernel needs it: plain scalars, built field by field from the LDS copy.
-struct LayerView {
+// The narrow last layer, read through the kernel's pointer argument with uniform indices, i.e. by scalar loads into scalar
+// registers.  Its constants: bias, then scale, [Np] each.
+struct LastLayer {
     const int8_t* wp;
-    gv4i_ptr pack;        // the layer's epilogue constants: four contiguous [Np] arrays, as 16-byte pieces
-    const int32_t* rshift;
-    gint_ptr z_w;
-    int N, NT, KS, act, pieces, fast, z_out;
-    float s_out;
-    bool last, ln;
+    gv4i_ptr pack;
+    int N, NT, KS, pieces;  // pieces of 16 bytes of the constants: one a thread at most
 };
-// The pack holds bias_fold, then by layer type: requantized M0, rz, sh (the general requantization
-// form reads its shifts from global memory); LayerNorm m, gamma, beta; last m (two arrays staged).
-__device__ __forceinline__ LayerView layer_view(const NetDev& n, int l, int n_layers) {
-    const LayerDev& s = n.L[l];
-    LayerView v;
-    v.last = l == n_layers - 1;
-    v.act = uni(s.act);
-    v.ln = !v.last && v.act == AQ_ACT_LN_TANH;
-    v.wp = uni_ptr(s.wp);
-    v.pack = (gv4i_ptr)uni_ptr(s.bias_fold);
-    v.rshift = uni_ptr(s.rshift);
-    v.z_w = (gint_ptr)uni_ptr(s.z_w);
-    v.N = uni(s.N);
-    v.NT = uni(s.NT);
-    v.KS = uni(s.KS);
-    v.pieces = (v.last ? 2 : 4) * v.NT * 8;
-    v.s_out = 1.0f;
-    v.z_out = 0;
-    v.fast = 0;
-    if (!v.last) {
-        v.s_out = unif(n.actq[l + 1].s);
-        v.z_out = uni(n.actq[l + 1].z);
-        v.fast = uni(n.fast[l]);
-    }
-    return v;
-}
-// this thread's share of a layer's constants: up to two 16-byte pieces (Np <= CST_MAXN)
-__device__ __forceinline__ void load_consts(const LayerView& v, int tid, v4i& c0, v4i& c1) {
-    if (tid < v.pieces) c0 = v.pack[tid];
-    if (tid + FT < v.pieces) c1 = v.pack[tid + FT];
-}
-__device__ __forceinline__ void park_consts(int pieces, int tid, int32_t* cst, const v4i& c0, const v4i& c1) {
-    if (tid < pieces) ((v4i*)cst)[tid] = c0;
-    if (tid + FT < pieces) ((v4i*)cst)[tid + FT] = c1;
+__device__ __forceinline__ LastLayer last_layer(const LayerDev& s) {
+    const int NT = uni(s.NT);
+    return LastLayer{uni_ptr(s.wp), (gv4i_ptr)uni_ptr(s.bias_fold), uni(s.N), NT, uni(s.KS), 2 * NT * 8};
 }
 
 // A last layer of at most two feature tiles would leave most waves idle.  It is spread over all
 // eight instead: its (feature tile, row tile) pairs go to different waves, and the waves left over
-// split K.  Partial accumulators meet in LDS (PART_WORDS ints per wave: 16 accumulator registers
-// and the row sums of the activations, lane-major).
+// split K.  Partial accumulators meet in LDS (PART_WORDS ints per wave: 16 accumulator registers, lane-major).
 constexpr int NARROW_NT = 2;
-constexpr int PART_WORDS = 17 * 64;
+constexpr int PART_WORDS = 16 * 64;
 constexpr int PART_BYTES = FW * PART_WORDS * 4;
 struct NarrowMap {
     int pairs, ksplit, pair, nt, mt, k0, k1;
@@ -122,7 +76,7 @@ __device__ __forceinline__ NarrowMap narrow_map(int NT, int KS, int wave) {
 // 2 * NT * MT outputs (lane-major, so its LDS reads are conflict-free) and reads the KSPLIT partial
 // sums of each; all reads of one output are independent and issued together.
 template <int MT, int NT, bool TAPS>
-__device__ __forceinline__ void narrow_reduce(const int32_t* part, const CPtrs& C, const LayerTaps& T, int N,
+__device__ __forceinline__ void narrow_reduce(const int32_t* part, const int32_t* cst, const LayerTaps& T, int N,
                                               int64_t row0, int64_t batch, float* yrow, int ldy, int tid, int head,
                                               float* actions, float* tap_y, const CallArgs& c) {
     constexpr int PAIRS = NT * MT, KSPLIT = FW / PAIRS;
@@ -139,13 +93,13 @@ __device__ __forceinline__ void narrow_reduce(const int32_t* part, const CPtrs& 
         const int nt = pr & (NT - 1), mt = pr / NT;
         const int n = nt * 32 + 8 * (reg >> 2) + 4 * (ln >> 5) + (reg & 3);
         const int m = mt * 32 + (ln & 31);
-        v += C.bias_fold[n];
+        v += cst[n];
         const int64_t row = row0 + m;
         const bool ok = row < batch && n < N;
         if (TAPS) {
             if (T.acc && ok) T.acc[row * N + n] = v;
         }
-        const float y = (float)v * C.m[n];
+        const float y = (float)v * __int_as_float(cst[NT * 32 + n]);
         if (actions) {
             // elementwise heads leave from here; only argmax needs the whole row in one place
             if (ok) {
@@ -445,7 +399,7 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
             lds_barrier();
         }
         if (active) {
-            if (k0 < sc.KS) start_ring(k0);  // (after the barrier: the ring reads two k-steps ahead)
+            if (k0 < sc.KS) start_ring(k0);  // (after the barrier: operands are read a k-step ahead)
             for (int k = k0; k < sc.KS; k += WPF) group(k);
             // park the constants: [bias_fold | M0 | rz | sh] x 64 features
             *(v4i*)(my_cst + (pass_no & 1) * WSLOT + (lane >> 4) * 64 + 4 * (lane & 15)) = cw;
@@ -479,10 +433,10 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
     }
     // The narrow last layer's constants and this wavefront's first weights of it do not depend on the hidden
     // layers: requested before the last epilogue.
-    const LayerView LL = layer_view(a, nh, n_layers);
+    const LastLayer LL = last_layer(a.L[nh]);
     const NarrowMap nm = narrow_map<2>(LL.NT, LL.KS, wave);
-    v4i cv0 = {0, 0, 0, 0}, cv1 = cv0;
-    load_consts(LL, tid, cv0, cv1);
+    v4i cv = {0, 0, 0, 0};
+    if (tid < LL.pieces) cv = LL.pack[tid];
     gv4i_ptr nwptr[1];
     nwptr[0] = (gv4i_ptr)LL.wp + (int64_t)nm.nt * LL.KS * 64 + lane;
     v4i nw[4][1];
@@ -496,13 +450,12 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
     // ---- narrow last layer (at most two feature tiles): spread over all eight wavefronts by splitting K
     {
         const int l = nh;
-        const LayerView& L = LL;
+        const LastLayer& L = LL;
         LayerTaps T{nullptr, nullptr, nullptr};
         if (TAPS) T = LayerTaps{t.acc[l], t.act[l], t.ln[l]};
         const int Np = L.NT * 32;
         lds_barrier();  // every hidden feature is in LDS
         const int8_t* in = buf(l);
-        const CPtrs C{cst_last, cst_last + Np, L.rshift, cst_last + 2 * Np, cst_last + 3 * Np, (const float*)(cst_last + Np)};
         v16i pacc[1][1], prs[1];
         pacc[0][0] = zero16();
         prs[0] = zero16();
@@ -514,7 +467,7 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
 #pragma unroll
             for (int r = 0; r < 16; ++r) mine[r * 64] = pacc[0][0][r];
         }
-        park_consts(L.pieces, tid, cst_last, cv0, cv1);
+        if (tid < L.pieces) ((v4i*)cst_last)[tid] = cv;
         lds_barrier();  // partial sums and the layer's constants are in LDS; the layer's input is free
         float* yrow = (float*)buf(l);
         const int ldy = Np + 1;
@@ -522,9 +475,9 @@ __global__ __launch_bounds__(FT) void k_mlp_wide(const NetDev* __restrict__ netp
         float* direct = head != AQ_HEAD_ARGMAX ? (float*)c.actions : nullptr;
         float* tap_y = TAPS ? t.y : nullptr;
         if (L.NT == 1)
-            narrow_reduce<2, 1, TAPS>(part, C, T, L.N, row0, c.batch, yrow, ldy, tid, head, direct, tap_y, c);
+            narrow_reduce<2, 1, TAPS>(part, cst_last, T, L.N, row0, c.batch, yrow, ldy, tid, head, direct, tap_y, c);
         else
-            narrow_reduce<2, 2, TAPS>(part, C, T, L.N, row0, c.batch, yrow, ldy, tid, head, direct, tap_y, c);
+            narrow_reduce<2, 2, TAPS>(part, cst_last, T, L.N, row0, c.batch, yrow, ldy, tid, head, direct, tap_y, c);
         if (direct) return;
         lds_barrier();
         // argmax over the dequantized rows (lowest index wins ties)
