@@ -434,7 +434,7 @@ __global__ __launch_bounds__(IT, NBM == 2 && RT <= 4 ? 4 : 2) void k_mlp_fused(c
             // Up to 256 features: code = round(t / s + z) with t = 1 - 2 / (e^{2y} + 1), straight from the reciprocal: 9 codes in a million off
             // the 64-bit ones.  More, what rows in memory get (ln_rows.hpp, 5 in a million): tanh from |y|, and t (1 / s) rounded once,
             // straight to an integer (in MAGIC's last place), before z is added: 4 in a million, tanh's error 3.5e-8 instead of 5.3e-8.
-            // It is three more instructions a value: 61-1024x2-36 at 16379 rows 34.3 -> 36.1 us, 61-263-163-2 at 32768 18.0 -> 19.0.
+            // It is three more instructions a value: 61-1024x2-36 at 16379 rows 34.3 -> 35.5 us, 61-263-163-2 at 32768 17.8 -> 18.9.
             auto codes = [&](auto wide_c) __attribute__((always_inline)) {
                 constexpr bool WIDE = decltype(wide_c)::value;
                 constexpr float MAGIC = 12582912.0f;  // 1.5 * 2^23

@@ -86,7 +86,8 @@ struct LayerIO {
     int8_t* out;      // hidden layers: int8 signed-domain [rows][N] (row stride N)
     float* ln_x;      // LN layers: fp32 scratch [rows][N]
     float* y;         // last layer: dequantized outputs [rows][N]
-    // between two layers of the few-row kernel the activations lie in operand order (skinny_layer.hip)
+    // the few-row and the many-row kernel leave their maps in operand order for each other (skinny_layer.hip, rows_layer.hip); the tiled
+    // one refuses such a map
     int in_blocked = 0, out_blocked = 0;
 };
 // bytes of such a map of `rows` rows and N features
@@ -102,13 +103,14 @@ bool skinny_layer_does_argmax(const FwdArgs& a, int l);
 // cold: the weights were just written
 constexpr int kFewMaxRows = 512, kFewMinWidth = 257;
 bool few_rows_faster(const FwdArgs& a, bool noise, bool guarded, bool cold);
-// whether launch_layer_int8 hands layer l at this batch to the K-split kernel
 // the leading convolution layers in one launch (0 layers = shapes it does not take); writes the last
 // convolution's signed codes to `out` ([batch * oh * ow][N])
 int conv_stack_layers(const FwdArgs& a);
 aq_status launch_conv_stack(const FwdArgs& a, int8_t* out, hipStream_t st);
+// whether launch_layer_int8 hands layer l at this batch to the K-split kernel
 bool layer_uses_skinny(const FwdArgs& a, int l);
-// fully connected layers at many rows (rows_layer.hip): input fp32 observations or a map in operand order, output such a map or fp32 rows
+// fully connected layers at many rows (rows_layer.hip): input fp32 observations or a map in operand order, output such a map or fp32
+// rows.  Whether layer l takes it, given that the next one reads such a map
 bool layer_uses_rows(const FwdArgs& a, int l);
 aq_status launch_layer_rows(const FwdArgs& a, int l, const LayerIO& io, hipStream_t st);
 aq_status launch_layer_skinny(const FwdArgs& a, int l, const LayerIO& io, hipStream_t st);

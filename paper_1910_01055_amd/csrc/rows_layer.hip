@@ -1,5 +1,5 @@
-// Wide fully connected 8-bit layers at some hundred to some thousand rows (Sec. 3.1 actor inference on the 8-bit policy of Sec. 3.2; policies wider than the
-// whole-network kernels hold): one launch per layer, the layers' maps in operand order (blocked_map_bytes).
+// Wide fully connected 8-bit layers at some hundred to some thousand rows (Sec. 3.1 actor inference on the 8-bit policy of Sec. 3.2;
+// policies wider than the whole-network kernels hold): one launch per layer, the layers' maps in operand order (blocked_map_bytes).
 //
 // A workgroup of 8 wavefronts takes 64 rows x 256 features; a wavefront 32 features, both halves of a tile by four row tiles of
 // v_mfma_i32_16x16x64_i8.  Weights go from memory straight into operand registers, each byte once per workgroup; the rows' codes go
@@ -10,8 +10,8 @@
 // What bounds it: the vector memory path, 20 KiB per k-step of 64 at 52 bytes a clock for 256 clocks of matrix work.  128 rows a
 // workgroup, which ask for less, were slower up to 8000 rows (67-2048x3-21 at 2000 rows 56 us, at 4500 98): too few workgroups.
 // The few-row kernel re-reads both operands for each 32 x 32 tile, the tiled one stages all of K before the first product with one
-// wavefront per SIMD, byte by byte where rows are no whole pieces.  us before / now: 67-2048x3-21 at 600 rows 45.3 / 34.8, 1300
-// 72.3 / 36.5, 4500 173 / 78; with a LayerNorm at 2000 97 / 55; 67-1300-1500-21 at 900 33.0 / 20.3, at 3000 336 / 30.
+// wavefront per SIMD, byte by byte where rows are no whole pieces.  us before / now: 67-2048x3-21 at 640 rows 44.6 / 33.3, 1300
+// 71.9 / 36.4, 4500 173 / 76; with a LayerNorm at 3000 160 / 78; 67-1300-1500-21 at 900 32.4 / 20.1, at 3000 336 / 30.
 #include <atomic>
 
 #include "int8_device.hpp"
