@@ -40,7 +40,8 @@ __device__ __forceinline__ float rsqrt_near(float v) {
     const bool tiny = v < 1e-30f;  // (a constant row and next to no eps: below, the unit takes v for zero)
     v = tiny ? v * 0x1p64f : v;
     const float r = __builtin_amdgcn_rsqf(v);
-    return fmaf(0.5f * r, fmaf(-v * r, r, 1.0f), r) * (tiny ? 0x1p32f : 1.0f);
+    const float n = fmaf(0.5f * r, fmaf(-v * r, r, 1.0f), r) * (tiny ? 0x1p32f : 1.0f);
+    return v < INFINITY ? n : r;  // (a variance beyond the largest float: 0)
 }
 
 struct Call {

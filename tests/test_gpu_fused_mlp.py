@@ -89,3 +89,19 @@ def test_wide_layernorm_loses_nothing_to_the_layers_launches(aq, n, scheme):
     assert got[1][0] <= 1.03 * got[2][0]
     assert got[1][1] <= got[2][1] + 4 * got[2][1] ** 0.5
     P.close()
+
+
+@pytest.mark.parametrize("n", [200, 700])
+def test_a_layernorm_whose_variance_overflows(aq, n):
+    """Rows of 1e20 and more: fp32 has no variance for them, its reciprocal root is zero and every value the offset's tanh, from the
+    whole-network kernel as from rows in memory."""
+    net = synth.small_net([fc(61, n, "ln_tanh"), fc(n, 300, "relu"), fc(300, 7, "none")])
+    params = synth.make_params(net, nonzero_bias=True)
+    obs = synth.make_obs(net, 100) * np.float32(1e21)
+    P, d = U.gpu_quantize(aq, net, params, [(-4e21, 4e21), (-1.0, 1.0), (0.0, 3.0)])
+    want = torch.tanh(d[3][0]).expand(100, n)
+    for path in (1, 2):
+        P.policy_set_path(path)
+        _, t = U.gpu_forward(P, net, obs)
+        assert torch.isfinite(t["ln_t"][0]).all() and (t["ln_t"][0] - want).abs().max() < 1e-6, path
+    P.close()
