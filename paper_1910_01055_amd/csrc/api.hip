@@ -1156,18 +1156,15 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
         s = launch_conv_stack(a, sc.i8[(nc - 1) & 1], st);
         if (s != AQ_OK) return s;
     }
-    // Wide layers at many rows take a kernel that writes operand order only (and reads it, behind the first layer).  Settled from the
-    // last layer backwards: a layer takes it if the next one reads that order, as one of its kind or of the few-row kernel's;
-    // and forwards from the first layer on, up to the first that does not.
-    bool takes_many[AQ_MAX_LAYERS] = {};
-    if (nc == 0 && sc.blocked && pair < 0) {
-        bool reads = false;
-        for (int l = nl - 1; l >= 0; --l) {
-            takes_many[l] = reads && layer_uses_rows(a, l);
-            reads = takes_many[l] || layer_uses_skinny(a, l);
-        }
+    // Wide layers at many rows may take a kernel that writes operand order only (and reads it, behind the first layer).  Settled from
+    // the last layer backwards: one takes it if the next one reads that order, as one of its kind or of the few-row kernel's; and
+    // in the loop only where its own input lies so.
+    bool takes_many[AQ_MAX_LAYERS] = {}, reads_blocked[AQ_MAX_LAYERS + 1] = {};
+    for (int l = nl - 1; l >= nc && sc.blocked; --l) {
+        if (!p->L[l].fc) continue;
+        takes_many[l] = nc == 0 && pair < 0 && reads_blocked[l + 1] && layer_uses_rows(a, l);
+        reads_blocked[l] = takes_many[l] || layer_uses_skinny(a, l);
     }
-    bool many = true;
     int blocked = 0;  // how the layer before left its output
     for (int l = nc; l < nl; ++l) {
         const LayerBuf& b = p->L[l];
@@ -1175,8 +1172,8 @@ static aq_status forward_int8_impl(aq_policy* p, const void* d_obs, int64_t batc
         LayerIO io;
         io.in_blocked = blocked;
         const bool ln = l < nl - 1 && b.d.act == AQ_ACT_LN_TANH;  // (its rows' kernel writes either order)
-        many = many && takes_many[l];
-        blocked = many || (sc.blocked && l < nl - 1 && b.fc && (ln || layer_uses_skinny(a, l)) && layer_uses_skinny(a, l + 1));
+        const bool many = takes_many[l] && (l == 0 || blocked);
+        blocked = many || (b.fc && reads_blocked[l + 1] && (ln || layer_uses_skinny(a, l)));
         io.out_blocked = ln ? 0 : blocked;
         io.in = l == 0 ? d_obs : (const void*)sc.i8[(l - 1) & 1];
         io.out = sc.i8[l & 1];

@@ -270,7 +270,9 @@ aq_status go(const RowsLayer& q, const TapArgs& t, hipStream_t st) {
 }
 }  // namespace
 
-// From 450 rows on: us on the few-row kernel / here, the first layer of 67-2048-2048-256-21 at 470 rows 31.5 / 23.3 for the policy.  A
+// From 450 rows on: us on the few-row kernel / here, the first layer of 67-2048-2048-256-21 at 470 rows 31.5 / 23.3 for the policy; but not
+// while the few-row kernel takes that layer in tiles of 16 rows, four rounds of them at most: 384-1100-300-9 at 450 rows 13.7 / 16.3,
+// 384-512-2048-9 at 560 16.6 / 20.3, per-tensor 200-700-1500-9 at 466 16.1 / 17.9.  A
 // layer behind the first, which the few-row kernel reads in the same order, comes here where the grid holds enough workgroups; for
 // whole policies us there / here, per-channel weights: N = 512 at 1800 rows 18.6 / 19.1, 2200 20.6 / 19.2; 700 at 1400 18.0 / 18.9, 1600
 // 19.9 / 19.3; 900 at 1100 17.6 / 18.5, 1300 19.3 / 18.8; two of 1100 at 900 25.1 / 28.4, 1200 30.0 / 29.3; two of 2048 at 512 29.8 / 34.2,
@@ -284,7 +286,11 @@ bool layer_uses_rows(const FwdArgs& a, int l) {
     auto fc = [](const LayerDev& X) { return X.kh == 1 && X.kw == 1 && X.in_h == 1 && X.in_w == 1; };
     if (l >= n.n_layers - 1 || !fc(L) || L.NT < 16 || a.c.batch < 450 || a.w4[l]) return false;
     if ((int64_t)L.NT * L.KS * 1024 >= 0x7fffffff) return false;
-    if (l == 0) return !n.in_u8 && L.K <= RL_MAXK0;
+    if (l == 0) {
+        int ft = 0, rt = 0;
+        few_row_tile(L.N, a.c.batch, false, &ft, &rt);
+        return !n.in_u8 && L.K <= RL_MAXK0 && (rt > 1 || !layer_uses_skinny(a, l));
+    }
     const int64_t groups = (L.NT + RL_W - 1) / RL_W, blocks = (a.c.batch + 16 * RL_RT - 1) / (16 * RL_RT);
     if (L.K <= 2048 && groups * blocks < 60 + 5 * groups + (n.asym ? 20 : 0) && layer_uses_skinny(a, l)) return false;
     return fc(n.L[l - 1]);

@@ -16,13 +16,14 @@ NETS = {
     "2048x3": ([fc(67, 2048, "relu"), fc(2048, 2048, "relu"), fc(2048, 2048, "relu"), fc(2048, 21, "none")], "tanh"),
     "narrow_third": ([fc(67, 2048, "ln_tanh"), fc(2048, 2048, "relu"), fc(2048, 256, "relu"), fc(256, 21, "none")], "tanh"),
     "wide_last": ([fc(67, 2048, "relu"), fc(2048, 1100, "ln_tanh"), fc(1100, 512, "none")], "linear"),
+    "narrow_first": ([fc(200, 200, "relu"), fc(200, 1300, "ln_tanh"), fc(1300, 1043, "relu"), fc(1043, 21, "none")], "tanh"),
     "narrow_between": ([fc(20, 1100, "relu"), fc(1100, 200, "relu"), fc(200, 1030, "relu"), fc(1030, 5, "none")], "tanh"),
 }
 
 
 CASES = [(name, batch) for name in ("whole", "ragged", "ln_first", "narrow_between") for batch in (449, 450, 513, 1024)] + [
     ("2048x3", 8128), ("2048x3", 8150), ("narrow_third", 960), ("narrow_third", 961), ("narrow_third", 1300), ("wide_last", 1300),
-    ("wide_last", 4500), ("narrow_between", 3000)]
+    ("wide_last", 4500), ("narrow_between", 3000), ("narrow_first", 640), ("narrow_first", 1300)]
 
 
 @pytest.mark.parametrize("name,batch", CASES)

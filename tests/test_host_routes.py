@@ -285,7 +285,7 @@ WIDE = {  # hidden widths, outputs, layers with a LayerNorm
     "1100-200-1030": ((1100, 200, 1030), 21, ()), "1100-200-1030 ln": ((1100, 200, 1030), 21, (0, 2)), "200-1300-1300": ((200, 1300, 1300), 21, ()),
     "1100-1000-1030-30": ((1100, 1000, 1030, 30), 5, (1, 3)), "1300": ((1300,), 300, ()),
     "1024x2-300": ((1024, 1024, 300), 9, (1,)), "800-600": ((800, 600), 9, ())}
-WIDE_BATCHES = (1, 449, 450, 900, 960, 961, 1300, 3000, 4500, 8000, 8128, 8129, 8150, 8191, 8192, 9000)
+WIDE_BATCHES = (1, 449, 450, 640, 900, 960, 961, 1300, 3000, 4500, 8000, 8128, 8129, 8150, 8191, 8192, 9000)
 
 
 def wide_layers_read_the_order_their_input_was_written_in(h):
@@ -325,7 +325,7 @@ def wide_layers_read_the_order_their_input_was_written_in(h):
     # where the many-row kernel serves and where it does not, because its reader could not follow
     for name, batch, many in (("2048x3", 449, False), ("2048x3", 450, True), ("2048x3", 8128, True), ("2048x3", 8129, False),
                               ("2048x2-256", 1300, True), ("2048x2-256 ln", 1300, True), ("1300x2-400", 3000, True), ("2048x2, wide last", 4500, False),
-                              ("1100-200-1030", 450, True), ("200-1300-1300", 900, False), ("1300", 900, True)):
+                              ("1100-200-1030", 450, False), ("1100-200-1030", 900, True), ("200-1300-1300", 640, False), ("200-1300-1300", 900, True), ("1300", 900, True)):
         assert ((name, batch, "rows") in seen) == many, (name, batch)
 
 
@@ -338,6 +338,12 @@ def wide_layers_behind_the_first_at_some_hundred_rows(h):
         for batch in (max(at - 1, 450), at):
             want = ["rows"] + ["rows" if batch >= at else "skinny"] * (len(widths) - 1) + ["skinny"]
             assert [layer_launch(e)[0] for e in h.forward(P, batch) if e.kind == LAUNCH] == want, (widths, scheme, batch)
+        P.close()
+    # the first one stays on the few-row kernel while that takes tiles of 16 rows; one behind a few-row layer needs no other
+    for widths, batch, want in (((1100, 300), 450, ["skinny"] * 3), ((1100, 300), 500, ["rows", "skinny", "skinny"]),
+                                ((300, 1300, 1300), 1200, ["skinny", "rows", "rows", "skinny"]), ((1100, 700, 1100), 1200, ["rows", "skinny", "rows", "skinny"])):
+        P = h.policy(*widths)
+        assert [layer_launch(e)[0] for e in h.forward(P, batch) if e.kind == LAUNCH] == want, (widths, batch)
         P.close()
 
 
