@@ -54,13 +54,6 @@ __device__ __forceinline__ float tanh_fast(float x) {
     return copysignf(t, x);
 }
 
-// The same value without the sign handling: tanh(x) = 1 - 2 / (e^{2x} + 1) for either sign, because
-// exp2 saturates to 0 and +inf and rcp(inf) = 0.  Absolute error about 2e-7.
-__device__ __forceinline__ float tanh_exp2(float x) {
-    const float e = __builtin_amdgcn_exp2f(x * 2.885390081777927f);
-    return fmaf(__builtin_amdgcn_rcpf(e + 1.0f), -2.0f, 1.0f);
-}
-
 // tanh for the action head: odd polynomial near zero (no cancellation), exponential form elsewhere;
 // relative error below 1e-6.
 __device__ __forceinline__ float tanh_head(float x) {
